@@ -424,8 +424,11 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                 const __amdgpu_buffer_rsrc_t xr =
                     make_rsrc(reinterpret_cast<const void*>(((unsigned long long)xb_hi << 32) | xb_lo), x_records);
                 // (with channel ranges in the place of taps: the same positions of every range, each range into its
-                // own part of the stage, 2 P pieces long)
-                for (int t = 0; t < p.groups; ++t)
+                // own part of the stage, 2 P pieces long.  A layer of nine taps has no ranges, and its loads sit in the
+                // straight run of code between the MFMAs: a loop there, even one that runs once, costs 1,100 spilled
+                // scalars in the 128 x 448 tile -- 128 -> 128 channels at 112 x 112, batch 64: 8,270 us with the loop)
+                const int ranges = FULL ? 1 : p.groups;
+                for (int t = 0; t < ranges; ++t)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(
                         xr, (lds_ptr)(ldsB + buf * 2 * p.plane_bytes + t * (2 * p.P * 1024) + id * 1024), 16,
                         (int)(stage_on ? agoff[j] : kInvalid), cb * 32 + t * (int)p.group_bytes, 0, 0);
