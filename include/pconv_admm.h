@@ -68,8 +68,8 @@ int pconv_assign_patterns_device(const void* w, int dtype, long long n, const ui
  * n = F*C kernels of a layer, the k = floor(keep*n + 0.5) with the largest squared norm of the pattern-pruned kernel
  * W o M_pid are kept; equal norms go to the lower index f*C + c.  Same rule and arithmetic as the host entry
  * pconv_select_connectivity (norms in double, taps ascending): the two agree bit for bit on finite weights.
- * The selection is a stable radix sort of (norm, index) pairs (the hipCUB device primitive) between two small
- * kernels of this library.
+ * The selection is a radix selection over the norms' bit patterns (nothing is sorted); up to 8,192 kernels it is a
+ * single launch.
  *   w          in,  device, n kernels of 9 weights, storage type `dtype`
  *   lib        in,  HOST, uint16[K]
  *   pid        in,  device, int32[n], every entry in [0, K) (not checked on the device: an entry outside reads

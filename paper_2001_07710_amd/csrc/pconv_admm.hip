@@ -3,9 +3,10 @@
 // include/pconv_admm.h.
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
-#include <hipcub/device/device_radix_sort.hpp>
 
+#include <algorithm>
 #include <cmath>
+#include <cstddef>
 #include <cstdint>
 
 #include "pconv_admm.h"
@@ -210,32 +211,440 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const T* __restrict__ 
     pid[first + threadIdx.x] = arg;
 }
 
-// squared norm of the pattern-pruned kernel as a sort key: a non-negative double's bit pattern orders like its value
+// ---- connectivity selection: the k largest squared norms, equal ones by ascending index, without sorting anything.
+//
+// The squared norm of a pattern-pruned kernel is its key: a non-negative double's bit pattern orders like its value.
+// Up to kSmallN kernels are one workgroup's work, keys in registers.  More of them go through a radix selection: one
+// pass computes the keys and counts their exponents, one counts the next 10 bits of the keys with the exponent of the
+// k-th largest, one gathers the keys that share those 21 bits (a few hundred of 1.6 million), and a single workgroup
+// finds the k-th largest among them; the last pass compares every key with it.  Every pass works out the position of
+// the k-th largest from the counts of the passes before it, redundantly in each workgroup, so that nothing waits for
+// anything but the end of the kernel before.  Where more keys share 21 bits than the list holds -- many equal norms:
+// kernels pruned to zero already -- three more counting passes of 14 bits settle the rest of the key, and equal keys
+// are ranked by index through counts per run of kernels; those passes return at once otherwise.
+// 1.6 million fp32 kernels: 300 us with a 64-bit radix sort of (norm, index) pairs, whose eight passes move the pairs
+// through memory and back; 55 us so, of which 15 read the weights (59 MB at the rate of a copy).
+constexpr int kSelThreads = 1024;
+constexpr long long kSmallN = 8 * kSelThreads;                 // up to 8 keys per thread: one workgroup's work
+constexpr int kBins = 2048;                                    // exponents
+constexpr int kBins1 = 1024;                                   // the 10 bits below
+constexpr int kReplicas = 8;                                   // copies of the first counts: blocks share few exponents
+constexpr int kSlowBits = 14, kSlowBins = 1 << kSlowBits;      // 42 bits below the first 21, in three passes
+constexpr int kListCap = 4096;
+constexpr int kRuns = 1024;                                    // runs of kernels whose equal keys are counted
+
+struct SelectState {
+    unsigned listed;                   // keys that share the first 21 bits with the k-th largest
+    unsigned slow;                     // 1: more of them than the list holds
+    unsigned last_index;               // of the keys equal to `threshold`, those with at most this index are kept
+    unsigned ties_kept;                // slow: how many of them
+    unsigned long long threshold;      // the k-th largest key
+    unsigned hist0[kReplicas][kBins];
+    unsigned hist1[kBins1];
+    unsigned slow_hist[3][kSlowBins];
+    unsigned run_ties[kRuns];
+    unsigned list_index[kListCap];
+    unsigned long long list_key[kListCap];
+};
+// words that have to be zero before the first pass: everything in front of the list
+constexpr unsigned kStateWords = offsetof(SelectState, list_index) / 4;
+
 template <typename T>
-__global__ __launch_bounds__(kThreads) void norm_key_kernel(const T* __restrict__ w, long long n, Library lib, int K,
-                                                            const int32_t* __restrict__ pid, uint64_t* __restrict__ key,
-                                                            uint32_t* __restrict__ idx) {
-    __shared__ uint32_t masks[126];
-    if ((int)threadIdx.x < K) masks[threadIdx.x] = lib.mask[threadIdx.x];
-    __syncthreads();
-    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (i >= n) return;
-    const int32_t j = pid[i];
-    const unsigned m = masks[(j >= 0 && j < K) ? j : 0];
+__device__ __forceinline__ unsigned long long norm_key(const T* k9, unsigned m) {
     double e = 0.0;
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
-        const double v = (double)(float)w[i * 9 + t];
+        const double v = (double)(float)k9[t];
         if (m >> t & 1u) e = e + v * v;                       // (taps ascending, product and sum rounded separately)
     }
-    key[i] = __builtin_bit_cast(uint64_t, e);
-    idx[i] = (uint32_t)i;
+    return __builtin_bit_cast(unsigned long long, e) & 0x7FFFFFFFFFFFFFFFull;
 }
 
-__global__ __launch_bounds__(kThreads) void mark_kept_kernel(const uint32_t* __restrict__ order, long long n, long long k,
-                                                             uint8_t* __restrict__ mask) {
-    const long long r = (long long)blockIdx.x * kThreads + threadIdx.x;
-    if (r < n) mask[order[r]] = r < k ? 1 : 0;
+// The sum over the workgroup's kSelThreads threads of what lane 0 of each wave passes.  `slots` are 32 words of LDS used
+// alternately, so one barrier per call is enough.
+typedef unsigned uint4v __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ unsigned block_total(unsigned wave_sum, uint4v* slots, unsigned& turn) {
+    uint4v* s = slots + (turn & 1u) * 4;
+    ++turn;
+    if ((threadIdx.x & 63) == 0) reinterpret_cast<unsigned*>(s)[threadIdx.x >> 6] = wave_sum;
+    __syncthreads();
+    const uint4v t = (s[0] + s[1]) + (s[2] + s[3]);
+    return (t.x + t.y) + (t.z + t.w);
+}
+// ... and, of the waves in front of the calling thread's own.
+__device__ __forceinline__ unsigned block_total(unsigned wave_sum, uint4v* slots, unsigned& turn, unsigned* before) {
+    const unsigned* s = reinterpret_cast<const unsigned*>(slots + (turn & 1u) * 4);
+    const unsigned total = block_total(wave_sum, slots, turn);
+    *before = 0;
+#pragma unroll
+    for (int q = 0; q < kSelThreads / 64; ++q) *before += q < (int)(threadIdx.x >> 6) ? s[q] : 0u;
+    return total;
+}
+
+// The largest value T of `bits` bits such that at least k of the workgroup's values are >= T (each thread holds PER,
+// those at and beyond its count are 0), found bit by bit; stops as soon as exactly k values are.
+template <int PER, typename V>
+__device__ __forceinline__ V block_kth(const V (&v)[PER], V base, int bits, unsigned k, uint4v* slots, unsigned& turn) {
+    V t = base;
+    for (int b = bits - 1; b >= 0; --b) {
+        const V cand = t | ((V)1 << b);
+        unsigned c = 0;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) c += (unsigned)__popcll(__ballot(v[j] >= cand));
+        const unsigned total = block_total(c, slots, turn);
+        if (total >= k) t = cand;
+        if (total == k) break;
+    }
+    return t;
+}
+
+template <typename T, int PER>
+__global__ __launch_bounds__(kSelThreads) void select_small_kernel(const T* __restrict__ w, int n, Library lib, int K,
+                                                                   const int32_t* __restrict__ pid, unsigned k,
+                                                                   uint8_t* __restrict__ mask) {
+    __shared__ uint32_t masks[126];
+    __shared__ uint4v slots[8];
+    if ((int)threadIdx.x < K) masks[threadIdx.x] = lib.mask[threadIdx.x];
+    __syncthreads();
+    // (keys of kernels that do not exist are 0 like those of kernels without weight, but come behind all of them)
+    unsigned long long key[PER];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * kSelThreads + (int)threadIdx.x;
+        key[j] = 0;
+        if (i < n) {
+            const int32_t q = pid[i];
+            key[j] = norm_key(w + (size_t)i * 9, masks[(q >= 0 && q < K) ? q : 0]);
+        }
+    }
+    unsigned turn = 0;
+    const unsigned long long t = block_kth(key, 0ull, 63, k, slots, turn);
+    unsigned above = 0, equal = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        above += (unsigned)__popcll(__ballot(key[j] > t));
+        equal += (unsigned)__popcll(__ballot(j * kSelThreads + (int)threadIdx.x < n && key[j] == t));
+    }
+    above = block_total(above, slots, turn);
+    equal = block_total(equal, slots, turn);
+    unsigned left = k - above;                                // of the keys equal to t, the first so many by index
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * kSelThreads + (int)threadIdx.x;
+        const bool tie = i < n && key[j] == t;
+        bool keep = key[j] > t || (tie && equal <= left);
+        if (equal > left && left > 0) {                       // (uniform: more equal keys than places)
+            const unsigned long long ties = __ballot(tie);
+            const unsigned before_lane = (unsigned)__popcll(ties & ((1ull << (threadIdx.x & 63)) - 1ull));
+            unsigned before_wave;
+            const unsigned total = block_total((unsigned)__popcll(ties), slots, turn, &before_wave);
+            keep = keep || (tie && before_wave + before_lane < left);
+            equal -= total;
+            left -= total < left ? total : left;
+        }
+        if (i < n) mask[i] = keep ? 1 : 0;
+    }
+}
+
+__global__ __launch_bounds__(kThreads) void select_clear_kernel(unsigned* words) {
+    const unsigned i = blockIdx.x * kThreads + threadIdx.x;
+    if (i < kStateWords) words[i] = 0u;
+}
+
+__global__ __launch_bounds__(kThreads) void select_all_kernel(uint8_t* mask, long long n, uint8_t value) {
+    const long long i = (long long)blockIdx.x * kThreads + threadIdx.x;
+    if (i < n) mask[i] = value;
+}
+
+// The weights of a block's kernels are loaded as one coalesced run and parked in LDS, as in assign_kernel.
+template <typename T>
+__global__ __launch_bounds__(kThreads) void norm_key_kernel(const T* __restrict__ w, long long n, Library lib, int K,
+                                                            const int32_t* __restrict__ pid,
+                                                            unsigned long long* __restrict__ key, SelectState* st) {
+    __shared__ __attribute__((aligned(16))) T tile[kThreads * 9];
+    __shared__ uint32_t masks[126];
+    __shared__ unsigned hist[kBins];
+    if ((int)threadIdx.x < K) masks[threadIdx.x] = lib.mask[threadIdx.x];
+    for (int b = threadIdx.x; b < kBins; b += kThreads) hist[b] = 0u;
+    constexpr int PER = 16 / (int)sizeof(T);
+    for (long long first = (long long)blockIdx.x * kThreads; first < n; first += (long long)gridDim.x * kThreads) {
+        const int count = (int)(n - first < kThreads ? n - first : kThreads);
+        const T* src = w + first * 9;
+        const bool aligned = (reinterpret_cast<uintptr_t>(src) & 15u) == 0;
+        const int pieces = aligned ? count * 9 / PER : 0;
+        const int32_t q = (int)threadIdx.x < count ? pid[first + threadIdx.x] : 0;
+        __syncthreads();                                      // (the tile's readers of the round before are done)
+        for (int i = threadIdx.x; i < pieces; i += kThreads)
+            reinterpret_cast<float4v*>(tile)[i] = reinterpret_cast<const float4v*>(src)[i];
+        for (int i = pieces * PER + threadIdx.x; i < count * 9; i += kThreads) tile[i] = src[i];
+        __syncthreads();
+        if ((int)threadIdx.x < count) {
+            const unsigned long long e = norm_key(tile + threadIdx.x * 9, masks[(q >= 0 && q < K) ? q : 0]);
+            key[first + threadIdx.x] = e;
+            atomicAdd(&hist[(unsigned)(e >> 52)], 1u);
+        }
+    }
+    __syncthreads();
+    for (int b = threadIdx.x; b < kBins; b += kThreads)
+        if (hist[b]) atomicAdd(&st->hist0[blockIdx.x % kReplicas][b], hist[b]);
+}
+
+// Where the k-th largest lies among `bins` counted digits: the digit, and its rank (from 1) among the keys with that
+// digit.  All threads of a workgroup of kSelThreads; `scratch` is 18 words of LDS.
+template <int BINS>
+__device__ __forceinline__ void find_digit(const unsigned* __restrict__ hist, int replicas, unsigned k, unsigned* scratch,
+                                           unsigned* digit, unsigned* rank) {
+    constexpr int PER = BINS / kSelThreads;
+    unsigned c[PER], sum = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {                           // largest digit first
+        const int b = BINS - 1 - ((int)threadIdx.x * PER + j);
+        c[j] = 0;
+        for (int r = 0; r < replicas; ++r) c[j] += hist[r * BINS + b];
+        sum += c[j];
+    }
+    unsigned incl = sum;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
+    }
+    __syncthreads();
+    if (lane == 63) scratch[wave] = incl;
+    if (threadIdx.x == 0) {
+        scratch[16] = 0;
+        scratch[17] = 1;
+    }
+    __syncthreads();
+    unsigned before = incl - sum;
+    for (int w = 0; w < wave; ++w) before += scratch[w];
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        if (before < k && k <= before + c[j]) {
+            scratch[16] = (unsigned)(BINS - 1 - ((int)threadIdx.x * PER + j));
+            scratch[17] = k - before;
+        }
+        before += c[j];
+    }
+    __syncthreads();
+    *digit = scratch[16];
+    *rank = scratch[17];
+    __syncthreads();
+}
+
+// A workgroup's keys, kAhead per thread in flight at a time.
+constexpr int kAhead = 8;
+template <typename Fn>
+__device__ __forceinline__ void for_keys(const unsigned long long* __restrict__ key, long long n, Fn fn) {
+    constexpr long long RUN = (long long)kSelThreads * kAhead;
+    for (long long first = (long long)blockIdx.x * RUN; first < n; first += (long long)gridDim.x * RUN) {
+        unsigned long long e[kAhead];
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const long long i = first + j * kSelThreads + threadIdx.x;
+            e[j] = i < n ? key[i] : 0ull;
+        }
+#pragma unroll
+        for (int j = 0; j < kAhead; ++j) {
+            const long long i = first + j * kSelThreads + threadIdx.x;
+            fn(e[j], i, i < n);
+        }
+    }
+}
+
+__global__ __launch_bounds__(kSelThreads) void select_count_kernel(const unsigned long long* __restrict__ key, long long n,
+                                                                   unsigned k, SelectState* st) {
+    __shared__ unsigned hist[kBins1], scratch[18];
+    for (int b = threadIdx.x; b < kBins1; b += kSelThreads) hist[b] = 0u;
+    unsigned exponent, rank;
+    find_digit<kBins>(&st->hist0[0][0], kReplicas, k, scratch, &exponent, &rank);
+    for_keys(key, n, [&](unsigned long long e, long long, bool there) {
+        if (there && (unsigned)(e >> 52) == exponent) atomicAdd(&hist[(unsigned)(e >> 42) & (kBins1 - 1)], 1u);
+    });
+    __syncthreads();
+    for (int b = threadIdx.x; b < kBins1; b += kSelThreads)
+        if (hist[b]) atomicAdd(&st->hist1[b], hist[b]);
+}
+
+__device__ __forceinline__ unsigned first_bits(const SelectState* st, unsigned k, unsigned* scratch, unsigned* rank) {
+    unsigned exponent, next;
+    find_digit<kBins>(&st->hist0[0][0], kReplicas, k, scratch, &exponent, rank);
+    find_digit<kBins1>(st->hist1, 1, *rank, scratch, &next, rank);
+    return exponent << 10 | next;
+}
+
+__global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const unsigned long long* __restrict__ key, long long n,
+                                                                    unsigned k, SelectState* st) {
+    __shared__ unsigned scratch[18], found, at0;
+    __shared__ unsigned index[kSelThreads];
+    if (threadIdx.x == 0) found = 0u;
+    unsigned rank;
+    const unsigned prefix = first_bits(st, k, scratch, &rank);
+    for_keys(key, n, [&](unsigned long long e, long long i, bool there) {
+        if (there && (unsigned)(e >> 42) == prefix) {
+            const unsigned at = atomicAdd(&found, 1u);
+            if (at < (unsigned)kSelThreads) index[at] = (unsigned)i;
+        }
+    });
+    __syncthreads();
+    // (more than a workgroup can hold: the list counts as overflown)
+    const unsigned m = found;
+    if (m == 0) return;
+    if (threadIdx.x == 0) at0 = atomicAdd(&st->listed, m <= (unsigned)kSelThreads ? m : (unsigned)kListCap + 1u);
+    __syncthreads();
+    const unsigned at = at0 + threadIdx.x;
+    if (m <= (unsigned)kSelThreads && threadIdx.x < m && at < (unsigned)kListCap) {
+        st->list_key[at] = key[index[threadIdx.x]];
+        st->list_index[at] = index[threadIdx.x];
+    }
+}
+
+// One workgroup: the k-th largest among the gathered keys, equal ones by index.
+__global__ __launch_bounds__(kSelThreads) void select_finish_kernel(unsigned k, SelectState* st) {
+    __shared__ unsigned scratch[18];
+    __shared__ uint4v slots[8];
+    unsigned rank;
+    const unsigned prefix = first_bits(st, k, scratch, &rank);
+    const unsigned m = st->listed;
+    if (m > (unsigned)kListCap) {
+        if (threadIdx.x == 0) st->slow = 1u;
+        return;
+    }
+    constexpr int PER = kListCap / kSelThreads;
+    unsigned long long key[PER];
+    unsigned late[PER];                                       // ~index: equal keys, lowest index first
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const unsigned at = (unsigned)j * kSelThreads + threadIdx.x;
+        key[j] = at < m ? st->list_key[at] : 0ull;
+        late[j] = at < m ? ~st->list_index[at] : 0u;
+    }
+    unsigned turn = 0;
+    const unsigned long long t = block_kth(key, (unsigned long long)prefix << 42, 42, rank, slots, turn);
+    unsigned above = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        above += (unsigned)__popcll(__ballot(key[j] > t));
+        if (key[j] != t) late[j] = 0u;
+    }
+    above = block_total(above, slots, turn);
+    const unsigned bound = block_kth(late, 0u, 32, rank - above, slots, turn);
+    if (threadIdx.x == 0) {
+        st->threshold = t;
+        st->last_index = ~bound;
+    }
+}
+
+// The bits below the first 21, 14 at a time, where too many keys share those.
+__device__ __forceinline__ unsigned long long slow_prefix(const SelectState* st, unsigned k, int passes, unsigned* scratch,
+                                                          unsigned* rank) {
+    unsigned long long prefix = first_bits(st, k, scratch, rank);
+    for (int p = 0; p < passes; ++p) {
+        unsigned digit;
+        find_digit<kSlowBins>(st->slow_hist[p], 1, *rank, scratch, &digit, rank);
+        prefix = prefix << kSlowBits | digit;
+    }
+    return prefix;
+}
+__global__ __launch_bounds__(kSelThreads) void select_slow_kernel(const unsigned long long* __restrict__ key, long long n,
+                                                                  unsigned k, int pass, SelectState* st) {
+    if (!st->slow) return;
+    __shared__ unsigned hist[kSlowBins], scratch[18];
+    for (int b = threadIdx.x; b < kSlowBins; b += kSelThreads) hist[b] = 0u;
+    unsigned rank;
+    const unsigned long long prefix = slow_prefix(st, k, pass, scratch, &rank);
+    const int top = 42 - kSlowBits * pass, low = top - kSlowBits;
+    for_keys(key, n, [&](unsigned long long e, long long, bool there) {
+        // (equal keys by the thousand are what brings a call here: a wave whose hits agree adds once)
+        const bool hit = there && (e >> top) == prefix;
+        const unsigned d = (unsigned)(e >> low) & (unsigned)(kSlowBins - 1);
+        const unsigned long long hits = __ballot(hit);
+        if (!hits) return;
+        const unsigned first = __shfl(d, __ffsll((long long)hits) - 1);
+        if (__ballot(hit && d == first) == hits) {
+            if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], (unsigned)__popcll(hits));
+        } else if (hit) {
+            atomicAdd(&hist[d], 1u);
+        }
+    });
+    __syncthreads();
+    for (int b = threadIdx.x; b < kSlowBins; b += kSelThreads)
+        if (hist[b]) atomicAdd(&st->slow_hist[pass][b], hist[b]);
+}
+
+// Runs of kernels: run r of kRuns is kernels r*run .. r*run + run - 1.
+__host__ __device__ __forceinline__ long long run_length(long long n) {
+    const long long per = (n + kRuns - 1) / kRuns;
+    return (per + kSelThreads - 1) / kSelThreads * kSelThreads;
+}
+__global__ __launch_bounds__(kSelThreads) void select_ties_kernel(const unsigned long long* __restrict__ key, long long n,
+                                                                  unsigned k, SelectState* st) {
+    if (!st->slow) return;
+    __shared__ unsigned scratch[18];
+    __shared__ uint4v slots[8];
+    unsigned rank, turn = 0;
+    const unsigned long long t = slow_prefix(st, k, 3, scratch, &rank);
+    const long long run = run_length(n);
+    for (int r = blockIdx.x; r < kRuns; r += gridDim.x) {
+        const long long first = (long long)r * run;
+        unsigned c = 0;
+        for (long long i = first + threadIdx.x; i < first + run && i - threadIdx.x < n; i += kSelThreads)
+            c += (unsigned)__popcll(__ballot(i < n && key[i] == t));
+        c = block_total(c, slots, turn);
+        if (threadIdx.x == 0) st->run_ties[r] = c;
+    }
+    if (threadIdx.x == 0 && blockIdx.x == 0) {
+        st->threshold = t;
+        st->ties_kept = rank;
+    }
+}
+
+// VEC: four keys and one word of marks per thread and round (n a multiple of 4, aligned buffers)
+template <bool VEC>
+__global__ __launch_bounds__(kSelThreads) void mark_kept_kernel(const unsigned long long* __restrict__ key, long long n,
+                                                                const SelectState* st, uint8_t* __restrict__ mask) {
+    const unsigned long long t = st->threshold;
+    if (!st->slow) {
+        const unsigned last = st->last_index;
+        auto kept = [&](unsigned long long e, long long i) { return e > t || (e == t && (unsigned)i <= last); };
+        const long long at = (long long)blockIdx.x * kSelThreads + threadIdx.x, step = (long long)gridDim.x * kSelThreads;
+        if constexpr (VEC) {
+            typedef unsigned long long u64x2 __attribute__((ext_vector_type(2)));
+            for (long long i = at * 4; i < n; i += step * 4) {
+                const u64x2 a = *reinterpret_cast<const u64x2*>(key + i), b = *reinterpret_cast<const u64x2*>(key + i + 2);
+                unsigned m = kept(a.x, i) ? 1u : 0u;
+                m |= kept(a.y, i + 1) ? 0x100u : 0u;
+                m |= kept(b.x, i + 2) ? 0x10000u : 0u;
+                m |= kept(b.y, i + 3) ? 0x1000000u : 0u;
+                *reinterpret_cast<unsigned*>(mask + i) = m;
+            }
+        } else {
+            for (long long i = at; i < n; i += step) mask[i] = kept(key[i], i) ? 1 : 0;
+        }
+        return;
+    }
+    __shared__ uint4v slots[8];
+    unsigned turn = 0;
+    const unsigned ties_kept = st->ties_kept;
+    const long long run = run_length(n);
+    for (int r = blockIdx.x; r < kRuns; r += gridDim.x) {
+        unsigned before = 0;
+        for (int q = threadIdx.x; q < r; q += kSelThreads) before += st->run_ties[q];
+        for (int d = 32; d > 0; d >>= 1) before += __shfl_down(before, d);
+        before = block_total(before, slots, turn);            // (a wave's lane 0 holds its sum)
+        const long long first = (long long)r * run;
+        for (long long i = first + threadIdx.x; i < first + run && i - threadIdx.x < n; i += kSelThreads) {
+            const unsigned long long e = i < n ? key[i] : 0ull;
+            const bool tie = i < n && e == t;
+            const unsigned long long ties = __ballot(tie);
+            unsigned before_wave;
+            const unsigned total = block_total((unsigned)__popcll(ties), slots, turn, &before_wave);
+            const unsigned rank = before + before_wave + (unsigned)__popcll(ties & ((1ull << (threadIdx.x & 63)) - 1ull));
+            before += total;
+            if (i < n) mask[i] = (e > t || (tie && rank < ties_kept)) ? 1 : 0;
+        }
+    }
 }
 
 size_t round256(size_t b) {
@@ -253,12 +662,9 @@ extern "C" int pconv_select_connectivity_device(const void* w, int dtype, long l
     if (!workspace_bytes || n < 0 || (dtype != PCONV_F32 && dtype != PCONV_F16)) return PCONV_EINVAL;
     if (n > 0x7FFFFFFFll) return PCONV_ESHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // workspace: keys in, keys out (8 bytes each), indices in, indices out (4 bytes each), the sort's own scratch
-    size_t sort_bytes = 0;
-    PCONV_HIP(hipcub::DeviceRadixSort::SortPairsDescending(nullptr, sort_bytes, (const uint64_t*)nullptr, (uint64_t*)nullptr,
-                                                          (const uint32_t*)nullptr, (uint32_t*)nullptr, (int)n, 0, 64, st));
-    const size_t kb = round256((size_t)n * 8), ib = round256((size_t)n * 4);
-    const size_t need = 2 * kb + 2 * ib + round256(sort_bytes) + 256;
+    // workspace: the keys and the selection's state (counts, list)
+    const size_t kb = round256((size_t)n * 8);
+    const size_t need = n <= kSmallN ? 256 : kb + round256(sizeof(SelectState));
     if (!workspace) {
         *workspace_bytes = need;
         return PCONV_OK;
@@ -272,26 +678,54 @@ extern "C" int pconv_select_connectivity_device(const void* w, int dtype, long l
     }
     if (*workspace_bytes < need || reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return PCONV_ESCRATCH;
     if (n == 0) return PCONV_OK;
-    long long k = (long long)std::floor(keep * (double)n + 0.5);
-    k = k < 0 ? 0 : (k > n ? n : k);
-    char* base = static_cast<char*>(workspace);
-    uint64_t* key_in = reinterpret_cast<uint64_t*>(base);
-    uint64_t* key_out = reinterpret_cast<uint64_t*>(base + kb);
-    uint32_t* idx_in = reinterpret_cast<uint32_t*>(base + 2 * kb);
-    uint32_t* idx_out = reinterpret_cast<uint32_t*>(base + 2 * kb + ib);
-    void* sort_tmp = base + 2 * kb + 2 * ib;
-    const dim3 grid(grid_for(n)), block(kThreads);
-    if (dtype == PCONV_F32)
-        hipLaunchKernelGGL(norm_key_kernel<float>, grid, block, 0, st, static_cast<const float*>(w), n, l, K, pid, key_in,
-                           idx_in);
+    long long kept = (long long)std::floor(keep * (double)n + 0.5);
+    kept = kept < 0 ? 0 : (kept > n ? n : kept);
+    const unsigned k = (unsigned)kept;
+    const bool f32 = dtype == PCONV_F32;
+    if (kept == 0 || kept == n) {                              // nothing to choose
+        hipLaunchKernelGGL(select_all_kernel, dim3(grid_for(n)), dim3(kThreads), 0, st, mask, n, (uint8_t)(kept ? 1 : 0));
+        PCONV_HIP(hipGetLastError());
+        return PCONV_OK;
+    }
+    if (n <= kSmallN) {
+#define PCONV_SELECT(T, PER)                                                                                             \
+    hipLaunchKernelGGL((select_small_kernel<T, PER>), dim3(1), dim3(kSelThreads), 0, st, static_cast<const T*>(w), (int)n, l, \
+                       K, pid, k, mask)
+        if (n <= kSelThreads) {
+            if (f32) PCONV_SELECT(float, 1); else PCONV_SELECT(_Float16, 1);
+        } else if (n <= 4 * kSelThreads) {
+            if (f32) PCONV_SELECT(float, 4); else PCONV_SELECT(_Float16, 4);
+        } else {
+            if (f32) PCONV_SELECT(float, 8); else PCONV_SELECT(_Float16, 8);
+        }
+#undef PCONV_SELECT
+        PCONV_HIP(hipGetLastError());
+        return PCONV_OK;
+    }
+    unsigned long long* key = static_cast<unsigned long long*>(workspace);
+    SelectState* state = reinterpret_cast<SelectState*>(static_cast<char*>(workspace) + kb);
+    hipLaunchKernelGGL(select_clear_kernel, dim3((kStateWords + kThreads - 1) / kThreads), dim3(kThreads), 0, st,
+                       reinterpret_cast<unsigned*>(state));
+    // (each block counts the exponents of several runs of kernels before it adds them to the counts in memory)
+    const dim3 norm_grid((unsigned)std::min<long long>(grid_for(n), 2048)), block(kThreads);
+    if (f32)
+        hipLaunchKernelGGL(norm_key_kernel<float>, norm_grid, block, 0, st, static_cast<const float*>(w), n, l, K, pid, key,
+                           state);
     else
-        hipLaunchKernelGGL(norm_key_kernel<_Float16>, grid, block, 0, st, static_cast<const _Float16*>(w), n, l, K, pid,
-                           key_in, idx_in);
-    PCONV_HIP(hipGetLastError());
-    // a stable sort, largest key first: equal norms stay in ascending index order
-    PCONV_HIP(hipcub::DeviceRadixSort::SortPairsDescending(sort_tmp, sort_bytes, key_in, key_out, idx_in, idx_out, (int)n, 0,
-                                                          64, st));
-    hipLaunchKernelGGL(mark_kept_kernel, grid, block, 0, st, idx_out, n, k, mask);
+        hipLaunchKernelGGL(norm_key_kernel<_Float16>, norm_grid, block, 0, st, static_cast<const _Float16*>(w), n, l, K, pid,
+                           key, state);
+    // (128 workgroups read 13 MB of keys in 4 us, and their counts are half as many additions in memory as 256's)
+    const dim3 sel(kSelThreads);
+    const dim3 pass_grid((unsigned)std::min<long long>((n + kAhead * kSelThreads - 1) / (kAhead * kSelThreads), 128));
+    hipLaunchKernelGGL(select_count_kernel, pass_grid, sel, 0, st, key, n, k, state);
+    hipLaunchKernelGGL(select_gather_kernel, pass_grid, sel, 0, st, key, n, k, state);
+    hipLaunchKernelGGL(select_finish_kernel, dim3(1), sel, 0, st, k, state);
+    for (int p = 0; p < 3; ++p) hipLaunchKernelGGL(select_slow_kernel, pass_grid, sel, 0, st, key, n, k, p, state);
+    hipLaunchKernelGGL(select_ties_kernel, pass_grid, sel, 0, st, key, n, k, state);
+    if (n % 4 == 0 && reinterpret_cast<uintptr_t>(mask) % 4 == 0)
+        hipLaunchKernelGGL(mark_kept_kernel<true>, pass_grid, sel, 0, st, key, n, state, mask);
+    else
+        hipLaunchKernelGGL(mark_kept_kernel<false>, pass_grid, sel, 0, st, key, n, state, mask);
     PCONV_HIP(hipGetLastError());
     return PCONV_OK;
 }

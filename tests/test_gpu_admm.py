@@ -134,6 +134,37 @@ def test_device_connectivity_selection_matches_the_oracle_bit_for_bit(dtype, kee
     assert int(mask.min()) == 7
 
 
+@pytest.mark.parametrize("n,values,keep", [
+    (1, 0, 1.0), (63, 0, 0.5), (1025, 3, 0.4), (8192, 0, 0.28), (8192, 2, 0.3), (3000, 1, 0.7),      # one workgroup, to its last size
+    (8193, 0, 0.28), (8193, 1, 0.5), (100003, 0, 0.15), (100004, 0, 0.0001), (262144, 5, 0.61),
+    (300000, 1, 0.999), (1048577, 40, 0.28)])
+def test_device_connectivity_selection_over_its_sizes(n, values, keep):
+    """One workgroup and several passes; `values` > 0: weights from so few values that thousands of norms are equal (the
+    list of candidates overflows, the ties are ranked by index), 0: all different.  Indices and marks are exact."""
+    import torch
+    import paper_2001_07710_amd as pc
+    from workloads import layers as L
+    print("[case]", n, values, keep, flush=True)
+    r = np.random.default_rng(n + values)
+    w = r.standard_normal((n, 9), dtype=np.float32) if not values else (
+        r.integers(0, values + 1, size=(n, 9)).astype(np.float32) * 0.25 * (r.random((n, 1)) < 0.6))
+    w = w.astype(np.float32)
+    lib = np.array(L.drawn_library(4, 8), dtype=np.uint16)
+    w4 = w.reshape(n, 1, 3, 3)
+    pid = oracle.assign_patterns(w4, lib)
+    ref = oracle.select_connectivity(w4, lib, pid, keep)
+    need = pc.select_connectivity_device_workspace(n)
+    ws = torch.empty(need, dtype=torch.uint8, device="cuda").fill_(0xA5)
+    mask = torch.full((n + 1,), 7, dtype=torch.uint8, device="cuda")
+    pc.select_connectivity_device(torch.from_numpy(w).cuda(), pc.F32, n, lib,
+                                  torch.from_numpy(pid.astype(np.int32).reshape(-1)).cuda(), keep, mask, ws, need,
+                                  torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = mask.cpu().numpy()
+    np.testing.assert_array_equal(got[:n], np.asarray(ref, dtype=np.uint8).reshape(-1))
+    assert got[n] == 7
+
+
 def test_assign_then_select_on_the_device_feed_pack_like_the_host_steps():
     """The two device steps chained, their outputs handed to pconv_pack: the packed layer is the one the host steps
     give (canonical form compared bit for bit)."""
