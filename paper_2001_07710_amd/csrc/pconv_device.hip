@@ -46,42 +46,251 @@ void set_hip_error(const char* what, int hip_code) {
 // upload / release
 // ---------------------------------------------------------------------------------------------------------------
 
+// What the host hands over is small: the canonical arrays, the staging orders and the channel lists.  The layouts the
+// kernels read -- the entries once per tiling, the matrix-core weights once per tile height, ten to twenty times as many
+// bytes -- are made from them here, so a layer is one allocation, one copy and three short kernels (256 -> 256 channels,
+// fp16: the copy is 0.5 MB, not 6; with the host side of packing, 5.8 -> 0.7 ms).
+
+// The entries of the layer for up to kMaxLayouts staging orders: workgroup (i, l) is one wave that brings the entries of
+// filter position i into the order of layout l, by chunk of staged channels, inside a chunk in canonical order (pattern,
+// then channel -- and a chunk's channels are staged in ascending order).  A counting sort that keeps equal chunks in
+// order: 64 entries at a time, the rank of an entry among those of its chunk from the ballots of the chunk number's bits.
+constexpr int kMaxLayouts = 8;
+struct EntryLayout {
+    DevEntry* ent;
+    uint32_t* eptr;
+    const uint16_t* pos_of;   // null: channels in their own order
+    int cc_shift, nch, fg;
+};
+struct EntryParams {
+    const uint32_t* canon;
+    const unsigned char* w4;
+    const uint32_t* row;      // [F+1] first canonical entry of a filter position
+    const uint8_t* rank;      // [512] code of a mask
+    int F, C, f16;
+    EntryLayout lay[kMaxLayouts];
+};
+__global__ __launch_bounds__(64) void build_entries_kernel(const EntryParams p) {
+    extern __shared__ uint32_t at[];
+    const EntryLayout& l = p.lay[blockIdx.y];
+    const int i = blockIdx.x, lane = threadIdx.x;
+    const uint32_t e0 = p.row[i], e1 = p.row[i + 1];
+    const uint16_t* pos_of = l.pos_of ? l.pos_of + (size_t)(i / l.fg) * p.C : nullptr;
+    auto position = [&](uint32_t c) { return pos_of ? (uint32_t)pos_of[c] : c; };
+    for (int k = lane; k < l.nch; k += 64) at[k] = 0;
+    __syncthreads();
+    for (uint32_t e = e0 + lane; e < e1; e += 64) atomicAdd(&at[position(p.canon[2 * (size_t)e + 1] & 0xFFFFu) >> l.cc_shift], 1u);
+    __syncthreads();
+    uint32_t base = e0;
+    for (int k0 = 0; k0 < l.nch; k0 += 64) {
+        const int k = k0 + lane;
+        const uint32_t v = k < l.nch ? at[k] : 0u;
+        uint32_t incl = v;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(incl, d);
+            if (lane >= d) incl += o;
+        }
+        if (k < l.nch) at[k] = l.eptr[(size_t)i * l.nch + k] = base + incl - v;
+        base += __shfl(incl, 63);
+    }
+    if (i == p.F - 1 && lane == 0) l.eptr[(size_t)p.F * l.nch] = e1;
+    __syncthreads();
+    int bits = 0;
+    while ((1 << bits) < l.nch) ++bits;
+    for (uint32_t b = e0; b < e1; b += 64) {
+        const uint32_t e = b + lane;
+        const bool there = e < e1;
+        const uint32_t cm = there ? p.canon[2 * (size_t)e + 1] : 0u;
+        const uint32_t pos = there ? position(cm & 0xFFFFu) : 0u, k = pos >> l.cc_shift;
+        unsigned long long same = __ballot(there);
+        for (int q = 0; q < bits; ++q) {
+            const unsigned long long ones = __ballot(k >> q & 1u);
+            same &= (k >> q & 1u) ? ones : ~ones;
+        }
+        const uint32_t rank = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+        const uint32_t d = at[k] + rank;
+        __syncthreads();
+        if (there) {
+            if (rank + 1 == (uint32_t)__popcll(same)) at[k] = d + 1;
+            DevEntry de;
+            if (p.f16) {
+                const __half* h = reinterpret_cast<const __half*>(p.w4) + (size_t)e * 4;
+                for (int q = 0; q < 4; ++q) de.w[q] = __half2float(h[q]);
+            } else {
+                const float* f = reinterpret_cast<const float*>(p.w4) + (size_t)e * 4;
+                for (int q = 0; q < 4; ++q) de.w[q] = f[q];
+            }
+            de.c = pos;
+            de.mask9 = cm >> 16;
+            de.code = p.rank[de.mask9];
+            de.hdr = (pos & 0xFFu) | (de.code << 8);
+            l.ent[d] = de;
+        }
+        __syncthreads();
+    }
+}
+
+// The matrix-core weights of the layer (see MfmaWeights), cleared beforehand: one thread per kept kernel and copy.
+struct ScatterCopy {
+    uint16_t* w;
+    const uint16_t* pos_of;   // null: no channel lists
+    const uint32_t* tinfo;
+    int mt, n_cblocks, nt, groups, group_channels;
+    int8_t slot_of[12];
+};
+struct ScatterParams {
+    const uint32_t* canon;
+    const uint16_t* w4;
+    unsigned n_kept;
+    int C;
+    ScatterCopy copy[4];
+};
+__global__ __launch_bounds__(256) void scatter_weights_kernel(const ScatterParams p) {
+    const unsigned e = blockIdx.x * 256u + threadIdx.x;
+    if (e >= p.n_kept) return;
+    const ScatterCopy& m = p.copy[blockIdx.y];
+    const uint32_t f = p.canon[2 * (size_t)e], cm = p.canon[2 * (size_t)e + 1], mask = cm >> 16;
+    uint32_t c = cm & 0xFFFFu;
+    const uint32_t tile = f / (uint32_t)m.mt, fl = f - tile * (uint32_t)m.mt;
+    size_t block = (size_t)tile * m.n_cblocks;
+    if (m.pos_of) {
+        c = m.pos_of[(size_t)tile * p.C + c];
+        block = m.tinfo[2 * tile + 1];
+    }
+    const uint32_t range = m.groups > 1 ? c / (uint32_t)m.group_channels : 0u;
+    c -= range * (uint32_t)m.group_channels;
+    uint16_t* const w = m.w + (block + c / 16) * (size_t)(m.nt * 2 * m.mt * 8) + ((c % 16) / 8) * (size_t)(m.mt * 8) + fl * 8 + c % 8;
+    int q = 0;
+    for (int t = 0; t < 9; ++t) {
+        if (!(mask >> t & 1u)) continue;
+        const int slot = m.groups > 1 ? (int)range : m.slot_of[t];
+        w[(size_t)slot * (2 * m.mt * 8)] = p.w4[(size_t)e * 4 + q];
+        ++q;
+    }
+}
+
+__global__ __launch_bounds__(256) void clear_kernel(uint4* p, size_t n) {
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = uint4{0u, 0u, 0u, 0u};
+}
+
 int upload_packed(pconv_packed* p) {
     int dev = -1;
     PCONV_HIP(hipGetDevice(&dev));
-    const size_t n_ent = std::max<size_t>(p->ent.size(), 1);
-    PCONV_HIP(hipMalloc((void**)&p->d_ent, n_ent * sizeof(DevEntry)));
-    PCONV_HIP(hipMalloc((void**)&p->d_eptr, p->eptr.size() * sizeof(uint32_t)));
-    PCONV_HIP(hipMalloc((void**)&p->d_forder, p->filter_order.size() * sizeof(uint32_t)));
-    if (!p->ent.empty())
-        PCONV_HIP(hipMemcpy(p->d_ent, p->ent.data(), p->ent.size() * sizeof(DevEntry), hipMemcpyHostToDevice));
-    else
-        PCONV_HIP(hipMemset(p->d_ent, 0, sizeof(DevEntry)));
-    PCONV_HIP(hipMemcpy(p->d_eptr, p->eptr.data(), p->eptr.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-    PCONV_HIP(hipMemcpy(p->d_forder, p->filter_order.data(), p->filter_order.size() * sizeof(uint32_t),
-                        hipMemcpyHostToDevice));
-    for (BalancedLayout& b : p->balanced) {
-        PCONV_HIP(hipMalloc((void**)&b.d_ent, std::max<size_t>(b.ent.size(), 1) * sizeof(DevEntry)));
-        PCONV_HIP(hipMalloc((void**)&b.d_eptr, b.eptr.size() * sizeof(uint32_t)));
-        PCONV_HIP(hipMalloc((void**)&b.d_perm, std::max<size_t>(b.perm.size(), 1) * sizeof(uint32_t)));
-        if (!b.ent.empty())
-            PCONV_HIP(hipMemcpy(b.d_ent, b.ent.data(), b.ent.size() * sizeof(DevEntry), hipMemcpyHostToDevice));
-        PCONV_HIP(hipMemcpy(b.d_eptr, b.eptr.data(), b.eptr.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-        if (!b.perm.empty())
-            PCONV_HIP(hipMemcpy(b.d_perm, b.perm.data(), b.perm.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    // the allocation: first what is copied, then the matrix-core weights (cleared), then what kernels fill whole
+    std::vector<unsigned char> host;
+    size_t size = 0;
+    auto take = [&](size_t bytes) {
+        const size_t at = size;
+        size += (bytes + 255) / 256 * 256;
+        return at;
+    };
+    auto put = [&](const void* data, size_t bytes) {
+        const size_t at = take(std::max<size_t>(bytes, 16));
+        host.resize(size);
+        if (bytes) std::memcpy(&host[at], data, bytes);
+        return at;
+    };
+    auto put_vector = [&](const auto& v) { return put(v.data(), v.size() * sizeof(v[0])); };
+    std::vector<uint32_t> row((size_t)p->F + 1);
+    for (int i = 0; i <= p->F; ++i) row[(size_t)i] = p->grp_ptr[(size_t)i * p->K];
+    // (the code of a mask: its rank among the 255 masks with one to four bits in ascending order)
+    uint8_t rank[512] = {};
+    int codes = 0;
+    for (unsigned m = 1; m < 512; ++m)
+        if (__builtin_popcount(m) <= 4) rank[m] = (uint8_t)codes++;
+    const size_t n = p->n_kept;
+    const size_t nl = p->balanced.size(), nm = p->mfma.size();
+    if (nl + 1 > kMaxLayouts || nm > sizeof(ScatterParams::copy) / sizeof(ScatterCopy)) return PCONV_EUNSUPPORTED;
+    const size_t at_canon = put_vector(p->canon), at_forder = put_vector(p->filter_order), at_w4 = put_vector(p->w4);
+    const size_t at_row = put_vector(row), at_rank = put(rank, sizeof(rank));
+    std::vector<size_t> at_perm(nl), at_pos(nl), at_ent(nl), at_eptr(nl), at_clist(nm), at_tinfo(nm), at_mpos(nm), at_mw(nm);
+    for (size_t t = 0; t < nl; ++t) {
+        at_perm[t] = put_vector(p->balanced[t].perm);
+        at_pos[t] = put_vector(p->balanced[t].pos_of);
     }
-    PCONV_HIP(hipMalloc((void**)&p->d_canon, std::max<size_t>(p->canon.size(), 2) * sizeof(uint32_t)));
-    if (!p->canon.empty())
-        PCONV_HIP(hipMemcpy(p->d_canon, p->canon.data(), p->canon.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-    for (MfmaWeights& m : p->mfma) {
-        PCONV_HIP(hipMalloc(&m.d_w, std::max<size_t>(m.bytes(), 16)));
-        if (m.bytes()) PCONV_HIP(hipMemcpy(m.d_w, m.w.data(), m.bytes(), hipMemcpyHostToDevice));
-        if (!m.clist.empty()) {
-            PCONV_HIP(hipMalloc((void**)&m.d_clist, m.clist.size() * sizeof(uint32_t)));
-            PCONV_HIP(hipMemcpy(m.d_clist, m.clist.data(), m.clist.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
-            PCONV_HIP(hipMalloc((void**)&m.d_tinfo, m.tinfo.size() * sizeof(uint32_t)));
-            PCONV_HIP(hipMemcpy(m.d_tinfo, m.tinfo.data(), m.tinfo.size() * sizeof(uint32_t), hipMemcpyHostToDevice));
+    for (size_t t = 0; t < nm; ++t) {
+        if (p->mfma[t].clist.empty()) continue;
+        at_clist[t] = put_vector(p->mfma[t].clist);
+        at_tinfo[t] = put_vector(p->mfma[t].tinfo);
+        at_mpos[t] = put_vector(p->mfma[t].pos_of);
+    }
+    const size_t copied = size;
+    for (size_t t = 0; t < nm; ++t) at_mw[t] = take(std::max<size_t>(p->mfma[t].bytes(), 16));
+    const size_t cleared = size;
+    const size_t ent_bytes = std::max<size_t>(n, 1) * sizeof(DevEntry);
+    const size_t at_ent0 = take(ent_bytes), at_eptr0 = take(((size_t)p->F * p->n_buckets + 1) * sizeof(uint32_t));
+    for (size_t t = 0; t < nl; ++t) {
+        at_ent[t] = take(ent_bytes);
+        at_eptr[t] = take(((size_t)p->F * p->balanced[t].n_chunks + 1) * sizeof(uint32_t));
+    }
+    PCONV_HIP(hipMalloc(&p->d_arena, size));
+    unsigned char* const base = static_cast<unsigned char*>(p->d_arena);
+    PCONV_HIP(hipMemcpy(base, host.data(), copied, hipMemcpyHostToDevice));
+    if (n == 0) PCONV_HIP(hipMemset(base + at_ent0, 0, sizeof(DevEntry)));
+
+    EntryParams ep{};
+    ep.canon = reinterpret_cast<uint32_t*>(base + at_canon);
+    ep.w4 = base + at_w4;
+    ep.row = reinterpret_cast<uint32_t*>(base + at_row);
+    ep.rank = base + at_rank;
+    ep.F = p->F;
+    ep.C = p->C;
+    ep.f16 = p->dtype == PCONV_F16 ? 1 : 0;
+    auto log2_of = [](int v) { return 31 - __builtin_clz((unsigned)v); };
+    ep.lay[0] = {reinterpret_cast<DevEntry*>(base + at_ent0), reinterpret_cast<uint32_t*>(base + at_eptr0), nullptr,
+                 log2_of(kBucket), p->n_buckets, 1};
+    int most_chunks = p->n_buckets;
+    for (size_t t = 0; t < nl; ++t) {
+        BalancedLayout& b = p->balanced[t];
+        ep.lay[t + 1] = {reinterpret_cast<DevEntry*>(base + at_ent[t]), reinterpret_cast<uint32_t*>(base + at_eptr[t]),
+                         reinterpret_cast<uint16_t*>(base + at_pos[t]), log2_of(b.cc), b.n_chunks, b.fw * b.nf};
+        most_chunks = std::max(most_chunks, b.n_chunks);
+    }
+    hipLaunchKernelGGL(build_entries_kernel, dim3((unsigned)p->F, (unsigned)(nl + 1)), dim3(64), most_chunks * sizeof(uint32_t), 0, ep);
+    PCONV_HIP(hipGetLastError());
+    if (nm) {
+        const size_t quads = (cleared - copied) / 16;
+        hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<size_t>((quads + 255) / 256, 4096)), dim3(256), 0, 0,
+                           reinterpret_cast<uint4*>(base + copied), quads);
+        ScatterParams sp{};
+        sp.canon = ep.canon;
+        sp.w4 = reinterpret_cast<uint16_t*>(base + at_w4);
+        sp.n_kept = (unsigned)n;
+        sp.C = p->C;
+        for (size_t t = 0; t < nm; ++t) {
+            const MfmaWeights& m = p->mfma[t];
+            ScatterCopy& c = sp.copy[t];
+            c.w = reinterpret_cast<uint16_t*>(base + at_mw[t]);
+            c.pos_of = m.clist.empty() ? nullptr : reinterpret_cast<uint16_t*>(base + at_mpos[t]);
+            c.tinfo = m.clist.empty() ? nullptr : reinterpret_cast<uint32_t*>(base + at_tinfo[t]);
+            c.mt = m.mt;
+            c.n_cblocks = m.n_cblocks;
+            c.nt = m.n_taps;
+            c.groups = m.groups;
+            c.group_channels = p->C / m.groups;
+            std::memcpy(c.slot_of, m.slot_of, sizeof(m.slot_of));
         }
+        if (n) hipLaunchKernelGGL(scatter_weights_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)nm), dim3(256), 0, 0, sp);
+        PCONV_HIP(hipGetLastError());
+    }
+    PCONV_HIP(hipStreamSynchronize(0));
+
+    p->d_canon = reinterpret_cast<uint32_t*>(base + at_canon);
+    p->d_forder = reinterpret_cast<uint32_t*>(base + at_forder);
+    p->d_ent = ep.lay[0].ent;
+    p->d_eptr = ep.lay[0].eptr;
+    for (size_t t = 0; t < nl; ++t) {
+        p->balanced[t].d_ent = ep.lay[t + 1].ent;
+        p->balanced[t].d_eptr = ep.lay[t + 1].eptr;
+        p->balanced[t].d_perm = reinterpret_cast<uint32_t*>(base + at_perm[t]);
+    }
+    for (size_t t = 0; t < nm; ++t) {
+        MfmaWeights& m = p->mfma[t];
+        m.d_w = base + at_mw[t];
+        if (m.clist.empty()) continue;
+        m.d_clist = reinterpret_cast<uint32_t*>(base + at_clist[t]);
+        m.d_tinfo = reinterpret_cast<uint32_t*>(base + at_tinfo[t]);
     }
     p->device = dev;
     return PCONV_OK;
@@ -89,26 +298,18 @@ int upload_packed(pconv_packed* p) {
 
 void release_device(pconv_packed* p) {
     for (MfmaWeights& m : p->mfma) {
-        if (m.d_w) (void)hipFree(m.d_w);
-        if (m.d_clist) (void)hipFree(m.d_clist);
-        if (m.d_tinfo) (void)hipFree(m.d_tinfo);
         m.d_w = nullptr;
         m.d_clist = nullptr;
         m.d_tinfo = nullptr;
     }
-    if (p->d_canon) (void)hipFree(p->d_canon);
-    p->d_canon = nullptr;
-    if (p->d_ent) (void)hipFree(p->d_ent);
-    if (p->d_eptr) (void)hipFree(p->d_eptr);
-    if (p->d_forder) (void)hipFree(p->d_forder);
     for (BalancedLayout& b : p->balanced) {
-        if (b.d_ent) (void)hipFree(b.d_ent);
-        if (b.d_eptr) (void)hipFree(b.d_eptr);
-        if (b.d_perm) (void)hipFree(b.d_perm);
         b.d_ent = nullptr;
         b.d_eptr = nullptr;
         b.d_perm = nullptr;
     }
+    p->d_canon = nullptr;
+    if (p->d_arena) (void)hipFree(p->d_arena);
+    p->d_arena = nullptr;
     if (p->d_ws) (void)hipFree(p->d_ws);
     if (p->d_counters) (void)hipFree(p->d_counters);
     if (p->d_planes) (void)hipFree(p->d_planes);

@@ -1,10 +1,13 @@
 // Host side of libpconv: argument checks, pattern assignment, connectivity selection, packing, export.
 // Pure C++ (no HIP calls here); the device upload lives in pconv_device.hip.
 #include <algorithm>
+#include <atomic>
 #include <cmath>
 #include <cstring>
+#include <exception>
 #include <new>
 #include <numeric>
+#include <thread>
 
 #include "pconv_internal.h"
 
@@ -35,40 +38,6 @@ int check_fc(int F, int C) {
     if (F <= 0 || C <= 0 || C >= 65536) return PCONV_ESHAPE;
     if ((long long)F * (long long)C > (1ll << 31) / 9) return PCONV_ESHAPE;
     return PCONV_OK;
-}
-
-// IEEE binary16 -> binary32, exact (subnormals, infinities and NaN payloads included).
-inline float half_bits_to_float(uint16_t h) {
-    const uint32_t sign = (uint32_t)(h & 0x8000u) << 16;
-    uint32_t exp = (h >> 10) & 0x1Fu, man = h & 0x3FFu, out;
-    if (exp == 0) {
-        if (man == 0) {
-            out = sign;
-        } else {
-            int e = -1;
-            do {
-                man <<= 1;
-                ++e;
-            } while (!(man & 0x400u));
-            out = sign | ((uint32_t)(127 - 15 - e) << 23) | ((man & 0x3FFu) << 13);
-        }
-    } else if (exp == 31) {
-        out = sign | 0x7F800000u | (man << 13);
-    } else {
-        out = sign | ((exp + 112u) << 23) | (man << 13);
-    }
-    float f;
-    std::memcpy(&f, &out, 4);
-    return f;
-}
-
-// Rank of a mask among the 255 masks with one to four bits in ascending order (the pattern code of the device
-// layout: the tiled kernel has one code section per such mask).
-inline uint32_t mask_rank(unsigned m) {
-    uint32_t rank = 0;
-    for (unsigned v = 1; v < m; ++v)
-        if (popcount9(v) >= 1 && popcount9(v) <= 4) ++rank;
-    return rank;
 }
 
 // Retained squared norm of one kernel under one mask: squares in double, added in ascending tap order.
@@ -141,7 +110,63 @@ extern "C" int pconv_select_connectivity(const float* w, int F, int C, const uin
 
 namespace {
 
-// Builds the balanced layout of `p` for one tiling (see pconv::BalancedLayout).
+// The kept kernels of a layer, filter by filter with channels ascending: what every way of making a layer hands to
+// pack_list.
+struct KernelList {
+    std::vector<uint32_t> row;        // [F+1]
+    std::vector<uint16_t> c;          // channel
+    std::vector<uint8_t> pid;         // pattern id
+    std::vector<unsigned char> w4;    // the kept weights, taps ascending, four of the storage type (missing ones zero)
+};
+
+// From a dense tensor, pattern ids and a mask.  The channel scan has no branch per kernel: every channel is written,
+// the kept ones advance.
+template <typename E>
+void list_kernels(const E* w, int F, int C, const uint16_t* lib, int K, const uint8_t* pid, const uint8_t* mask,
+                  KernelList* out) {
+    std::vector<int> taps((size_t)K * 4, -1);
+    for (int j = 0; j < K; ++j) {
+        int q = 0;
+        for (int t = 0; t < 9; ++t)
+            if ((lib[j] >> t) & 1u) taps[(size_t)j * 4 + q++] = t;
+    }
+    out->row.resize((size_t)F + 1);
+    size_t n = 0;
+    for (int f = 0; f < F; ++f) {
+        const uint8_t* m = mask + (size_t)f * C;
+        uint32_t kept = 0;
+        for (int c = 0; c < C; ++c) kept += m[c] ? 1u : 0u;
+        out->row[(size_t)f] = (uint32_t)n;
+        n += kept;
+    }
+    out->row[(size_t)F] = (uint32_t)n;
+    out->c.resize(n + 1);             // (one more: the scan writes behind the last kept kernel)
+    out->pid.resize(n);
+    out->w4.resize(n * 4 * sizeof(E));
+    E* const w4 = reinterpret_cast<E*>(out->w4.data());
+    for (int f = 0; f < F; ++f) {
+        const uint8_t* m = mask + (size_t)f * C;
+        size_t e = out->row[(size_t)f];
+        const size_t end = out->row[(size_t)f + 1];
+        for (int c = 0; c < C && e < end; ++c) {
+            out->c[e] = (uint16_t)c;
+            e += m[c] ? 1 : 0;
+        }
+        for (e = out->row[(size_t)f]; e < end; ++e) {
+            const size_t fc = (size_t)f * C + out->c[e];
+            const int j = pid[fc];
+            out->pid[e] = (uint8_t)j;
+            const E* k9 = w + fc * 9;
+            for (int q = 0; q < 4; ++q) {
+                const int t = taps[(size_t)j * 4 + q];
+                w4[e * 4 + q] = t >= 0 ? k9[t] : (E)0;
+            }
+        }
+    }
+    out->c.resize(n);
+}
+
+// Builds the balanced order of `p` for one tiling (see pconv::BalancedLayout).
 void build_balanced(const pconv_packed* p, int fw, int nf, int cc, pconv::BalancedLayout* out) {
     const int F = p->F, C = p->C, K = p->K;
     const int fg = fw * nf;
@@ -152,97 +177,111 @@ void build_balanced(const pconv_packed* p, int fw, int nf, int cc, pconv::Balanc
     out->n_chunks = (C + cc - 1) / cc;
     const int nch = out->n_chunks, npos = nch * cc;
     out->perm.assign((size_t)out->n_groups * npos, pconv::kNoChannel);
-    out->ent.resize(p->n_kept);
-    out->eptr.assign((size_t)F * nch + 1, 0);
+    out->pos_of.assign((size_t)out->n_groups * C, 0);
 
-    // kept kernels of every filter position as (channel, canonical entry index), from the canonical arrays
-    std::vector<std::vector<std::pair<uint16_t, uint32_t>>> kept((size_t)F);
-    for (int i = 0; i < F; ++i)
-        for (uint32_t e = p->grp_ptr[(size_t)i * K]; e < p->grp_ptr[(size_t)(i + 1) * K]; ++e)
-            kept[(size_t)i].push_back({p->cin[e], e});
-    std::vector<uint8_t> pattern_of(p->n_kept);
-    for (int i = 0; i < F; ++i)
-        for (int j = 0; j < K; ++j)
-            for (uint32_t e = p->grp_ptr[(size_t)i * K + j]; e < p->grp_ptr[(size_t)i * K + j + 1]; ++e)
-                pattern_of[e] = (uint8_t)j;
-
-    std::vector<uint32_t> pos_of((size_t)C);          // position of a channel in the group's staging order
-    std::vector<std::vector<uint8_t>> uses;           // [wave][channel] kept kernels of the wave's filters
-    size_t d = 0;
-    std::vector<std::vector<std::pair<uint32_t, uint32_t>>> per_chunk;   // scratch: (sort key, entry) per chunk
-    // entries must be emitted in filter-position order; groups are consecutive positions, so go group by group
+    // 16 chunks side by side in one vector of bytes: loads are at most nf * cc = 64
+    constexpr int kMaxWaves = 16;
+    constexpr uint8_t kFull = 192;                            // load of a chunk that takes no more channels
+    typedef uint8_t Bytes __attribute__((vector_size(16)));
+    const int nblk = (nch + 15) / 16;
+    Bytes step[4];                                            // u in every byte, u <= nf <= 2
+    for (int u = 0; u < 4; ++u)
+        for (int i = 0; i < 16; ++i) step[u][i] = (uint8_t)u;
+    std::vector<uint8_t> uses((size_t)C * kMaxWaves);        // [channel][wave] kept kernels of the wave's filters
+    std::vector<uint32_t> weight((size_t)C), by_weight((size_t)fg + 2), order((size_t)C), fill((size_t)nch);
+    std::vector<Bytes> load((size_t)nblk * kMaxWaves);        // [16 chunks][wave]
+    std::vector<uint32_t> total((size_t)nblk * 16);           // per chunk: kernels << 12 | chunk
+    std::vector<uint16_t> chunk_of((size_t)C);
     for (int g = 0; g < out->n_groups; ++g) {
         const int i0 = g * fg, i1 = std::min(F, i0 + fg);
-        uses.assign((size_t)fw, std::vector<uint8_t>((size_t)C, 0));
-        std::vector<uint32_t> weight((size_t)C, 0);
+        std::fill(uses.begin(), uses.end(), 0);
+        std::fill(weight.begin(), weight.end(), 0u);
         for (int i = i0; i < i1; ++i) {
-            const int w = (i - i0) % fw;                 // wave w holds positions i0 + w + a*fw
-            for (auto& ce : kept[(size_t)i]) {
-                ++uses[(size_t)w][ce.first];
-                ++weight[ce.first];
+            const int w = (i - i0) % fw;                      // wave w holds positions i0 + w + a*fw
+            const uint32_t e1 = p->grp_ptr[(size_t)(i + 1) * K];
+            for (uint32_t e = p->grp_ptr[(size_t)i * K]; e < e1; ++e) {
+                ++uses[(size_t)p->cin[e] * kMaxWaves + w];
+                ++weight[p->cin[e]];
             }
         }
-        // channels by decreasing number of users (unused ones are dropped), then index
-        std::vector<uint32_t> order;
+        // channels by decreasing number of users (at most fg; unused ones are dropped), then index: a counting sort
+        std::fill(by_weight.begin(), by_weight.end(), 0u);
+        for (int c = 0; c < C; ++c) ++by_weight[(size_t)fg - weight[(size_t)c] + 1];
+        for (int u = 0; u <= fg; ++u) by_weight[(size_t)u + 1] += by_weight[(size_t)u];
+        const uint32_t n_used = by_weight[(size_t)fg];
         for (int c = 0; c < C; ++c)
-            if (weight[(size_t)c]) order.push_back((uint32_t)c);
-        std::stable_sort(order.begin(), order.end(), [&](uint32_t a, uint32_t b) { return weight[a] > weight[b]; });
-        // greedy vector bin packing: put each channel into the chunk where the busiest wave stays least busy
-        std::vector<std::vector<uint32_t>> load((size_t)nch, std::vector<uint32_t>((size_t)fw, 0));
-        std::vector<uint32_t> fill((size_t)nch, 0), total((size_t)nch, 0);
-        std::vector<std::vector<uint32_t>> members((size_t)nch);
-        for (uint32_t c : order) {
-            int best = -1;
-            uint32_t best_max = 0, best_total = 0;
-            for (int k = 0; k < nch; ++k) {
-                if ((int)fill[(size_t)k] >= cc) continue;
-                uint32_t mx = 0;
-                for (int w = 0; w < fw; ++w) mx = std::max(mx, load[(size_t)k][(size_t)w] + uses[(size_t)w][c]);
-                if (best < 0 || mx < best_max || (mx == best_max && total[(size_t)k] < best_total)) {
-                    best = k;
-                    best_max = mx;
-                    best_total = total[(size_t)k];
+            if (weight[(size_t)c]) order[by_weight[(size_t)fg - weight[(size_t)c]]++] = (uint32_t)c;
+        // greedy vector bin packing: put each channel into the chunk where the busiest wave stays least busy (then the
+        // one with the fewest kernels, at most fg * cc = 1024, then the first of at most 4096: one number to minimise)
+        std::fill(load.begin(), load.end(), step[0]);
+        std::fill(fill.begin(), fill.end(), 0u);
+        for (int k = 0; k < nblk * 16; ++k) total[(size_t)k] = (uint32_t)k;
+        for (int k = nch; k < nblk * 16; ++k) load[(size_t)(k / 16) * kMaxWaves][k % 16] = kFull;
+        for (uint32_t r = 0; r < n_used; ++r) {
+            const uint32_t c = order[r];
+            const uint8_t* u = &uses[(size_t)c * kMaxWaves];
+            uint32_t best_key = ~0u;
+            for (int blk = 0; blk < nblk; ++blk) {
+                const Bytes* l = &load[(size_t)blk * kMaxWaves];
+                Bytes mx = l[0] + step[u[0]];
+                for (int w = 1; w < fw; ++w) {
+                    const Bytes v = l[w] + step[u[w]];
+                    mx = v > mx ? v : mx;
+                }
+                for (int k = 0; k < 16; ++k) {
+                    const uint32_t key = total[(size_t)blk * 16 + k] + ((uint32_t)mx[k] << 23);
+                    best_key = key < best_key ? key : best_key;
                 }
             }
-            for (int w = 0; w < fw; ++w) load[(size_t)best][(size_t)w] += uses[(size_t)w][c];
-            total[(size_t)best] += weight[c];
-            ++fill[(size_t)best];
-            members[(size_t)best].push_back(c);
+            const uint32_t best = best_key & 0xFFFu;
+            Bytes* l = &load[(size_t)(best / 16) * kMaxWaves];
+            for (int w = 0; w < fw; ++w) l[w][best % 16] = (uint8_t)(l[w][best % 16] + u[w]);
+            total[best] += weight[c] << 12;
+            if (++fill[best] == (uint32_t)cc) l[0][best % 16] = kFull;
+            chunk_of[c] = (uint16_t)best;
         }
-        for (int k = 0; k < nch; ++k) {
-            std::sort(members[(size_t)k].begin(), members[(size_t)k].end());
-            for (size_t m = 0; m < members[(size_t)k].size(); ++m) {
-                const uint32_t c = members[(size_t)k][m];
-                pos_of[c] = (uint32_t)(k * cc + (int)m);
-                out->perm[(size_t)g * npos + pos_of[c]] = c;
-            }
-        }
-        // entries of the group's filters: by chunk, then pattern, then position
-        for (int i = i0; i < i1; ++i) {
-            per_chunk.assign((size_t)nch, {});
-            for (auto& ce : kept[(size_t)i]) {
-                const uint32_t pos = pos_of[ce.first];
-                per_chunk[pos / (uint32_t)cc].push_back({((uint32_t)pattern_of[ce.second] << 20) | pos, ce.second});
-            }
-            for (int k = 0; k < nch; ++k) {
-                out->eptr[(size_t)i * nch + k] = (uint32_t)d;
-                auto& v = per_chunk[(size_t)k];
-                std::sort(v.begin(), v.end());
-                for (auto& ke : v) {
-                    pconv::DevEntry de = p->ent[p->ent_of_canonical[ke.second]];
-                    de.c = ke.first & 0xFFFFFu;
-                    de.hdr = (de.c & 0xFFu) | (de.code << 8);
-                    out->ent[d++] = de;
-                }
-            }
+        // channels of a chunk in ascending order
+        std::fill(fill.begin(), fill.end(), 0u);
+        for (int c = 0; c < C; ++c) {
+            if (!weight[(size_t)c]) continue;
+            const uint32_t k = chunk_of[(size_t)c], pos = k * (uint32_t)cc + fill[k]++;
+            out->pos_of[(size_t)g * C + c] = (uint16_t)pos;
+            out->perm[(size_t)g * npos + pos] = (uint32_t)c;
         }
     }
-    out->eptr[(size_t)F * nch] = (uint32_t)d;
 }
 
-// The layer's weights in matrix-core order for workgroup tiles of mt filters (see pconv::MfmaWeights), from the
-// canonical arrays.  fp16 storage only: the 16-bit patterns are copied as they are.
-void build_mfma_weights(const pconv_packed* p, int mt, int groups, pconv::MfmaWeights* out) {
+// The balanced layouts for the tilings of the automatic choice (waves, filters per wave, channels per chunk; the
+// 16-channel ones are the quad kernel's).  They do not depend on each other and are most of the time of packing a layer,
+// so a layer that is worth it (below: less than a thread's start) has two more threads take them off one list.
+void build_all_balanced(pconv_packed* p) {
+    static const int tilings[5][3] = {{8, 1, 32}, {16, 1, 16}, {16, 1, 32}, {16, 2, 32}, {16, 2, 16}};   // (longest first)
+    p->balanced.resize(5);
+    std::atomic<int> next{0};
+    std::atomic<bool> no_memory{false};
+    auto work = [&] {
+        try {
+            for (int t = next++; t < 5; t = next++)
+                build_balanced(p, tilings[t][0], tilings[t][1], tilings[t][2], &p->balanced[(size_t)t]);
+        } catch (const std::bad_alloc&) {
+            no_memory = true;
+        }
+    };
+    std::thread helpers[2];
+    if ((long long)p->F * p->C >= 128 * 128) {
+        try {
+            for (std::thread& h : helpers) h = std::thread(work);
+        } catch (const std::exception&) {}                    // (no thread to be had: what there is does the work)
+    }
+    work();
+    for (std::thread& h : helpers)
+        if (h.joinable()) h.join();
+    if (no_memory) throw std::bad_alloc();
+}
+
+// What the device needs to lay out the layer's weights in matrix-core order for workgroup tiles of mt filters (see
+// pconv::MfmaWeights): tap slots and channel lists.
+void plan_mfma_weights(const pconv_packed* p, int mt, int groups, pconv::MfmaWeights* out) {
     const int F = p->F, C = p->C, K = p->K;
     out->mt = mt;
     out->groups = groups;
@@ -253,12 +292,11 @@ void build_mfma_weights(const pconv_packed* p, int mt, int groups, pconv::MfmaWe
     for (int i = 0; i < F; ++i)
         for (int j = 0; j < K; ++j)
             if (p->grp_ptr[(size_t)i * K + j + 1] > p->grp_ptr[(size_t)i * K + j]) present |= p->lib[(size_t)j];
-    int slot_of[9];
     out->n_taps = 0;
     for (int t = 0; t < 9; ++t) {
-        slot_of[t] = -1;
+        out->slot_of[t] = -1;
         if ((present >> t) & 1u) {
-            slot_of[t] = out->n_taps;
+            out->slot_of[t] = (int8_t)out->n_taps;
             out->taps[out->n_taps++] = (uint8_t)t;
         }
     }
@@ -267,95 +305,54 @@ void build_mfma_weights(const pconv_packed* p, int mt, int groups, pconv::MfmaWe
         for (int g = 1; g < groups; ++g) out->taps[g] = out->taps[0];
         out->n_taps = groups;
     }
-    const int nt = out->n_taps;
-    const size_t group_channels = (size_t)(C / groups);
     // Channels that the filters of every tile keep.  Lists are made where they save at least a tenth of the blocks;
     // otherwise every tile takes all channels in their own order.
-    std::vector<std::vector<uint8_t>> used((size_t)out->n_mtiles, std::vector<uint8_t>((size_t)C, 0));
+    std::vector<uint8_t> used((size_t)out->n_mtiles * C, 0);
     for (int i = 0; i < F; ++i) {
-        const uint32_t f = p->filter_order[(size_t)i];
-        for (uint32_t e = p->grp_ptr[(size_t)i * K]; e < p->grp_ptr[(size_t)(i + 1) * K]; ++e)
-            used[f / (uint32_t)mt][p->cin[e]] = 1;
+        uint8_t* const u = &used[p->filter_order[(size_t)i] / (uint32_t)mt * (size_t)C];
+        const uint32_t e1 = p->grp_ptr[(size_t)(i + 1) * K];
+        for (uint32_t e = p->grp_ptr[(size_t)i * K]; e < e1; ++e) u[p->cin[e]] = 1;
     }
-    std::vector<std::vector<uint32_t>> pos_of((size_t)out->n_mtiles);     // with lists: position of a channel in its tile
-    std::vector<size_t> first_block((size_t)out->n_mtiles, 0);
     size_t listed = 0;
     for (int t = 0; t < out->n_mtiles; ++t) {
         size_t n = 0;
-        for (int c = 0; c < C; ++c) n += used[(size_t)t][(size_t)c];
+        for (int c = 0; c < C; ++c) n += used[(size_t)t * C + c];
         listed += std::max<size_t>(1, (n + 15) / 16);
     }
     const bool lists = groups == 1 && listed * 10 <= (size_t)out->n_mtiles * out->n_cblocks * 9;
     out->clist.clear();
     out->tinfo.clear();
+    out->pos_of.clear();
     out->min_blocks = out->n_cblocks;
     out->total_blocks = out->n_mtiles * out->n_cblocks;
     if (lists) {
         out->min_blocks = 1 << 30;
+        out->pos_of.assign((size_t)out->n_mtiles * C, 0);
         size_t at_block = 0;
         for (int t = 0; t < out->n_mtiles; ++t) {
-            pos_of[(size_t)t].assign((size_t)C, 0);
             size_t n = 0;
             for (int c = 0; c < C; ++c)
-                if (used[(size_t)t][(size_t)c]) {
-                    pos_of[(size_t)t][(size_t)c] = (uint32_t)n++;
+                if (used[(size_t)t * C + c]) {
+                    out->pos_of[(size_t)t * C + c] = (uint16_t)n++;
                     out->clist.push_back((uint32_t)c);
                 }
             const size_t nb = std::max<size_t>(1, (n + 15) / 16);
             out->clist.resize((at_block + nb) * 16, pconv::kNoChannel);
             out->tinfo.push_back((uint32_t)nb);
             out->tinfo.push_back((uint32_t)at_block);
-            first_block[(size_t)t] = at_block;
             out->min_blocks = std::min(out->min_blocks, (int)nb);
             at_block += nb;
         }
         out->total_blocks = (int)at_block;
-    } else {
-        for (int t = 0; t < out->n_mtiles; ++t) first_block[(size_t)t] = (size_t)t * out->n_cblocks;
     }
-    out->w.assign((size_t)out->total_blocks * nt * 2 * mt * 8, 0);
-    for (int i = 0; i < F; ++i) {
-        const uint32_t f = p->filter_order[(size_t)i];
-        const size_t tile = f / (uint32_t)mt, fl = f % (uint32_t)mt;
-        for (int j = 0; j < K; ++j) {
-            int taps[4], q = 0;
-            for (int t = 0; t < 9; ++t)
-                if ((p->lib[(size_t)j] >> t) & 1u) taps[q++] = t;
-            for (uint32_t e = p->grp_ptr[(size_t)i * K + j]; e < p->grp_ptr[(size_t)i * K + j + 1]; ++e) {
-                size_t c = lists ? pos_of[tile][p->cin[e]] : p->cin[e];      // position among the tile's channels
-                const size_t range = groups > 1 ? c / group_channels : 0;
-                if (groups > 1) c -= range * group_channels;
-                const size_t cb = c / 16, kb = (c % 16) / 8, c8 = c % 8;
-                for (int k = 0; k < q; ++k) {
-                    const size_t ts = groups > 1 ? range : (size_t)slot_of[taps[k]];
-                    const size_t at = ((((first_block[tile] + cb) * nt + ts) * 2 + kb) * mt + fl) * 8 + c8;
-                    std::memcpy(&out->w[at], &p->w4[((size_t)e * 4 + k) * 2], 2);
-                }
-            }
-        }
-    }
+    out->elements = (size_t)out->total_blocks * out->n_taps * 2 * mt * 8;
 }
 
-}  // namespace
-
-// pconv_pack, and the packing of a layer re-packed over parity planes (`partial`: masks of one to four taps, up to
-// 255 of them; missing taps of a kernel are stored as zero weights).
-static int pack_impl(const void* w_oihw, int dtype, int F, int C, const uint16_t* lib, int K, const uint8_t* pid,
-                     const uint8_t* mask, unsigned flags, bool partial, bool want_mfma, pconv_packed** out,
-                     bool one_by_one = false) {
-    if (!out) return PCONV_EINVAL;
-    *out = nullptr;
-    if (!w_oihw || !pid || !mask) return PCONV_EINVAL;
-    if (dtype != PCONV_F32 && dtype != PCONV_F16) return PCONV_EINVAL;
-    if (flags & ~(unsigned)PCONV_PACK_HOST_ONLY) return PCONV_EINVAL;
-    if (int rc = partial ? check_partial_library(lib, K) : check_library(lib, K)) return rc;
-    if (int rc = check_fc(F, C)) return rc;
-    const size_t esize = dtype == PCONV_F16 ? 2 : 4;
-    const unsigned char* wb = static_cast<const unsigned char*>(w_oihw);
-
-    for (long long i = 0; i < (long long)F * C; ++i)
-        if (mask[i] && pid[i] >= K) return PCONV_EPATTERN;
-
+// Packs a list of kept kernels: the canonical arrays, and what the device needs to make its layouts from them.  Masks
+// of one to four taps, up to 255 of them; arguments are checked by the callers.
+int pack_list(const KernelList& list, int dtype, int F, int C, const uint16_t* lib, int K, unsigned flags, bool want_mfma,
+              bool one_by_one, pconv_packed** out) {
+    const size_t kernel_bytes = dtype == PCONV_F16 ? 8 : 16;
     pconv_packed* p = new (std::nothrow) pconv_packed;
     if (!p) return PCONV_ENOMEM;
     try {
@@ -364,118 +361,54 @@ static int pack_impl(const void* w_oihw, int dtype, int F, int C, const uint16_t
         p->K = K;
         p->dtype = dtype;
         p->lib.assign(lib, lib + K);
-
-        // taps of every mask, ascending (-1: the mask has fewer than four)
-        std::vector<int> taps((size_t)K * 4, -1);
-        for (int j = 0; j < K; ++j) {
-            int q = 0;
-            for (int t = 0; t < 9; ++t)
-                if ((lib[j] >> t) & 1u) taps[(size_t)j * 4 + q++] = t;
-        }
+        const size_t n_kept = list.row[(size_t)F];
+        p->n_kept = n_kept;
 
         // filter order: kept-kernel count descending, filter index ascending
-        std::vector<uint32_t> count((size_t)F, 0);
-        size_t n_kept = 0;
-        for (int f = 0; f < F; ++f) {
-            uint32_t n = 0;
-            for (int c = 0; c < C; ++c) n += mask[(size_t)f * C + c] ? 1u : 0u;
-            count[(size_t)f] = n;
-            n_kept += n;
-        }
-        p->n_kept = n_kept;
         p->filter_order.resize((size_t)F);
         std::iota(p->filter_order.begin(), p->filter_order.end(), 0u);
-        std::stable_sort(p->filter_order.begin(), p->filter_order.end(),
-                         [&](uint32_t a, uint32_t b) { return count[a] > count[b]; });
+        std::stable_sort(p->filter_order.begin(), p->filter_order.end(), [&](uint32_t a, uint32_t b) {
+            return list.row[a + 1] - list.row[a] > list.row[b + 1] - list.row[b];
+        });
 
         // canonical arrays: per (position i, pattern j) the kept kernels in ascending channel
         p->grp_ptr.assign((size_t)F * K + 1, 0);
         p->cin.resize(n_kept);
-        p->w4.resize(n_kept * 4 * esize);
-        size_t e = 0;
-        for (int i = 0; i < F; ++i) {
-            const uint32_t f = p->filter_order[(size_t)i];
-            for (int j = 0; j < K; ++j) {
-                p->grp_ptr[(size_t)i * K + j] = (uint32_t)e;
-                for (int c = 0; c < C; ++c) {
-                    const size_t fc = (size_t)f * C + c;
-                    if (!mask[fc] || pid[fc] != j) continue;
-                    p->cin[e] = (uint16_t)c;
-                    for (int q = 0; q < 4; ++q) {
-                        const int t = taps[(size_t)j * 4 + q];
-                        if (t >= 0) std::memcpy(&p->w4[(e * 4 + q) * esize], wb + (fc * 9 + t) * esize, esize);
-                        else std::memset(&p->w4[(e * 4 + q) * esize], 0, esize);
-                    }
-                    ++e;
-                }
-            }
-        }
-        p->grp_ptr[(size_t)F * K] = (uint32_t)e;
+        p->w4.resize(n_kept * kernel_bytes);
         p->canon.resize(n_kept * 2);
-        for (int i = 0; i < F; ++i)
-            for (int j = 0; j < K; ++j)
-                for (uint32_t q = p->grp_ptr[(size_t)i * K + j]; q < p->grp_ptr[(size_t)i * K + j + 1]; ++q) {
-                    p->canon[(size_t)q * 2] = p->filter_order[(size_t)i];
-                    p->canon[(size_t)q * 2 + 1] = (uint32_t)p->cin[q] | ((uint32_t)lib[j] << 16);
-                }
-
-        // device layout, derived from the canonical one: per (position i, channel bucket) the entries by pattern,
-        // then channel; weights widened to fp32
-        const int chunk = pconv::kBucket;
-        p->n_buckets = (C + chunk - 1) / chunk;
-        p->ent.resize(n_kept);
-        p->ent_of_canonical.resize(n_kept);
-        p->eptr.assign((size_t)F * p->n_buckets + 1, 0);
-        std::vector<uint32_t> cursor((size_t)K), code_of((size_t)K);
-        for (int j = 0; j < K; ++j) code_of[(size_t)j] = mask_rank(lib[j]);
-        size_t d = 0;
+        std::vector<uint32_t> at((size_t)K);
+        uint32_t e = 0;
         for (int i = 0; i < F; ++i) {
-            for (int j = 0; j < K; ++j) cursor[(size_t)j] = p->grp_ptr[(size_t)i * K + j];
-            for (int k = 0; k < p->n_buckets; ++k) {
-                p->eptr[(size_t)i * p->n_buckets + k] = (uint32_t)d;
-                const int c_end = std::min(C, (k + 1) * chunk);
-                for (int j = 0; j < K; ++j) {
-                    const uint32_t g_end = p->grp_ptr[(size_t)i * K + j + 1];
-                    uint32_t& cur = cursor[(size_t)j];
-                    while (cur < g_end && (int)p->cin[cur] < c_end) {
-                        p->ent_of_canonical[cur] = (uint32_t)d;
-                        pconv::DevEntry& de = p->ent[d++];
-                        for (int q = 0; q < 4; ++q) {
-                            if (dtype == PCONV_F16) {
-                                uint16_t hb;
-                                std::memcpy(&hb, &p->w4[((size_t)cur * 4 + q) * 2], 2);
-                                de.w[q] = half_bits_to_float(hb);
-                            } else {
-                                std::memcpy(&de.w[q], &p->w4[((size_t)cur * 4 + q) * 4], 4);
-                            }
-                        }
-                        de.c = p->cin[cur];
-                        de.mask9 = lib[j];
-                        de.code = code_of[(size_t)j];
-                        de.hdr = (de.c & 0xFFu) | (de.code << 8);
-                        ++cur;
-                    }
-                }
+            const uint32_t f = p->filter_order[(size_t)i], r0 = list.row[f], r1 = list.row[f + 1];
+            std::fill(at.begin(), at.end(), 0u);
+            for (uint32_t r = r0; r < r1; ++r) ++at[list.pid[r]];
+            for (int j = 0; j < K; ++j) {
+                const uint32_t n = at[(size_t)j];
+                p->grp_ptr[(size_t)i * K + j] = at[(size_t)j] = e;
+                e += n;
+            }
+            for (uint32_t r = r0; r < r1; ++r) {
+                const uint32_t j = list.pid[r], d = at[j]++;
+                p->cin[d] = list.c[r];
+                p->canon[(size_t)d * 2] = f;
+                p->canon[(size_t)d * 2 + 1] = (uint32_t)list.c[r] | ((uint32_t)lib[j] << 16);
+                std::memcpy(&p->w4[d * kernel_bytes], &list.w4[r * kernel_bytes], kernel_bytes);
             }
         }
-        p->eptr[(size_t)F * p->n_buckets] = (uint32_t)d;
+        p->grp_ptr[(size_t)F * K] = e;
+        p->n_buckets = (C + pconv::kBucket - 1) / pconv::kBucket;
 
-        // balanced layouts for the tilings of the automatic choice (waves, filters per wave, channels per chunk);
-        // the 16-channel ones are the quad kernel's
-        static const int tilings[5][3] = {{16, 2, 32}, {16, 1, 32}, {8, 1, 32}, {16, 2, 16}, {16, 1, 16}};
-        p->balanced.resize(5);
-        for (int t = 0; t < 5; ++t)
-            build_balanced(p, tilings[t][0], tilings[t][1], tilings[t][2], &p->balanced[(size_t)t]);
+        build_all_balanced(p);
         if (dtype == PCONV_F16 && want_mfma) {
             const int nh = (int)(sizeof(pconv::kMfmaTileHeights) / sizeof(int));
             p->mfma.resize((size_t)nh);
-            for (int h = 0; h < nh; ++h) build_mfma_weights(p, pconv::kMfmaTileHeights[h], 1, &p->mfma[(size_t)h]);
+            for (int h = 0; h < nh; ++h) plan_mfma_weights(p, pconv::kMfmaTileHeights[h], 1, &p->mfma[(size_t)h]);
             // (a 1x1 layer is bound by the round trips of its many short channel blocks: kept a second time with
             // several channel ranges per block)
             if (one_by_one && K == 1 && C % (16 * pconv::kOneByOneGroups) == 0) {
                 p->mfma.resize((size_t)(2 * nh));
                 for (int h = 0; h < nh; ++h)
-                    build_mfma_weights(p, pconv::kMfmaTileHeights[h], pconv::kOneByOneGroups, &p->mfma[(size_t)(nh + h)]);
+                    plan_mfma_weights(p, pconv::kMfmaTileHeights[h], pconv::kOneByOneGroups, &p->mfma[(size_t)(nh + h)]);
             }
         }
     } catch (const std::bad_alloc&) {
@@ -493,6 +426,34 @@ static int pack_impl(const void* w_oihw, int dtype, int F, int C, const uint16_t
     }
     *out = p;
     return PCONV_OK;
+}
+
+}  // namespace
+
+// pconv_pack, and the packing of a layer re-packed over parity planes (`partial`: masks of one to four taps, up to
+// 255 of them; missing taps of a kernel are stored as zero weights).
+static int pack_impl(const void* w_oihw, int dtype, int F, int C, const uint16_t* lib, int K, const uint8_t* pid,
+                     const uint8_t* mask, unsigned flags, bool partial, bool want_mfma, pconv_packed** out,
+                     bool one_by_one = false) {
+    if (!out) return PCONV_EINVAL;
+    *out = nullptr;
+    if (!w_oihw || !pid || !mask) return PCONV_EINVAL;
+    if (dtype != PCONV_F32 && dtype != PCONV_F16) return PCONV_EINVAL;
+    if (flags & ~(unsigned)PCONV_PACK_HOST_ONLY) return PCONV_EINVAL;
+    if (int rc = partial ? check_partial_library(lib, K) : check_library(lib, K)) return rc;
+    if (int rc = check_fc(F, C)) return rc;
+    for (long long i = 0; i < (long long)F * C; ++i)
+        if (mask[i] && pid[i] >= K) return PCONV_EPATTERN;
+    try {
+        KernelList list;
+        if (dtype == PCONV_F16)
+            list_kernels(static_cast<const uint16_t*>(w_oihw), F, C, lib, K, pid, mask, &list);
+        else
+            list_kernels(static_cast<const uint32_t*>(w_oihw), F, C, lib, K, pid, mask, &list);
+        return pack_list(list, dtype, F, C, lib, K, flags, want_mfma, one_by_one, out);
+    } catch (const std::bad_alloc&) {
+        return PCONV_ENOMEM;
+    }
 }
 
 extern "C" int pconv_pack(const void* w_oihw, int dtype, int F, int C, const uint16_t* lib, int K, const uint8_t* pid,
@@ -520,24 +481,30 @@ extern "C" int pconv_packed_transpose(const pconv_packed* p, unsigned flags, pco
     try {
         std::vector<uint16_t> lib((size_t)K);
         for (int j = 0; j < K; ++j) lib[(size_t)j] = rotate_mask(p->lib[(size_t)j]);
-        std::vector<unsigned char> w((size_t)C * F * 9 * esize, 0);
-        std::vector<uint8_t> pid((size_t)C * F, 0), mask((size_t)C * F, 0);
-        for (int i = 0; i < F; ++i) {
-            const uint32_t f = p->filter_order[(size_t)i];
-            for (int j = 0; j < K; ++j) {
-                int taps[4], q = 0;
-                for (int t = 0; t < 9; ++t)
-                    if ((p->lib[(size_t)j] >> t) & 1u) taps[q++] = t;
-                for (uint32_t e = p->grp_ptr[(size_t)i * K + j]; e < p->grp_ptr[(size_t)i * K + j + 1]; ++e) {
-                    const size_t cf = (size_t)p->cin[e] * F + f;
-                    pid[cf] = (uint8_t)j;
-                    mask[cf] = 1;
+        // the kernels by channel, filters ascending: filters are visited in that order and dropped into their channel's
+        // row.  Tap t becomes tap 8 - t, so the kept weights of a kernel come in the opposite order.
+        std::vector<uint32_t> pos_of_filter((size_t)F);
+        for (int i = 0; i < F; ++i) pos_of_filter[p->filter_order[(size_t)i]] = (uint32_t)i;
+        KernelList list;
+        list.row.assign((size_t)C + 1, 0);
+        for (size_t e = 0; e < p->n_kept; ++e) ++list.row[(size_t)p->cin[e] + 1];
+        for (int c = 0; c < C; ++c) list.row[(size_t)c + 1] += list.row[(size_t)c];
+        list.c.resize(p->n_kept);
+        list.pid.resize(p->n_kept);
+        list.w4.resize(p->n_kept * 4 * esize);
+        std::vector<uint32_t> at(list.row.begin(), list.row.end() - 1);
+        for (int f = 0; f < F; ++f) {
+            const size_t i = pos_of_filter[(size_t)f];
+            for (int j = 0; j < K; ++j)
+                for (uint32_t e = p->grp_ptr[i * K + j]; e < p->grp_ptr[i * K + j + 1]; ++e) {
+                    const size_t d = at[p->cin[e]]++;
+                    list.c[d] = (uint16_t)f;
+                    list.pid[d] = (uint8_t)j;
                     for (int k = 0; k < 4; ++k)
-                        std::memcpy(&w[(cf * 9 + (size_t)(8 - taps[k])) * esize], &p->w4[((size_t)e * 4 + k) * esize], esize);
+                        std::memcpy(&list.w4[(d * 4 + 3 - k) * esize], &p->w4[((size_t)e * 4 + k) * esize], esize);
                 }
-            }
         }
-        return pack_impl(w.data(), p->dtype, C, F, lib.data(), K, pid.data(), mask.data(), flags, false, true, out);
+        return pack_list(list, p->dtype, C, F, lib.data(), K, flags, true, false, out);
     } catch (const std::bad_alloc&) {
         return PCONV_ENOMEM;
     }
@@ -791,12 +758,19 @@ extern "C" int pconv_packed_balance(const pconv_packed* p, int waves, int filter
         if (b.fw == waves && b.nf == filters_per_wave && b.cc == cc) bl = &b;
     if (balanced && !bl) return PCONV_EUNSUPPORTED;
     const int nch = balanced ? bl->n_chunks : (p->C + cc - 1) / cc;
-    const int per = cc / pconv::kBucket;
-    auto count = [&](int pos, int k) -> uint32_t {
-        if (balanced) return bl->eptr[(size_t)pos * nch + k + 1] - bl->eptr[(size_t)pos * nch + k];
-        const int b0 = k * per, b1 = std::min(p->n_buckets, b0 + per);
-        return p->eptr[(size_t)pos * p->n_buckets + b1] - p->eptr[(size_t)pos * p->n_buckets + b0];
-    };
+    // kept kernels of (filter position, chunk of 32 staged channels), from the canonical arrays
+    std::vector<uint32_t> counts;
+    try {
+        counts.assign((size_t)F * nch, 0);
+    } catch (const std::bad_alloc&) {
+        return PCONV_ENOMEM;
+    }
+    for (int i = 0; i < F; ++i)
+        for (uint32_t e = p->grp_ptr[(size_t)i * p->K]; e < p->grp_ptr[(size_t)(i + 1) * p->K]; ++e) {
+            const uint32_t at = balanced ? bl->pos_of[(size_t)(i / fg) * p->C + p->cin[e]] : p->cin[e];
+            ++counts[(size_t)i * nch + at / cc];
+        }
+    auto count = [&](int pos, int k) -> uint32_t { return counts[(size_t)pos * nch + k]; };
     double sum = 0.0, sum_max = 0.0;
     long long n_wave_chunks = 0, n_chunks = 0;
     for (int g = 0; g * fg < F; ++g)

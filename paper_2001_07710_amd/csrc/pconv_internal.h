@@ -37,11 +37,11 @@ static_assert(sizeof(DevEntry) == 32, "DevEntry must be 32 bytes");
 struct BalancedLayout {
     int fw = 0, nf = 0, cc = 0;
     int n_groups = 0, n_chunks = 0;
-    std::vector<DevEntry> ent;       // [n_kept]; DevEntry::c is the POSITION of the channel in the staging order
-    std::vector<uint32_t> eptr;      // [F*n_chunks + 1]: entries of (filter position i, chunk k)
     std::vector<uint32_t> perm;      // [n_groups][n_chunks*cc]: channel staged at each position, 0xFFFFFFFF = none
-    DevEntry* d_ent = nullptr;
-    uint32_t* d_eptr = nullptr;
+    std::vector<uint16_t> pos_of;    // [n_groups][C]: position of a channel in its group's order (channels it stages)
+    // on the device only, made there from the canonical arrays and pos_of (build_entries_kernel):
+    DevEntry* d_ent = nullptr;       // [n_kept]; DevEntry::c is the POSITION of the channel in the staging order
+    uint32_t* d_eptr = nullptr;      // [F*n_chunks + 1]: entries of (filter position i, chunk k)
     uint32_t* d_perm = nullptr;
 };
 
@@ -57,9 +57,10 @@ struct MfmaWeights {
     int mt = 0;
     int n_mtiles = 0, n_cblocks = 0, n_taps = 0;
     uint8_t taps[9] = {};             // tap index t = 3*ky + kx of every tap slot, ascending
-    std::vector<uint16_t> w;          // host copy (fp16 bit patterns)
-    void* d_w = nullptr;
-    size_t bytes() const { return w.size() * sizeof(uint16_t); }
+    int8_t slot_of[9] = {};           // tap slot of every tap, -1: the tap does not occur
+    size_t elements = 0;              // of w
+    void* d_w = nullptr;              // on the device only, made there from the canonical arrays (scatter_weights_kernel)
+    size_t bytes() const { return elements * sizeof(uint16_t); }
     // Channel lists (empty: every filter tile takes the channels in their own order, n_cblocks blocks each).  Where
     // the filters of a tile keep only part of the input channels -- connectivity pruning that removes the same
     // channels for similar filters, and filters ordered so that similar ones share a tile -- the tile's blocks are
@@ -69,6 +70,7 @@ struct MfmaWeights {
     // storage of section 6.2 of the paper at the granularity the matrix cores work at.
     std::vector<uint32_t> clist;      // [total blocks][16] channel of every position
     std::vector<uint32_t> tinfo;      // [n_mtiles][2]
+    std::vector<uint16_t> pos_of;     // with lists, [n_mtiles][C]: position of a channel in its tile's list
     int min_blocks = 0, total_blocks = 0;
     uint32_t* d_clist = nullptr;
     uint32_t* d_tinfo = nullptr;
@@ -92,12 +94,10 @@ struct pconv_packed {
     std::vector<uint16_t> cin;            // [n_kept]
     std::vector<unsigned char> w4;        // [n_kept*4] in the storage dtype, raw bytes
 
-    // device layout, host copy: entries ordered by (position i in filter_order, channel bucket, pattern, channel)
+    // device layout: entries ordered by (position i in filter_order, channel bucket, pattern, channel); made on the device
     int n_buckets = 0;
-    std::vector<pconv::DevEntry> ent;     // [n_kept]
-    std::vector<uint32_t> eptr;           // [F*n_buckets + 1]: entries of (i, bucket) are eptr[i*n_buckets+bucket] ..
-    std::vector<uint32_t> ent_of_canonical;   // [n_kept]: index in `ent` of each canonical entry
-    // per canonical entry {filter, channel | mask << 16}: what the weight-gradient pass needs to find an entry's sums
+    // per canonical entry {filter, channel | mask << 16}: what the weight-gradient pass needs to find an entry's sums,
+    // and what the device's layouts are made from
     std::vector<uint32_t> canon;              // [n_kept*2]
     uint32_t* d_canon = nullptr;
 
@@ -122,8 +122,9 @@ struct pconv_packed {
     mutable size_t planes_bytes = 0;
     // device copies (null when packed host-only)
     int device = -1;
-    pconv::DevEntry* d_ent = nullptr;
-    uint32_t* d_eptr = nullptr;
+    void* d_arena = nullptr;              // one allocation behind all of the pointers below and those of the layouts
+    pconv::DevEntry* d_ent = nullptr;     // [n_kept]
+    uint32_t* d_eptr = nullptr;           // [F*n_buckets + 1]: entries of (i, bucket) are eptr[i*n_buckets+bucket] ..
     uint32_t* d_forder = nullptr;
 };
 

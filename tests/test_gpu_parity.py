@@ -678,3 +678,24 @@ def test_maxpool(dtype):
     pc.maxpool2x2(dx, dy, pc.F16 if dtype == "f16" else pc.F32, 3, 5, 14, 10, torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
     assert np.array_equal(dy.cpu().numpy().astype(np.float32), oracle.maxpool2x2(x))
+
+
+@pytest.mark.parametrize("C,F,keep", [(1030, 40, 0.05), (2100, 17, 0.3), (3, 130, 1.0), (16, 1, 0.5)])
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+def test_layouts_made_on_the_device(C, F, keep, dtype):
+    """The entries and matrix-core weights are laid out on the device by counting sorts: more chunks than a wave's 64
+    lanes, rows of entries longer than a wave, filters that keep next to nothing, groups and tiles that are not full."""
+    spec = L.LayerSpec(cfg=35, idx=C, name="layouts", N=1, C=C, F=F, H=8, W=8, dtype=dtype, K=12, keep=keep)
+    layer = GpuLayer(spec)
+    x = L.gen_activations(spec)
+    ref = layer.oracle(x, False)
+    tunings = [dict(), dict(kernel=pc.KERNEL_GENERIC), dict(kernel=pc.KERNEL_QUAD, channel_order=pc.ORDER_BALANCED)]
+    tunings += [dict(kernel=pc.KERNEL_TILED, waves=w, filters_per_wave=nf, channels_per_wave=cpw, channel_order=pc.ORDER_BALANCED)
+                for w, nf, cpw in ((16, 2, 2), (16, 1, 2), (8, 1, 4))]
+    if dtype == "f16":
+        tunings += [dict(kernel=pc.KERNEL_MFMA, mfma_shape=s) for s in (1, 4)]
+    for t in tunings:
+        print("[case]", spec, t, flush=True)
+        err = rel_err(layer.run(x, False, **t), ref)
+        assert err <= TOL[dtype], (t, err)
+    layer.free()
