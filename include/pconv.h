@@ -272,7 +272,10 @@ size_t pconv_noalloc_scratch_bytes(void);
  *   mfma_shape        PCONV_KERNEL_MFMA (fp16 storage only; any stride and pad): the layer as a dense contraction
  *                     over its masked weights on the matrix cores, the automatic choice for fp16 storage.  Workgroup
  *                     tile: 0 = chosen by the library, 1 = 128 filters x 448 output pixels, 2 = 64 x 448,
- *                     3 = 128 x 224, 4 = 64 x 224.  `rows` (0 = as many as fit) caps the output rows per tile;
+ *                     3 = 128 x 224, 4 = 64 x 224; and, for layers of few tiles, 5 = 32 x 32, 6 = 32 x 64, 7 = 64 x 64
+ *                     (output pixels of one image; one workgroup per tile whose waves share the channel blocks and meet in
+ *                     LDS: channel_splits is their number, 1, 2, 4 or 8, 0 = chosen; no workspace; the other fields are
+ *                     not read).  For 1 to 4: `rows` (0 = as many as fit) caps the output rows per tile;
  *                     slot_walk = 1 gives every tile a workgroup of its own instead of persistent workgroups that
  *                     walk over the tiles; channel_splits (0 = chosen by the library: 1, 2, 4 or 8;
  *                     or 1, 2, 4, 8, 16, at most the number of 16-channel blocks) lets that many workgroups share a

@@ -2403,6 +2403,53 @@ static int check_conv_args(const void* x, const void* y, int N, int C, int F, in
 struct PlanOut {
     int kernel, mfma_shape;
 };
+
+// The matrix-core weights of one tile height into a launch's description; false if the layer has none.
+static bool use_weights(const pconv_packed* wp, int mt, int groups, MfmaConv* a) {
+    for (const MfmaWeights& m : wp->mfma) {
+        if (!m.d_w || m.mt != mt || m.groups != groups) continue;
+        a->d_w = m.d_w; a->mt = m.mt; a->n_taps = m.n_taps; a->groups = m.groups;
+        a->d_clist = m.d_clist; a->d_tinfo = m.d_tinfo;
+        a->min_blocks = m.min_blocks; a->total_blocks = m.total_blocks; a->w_bytes = m.bytes();
+        std::memcpy(a->taps, m.taps, sizeof(a->taps));
+        if (a->kext == 1) std::memset(a->taps, 0, sizeof(a->taps));
+        return true;
+    }
+    return false;
+}
+
+// What the kernel for layers of few tiles is to compute: the layer as it is, or a 1x1 layer as a kernel of extent 1
+// (see below) whose image, at stride 1, is cut into rows that make the fewest tiles of 64 pixels, of a multiple of 4
+// pixels (the widest loads) where the image allows it.
+static MfmaConv small_conv(const pconv_packed* wp, const void* x, void* y, const float* bias, int N, int H, int W, int Ho,
+                           int Wo, int stride, int pad, int relu, bool nhwc) {
+    MfmaConv a{};
+    a.x = x; a.y = y; a.bias = bias;
+    a.N = N; a.C = wp->C; a.F = wp->F; a.H = H; a.W = W; a.Ho = Ho; a.Wo = Wo;
+    a.stride = stride; a.pad = pad; a.relu = relu;
+    a.nhwc = nhwc ? 1 : 0;
+    a.kext = 3;
+    if (wp->is_1x1 && pad == 1) {
+        a.kext = 1;
+        a.pad = 0;
+        if (stride == 1) {
+            const long long hw = (long long)H * W;
+            const int unit = hw % 4 == 0 ? 4 : hw % 2 == 0 ? 2 : 1;
+            long long fewest = -1;
+            for (int w = unit; w <= 64 && w <= hw; w += unit) {
+                if (hw % w) continue;
+                const long long rows = hw / w, th = std::min<long long>(64 / w, rows), tiles = (rows + th - 1) / th;
+                if (fewest < 0 || tiles <= fewest) {
+                    fewest = tiles;
+                    a.W = a.Wo = w;
+                    a.H = a.Ho = (int)rows;
+                }
+            }
+        }
+    }
+    return a;
+}
+
 static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const float* bias, int N, int H, int W,
                         int stride, int pad, unsigned flags, void* stream, const pconv_tuning* tuning,
                         const WsArena* arena, PlanOut* plan = nullptr) {
@@ -2451,7 +2498,7 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
         a.shape = tuning ? tuning->mfma_shape : 0;
         a.rows = tuning ? tuning->rows : 0;
         a.walk = tuning ? tuning->slot_walk : 0;
-        if (a.shape < 0 || a.shape > kMfmaShapes) return PCONV_EINVAL;
+        if (a.shape < 0 || a.shape > kMfmaShapes + kSmallShapes) return PCONV_EINVAL;
         // (a layer of 1x1 kernels: its one tap is the centre of a 3x3 kernel at padding 1, which is tap 0 of a kernel
         // of extent 1 at padding 0 -- the same outputs, and no halo rows and columns to stage; and the copy of its
         // weights with channel ranges in the place of taps, if the layer has one: a quarter of the blocks, each four
@@ -2493,12 +2540,26 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
                 break;
             }
         // tile shape and number of workgroups per tile (each with a part of the channel blocks), where not given
+        // (a call without a tuning looks first whether it has been made before with these sizes)
         double best_us = -1.0;
+        Choice made;
+        made.N = N; made.H = H; made.W = W; made.stride = stride; made.pad = pad;
+        made.bits = (nhwc ? 256u : 0u) | (unsigned)(reinterpret_cast<uintptr_t>(x) & 15u) << 4 |
+                    (unsigned)(reinterpret_cast<uintptr_t>(y) & 15u);
+        bool known = false;
+        if (!tuning && !plan) {
+            std::lock_guard<std::mutex> lock(wp->choice_mutex);
+            for (const Choice& c : wp->choices)
+                if (c.N == N && c.H == H && c.W == W && c.stride == stride && c.pad == pad && c.bits == made.bits) {
+                    made = c;
+                    known = true;
+                }
+        }
         const int want_shape = a.shape, want_splits = tuning ? tuning->channel_splits : 0;
         const int want_reduce = tuning ? tuning->split_reduce : 0;
         int best_sp = 0;
         if (want_splits < 0 || want_reduce < 0 || want_reduce > 2) return PCONV_EINVAL;
-        for (int sh = 1; sh <= kMfmaShapes; ++sh) {
+        for (int sh = 1; sh <= kMfmaShapes && !known; ++sh) {
             if (want_shape && sh != want_shape) continue;
             // (A split pays where a layer has fewer tiles than compute units and many channel blocks in sequence --
             // ResNet-50's 512 -> 512 layers at batch 32: 83 -> 55 us in two parts at 14x14 stride 2, 69 -> 40 us in
@@ -2527,6 +2588,26 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
                 }
         }
         a.second_pass = best_sp;
+        // ... or the kernel for layers of few tiles, whose waves share a tile's channel blocks (channel_splits: how many)
+        int small_shape = -1;
+        MfmaConv small = small_conv(wp, x, y, bias, N, H, W, Ho, Wo, stride, pad, relu, nhwc);
+        // (its estimate is of the whole launch; the other's leaves out some 6 us, measured on layers of few blocks)
+        if (best_us >= 0.0) best_us += 6.0;
+        if (!known && (want_shape == 0 ? !forced || (nhwc && all_auto) : want_shape > kMfmaShapes) && use_weights(wp, 64, 1, &small)) {
+            const MfmaConv base = small;
+            for (int sh = 0; sh < kSmallShapes; ++sh) {
+                if (want_shape && sh != want_shape - kMfmaShapes - 1) continue;
+                MfmaConv one = base;
+                one.splits = want_shape ? want_splits : 0;
+                const double t = small_estimate_us(&one, sh);
+                if (t >= 0.0 && (best_us < 0.0 || t < best_us)) {
+                    best_us = t;
+                    small_shape = sh;
+                    small = one;
+                }
+            }
+        }
+        if (want_shape > kMfmaShapes && small_shape < 0) return PCONV_EUNSUPPORTED;
         if (best_us < 0.0) {
             a.shape = want_shape;                // (nothing fits: launch_mfma_conv says so)
             a.splits = want_splits ? want_splits : 1;
@@ -2540,20 +2621,32 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
             const double rate = stride == 2 ? 5e6 : Wo < 14 ? 10e6 : 20e6;      // multiply-adds per microsecond
             take = best_us < macs / rate + 8.0;
         }
+        if (known) {
+            take = made.kernel != 0;
+            if (made.kernel == 1) { a.shape = made.shape; a.splits = made.splits; a.second_pass = made.second_pass; }
+            if (made.kernel == 2 && use_weights(wp, 64, 1, &small)) {
+                small_shape = made.shape;
+                small.splits = made.splits; small.tile_w = made.tile_w; small.tile_lw = made.tile_lw;
+            }
+        } else if (!tuning && !plan) {
+            made.kernel = !take ? 0 : small_shape >= 0 ? 2 : 1;
+            made.shape = small_shape >= 0 ? small_shape : a.shape;
+            made.splits = small_shape >= 0 ? small.splits : a.splits;
+            made.second_pass = a.second_pass;
+            made.tile_w = small.tile_w; made.tile_lw = small.tile_lw;
+            std::lock_guard<std::mutex> lock(wp->choice_mutex);
+            wp->choices[wp->next_choice++ % kChoices] = made;
+        }
         if (take && plan && best_us >= 0.0) {
             plan->kernel = PCONV_KERNEL_MFMA;
-            plan->mfma_shape = a.shape;
+            plan->mfma_shape = small_shape >= 0 ? kMfmaShapes + 1 + small_shape : a.shape;
             return PCONV_OK;
         }
+        if (take && small_shape >= 0) return launch_small_conv(small, small_shape, stream);
         int rc = PCONV_EUNSUPPORTED;
         if (take)
-            for (const MfmaWeights& m : wp->mfma) {
-                if (!m.d_w || m.mt != mfma_shape_height(a.shape) || m.groups != a.groups) continue;
-                a.d_w = m.d_w; a.mt = m.mt; a.n_taps = m.n_taps;
-                a.d_clist = m.d_clist; a.d_tinfo = m.d_tinfo;
-                a.min_blocks = m.min_blocks; a.total_blocks = m.total_blocks; a.w_bytes = m.bytes();
-                std::memcpy(a.taps, m.taps, sizeof(a.taps));
-                if (a.kext == 1) std::memset(a.taps, 0, sizeof(a.taps));
+            if (use_weights(wp, mfma_shape_height(a.shape), a.groups, &a)) {
+                rc = PCONV_OK;
                 if (a.splits > 1) {
                     size_t floats = 0, counters = 0;
                     rc = mfma_workspace(a, &floats, &counters);
@@ -2567,9 +2660,8 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
                         a.counters = nullptr;
                         rc = PCONV_OK;
                     }
-                    if (rc != PCONV_OK) break;
                 }
-                rc = launch_mfma_conv(a, stream);
+                if (rc == PCONV_OK) rc = launch_mfma_conv(a, stream);
             }
         if (rc != PCONV_EUNSUPPORTED || forced) return rc;
         // (no tile shape takes the layer, or the vector kernels are expected to be faster: go on below)

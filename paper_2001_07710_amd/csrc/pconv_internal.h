@@ -3,6 +3,7 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <mutex>
 #include <vector>
 
 #include "pconv.h"
@@ -80,6 +81,16 @@ struct MfmaWeights {
     int groups = 1;
 };
 
+// What the automatic choice between the kernels came to for a call's sizes (fp16 storage).  It is worked out from
+// run-time estimates of a hundred or more launch shapes, 5 to 20 us of host time, so the handle keeps the last few.
+struct Choice {
+    int N = 0, H = 0, W = 0, stride = 0, pad = 0;
+    unsigned bits = 0;                // layout, alignment of x and y
+    int kernel = 0;                   // 0: vector kernels, 1: matrix-core kernel, 2: matrix-core kernel for few tiles
+    int shape = 0, splits = 0, second_pass = 0, tile_w = 0, tile_lw = 0;
+};
+constexpr int kChoices = 16;
+
 }  // namespace pconv
 
 struct pconv_packed {
@@ -120,6 +131,9 @@ struct pconv_packed {
     mutable pconv_packed* by_parity[2] = {nullptr, nullptr};
     mutable void* d_planes = nullptr;
     mutable size_t planes_bytes = 0;
+    mutable std::mutex choice_mutex;
+    mutable pconv::Choice choices[pconv::kChoices];
+    mutable unsigned next_choice = 0;
     // device copies (null when packed host-only)
     int device = -1;
     void* d_arena = nullptr;              // one allocation behind all of the pointers below and those of the layouts
@@ -155,11 +169,13 @@ struct MfmaConv {
     int rows;                   // 0: as many output rows per tile as fit; else that many
     int walk;                   // 1: one workgroup per tile; otherwise persistent workgroups that walk over the tiles
     int splits;                 // workgroups per tile, each with a part of the channel blocks (1: no split)
+    int tile_w, tile_lw;        // kernel for few tiles: columns of a tile and load width (tile_w 0: chosen by the library)
     int second_pass;            // splits > 1: the parts are added and stored by a second kernel, not by the last arriver
     float* ws;                  // splits > 1: workspace of mfma_workspace() floats
     unsigned* counters;         // splits > 1: mfma_workspace() counters, zero
 };
 constexpr int kMfmaShapes = 4;
+constexpr int kSmallShapes = 3;          // of the kernel for layers of few tiles: numbers kMfmaShapes + 1 .. in `shape`
 // tile heights (filters per workgroup) that the kernel's tile shapes use; weights are kept for each
 constexpr int kMfmaTileHeights[2] = {128, 64};
 constexpr int kOneByOneGroups = 4;       // channel ranges per block of the second copy of a 1x1 layer's weights
@@ -170,6 +186,10 @@ double mfma_estimate_us(const MfmaConv& a, int shape, int splits);
 // workspace that a launch with a.shape and a.splits > 1 needs
 int mfma_workspace(const MfmaConv& a, size_t* floats, size_t* counters);
 int launch_mfma_conv(const MfmaConv& a, void* stream);
+// implemented in pconv_small.hip: the matrix-core kernel for layers of few tiles, shapes 0..kSmallShapes-1
+// (chosen: tile_w, tile_lw and splits of *a are set to what the estimate is for)
+double small_estimate_us(MfmaConv* a, int shape);
+int launch_small_conv(const MfmaConv& a, int shape, void* stream);
 // dense fp16 weights OIHW on the device -> MfmaWeights order for tile height mt, all nine taps (the dense baseline)
 int launch_mfma_arrange(const void* w_oihw, void* out, int F, int C, int mt, void* stream);
 size_t mfma_weight_bytes(int F, int C, int mt, int n_taps);

@@ -51,6 +51,7 @@
 #include <mutex>
 
 #include "pconv_internal.h"
+#include "pconv_mfma_util.h"
 
 namespace pconv {
 
@@ -64,38 +65,6 @@ namespace pconv {
     } while (0)
 
 namespace {
-
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
-typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-typedef float float2v __attribute__((ext_vector_type(2)));
-typedef float float4v __attribute__((ext_vector_type(4)));
-typedef _Float16 half2v __attribute__((ext_vector_type(2)));
-
-constexpr uint32_t kInvalid = 0x80000000u;
-
-// Division by a divisor fixed for the launch (Granlund and Montgomery's round-up method, exact for 32-bit dividends).
-struct FastDiv {
-    unsigned m, s1, s2;
-};
-FastDiv make_fastdiv(unsigned d) {
-    unsigned l = 0;
-    while ((1ull << l) < d) ++l;
-    FastDiv f;
-    f.m = (unsigned)((((1ull << l) - d) << 32) / d + 1);
-    f.s1 = l < 1 ? l : 1;
-    f.s2 = l > 0 ? l - 1 : 0;
-    return f;
-}
-__device__ __forceinline__ unsigned fastdiv(unsigned x, const FastDiv& f) {
-    const unsigned t = __umulhi(x, f.m);
-    return (t + ((x - t) >> f.s1)) >> f.s2;
-}
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
 
 struct MfmaParams {
     const unsigned char* x;
@@ -146,46 +115,6 @@ struct MfmaParams {
     FastDiv div_Wo, div_Ho, div_G, div_cnt_full, div_tiles_m, div_sw_groups;
     int sw_groups;          // store pieces per output row: Wo / sw
 };
-
-template <int LW>
-struct Piece;   // LW pixels of one channel, as loaded
-template <>
-struct Piece<8> {
-    uint4v v;
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-        v = __builtin_amdgcn_raw_buffer_load_b128(r, (int)voff, (int)soff, 0);
-    }
-    __device__ __forceinline__ unsigned dword(int i) const { return i == 0 ? v.x : i == 1 ? v.y : i == 2 ? v.z : v.w; }
-};
-template <>
-struct Piece<4> {
-    uint2v v;
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-        v = __builtin_amdgcn_raw_buffer_load_b64(r, (int)voff, (int)soff, 0);
-    }
-    __device__ __forceinline__ unsigned dword(int i) const { return i ? v.y : v.x; }
-};
-template <>
-struct Piece<2> {
-    unsigned v;
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-        v = __builtin_amdgcn_raw_buffer_load_b32(r, (int)voff, (int)soff, 0);
-    }
-    __device__ __forceinline__ unsigned dword(int) const { return v; }
-};
-template <>
-struct Piece<1> {
-    unsigned v;
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t r, uint32_t voff, uint32_t soff) {
-        v = (unsigned short)__builtin_amdgcn_raw_buffer_load_b16(r, (int)voff, (int)soff, 0);
-    }
-    __device__ __forceinline__ unsigned dword(int) const { return v; }
-};
-
-// pixel `px` (0: low halves, 1: high halves) of two channels' dwords -> one dword {channel a, channel b}
-__device__ __forceinline__ unsigned interleave(unsigned a, unsigned b, int px) {
-    return px ? __builtin_amdgcn_perm(b, a, 0x07060302u) : __builtin_amdgcn_perm(b, a, 0x05040100u);
-}
 
 // Geometry of one tile (all wave-uniform): the m-tile, and the R consecutive output rows of the batch it covers.
 struct TileGeo {
@@ -1003,12 +932,20 @@ const Shape kShapes[kMfmaShapes] = {{2, 7, 2, 2}, {1, 7, 2, 2}, {1, 7, 4, 1}, {1
 
 // Workgroups of the persistent grid: as many as the device holds at once (compute units x workgroups that fit one),
 // no more than there are tiles, a multiple of 8 (one share per XCD).
-int persistent_grid(const void* kern, int threads, size_t lds, long long ntiles, int walk) {
+int persistent_grid(const void* kern, int threads, size_t lds, long long ntiles, int walk, std::atomic<unsigned>& resident) {
     if (walk == 1) return (int)std::min<long long>((ntiles + 7) / 8 * 8, 0x7FFFFFF8);   // one workgroup per tile
+    // (the runtime's answer is kept for the LDS size it was last asked about: LDS size << 8 | workgroups; every device of a
+    // machine that this library runs on is the same chip)
     int per_cu = 1;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-    const long long resident = (long long)compute_units() * per_cu / 8 * 8;
-    return (int)std::max<long long>(8, std::min<long long>((ntiles + 7) / 8 * 8, resident));
+    const unsigned known = resident.load(std::memory_order_relaxed);
+    if (known >> 8 == lds && known) {
+        per_cu = (int)(known & 255u);
+    } else {
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds) != hipSuccess || per_cu < 1) per_cu = 1;
+        resident.store((unsigned)(lds << 8) | (unsigned)std::min(per_cu, 255), std::memory_order_relaxed);
+    }
+    const long long at_once = (long long)compute_units() * per_cu / 8 * 8;
+    return (int)std::max<long long>(8, std::min<long long>((ntiles + 7) / 8 * 8, at_once));
 }
 
 // Steps of 2048 clocks by which every second workgroup starts late (0: all start together).  Half a tile's time,
@@ -1031,9 +968,10 @@ int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, doub
 #define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv)                                                                \
     if (lw == LWv && ki == KIv && full == FULLv && (p.nhwc != 0) == NHWCv) {                                    \
         auto kern = mfma_conv_kernel<AF, BF, WM, WN, LWv, KIv, FULLv, NHWCv>;                                   \
-        if (lds > 64 * 1024)                                                                                    \
-            PCONV_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-        const int grid = persistent_grid((const void*)kern, WM * WN * 64, lds, ntiles, walk);                        \
+        static LdsAllowance allowed;                                                                            \
+        static std::atomic<unsigned> resident{0};                                                               \
+        if (lds > 64 * 1024) PCONV_HIP(allowed.ask((const void*)kern));                                         \
+        const int grid = persistent_grid((const void*)kern, WM * WN * 64, lds, ntiles, walk, resident);         \
         MfmaParams q = p;                                                                                       \
         q.stagger = stagger_steps(p, grid, ntiles, walk, block_us);                                             \
         hipLaunchKernelGGL(kern, dim3(grid), dim3(WM* WN * 64), lds, st, q);                                    \

@@ -1,0 +1,152 @@
+"""The matrix-core kernel for layers of few tiles (mfma_shape 5, 6, 7; channel_splits = waves that share a tile) against
+the oracle: every shape with one to eight waves, sizes around its tiles (32 or 64 filters, 32 or 64 pixels), channel
+counts around its blocks and its steps of four blocks, rows that allow loads of four, two and one pixels, both strides
+and paddings, both layouts, channel lists, 1x1 layers."""
+import numpy as np
+import pytest
+
+import oracle
+import paper_2001_07710_amd as pc
+from workloads import layers as L
+
+from gpu_util import TOL, GpuLayer, rel_err
+from test_gpu_nhwc import run_nhwc
+
+pytestmark = pytest.mark.gpu
+M = pc.KERNEL_MFMA
+
+
+def say(*a):
+    print("[case]", *a, flush=True)
+
+
+SHAPES = [  # N, C, F, H, W, stride, pad
+    (1, 16, 32, 4, 8, 1, 1), (1, 3, 1, 1, 1, 1, 1), (2, 17, 33, 5, 9, 1, 1), (1, 136, 65, 8, 64, 1, 1),
+    (3, 40, 31, 7, 7, 1, 1), (1, 200, 64, 9, 33, 1, 0), (2, 24, 40, 13, 12, 2, 1), (1, 72, 96, 16, 28, 2, 1),
+    (2, 64, 24, 11, 30, 2, 0), (1, 8, 70, 3, 225, 1, 1), (1, 32, 16, 40, 56, 1, 1)]
+
+
+@pytest.mark.parametrize("case", SHAPES, ids=["n%dc%df%dh%dw%ds%dp%d" % c for c in SHAPES])
+def test_every_shape_and_number_of_waves(case):
+    N, C, F, H, W, stride, pad = case
+    spec = L.LayerSpec(cfg=36, idx=SHAPES.index(case), name="small", N=N, C=C, F=F, H=H, W=W, stride=stride, pad=pad,
+                       dtype="f16", K=12, keep=0.4)
+    layer = GpuLayer(spec)
+    x = L.gen_activations(spec)
+    for relu in (False, True):
+        ref = layer.oracle(x, relu)
+        for shape in (5, 6, 7):
+            for waves in (0, 1, 2, 4, 8):
+                say(case, shape, waves, relu)
+                try:
+                    got = layer.run(x, relu, kernel=M, mfma_shape=shape, channel_splits=waves)
+                except pc.PconvError as e:
+                    # (a patch that does not fit the loads or the LDS of so many waves; the automatic number always does)
+                    assert e.code == pc.EUNSUPPORTED and (waves == 8 or waves > (C + 15) // 16)
+                    continue
+                assert rel_err(got, ref) <= TOL["f16"], (case, shape, waves)
+        assert rel_err(layer.run(x, relu), ref) <= TOL["f16"]
+    for xs, ys in ((1, 0), (2, 3), (0, 2)):              # narrower loads, narrower stores
+        say(case, "x shifted by", xs, "y by", ys)
+        assert rel_err(layer.run(x, True, x_shift=xs, y_shift=ys, kernel=M, mfma_shape=6), layer.oracle(x, True)) <= TOL["f16"]
+    layer.free()
+
+
+@pytest.mark.parametrize("case", [(1, 16, 32, 4, 8, 1), (2, 24, 40, 7, 9, 1), (3, 136, 72, 14, 14, 1), (2, 64, 16, 9, 15, 2),
+                                  (1, 8, 96, 20, 56, 1)])
+def test_channel_minor_layout(case):
+    N, C, F, H, W, stride = case
+    spec = L.LayerSpec(cfg=37, idx=C + F, name="smallnhwc", N=N, C=C, F=F, H=H, W=W, stride=stride, dtype="f16", K=8, keep=0.6)
+    layer = GpuLayer(spec)
+    x = L.gen_activations(spec)
+    ref = layer.oracle(x, True)
+    for shape in (5, 6, 7):
+        for waves in (0, 1, 4):
+            if waves > (C + 15) // 16:
+                continue
+            say("nhwc", case, shape, waves)
+            assert rel_err(run_nhwc(layer, x, True, kernel=M, mfma_shape=shape, channel_splits=waves), ref) <= TOL["f16"]
+    assert rel_err(run_nhwc(layer, x, True), ref) <= TOL["f16"]
+    layer.free()
+
+
+def test_channel_lists_and_few_taps():
+    spec = L.LayerSpec(cfg=38, idx=1, name="smalllists", N=2, C=200, F=128, H=9, W=12, dtype="f16", K=8, keep=0.1)
+    w, _ = L.gen_clustered_weights(spec, 4, 0.2)
+    order = None
+    layer = GpuLayer(spec, w=w)
+    order = pc.filter_similarity_order(layer.mask, 64)
+    layer = GpuLayer(spec, w=w[order])
+    listed, blocks = pc.packed_mfma_blocks(layer.packed, 64)
+    assert listed < blocks                               # (the layer has channel lists)
+    x = L.gen_activations(spec)
+    ref = layer.oracle(x, False)
+    for shape in (5, 6, 7):
+        say("lists", shape)
+        assert rel_err(layer.run(x, False, kernel=M, mfma_shape=shape), ref) <= TOL["f16"]
+    layer.free()
+    # one pattern: four of the nine taps occur
+    spec = L.LayerSpec(cfg=38, idx=2, name="fourtaps", N=2, C=48, F=40, H=9, W=12, dtype="f16", K=1, keep=0.5, lib_kind="all126")
+    layer = GpuLayer(spec)
+    x = L.gen_activations(spec)
+    for shape in (5, 6, 7):
+        say("four taps", shape)
+        assert rel_err(layer.run(x, False, kernel=M, mfma_shape=shape), layer.oracle(x, False)) <= TOL["f16"]
+    layer.free()
+
+
+@pytest.mark.parametrize("case", [(1, 16, 32, 1, 1, 1), (2, 40, 33, 7, 7, 1), (1, 72, 130, 14, 14, 1), (2, 200, 64, 10, 9, 2),
+                                  (3, 64, 24, 8, 16, 2), (1, 528, 40, 6, 10, 1)])
+@pytest.mark.parametrize("nhwc", [False, True])
+def test_1x1_layers(case, nhwc):
+    import torch
+    N, C, F, H, W, stride = case
+    if nhwc and F % 8:
+        F = 40
+    r = np.random.default_rng(C + F + H)
+    G = -(-C // 9)
+    w = (r.standard_normal((F, C)) * np.sqrt(2.0 / C)).astype(np.float16)
+    lib = np.array(L.drawn_library(4, 8), dtype=np.uint16)
+    pid = r.integers(0, 8, (F, G)).astype(np.uint8)
+    mask = (r.random((F, G)) < 0.6).astype(np.uint8)
+    p = pc.pack_1x1(w, lib, pid, mask)
+    x = np.maximum(r.standard_normal((N, C, H, W)), 0).astype(np.float16)
+    b = (r.standard_normal(F) * 0.1).astype(np.float32)
+    ref = oracle.conv1x1(x, w, pid, mask, lib, b, stride)
+    Ho, Wo = ref.shape[2:]
+    dx = torch.from_numpy(np.ascontiguousarray(x.transpose(0, 2, 3, 1)) if nhwc else x).cuda()
+    st = torch.cuda.current_stream().cuda_stream
+    for shape in (0, 5, 6, 7):
+        for waves in (0, 1, 2) if shape else (0,):
+            if waves > (C + 63) // 64:
+                continue
+            say("1x1", case, nhwc, shape, waves)
+            dy = torch.full((N * F * Ho * Wo + 64,), -7.0, dtype=torch.float16, device="cuda")
+            pc.conv3x3_tuned(dx, dy, p, torch.from_numpy(b).cuda(), N, H, W, stride, 1, pc.FLAG_NHWC if nhwc else 0, st,
+                             kernel=M if shape else 0, mfma_shape=shape, channel_splits=waves)
+            torch.cuda.synchronize()
+            out = dy.cpu().numpy()
+            assert np.all(out[N * F * Ho * Wo:] == -7.0)
+            got = out[:N * F * Ho * Wo]
+            got = got.reshape(N, Ho, Wo, F).transpose(0, 3, 1, 2) if nhwc else got.reshape(N, F, Ho, Wo)
+            assert rel_err(got, ref) <= TOL["f16"], (case, shape, waves)
+    p.free()
+
+
+def test_the_choice_is_the_same_on_every_call():
+    """The handle keeps what the automatic choice came to; results are bit-equal from call to call, also when more sizes
+    than it keeps come by in between."""
+    spec = L.LayerSpec(cfg=39, idx=1, name="choice", N=1, C=64, F=48, H=14, W=14, dtype="f16", K=8, keep=0.3)
+    layer = GpuLayer(spec)
+    x = L.gen_activations(spec)
+    first = layer.run(x, True)
+    for round_ in range(2):
+        for h in range(3, 24):
+            sub = L.shrink(spec, H=h, W=h + 1)
+            layer.spec = sub
+            xs = L.gen_activations(sub)
+            a = layer.run(xs, True)
+            assert rel_err(a, layer.oracle(xs, True)) <= TOL["f16"]
+        layer.spec = spec
+        assert np.array_equal(layer.run(x, True).view(np.uint16), first.view(np.uint16))
+    layer.free()
