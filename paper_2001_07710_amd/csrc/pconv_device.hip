@@ -131,6 +131,167 @@ __global__ __launch_bounds__(64) void build_entries_kernel(const EntryParams p) 
     }
 }
 
+// The staging orders of the layer's tilings (see BalancedLayout), by the same greedy rule and with the same result as the
+// host's find_balanced(): channels by decreasing number of users go, one after the other, into the chunk where the busiest
+// wave stays least busy.  A chain of C short steps per filter group, and the groups are independent: one wave per group
+// and tiling, a lane per chunk (NBLK chunks), a step some 400 clocks of register arithmetic and one minimum over the lanes
+// -- 256 -> 256 channels: 45 us for the five tilings side by side, 210 us on three host threads.
+struct OrderLayout {
+    uint32_t* perm;
+    uint16_t* pos_of;
+    int fw, fg, cc_shift, nch, groups;
+};
+struct OrderParams {
+    const uint32_t* canon;
+    const uint32_t* row;
+    int F, C;
+    OrderLayout lay[kMaxLayouts];
+};
+// smallest value of the wave's lanes
+__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+#define PCONV_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, ctrl, 0xF, 0xF, false))
+    PCONV_DPP_MIN(0x111);   // row_shr:1, 2, 4, 8
+    PCONV_DPP_MIN(0x112);
+    PCONV_DPP_MIN(0x114);
+    PCONV_DPP_MIN(0x118);
+    PCONV_DPP_MIN(0x142);   // row_bcast:15
+    PCONV_DPP_MIN(0x143);   // row_bcast:31
+#undef PCONV_DPP_MIN
+    return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// Stable counting sort of the wave's channels: fn(c) -> bin (negative: left out) of fewer than 2^bits bins; at[] are the
+// bins' cursors, place(c, cursor value) is called for every channel, channels ascending inside a bin.
+template <typename Bin, typename Place>
+__device__ __forceinline__ void place_channels(int C, int bits, uint32_t* at, Bin bin, Place place) {
+    const int lane = threadIdx.x;
+    for (int c0 = 0; c0 < C; c0 += 64) {
+        const int c = c0 + lane, k = c < C ? bin(c) : -1;
+        unsigned long long same = __ballot(k >= 0);
+        for (int q = 0; q < bits; ++q) {
+            const unsigned long long ones = __ballot(k >> q & 1);
+            same &= (k >> q & 1) ? ones : ~ones;
+        }
+        const uint32_t rank = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
+        const uint32_t d = k >= 0 ? at[k] + rank : 0u;
+        __syncthreads();
+        if (k >= 0) {
+            if (rank + 1 == (uint32_t)__popcll(same)) at[k] = d + 1;
+            place(c, d);
+        }
+        __syncthreads();
+    }
+}
+template <int NBLK>
+__global__ __launch_bounds__(64) void order_channels_kernel(const OrderParams p) {
+    extern __shared__ __align__(16) unsigned char order_lds[];
+    const OrderLayout& l = p.lay[blockIdx.y];
+    const int g = blockIdx.x, lane = threadIdx.x, C = p.C;
+    if (g >= l.groups) return;
+    uint32_t* const uses = reinterpret_cast<uint32_t*>(order_lds);              // [C][16] bytes: kernels per wave
+    uint16_t* const order = reinterpret_cast<uint16_t*>(uses + (size_t)C * 4);  // [C]
+    uint16_t* const chunk = order + C;                                          // [C]
+    uint8_t* const weight = reinterpret_cast<uint8_t*>(chunk + C);              // [C]
+    uint32_t* const at = reinterpret_cast<uint32_t*>(order_lds + ((size_t)C * 21 + 15) / 16 * 16);    // [max(64, nch)]
+    const int npos = l.nch << l.cc_shift;
+    for (int i = lane; i < C * 4; i += 64) uses[i] = 0u;
+    for (int i = lane; i < npos; i += 64) l.perm[(size_t)g * npos + i] = kNoChannel;
+    at[lane] = 0u;
+    __syncthreads();
+    const int i0 = g * l.fg, i1 = min(p.F, i0 + l.fg);
+    for (int i = i0; i < i1; ++i) {
+        const int w = (i - i0) % l.fw;
+        for (uint32_t e = p.row[i] + lane; e < p.row[i + 1]; e += 64)
+            atomicAdd(&uses[(p.canon[2 * (size_t)e + 1] & 0xFFFFu) * 4 + (w >> 2)], 1u << (w & 3) * 8);
+    }
+    __syncthreads();
+    for (int c = lane; c < C; c += 64) {
+        uint32_t n = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const uint32_t u = uses[c * 4 + q];
+            n += (u & 0xFFu) + (u >> 8 & 0xFFu) + (u >> 16 & 0xFFu) + (u >> 24);
+        }
+        weight[c] = (uint8_t)n;                                                 // (at most fg <= 32)
+        atomicAdd(&at[32 - n], 1u);
+    }
+    __syncthreads();
+    {   // bins are 32 - weight: most users first
+        uint32_t incl = lane <= 32 ? at[lane] : 0u;
+        const uint32_t own = incl;
+#pragma unroll
+        for (int d = 1; d < 64; d <<= 1) {
+            const uint32_t o = __shfl_up(incl, d);
+            if (lane >= d) incl += o;
+        }
+        __syncthreads();
+        at[lane] = incl - own;
+    }
+    __syncthreads();
+    const int n_used = (int)at[32];                                             // (where the unused ones begin)
+    place_channels(C, 6, at, [&](int c) { return weight[c] ? 32 - (int)weight[c] : -1; },
+                   [&](int c, uint32_t d) { order[d] = (uint16_t)c; });
+    // the chunks: kernels per wave in bytes, and users << 12 | number of the chunk
+    uint32_t load[NBLK][4], total[NBLK], room[NBLK];
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b) {
+        const int k = b * 64 + lane;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) load[b][q] = 0u;
+        total[b] = (uint32_t)k;
+        room[b] = k < l.nch ? 1u << l.cc_shift : 0u;
+    }
+    __syncthreads();
+    uint32_t u[4], c = n_used > 0 ? order[0] : 0u, wt = n_used > 0 ? weight[c] : 0u;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) u[q] = n_used > 0 ? uses[c * 4 + q] : 0u;
+    for (int r = 0; r < n_used; ++r) {
+        // (the next channel's numbers are read while this one is placed)
+        const uint32_t cn = r + 1 < n_used ? order[r + 1] : 0u, wn = weight[cn];
+        uint32_t un[4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) un[q] = uses[cn * 4 + q];
+        uint32_t key = ~0u;
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b) {
+            uint32_t m = 0;                                                     // maximum of the 16 bytes, in two halves
+            typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const uint32_t v = load[b][q] + u[q];
+                const ushort2v even = __builtin_bit_cast(ushort2v, v & 0x00FF00FFu), odd = __builtin_bit_cast(ushort2v, v >> 8 & 0x00FF00FFu);
+                m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2v, m), __builtin_elementwise_max(even, odd)));
+            }
+            m = max(m & 0xFFFFu, m >> 16);
+            key = min(key, room[b] ? total[b] + (m << 23) : ~0u);
+        }
+        const uint32_t best = wave_min(key) & 0xFFFu;
+#pragma unroll
+        for (int b = 0; b < NBLK; ++b)
+            if (best == (uint32_t)(b * 64 + lane)) {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) load[b][q] += u[q];
+                total[b] += wt << 12;
+                --room[b];
+                chunk[c] = (uint16_t)best;
+            }
+        c = cn;
+        wt = wn;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) u[q] = un[q];
+    }
+    __syncthreads();
+    // positions: the channels of a chunk in ascending order
+    for (int k = lane; k < l.nch; k += 64) at[k] = (uint32_t)k << l.cc_shift;
+    __syncthreads();
+    int bits = 0;
+    while ((1 << bits) < l.nch) ++bits;
+    place_channels(C, bits, at, [&](int ch) { return weight[ch] ? (int)chunk[ch] : -1; },
+                   [&](int ch, uint32_t d) {
+                       l.pos_of[(size_t)g * C + ch] = (uint16_t)d;
+                       l.perm[(size_t)g * npos + d] = (uint32_t)ch;
+                   });
+}
+
 // The matrix-core weights of the layer (see MfmaWeights), cleared beforehand: one thread per kept kernel and copy.
 struct ScatterCopy {
     uint16_t* w;
@@ -205,7 +366,8 @@ int upload_packed(pconv_packed* p) {
     const size_t at_canon = put_vector(p->canon), at_forder = put_vector(p->filter_order), at_w4 = put_vector(p->w4);
     const size_t at_row = put_vector(row), at_rank = put(rank, sizeof(rank));
     std::vector<size_t> at_perm(nl), at_pos(nl), at_ent(nl), at_eptr(nl), at_clist(nm), at_tinfo(nm), at_mpos(nm), at_mw(nm);
-    for (size_t t = 0; t < nl; ++t) {
+    const bool order_here = p->C <= kOrderChannels;
+    for (size_t t = 0; t < nl && !order_here; ++t) {
         at_perm[t] = put_vector(p->balanced[t].perm);
         at_pos[t] = put_vector(p->balanced[t].pos_of);
     }
@@ -220,6 +382,11 @@ int upload_packed(pconv_packed* p) {
     const size_t cleared = size;
     const size_t ent_bytes = std::max<size_t>(n, 1) * sizeof(DevEntry);
     const size_t at_ent0 = take(ent_bytes), at_eptr0 = take(((size_t)p->F * p->n_buckets + 1) * sizeof(uint32_t));
+    for (size_t t = 0; t < nl && order_here; ++t) {
+        const BalancedLayout& b = p->balanced[t];
+        at_perm[t] = take((size_t)b.n_groups * b.n_chunks * b.cc * sizeof(uint32_t));
+        at_pos[t] = take((size_t)b.n_groups * p->C * sizeof(uint16_t));
+    }
     for (size_t t = 0; t < nl; ++t) {
         at_ent[t] = take(ent_bytes);
         at_eptr[t] = take(((size_t)p->F * p->balanced[t].n_chunks + 1) * sizeof(uint32_t));
@@ -246,6 +413,27 @@ int upload_packed(pconv_packed* p) {
         ep.lay[t + 1] = {reinterpret_cast<DevEntry*>(base + at_ent[t]), reinterpret_cast<uint32_t*>(base + at_eptr[t]),
                          reinterpret_cast<uint16_t*>(base + at_pos[t]), log2_of(b.cc), b.n_chunks, b.fw * b.nf};
         most_chunks = std::max(most_chunks, b.n_chunks);
+    }
+    if (order_here && nl) {
+        OrderParams op{};
+        op.canon = ep.canon;
+        op.row = ep.row;
+        op.F = p->F;
+        op.C = p->C;
+        int most_groups = 0;
+        for (size_t t = 0; t < nl; ++t) {
+            const BalancedLayout& b = p->balanced[t];
+            op.lay[t] = {reinterpret_cast<uint32_t*>(base + at_perm[t]), reinterpret_cast<uint16_t*>(base + at_pos[t]), b.fw,
+                         b.fw * b.nf, log2_of(b.cc), b.n_chunks, b.n_groups};
+            most_groups = std::max(most_groups, b.n_groups);
+        }
+        const size_t lds = ((size_t)p->C * 21 + 15) / 16 * 16 + (size_t)std::max(64, most_chunks) * sizeof(uint32_t);
+        const dim3 grid((unsigned)most_groups, (unsigned)nl);
+        if (most_chunks <= 64)
+            hipLaunchKernelGGL(order_channels_kernel<1>, grid, dim3(64), lds, 0, op);
+        else
+            hipLaunchKernelGGL(order_channels_kernel<2>, grid, dim3(64), lds, 0, op);
+        PCONV_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(build_entries_kernel, dim3((unsigned)p->F, (unsigned)(nl + 1)), dim3(64), most_chunks * sizeof(uint32_t), 0, ep);
     PCONV_HIP(hipGetLastError());

@@ -1,13 +1,10 @@
 // Host side of libpconv: argument checks, pattern assignment, connectivity selection, packing, export.
 // Pure C++ (no HIP calls here); the device upload lives in pconv_device.hip.
 #include <algorithm>
-#include <atomic>
 #include <cmath>
 #include <cstring>
-#include <exception>
 #include <new>
 #include <numeric>
-#include <thread>
 
 #include "pconv_internal.h"
 
@@ -166,15 +163,10 @@ void list_kernels(const E* w, int F, int C, const uint16_t* lib, int K, const ui
     out->c.resize(n);
 }
 
-// Builds the balanced order of `p` for one tiling (see pconv::BalancedLayout).
-void build_balanced(const pconv_packed* p, int fw, int nf, int cc, pconv::BalancedLayout* out) {
+// Finds the balanced order of `p` for the tiling that *out describes (see pconv::BalancedLayout).
+void find_balanced(const pconv_packed* p, pconv::BalancedLayout* out) {
     const int F = p->F, C = p->C, K = p->K;
-    const int fg = fw * nf;
-    out->fw = fw;
-    out->nf = nf;
-    out->cc = cc;
-    out->n_groups = (F + fg - 1) / fg;
-    out->n_chunks = (C + cc - 1) / cc;
+    const int fw = out->fw, fg = fw * out->nf, cc = out->cc;
     const int nch = out->n_chunks, npos = nch * cc;
     out->perm.assign((size_t)out->n_groups * npos, pconv::kNoChannel);
     out->pos_of.assign((size_t)out->n_groups * C, 0);
@@ -251,32 +243,21 @@ void build_balanced(const pconv_packed* p, int fw, int nf, int cc, pconv::Balanc
     }
 }
 
-// The balanced layouts for the tilings of the automatic choice (waves, filters per wave, channels per chunk; the
-// 16-channel ones are the quad kernel's).  They do not depend on each other and are most of the time of packing a layer,
-// so a layer that is worth it (below: less than a thread's start) has two more threads take them off one list.
-void build_all_balanced(pconv_packed* p) {
-    static const int tilings[5][3] = {{8, 1, 32}, {16, 1, 16}, {16, 1, 32}, {16, 2, 32}, {16, 2, 16}};   // (longest first)
+// The tilings of the automatic choice (waves, filters per wave, channels per chunk; the 16-channel ones are the quad
+// kernel's).
+void plan_balanced(pconv_packed* p) {
+    static const int tilings[5][3] = {{16, 2, 32}, {16, 1, 32}, {8, 1, 32}, {16, 2, 16}, {16, 1, 16}};
     p->balanced.resize(5);
-    std::atomic<int> next{0};
-    std::atomic<bool> no_memory{false};
-    auto work = [&] {
-        try {
-            for (int t = next++; t < 5; t = next++)
-                build_balanced(p, tilings[t][0], tilings[t][1], tilings[t][2], &p->balanced[(size_t)t]);
-        } catch (const std::bad_alloc&) {
-            no_memory = true;
-        }
-    };
-    std::thread helpers[2];
-    if ((long long)p->F * p->C >= 128 * 128) {
-        try {
-            for (std::thread& h : helpers) h = std::thread(work);
-        } catch (const std::exception&) {}                    // (no thread to be had: what there is does the work)
+    for (int t = 0; t < 5; ++t) {
+        pconv::BalancedLayout& b = p->balanced[(size_t)t];
+        b.fw = tilings[t][0];
+        b.nf = tilings[t][1];
+        b.cc = tilings[t][2];
+        const int fg = b.fw * b.nf;
+        b.n_groups = (p->F + fg - 1) / fg;
+        b.n_chunks = (p->C + b.cc - 1) / b.cc;
+        if (p->C > pconv::kOrderChannels) find_balanced(p, &b);
     }
-    work();
-    for (std::thread& h : helpers)
-        if (h.joinable()) h.join();
-    if (no_memory) throw std::bad_alloc();
 }
 
 // What the device needs to lay out the layer's weights in matrix-core order for workgroup tiles of mt filters (see
@@ -398,7 +379,7 @@ int pack_list(const KernelList& list, int dtype, int F, int C, const uint16_t* l
         p->grp_ptr[(size_t)F * K] = e;
         p->n_buckets = (C + pconv::kBucket - 1) / pconv::kBucket;
 
-        build_all_balanced(p);
+        plan_balanced(p);
         if (dtype == PCONV_F16 && want_mfma) {
             const int nh = (int)(sizeof(pconv::kMfmaTileHeights) / sizeof(int));
             p->mfma.resize((size_t)nh);
@@ -757,6 +738,16 @@ extern "C" int pconv_packed_balance(const pconv_packed* p, int waves, int filter
     for (const pconv::BalancedLayout& b : p->balanced)
         if (b.fw == waves && b.nf == filters_per_wave && b.cc == cc) bl = &b;
     if (balanced && !bl) return PCONV_EUNSUPPORTED;
+    pconv::BalancedLayout found;
+    if (balanced && bl->pos_of.empty()) {                    // (the order is on the device only: found again)
+        try {
+            found = *bl;
+            find_balanced(p, &found);
+            bl = &found;
+        } catch (const std::bad_alloc&) {
+            return PCONV_ENOMEM;
+        }
+    }
     const int nch = balanced ? bl->n_chunks : (p->C + cc - 1) / cc;
     // kept kernels of (filter position, chunk of 32 staged channels), from the canonical arrays
     std::vector<uint32_t> counts;

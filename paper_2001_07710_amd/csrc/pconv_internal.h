@@ -38,6 +38,8 @@ static_assert(sizeof(DevEntry) == 32, "DevEntry must be 32 bytes");
 struct BalancedLayout {
     int fw = 0, nf = 0, cc = 0;
     int n_groups = 0, n_chunks = 0;
+    // the order itself is found on the device (order_channels_kernel) for layers of at most kOrderChannels channels, whose
+    // two vectors here stay empty, and on the host by find_balanced() for larger ones and for introspection
     std::vector<uint32_t> perm;      // [n_groups][n_chunks*cc]: channel staged at each position, 0xFFFFFFFF = none
     std::vector<uint16_t> pos_of;    // [n_groups][C]: position of a channel in its group's order (channels it stages)
     // on the device only, made there from the canonical arrays and pos_of (build_entries_kernel):
@@ -47,6 +49,7 @@ struct BalancedLayout {
 };
 
 constexpr uint32_t kNoChannel = 0xFFFFFFFFu;
+constexpr int kOrderChannels = 2048;
 
 // The layer's weights as the matrix-core kernel (fp16 storage) stages them: dense over the taps that occur in the
 // layer, explicit zeros where a kernel is removed or a tap lies outside its pattern.  For workgroup tiles of `mt`
