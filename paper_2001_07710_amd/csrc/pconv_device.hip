@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64) void build_entries_kernel(const EntryParams p) 
 // host's find_balanced(): channels by decreasing number of users go, one after the other, into the chunk where the busiest
 // wave stays least busy.  A chain of C short steps per filter group, and the groups are independent: one wave per group
 // and tiling, a lane per chunk (NBLK chunks), a step some 400 clocks of register arithmetic and one minimum over the lanes
-// -- 256 -> 256 channels: 45 us for the five tilings side by side, 210 us on three host threads.
+// -- 256 -> 256 channels: 50 us for the five tilings side by side, 210 us on three host threads.
 struct OrderLayout {
     uint32_t* perm;
     uint16_t* pos_of;
@@ -195,14 +195,34 @@ __global__ __launch_bounds__(64) void order_channels_kernel(const OrderParams p)
     const int npos = l.nch << l.cc_shift;
     for (int i = lane; i < C * 4; i += 64) uses[i] = 0u;
     for (int i = lane; i < npos; i += 64) l.perm[(size_t)g * npos + i] = kNoChannel;
-    at[lane] = 0u;
-    __syncthreads();
     const int i0 = g * l.fg, i1 = min(p.F, i0 + l.fg);
-    for (int i = i0; i < i1; ++i) {
-        const int w = (i - i0) % l.fw;
-        for (uint32_t e = p.row[i] + lane; e < p.row[i + 1]; e += 64)
-            atomicAdd(&uses[(p.canon[2 * (size_t)e + 1] & 0xFFFFu) * 4 + (w >> 2)], 1u << (w & 3) * 8);
+    // (all entries of the group in one run, eight loads at a time, an entry's filter by bisection: filter by filter this was
+    // half the kernel, one trip to memory after the other)
+    if (lane <= i1 - i0) at[lane] = p.row[i0 + lane];                           // (at most 33 rows)
+    __syncthreads();
+    const uint32_t e0 = at[0], e1 = at[i1 - i0];
+    for (uint32_t first = e0; first < e1; first += 64 * 8) {
+        uint32_t cm[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t e = first + k * 64 + lane;
+            cm[k] = e < e1 ? p.canon[2 * (size_t)e + 1] : 0u;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const uint32_t e = first + k * 64 + lane;
+            if (e >= e1) continue;
+            int lo = 0, hi = i1 - i0;                                           // at[lo] <= e < at[hi]
+            while (hi - lo > 1) {
+                const int mid = (lo + hi) >> 1;
+                if (at[mid] <= e) lo = mid; else hi = mid;
+            }
+            const int w = lo % l.fw;
+            atomicAdd(&uses[(cm[k] & 0xFFFFu) * 4 + (w >> 2)], 1u << (w & 3) * 8);
+        }
     }
+    __syncthreads();
+    at[lane] = 0u;
     __syncthreads();
     for (int c = lane; c < C; c += 64) {
         uint32_t n = 0;
@@ -241,43 +261,47 @@ __global__ __launch_bounds__(64) void order_channels_kernel(const OrderParams p)
         room[b] = k < l.nch ? 1u << l.cc_shift : 0u;
     }
     __syncthreads();
-    uint32_t u[4], c = n_used > 0 ? order[0] : 0u, wt = n_used > 0 ? weight[c] : 0u;
+    // 64 channels at a time: lane i holds the i-th one's numbers, from where they are broadcast as scalars (from LDS, each
+    // step would wait for two dependent reads)
+    for (int r0 = 0; r0 < n_used; r0 += 64) {
+        const bool there = r0 + lane < n_used;
+        const uint32_t mine = there ? order[r0 + lane] : 0u, my_weight = there ? (uint32_t)weight[mine] << 12 : 0u;
+        uint32_t my_uses[4], my_chunk = 0;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) u[q] = n_used > 0 ? uses[c * 4 + q] : 0u;
-    for (int r = 0; r < n_used; ++r) {
-        // (the next channel's numbers are read while this one is placed)
-        const uint32_t cn = r + 1 < n_used ? order[r + 1] : 0u, wn = weight[cn];
-        uint32_t un[4];
+        for (int q = 0; q < 4; ++q) my_uses[q] = there ? uses[mine * 4 + q] : 0u;
+        const int count = min(64, n_used - r0);
+        for (int i = 0; i < count; ++i) {
+            uint32_t u[4];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) un[q] = uses[cn * 4 + q];
-        uint32_t key = ~0u;
+            for (int q = 0; q < 4; ++q) u[q] = (uint32_t)__builtin_amdgcn_readlane((int)my_uses[q], i);
+            const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)my_weight, i);
+            uint32_t key = ~0u;
 #pragma unroll
-        for (int b = 0; b < NBLK; ++b) {
-            uint32_t m = 0;                                                     // maximum of the 16 bytes, in two halves
-            typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+            for (int b = 0; b < NBLK; ++b) {
+                typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+                ushort2v m[4];                                                  // maxima of the 16 bytes, in halves
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const uint32_t v = load[b][q] + u[q];
-                const ushort2v even = __builtin_bit_cast(ushort2v, v & 0x00FF00FFu), odd = __builtin_bit_cast(ushort2v, v >> 8 & 0x00FF00FFu);
-                m = __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(ushort2v, m), __builtin_elementwise_max(even, odd)));
+                for (int q = 0; q < 4; ++q) {
+                    const uint32_t v = load[b][q] + u[q];
+                    m[q] = __builtin_elementwise_max(__builtin_bit_cast(ushort2v, v & 0x00FF00FFu),
+                                                     __builtin_bit_cast(ushort2v, v >> 8 & 0x00FF00FFu));
+                }
+                const ushort2v m2 = __builtin_elementwise_max(__builtin_elementwise_max(m[0], m[1]), __builtin_elementwise_max(m[2], m[3]));
+                const uint32_t most = max((uint32_t)m2.x, (uint32_t)m2.y);
+                key = min(key, room[b] ? total[b] + (most << 23) : ~0u);
             }
-            m = max(m & 0xFFFFu, m >> 16);
-            key = min(key, room[b] ? total[b] + (m << 23) : ~0u);
+            const uint32_t best = wave_min(key) & 0xFFFu;
+#pragma unroll
+            for (int b = 0; b < NBLK; ++b) {
+                const bool hit = best == (uint32_t)(b * 64 + lane);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) load[b][q] += hit ? u[q] : 0u;
+                total[b] += hit ? wt : 0u;
+                room[b] -= hit ? 1u : 0u;
+            }
+            my_chunk = lane == i ? best : my_chunk;
         }
-        const uint32_t best = wave_min(key) & 0xFFFu;
-#pragma unroll
-        for (int b = 0; b < NBLK; ++b)
-            if (best == (uint32_t)(b * 64 + lane)) {
-#pragma unroll
-                for (int q = 0; q < 4; ++q) load[b][q] += u[q];
-                total[b] += wt << 12;
-                --room[b];
-                chunk[c] = (uint16_t)best;
-            }
-        c = cn;
-        wt = wn;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) u[q] = un[q];
+        if (there) chunk[mine] = (uint16_t)my_chunk;
     }
     __syncthreads();
     // positions: the channels of a chunk in ascending order
