@@ -214,7 +214,8 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const T* __restrict__ 
 // ---- connectivity selection: the k largest squared norms, equal ones by ascending index, without sorting anything.
 //
 // The squared norm of a pattern-pruned kernel is its key: a non-negative double's bit pattern orders like its value.
-// Up to kSmallN kernels are one workgroup's work, keys in registers.  More of them go through a radix selection: one
+// Up to kSmallN kernels are one workgroup's work, keys in registers; up to kMidN one workgroup still ranks them, while
+// many compute the keys.  More of them go through a radix selection: one
 // pass computes the keys and counts their exponents, one counts the next 10 bits of the keys with the exponent of the
 // k-th largest, one gathers the keys that share those 21 bits (a few hundred of 1.6 million), and a single workgroup
 // finds the k-th largest among them; the last pass compares every key with it.  Every pass works out the position of
@@ -226,6 +227,7 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const T* __restrict__ 
 // through memory and back; 55 us so, of which 15 read the weights (59 MB at the rate of a copy).
 constexpr int kSelThreads = 1024;
 constexpr long long kSmallN = 8 * kSelThreads;                 // up to 8 keys per thread: one workgroup's work
+constexpr long long kMidN = 32 * kSelThreads;                  // ... and 32, with two registers a key
 constexpr int kBins = 2048;                                    // exponents
 constexpr int kBins1 = 1024;                                   // the 10 bits below
 constexpr int kReplicas = 8;                                   // copies of the first counts: blocks share few exponents
@@ -357,15 +359,16 @@ __global__ __launch_bounds__(kThreads) void select_all_kernel(uint8_t* mask, lon
 }
 
 // The weights of a block's kernels are loaded as one coalesced run and parked in LDS, as in assign_kernel.
-template <typename T>
+template <typename T, bool COUNT>
 __global__ __launch_bounds__(kThreads) void norm_key_kernel(const T* __restrict__ w, long long n, Library lib, int K,
                                                             const int32_t* __restrict__ pid,
                                                             unsigned long long* __restrict__ key, SelectState* st) {
     __shared__ __attribute__((aligned(16))) T tile[kThreads * 9];
     __shared__ uint32_t masks[126];
-    __shared__ unsigned hist[kBins];
+    __shared__ unsigned hist[COUNT ? kBins : 1];
     if ((int)threadIdx.x < K) masks[threadIdx.x] = lib.mask[threadIdx.x];
-    for (int b = threadIdx.x; b < kBins; b += kThreads) hist[b] = 0u;
+    if constexpr (COUNT)
+        for (int b = threadIdx.x; b < kBins; b += kThreads) hist[b] = 0u;
     constexpr int PER = 16 / (int)sizeof(T);
     for (long long first = (long long)blockIdx.x * kThreads; first < n; first += (long long)gridDim.x * kThreads) {
         const int count = (int)(n - first < kThreads ? n - first : kThreads);
@@ -381,12 +384,14 @@ __global__ __launch_bounds__(kThreads) void norm_key_kernel(const T* __restrict_
         if ((int)threadIdx.x < count) {
             const unsigned long long e = norm_key(tile + threadIdx.x * 9, masks[(q >= 0 && q < K) ? q : 0]);
             key[first + threadIdx.x] = e;
-            atomicAdd(&hist[(unsigned)(e >> 52)], 1u);
+            if constexpr (COUNT) atomicAdd(&hist[(unsigned)(e >> 52)], 1u);
         }
     }
-    __syncthreads();
-    for (int b = threadIdx.x; b < kBins; b += kThreads)
-        if (hist[b]) atomicAdd(&st->hist0[blockIdx.x % kReplicas][b], hist[b]);
+    if constexpr (COUNT) {
+        __syncthreads();
+        for (int b = threadIdx.x; b < kBins; b += kThreads)
+            if (hist[b]) atomicAdd(&st->hist0[blockIdx.x % kReplicas][b], hist[b]);
+    }
 }
 
 // Where the k-th largest lies among `bins` counted digits: the digit, and its rank (from 1) among the keys with that
@@ -500,6 +505,24 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const unsign
     }
 }
 
+// The k-th largest of the workgroup's keys, all of them at least `base` and alike above the lowest `bits`, and of those
+// equal to it the index of the last to be kept, lowest index first (`late`: ~index, 0 where there is no key).
+template <int PER>
+__device__ __forceinline__ void block_rank(const unsigned long long (&key)[PER], unsigned (&late)[PER],
+                                           unsigned long long base, int bits, unsigned k, uint4v* slots,
+                                           unsigned long long* kth, unsigned* last_index) {
+    unsigned turn = 0, above = 0;
+    const unsigned long long t = block_kth(key, base, bits, k, slots, turn);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        above += (unsigned)__popcll(__ballot(key[j] > t));
+        if (key[j] != t) late[j] = 0u;
+    }
+    above = block_total(above, slots, turn);
+    *kth = t;
+    *last_index = ~block_kth(late, 0u, 32, k - above, slots, turn);
+}
+
 // One workgroup: the k-th largest among the gathered keys, equal ones by index.
 __global__ __launch_bounds__(kSelThreads) void select_finish_kernel(unsigned k, SelectState* st) {
     __shared__ unsigned scratch[18];
@@ -520,19 +543,96 @@ __global__ __launch_bounds__(kSelThreads) void select_finish_kernel(unsigned k, 
         key[j] = at < m ? st->list_key[at] : 0ull;
         late[j] = at < m ? ~st->list_index[at] : 0u;
     }
-    unsigned turn = 0;
-    const unsigned long long t = block_kth(key, (unsigned long long)prefix << 42, 42, rank, slots, turn);
-    unsigned above = 0;
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        above += (unsigned)__popcll(__ballot(key[j] > t));
-        if (key[j] != t) late[j] = 0u;
-    }
-    above = block_total(above, slots, turn);
-    const unsigned bound = block_kth(late, 0u, 32, rank - above, slots, turn);
+    unsigned long long t;
+    unsigned last;
+    block_rank(key, late, (unsigned long long)prefix << 42, 42, rank, slots, &t, &last);
     if (threadIdx.x == 0) {
         st->threshold = t;
-        st->last_index = ~bound;
+        st->last_index = last;
+    }
+}
+
+// kSmallN < n <= kMidN: one workgroup ranks the keys that norm_key_kernel left, from registers.  Their leading 19 bits
+// are counted as a distance from the largest key's -- 256 bins an octave over the 16 octaves below it, everything
+// smaller in the last bin -- and only the keys that share the k-th largest's bin are ranked bit by bit; where those do
+// not fit the list (equal norms by the thousand), all keys are.  The radix selection's nine launches took 52 us of an iteration at
+// 12607 fp16 kernels (46 us with a library's sort); two launches take 23 us.
+template <int PER>
+__global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned long long* __restrict__ src, int n,
+                                                                 unsigned k, uint8_t* __restrict__ mask) {
+    constexpr int DIST = 4096, LIST = kListCap / kSelThreads, LOW = 44;
+    __shared__ unsigned hist[DIST], scratch[18], listed;
+    __shared__ unsigned long long list_key[kListCap], wave_max[kSelThreads / 64];
+    __shared__ unsigned list_late[kListCap];
+    __shared__ uint4v slots[8];
+    unsigned long long key[PER], top = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * kSelThreads + (int)threadIdx.x;
+        key[j] = i < n ? src[i] : 0ull;
+    }
+    for (int b = threadIdx.x; b < DIST; b += kSelThreads) hist[b] = 0u;
+    if (threadIdx.x == 0) listed = 0u;
+#pragma unroll
+    for (int j = 0; j < PER; ++j) top = key[j] > top ? key[j] : top;
+    for (int d = 32; d > 0; d >>= 1) {
+        const unsigned long long o = __shfl_xor(top, d);
+        top = o > top ? o : top;
+    }
+    if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = top;
+    __syncthreads();
+    for (int q = 0; q < kSelThreads / 64; ++q) top = wave_max[q] > top ? wave_max[q] : top;
+    const unsigned first = (unsigned)(top >> LOW);            // (19 bits)
+    auto bin = [&](unsigned long long e) {                    // larger keys, larger bins
+        const unsigned d = first - (unsigned)(e >> LOW);
+        return d < (unsigned)DIST ? (unsigned)DIST - 1u - d : 0u;
+    };
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (j * kSelThreads + (int)threadIdx.x < n) atomicAdd(&hist[bin(key[j])], 1u);
+    __syncthreads();
+    unsigned digit, rank;
+    find_digit<DIST>(hist, 1, k, scratch, &digit, &rank);
+    const bool fits = hist[digit] <= (unsigned)kListCap;
+    unsigned long long t;
+    unsigned last;
+    if (fits) {                                               // (uniform)
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * kSelThreads + (int)threadIdx.x;
+            if (i < n && bin(key[j]) == digit) {
+                const unsigned at = atomicAdd(&listed, 1u);
+                list_key[at] = key[j];
+                list_late[at] = ~(unsigned)i;
+            }
+        }
+        __syncthreads();
+        const unsigned m = listed;
+        unsigned long long some[LIST];
+        unsigned late[LIST];
+#pragma unroll
+        for (int j = 0; j < LIST; ++j) {
+            const unsigned at = (unsigned)j * kSelThreads + threadIdx.x;
+            some[j] = at < m ? list_key[at] : 0ull;
+            late[j] = at < m ? list_late[at] : 0u;
+        }
+        // (the last bin's keys share no leading bits)
+        const bool whole = digit == 0;
+        const unsigned long long base = (unsigned long long)(first - ((unsigned)DIST - 1u - digit)) << LOW;
+        block_rank(some, late, whole ? 0ull : base, whole ? 63 : LOW, rank, slots, &t, &last);
+    } else {
+        unsigned late[PER];
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * kSelThreads + (int)threadIdx.x;
+            late[j] = i < n ? ~(unsigned)i : 0u;
+        }
+        block_rank(key, late, 0ull, 63, k, slots, &t, &last);
+    }
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const int i = j * kSelThreads + (int)threadIdx.x;
+        if (i < n) mask[i] = key[j] > t || (key[j] == t && (unsigned)i <= last) ? 1 : 0;
     }
 }
 
@@ -662,9 +762,9 @@ extern "C" int pconv_select_connectivity_device(const void* w, int dtype, long l
     if (!workspace_bytes || n < 0 || (dtype != PCONV_F32 && dtype != PCONV_F16)) return PCONV_EINVAL;
     if (n > 0x7FFFFFFFll) return PCONV_ESHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // workspace: the keys and the selection's state (counts, list)
+    // workspace: the keys and the radix selection's state (counts, list)
     const size_t kb = round256((size_t)n * 8);
-    const size_t need = n <= kSmallN ? 256 : kb + round256(sizeof(SelectState));
+    const size_t need = n <= kSmallN ? 256 : n <= kMidN ? kb : kb + round256(sizeof(SelectState));
     if (!workspace) {
         *workspace_bytes = need;
         return PCONV_OK;
@@ -703,19 +803,32 @@ extern "C" int pconv_select_connectivity_device(const void* w, int dtype, long l
         return PCONV_OK;
     }
     unsigned long long* key = static_cast<unsigned long long*>(workspace);
+    // (each block counts the exponents of several runs of kernels before it adds them to the counts in memory)
+    const dim3 norm_grid((unsigned)std::min<long long>(grid_for(n), 2048)), block(kThreads), sel(kSelThreads);
+#define PCONV_NORMS(COUNT, STATE)                                                                                        \
+    do {                                                                                                                 \
+        if (f32)                                                                                                         \
+            hipLaunchKernelGGL((norm_key_kernel<float, COUNT>), norm_grid, block, 0, st, static_cast<const float*>(w), n, l, \
+                               K, pid, key, STATE);                                                                      \
+        else                                                                                                             \
+            hipLaunchKernelGGL((norm_key_kernel<_Float16, COUNT>), norm_grid, block, 0, st,                              \
+                               static_cast<const _Float16*>(w), n, l, K, pid, key, STATE);                               \
+    } while (0)
+    if (n <= kMidN) {
+        PCONV_NORMS(false, nullptr);
+        if (n <= kMidN / 2)
+            hipLaunchKernelGGL(select_mid_kernel<16>, dim3(1), sel, 0, st, key, (int)n, k, mask);
+        else
+            hipLaunchKernelGGL(select_mid_kernel<32>, dim3(1), sel, 0, st, key, (int)n, k, mask);
+        PCONV_HIP(hipGetLastError());
+        return PCONV_OK;
+    }
     SelectState* state = reinterpret_cast<SelectState*>(static_cast<char*>(workspace) + kb);
     hipLaunchKernelGGL(select_clear_kernel, dim3((kStateWords + kThreads - 1) / kThreads), dim3(kThreads), 0, st,
                        reinterpret_cast<unsigned*>(state));
-    // (each block counts the exponents of several runs of kernels before it adds them to the counts in memory)
-    const dim3 norm_grid((unsigned)std::min<long long>(grid_for(n), 2048)), block(kThreads);
-    if (f32)
-        hipLaunchKernelGGL(norm_key_kernel<float>, norm_grid, block, 0, st, static_cast<const float*>(w), n, l, K, pid, key,
-                           state);
-    else
-        hipLaunchKernelGGL(norm_key_kernel<_Float16>, norm_grid, block, 0, st, static_cast<const _Float16*>(w), n, l, K, pid,
-                           key, state);
+    PCONV_NORMS(true, state);
+#undef PCONV_NORMS
     // (128 workgroups read 13 MB of keys in 4 us, and their counts are half as many additions in memory as 256's)
-    const dim3 sel(kSelThreads);
     const dim3 pass_grid((unsigned)std::min<long long>((n + kAhead * kSelThreads - 1) / (kAhead * kSelThreads), 128));
     hipLaunchKernelGGL(select_count_kernel, pass_grid, sel, 0, st, key, n, k, state);
     hipLaunchKernelGGL(select_gather_kernel, pass_grid, sel, 0, st, key, n, k, state);

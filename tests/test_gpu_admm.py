@@ -136,7 +136,8 @@ def test_device_connectivity_selection_matches_the_oracle_bit_for_bit(dtype, kee
 
 @pytest.mark.parametrize("n,values,keep", [
     (1, 0, 1.0), (63, 0, 0.5), (1025, 3, 0.4), (8192, 0, 0.28), (8192, 2, 0.3), (3000, 1, 0.7),      # one workgroup, to its last size
-    (8193, 0, 0.28), (8193, 1, 0.5), (100003, 0, 0.15), (100004, 0, 0.0001), (262144, 5, 0.61),
+    (8193, 0, 0.28), (8193, 1, 0.5), (16385, 0, 0.9), (16385, 2, 0.35), (32768, 0, 0.0001), (32768, 1, 0.61),     # two
+    (32769, 0, 0.28), (32769, 1, 0.5), (100003, 0, 0.15), (100004, 0, 0.0001), (262144, 5, 0.61),
     (300000, 1, 0.999), (1048577, 40, 0.28)])
 def test_device_connectivity_selection_over_its_sizes(n, values, keep):
     """One workgroup and several passes; `values` > 0: weights from so few values that thousands of norms are equal (the
