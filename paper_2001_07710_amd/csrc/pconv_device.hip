@@ -2695,7 +2695,7 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
     // choice: the tile shape with the smallest estimated time, if that is below an estimate for the vector kernels
     // (effective multiply-adds at the rate they reach on such a layer plus a fixed part: measured 20 TMAC/s at unit
     // stride, half of that on maps narrower than 14 columns, 5 TMAC/s at stride 2).  Layers with few output tiles
-    // (batch 1, small maps with many channels) stay with the vector kernels, whose channel split fills the GPU.
+    // (batch 1, small maps with many channels) go to the kernel of pconv_small.hip where its estimate is below that too.
     const bool all_auto = !tuning || (tuning->rows == 0 && tuning->filters_per_wave == 0 && tuning->waves == 0 &&
                                       tuning->channels_per_wave == 0 && tuning->channel_order == 0 &&
                                       tuning->channel_splits == 0 && tuning->buffers == 0 && tuning->split_reduce == 0);
@@ -2831,7 +2831,12 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
             // against 5 for the 3x3 layers the rate below is quoted for)
             const double macs = (double)N * Ho * Wo * (wp->is_1x1 ? 6.4 : 4.0) * (double)wp->n_kept;
             const double rate = stride == 2 ? 5e6 : Wo < 14 ? 10e6 : 20e6;      // multiply-adds per microsecond
-            take = best_us < macs / rate + 8.0;
+            // (against the kernel for few tiles the fixed part is counted with the chunks of channels the vector kernels
+            // take one after the other: 3x3, batch 1, 15 % to 30 % kept, they measured 8.0 us at 64 channels of 7 x 7, 8.4 at
+            // 128, 9.9 at 256, 14.2 to 15.9 at 512 -- where the other took 8.5 us and was not chosen by 8.0 alone --
+            // and 14.2 against 10.7 at 512 channels of 14 x 14, 15 % kept)
+            const double chunks = small_shape >= 0 && !wp->is_1x1 ? 0.01 * std::min(wp->C, 512) : 0.0;
+            take = best_us < macs / rate + 8.0 + chunks;
         }
         if (known) {
             take = made.kernel != 0;

@@ -150,3 +150,16 @@ def test_the_choice_is_the_same_on_every_call():
         layer.spec = spec
         assert np.array_equal(layer.run(x, True).view(np.uint16), first.view(np.uint16))
     layer.free()
+
+
+@pytest.mark.parametrize("case", [(512, 40, 7, 7), (500, 33, 7, 9), (700, 24, 5, 5)])
+def test_many_channels_on_a_small_map_by_the_automatic_choice(case):
+    C, F, H, W = case
+    spec = L.LayerSpec(cfg=39, idx=C, name="smalldeep", N=1, C=C, F=F, H=H, W=W, dtype="f16", K=8, keep=0.3)
+    layer = GpuLayer(spec)
+    x = L.gen_activations(spec)
+    say("deep", case)
+    kernel, shape = pc.conv3x3_choice(layer.packed, 1, H, W, 1, 1)
+    assert kernel == M and shape >= 5
+    assert rel_err(layer.run(x, True), layer.oracle(x, True)) <= TOL["f16"]
+    layer.free()
