@@ -2803,8 +2803,11 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
         // ... or the kernel for layers of few tiles, whose waves share a tile's channel blocks (channel_splits: how many)
         int small_shape = -1;
         MfmaConv small = small_conv(wp, x, y, bias, N, H, W, Ho, Wo, stride, pad, relu, nhwc);
-        // (its estimate is of the whole launch; the other's leaves out some 6 us, measured on layers of few blocks)
-        if (best_us >= 0.0) best_us += 6.0;
+        // Against each other, the kernels' estimates need a common scale: this one's is of the whole launch, the tile
+        // kernel's leaves out some 6 us (measured on layers of few blocks), and so does what the vector kernels are
+        // compared with below -- there the tile kernel stands with its own number.
+        const double tile_us = best_us;
+        double bar_us = tile_us >= 0.0 ? tile_us + 6.0 : -1.0;
         if (!known && (want_shape == 0 ? !forced || (nhwc && all_auto) : want_shape > kMfmaShapes) && use_weights(wp, 64, 1, &small)) {
             const MfmaConv base = small;
             for (int sh = 0; sh < kSmallShapes; ++sh) {
@@ -2812,8 +2815,8 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
                 MfmaConv one = base;
                 one.splits = want_shape ? want_splits : 0;
                 const double t = small_estimate_us(&one, sh);
-                if (t >= 0.0 && (best_us < 0.0 || t < best_us)) {
-                    best_us = t;
+                if (t >= 0.0 && (bar_us < 0.0 || t < bar_us)) {
+                    best_us = bar_us = t;
                     small_shape = sh;
                     small = one;
                 }
@@ -2831,12 +2834,18 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
             // against 5 for the 3x3 layers the rate below is quoted for)
             const double macs = (double)N * Ho * Wo * (wp->is_1x1 ? 6.4 : 4.0) * (double)wp->n_kept;
             const double rate = stride == 2 ? 5e6 : Wo < 14 ? 10e6 : 20e6;      // multiply-adds per microsecond
+            const double vector_us = macs / rate + 8.0;
             // (against the kernel for few tiles the fixed part is counted with the chunks of channels the vector kernels
             // take one after the other: 3x3, batch 1, 15 % to 30 % kept, they measured 8.0 us at 64 channels of 7 x 7, 8.4 at
             // 128, 9.9 at 256, 14.2 to 15.9 at 512 -- where the other took 8.5 us and was not chosen by 8.0 alone --
-            // and 14.2 against 10.7 at 512 channels of 14 x 14, 15 % kept)
-            const double chunks = small_shape >= 0 && !wp->is_1x1 ? 0.01 * std::min(wp->C, 512) : 0.0;
-            take = best_us < macs / rate + 8.0 + chunks;
+            // and 14.2 against 10.7 at 512 channels of 14 x 14, 15 % kept.  Over 7,000 random layers, batch 1 to 64 and maps
+            // to 224 x 224, the choice with the term is 3 % faster in the mean than without)
+            const double chunks = wp->is_1x1 ? 0.0 : 0.01 * std::min(wp->C, 512);
+            // A layer whose tile kernel beats the vector kernels goes to the matrix cores, by that kernel or by the one for
+            // few tiles, whichever is ahead on their own scale.  (With the 6 us in this comparison too, 2 % of the layers
+            // of 3 to 512 channels went to the vector kernels instead: 7 -> 224 channels at 224 x 224, batch 1, 13.2 ->
+            // 18.2 us; 9 -> 480 at 144 x 144, batch 6, 47 -> 102.)
+            take = (tile_us >= 0.0 && tile_us < vector_us) || (small_shape >= 0 && best_us < vector_us + chunks);
         }
         if (known) {
             take = made.kernel != 0;

@@ -163,3 +163,25 @@ def test_many_channels_on_a_small_map_by_the_automatic_choice(case):
     assert kernel == M and shape >= 5
     assert rel_err(layer.run(x, True), layer.oracle(x, True)) <= TOL["f16"]
     layer.free()
+
+
+@pytest.mark.parametrize("case", [  # N, C, F, H, W, stride, K, keep
+    (1, 7, 224, 224, 224, 1, 12, 0.35), (4, 8, 224, 224, 224, 1, 8, 0.35), (6, 9, 480, 144, 144, 1, 8, 0.3),
+    (17, 6, 93, 50, 76, 1, 8, 0.28), (4, 16, 46, 224, 224, 1, 8, 0.28), (31, 4, 160, 99, 64, 2, 12, 0.15),
+    (24, 18, 191, 42, 35, 2, 4, 0.15), (53, 4, 336, 56, 56, 2, 12, 0.2), (3, 32, 48, 60, 55, 2, 4, 0.2)])
+def test_layers_of_few_channels_and_many_tiles_stay_on_the_matrix_cores(case):
+    """A layer whose tile kernel is expected to beat the vector kernels is not given to them because a third kernel is
+    there to compare with; at stride 2 the non-allocating entry takes such a layer on its first call."""
+    import torch
+    N, C, F, H, W, stride, K, keep = case
+    spec = L.LayerSpec(cfg=40, idx=C + F, name="fewchannels", N=N, C=C, F=F, H=H, W=W, stride=stride, dtype="f16", K=K, keep=keep)
+    layer = GpuLayer(spec)
+    say("few channels", case)
+    kernel, _ = pc.conv3x3_choice(layer.packed, N, H, W, stride, 1)
+    assert kernel == M
+    x = torch.zeros((N, C, H, W), dtype=torch.float16, device="cuda")
+    y = torch.full((N, F, spec.Ho, spec.Wo), -7.0, dtype=torch.float16, device="cuda")
+    pc.conv3x3_noalloc(x, y, layer.packed, layer.d_bias, N, H, W, stride, 1, 0, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert bool((y == layer.d_bias.half()[None, :, None, None]).all())      # zero input: the bias alone
+    layer.free()
