@@ -439,6 +439,13 @@ bool plan(const MfmaConv& a, int shape, SmallPlan* out) {
     static const double kSomeTaps[kSmallShapes] = {1.16, 1.28, 1.3};
     const double taps_cost = a.n_taps == 1 || a.n_taps == 9 ? 1.0 : kSomeTaps[shape];
     static const int kWavesPerCu[kSmallShapes][2] = {{16, 16}, {12, 16}, {8, 16}};
+    // (a step of a 1x1 layer reads one short run from each of 64 planes: planes a multiple of 512 or of 2048 bytes apart
+    // fall on few of the L2's channels, and the activations come at half or a quarter of the rate.  3,200 random layers,
+    // 32 to 2048 channels: with the rate of other maps one in 140 was slower by a tenth or more than the tile kernel it
+    // was chosen over -- 1082 -> 114 at 32 x 32, batch 11, 37.8 -> 54.4 us, where the 64 x 64 tile takes 24.6 -- so one in
+    // 460.  Layers of nine taps, channel-minor tensors and stride 2 showed no such difference)
+    const long long plane = 2ll * a.H * a.W;
+    const double crowded = a.nhwc || ext != 1 || s != 1 || a.C < 64 ? 1.0 : plane % 2048 == 0 ? 4.0 : plane % 512 == 0 ? 2.0 : 1.0;
     SmallPlan best{};
     best.us = -1.0;
     const int cus = compute_units();
@@ -472,7 +479,7 @@ bool plan(const MfmaConv& a, int shape, SmallPlan* out) {
             // a wave's step: bytes it fetches, and the instructions that take them
             // (a row of the patch comes in whole memory lines; the rows of a 1x1 layer are one run of pixels)
             const double row_bytes = ext == 1 && s == 1 ? pw * 2.0 : 64.0 + pw * cs * 2.0;
-            const double fetched = sh.af * 1024.0 * a.n_taps * nb + rows * row_bytes * 16.0 * nb;
+            const double fetched = sh.af * 1024.0 * a.n_taps * nb + crowded * rows * row_bytes * 16.0 * nb;
             const int loads = (a.nhwc ? ki : 8 * ki) + sh.af * a.n_taps * nb;
             const double traffic_us = (double)tiles * steps * fetched / 16e6 + (double)a.N * a.F * a.Ho * a.Wo * 2.0 / 4e6;
             for (int waves = 8; waves >= 1; waves /= 2) {

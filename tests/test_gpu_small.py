@@ -203,3 +203,18 @@ def test_layers_whose_patterns_leave_out_a_tap_are_priced_as_such(case):
     kernel, shape = pc.conv3x3_choice(p, N, H, W, 1, pad)
     assert kernel != M or shape < 5
     p.free()
+
+
+@pytest.mark.parametrize("case", [(2, 1844, 96, 224, 224, 0.35), (1, 1104, 219, 224, 224, 0.5), (17, 1680, 768, 32, 32, 0.3),
+                                  (1, 419, 208, 224, 224, 0.28), (11, 1082, 114, 32, 32, 0.28)])
+def test_1x1_layers_whose_planes_crowd_the_cache_are_priced_as_such(case):
+    """Planes a multiple of 2 KB apart: small tiles, which read them over and over, are not what such a layer gets."""
+    N, C, F, H, W, keep = case
+    say("crowded planes", case)
+    r = np.random.default_rng(C + F)
+    G = -(-C // 9)
+    p = pc.pack_1x1(r.standard_normal((F, C)).astype(np.float16), np.array(L.drawn_library(4, 8), dtype=np.uint16),
+                    r.integers(0, 8, (F, G)).astype(np.uint8), (r.random((F, G)) < keep).astype(np.uint8))
+    kernel, shape = pc.conv3x3_choice(p, N, H, W, 1, 1)                 # (a 1x1 layer is a 3x3 one of centre taps)
+    assert kernel == M and shape not in (5, 6) and (shape != 7 or H == 32)
+    p.free()
