@@ -245,9 +245,16 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
         for (int bf = 0; bf < BF; ++bf)
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[af][bf][i] = 0.f;
+    // Lanes read what other lanes of their wave have written to the patch, and write over what others have read.  The
+    // hardware takes a wave's LDS accesses in program order, so nothing has to wait; this keeps the compiler to it.
+    auto hand_over = [] {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
     auto multiply = [&](int b, auto more) {
         // (the next block's loads, if there is one, are issued as the registers they fill become free)
         write_patch();
+        hand_over();
         if constexpr (decltype(more)::value) load_patch(b + 1);
         // (the operands of a tap are read from LDS while the tap before is multiplied)
         half8 fb[2][BF];
@@ -273,6 +280,7 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
                     acc[af][bf] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ts][af], fb[ts & 1][bf], acc[af][bf], 0, 0, 0);
             if constexpr (decltype(more)::value) load_a(b + 1, ts);
         }
+        if constexpr (decltype(more)::value) hand_over();
     };
     if (b0 < b1) {
         load_patch(b0);
