@@ -233,18 +233,27 @@ constexpr int kBins1 = 1024;                                   // the 10 bits be
 constexpr int kReplicas = 8;                                   // copies of the first counts: blocks share few exponents
 constexpr int kSlowBits = 14, kSlowBins = 1 << kSlowBits;      // 42 bits below the first 21, in three passes
 constexpr int kListCap = 4096;
+// (128 workgroups read 13 MB of keys in 4 us, and their counts are half as many additions in memory as 256's)
+constexpr int kPassGrid = 128;
 constexpr int kRuns = 1024;                                    // runs of kernels whose equal keys are counted
 
 struct SelectState {
     unsigned listed;                   // keys that share the first 21 bits with the k-th largest
-    unsigned slow;                     // 1: more of them than the list holds
+    unsigned slow;                     // more of them than the list holds: 1, or 2 where they are all the same
     unsigned last_index;               // of the keys equal to `threshold`, those with at most this index are kept
     unsigned ties_kept;                // slow: how many of them
     unsigned long long threshold;      // the k-th largest key
-    unsigned hist0[kReplicas][kBins];
+    unsigned long long prefix[3];      // slow: its leading bits before each of the three passes, and its rank among the keys with them
+    unsigned prefix_rank[3];
+    alignas(16) unsigned hist0[kReplicas][kBins];
     unsigned hist1[kBins1];
     unsigned slow_hist[3][kSlowBins];
-    unsigned run_ties[kRuns];
+    union {
+        unsigned run_ties[kRuns];
+        // (before that) of each workgroup's keys that share the first 21 bits with the k-th largest: the largest, and the
+        // largest complement
+        unsigned long long ends[kPassGrid][2];
+    };
     unsigned list_index[kListCap];
     unsigned long long list_key[kListCap];
 };
@@ -283,20 +292,66 @@ __device__ __forceinline__ unsigned block_total(unsigned wave_sum, uint4v* slots
     return total;
 }
 
-// The largest value T of `bits` bits such that at least k of the workgroup's values are >= T (each thread holds PER,
-// those at and beyond its count are 0), found bit by bit; stops as soon as exactly k values are.
+// The largest of the threads' `h` and of their `l` (of some values: the largest, and the largest complement -- not 0, a key
+// is below 2^63 -- or 0 and 0 where a thread has none).  `ends` is 2 words of LDS that nothing else uses; the call begins
+// and ends with a barrier.
+__device__ __forceinline__ void block_ends(unsigned long long h, unsigned long long l, unsigned long long* ends,
+                                           unsigned long long* high, unsigned long long* not_low) {
+    if (threadIdx.x == 0) ends[0] = ends[1] = 0ull;
+    __syncthreads();
+    if (__any(l != 0ull)) {
+        for (int d = 32; d > 0; d >>= 1) {
+            const unsigned long long oh = __shfl_xor(h, d), ol = __shfl_xor(l, d);
+            h = oh > h ? oh : h;
+            l = ol > l ? ol : l;
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicMax(&ends[0], h);
+            atomicMax(&ends[1], l);
+        }
+    }
+    __syncthreads();
+    *high = ends[0];
+    *not_low = ends[1];
+    __syncthreads();
+}
+
+// Bits hi - 1 to lo of the largest value T such that at least k of the workgroup's values are >= T (each thread holds PER,
+// those at and beyond its count are 0), whose bits above are in `t`, found bit by bit; true as soon as exactly k values are.
 template <int PER, typename V>
-__device__ __forceinline__ V block_kth(const V (&v)[PER], V base, int bits, unsigned k, uint4v* slots, unsigned& turn) {
-    V t = base;
-    for (int b = bits - 1; b >= 0; --b) {
+__device__ __forceinline__ bool block_bits(const V (&v)[PER], V& t, int hi, int lo, unsigned k, uint4v* slots, unsigned& turn) {
+    for (int b = hi - 1; b >= lo; --b) {
         const V cand = t | ((V)1 << b);
         unsigned c = 0;
 #pragma unroll
         for (int j = 0; j < PER; ++j) c += (unsigned)__popcll(__ballot(v[j] >= cand));
         const unsigned total = block_total(c, slots, turn);
         if (total >= k) t = cand;
-        if (total == k) break;
+        if (total == k) return true;
     }
+    return false;
+}
+
+// The k-th largest of the workgroup's keys, or a value below it and above the next, where they are alike above the lowest
+// `bits` and `base` there.  Keys that differ are apart after a third of their bits; where they are not, it is looked at
+// whether those that are left are all the same (kernels pruned to zero, weights of few values: 256 of them took 21 us bit
+// by bit to the last).
+template <int PER>
+__device__ __forceinline__ unsigned long long block_kth(const unsigned long long (&v)[PER], unsigned long long base, int bits,
+                                                        unsigned k, uint4v* slots, unsigned& turn, unsigned long long* ends) {
+    constexpr int LOOK = 26;
+    unsigned long long t = base;
+    if (block_bits(v, t, bits, bits < LOOK ? 0 : LOOK, k, slots, turn) || bits <= LOOK) return t;
+    unsigned long long high = 0, not_low = 0;
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (v[j] >> LOOK == t >> LOOK) {
+            high = v[j] > high ? v[j] : high;
+            not_low = ~v[j] > not_low ? ~v[j] : not_low;
+        }
+    block_ends(high, not_low, ends, &high, &not_low);
+    if (high == ~not_low) return high;
+    block_bits(v, t, LOOK, 0, k, slots, turn);
     return t;
 }
 
@@ -306,6 +361,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(const T* __re
                                                                    uint8_t* __restrict__ mask) {
     __shared__ uint32_t masks[126];
     __shared__ uint4v slots[8];
+    __shared__ unsigned long long ends[2];
     if ((int)threadIdx.x < K) masks[threadIdx.x] = lib.mask[threadIdx.x];
     __syncthreads();
     // (keys of kernels that do not exist are 0 like those of kernels without weight, but come behind all of them)
@@ -320,7 +376,7 @@ __global__ __launch_bounds__(kSelThreads) void select_small_kernel(const T* __re
         }
     }
     unsigned turn = 0;
-    const unsigned long long t = block_kth(key, 0ull, 63, k, slots, turn);
+    const unsigned long long t = block_kth(key, 0ull, 63, k, slots, turn, ends);
     unsigned above = 0, equal = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
@@ -400,13 +456,27 @@ template <int BINS>
 __device__ __forceinline__ void find_digit(const unsigned* __restrict__ hist, int replicas, unsigned k, unsigned* scratch,
                                            unsigned* digit, unsigned* rank) {
     constexpr int PER = BINS / kSelThreads;
-    unsigned c[PER], sum = 0;
+    unsigned c[PER], sum = 0;                                 // largest digit first
+    if constexpr (PER % 4 == 0) {                             // (one copy of the counts, 16 bytes at a time)
+        const uint4v* const mine = reinterpret_cast<const uint4v*>(hist + BINS - ((int)threadIdx.x + 1) * PER);
 #pragma unroll
-    for (int j = 0; j < PER; ++j) {                           // largest digit first
-        const int b = BINS - 1 - ((int)threadIdx.x * PER + j);
-        c[j] = 0;
-        for (int r = 0; r < replicas; ++r) c[j] += hist[r * BINS + b];
-        sum += c[j];
+        for (int j = 0; j < PER / 4; ++j) {
+            const uint4v v = mine[PER / 4 - 1 - j];
+            c[4 * j] = v.w;
+            c[4 * j + 1] = v.z;
+            c[4 * j + 2] = v.y;
+            c[4 * j + 3] = v.x;
+        }
+#pragma unroll
+        for (int j = 0; j < PER; ++j) sum += c[j];
+    } else {
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+            const int b = BINS - 1 - ((int)threadIdx.x * PER + j);
+            c[j] = 0;
+            for (int r = 0; r < replicas; ++r) c[j] += hist[r * BINS + b];
+            sum += c[j];
+        }
     }
     unsigned incl = sum;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -458,6 +528,23 @@ __device__ __forceinline__ void for_keys(const unsigned long long* __restrict__ 
     }
 }
 
+// One count more for the digits of the lanes with a hit.  (Equal keys come by the thousand, and additions to one address
+// one after the other: where a quarter of a wave agrees with its first lane, those add once.  With an addition each, 32768
+// kernels of which four fifths are zero took 15 us here.)
+__device__ __forceinline__ void add_digit(unsigned* hist, bool hit, unsigned digit) {
+    const unsigned long long hits = __ballot(hit);
+    if (!hits) return;
+    const int leader = __ffsll((long long)hits) - 1;
+    const unsigned first = (unsigned)__builtin_amdgcn_readlane((int)digit, leader);
+    const unsigned same = (unsigned)__popcll(__ballot(hit && digit == first));
+    if (same < 16u) {
+        if (hit) atomicAdd(&hist[digit], 1u);
+    } else {
+        const bool leads = (int)(threadIdx.x & 63) == leader;
+        if (leads || (hit && digit != first)) atomicAdd(&hist[digit], leads ? same : 1u);
+    }
+}
+
 __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const unsigned long long* __restrict__ key, long long n,
                                                                    unsigned k, SelectState* st) {
     __shared__ unsigned hist[kBins1], scratch[18];
@@ -465,7 +552,7 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const unsigne
     unsigned exponent, rank;
     find_digit<kBins>(&st->hist0[0][0], kReplicas, k, scratch, &exponent, &rank);
     for_keys(key, n, [&](unsigned long long e, long long, bool there) {
-        if (there && (unsigned)(e >> 52) == exponent) atomicAdd(&hist[(unsigned)(e >> 42) & (kBins1 - 1)], 1u);
+        add_digit(hist, there && (unsigned)(e >> 52) == exponent, (unsigned)(e >> 42) & (unsigned)(kBins1 - 1));
     });
     __syncthreads();
     for (int b = threadIdx.x; b < kBins1; b += kSelThreads)
@@ -483,19 +570,45 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const unsign
                                                                     unsigned k, SelectState* st) {
     __shared__ unsigned scratch[18], found, at0;
     __shared__ unsigned index[kSelThreads];
-    if (threadIdx.x == 0) found = 0u;
+    __shared__ unsigned long long ends[2];
+    if (threadIdx.x == 0) {
+        found = 0u;
+        ends[0] = ends[1] = 0ull;
+    }
     unsigned rank;
+    unsigned long long high = 0, not_low = 0;
     const unsigned prefix = first_bits(st, k, scratch, &rank);
     for_keys(key, n, [&](unsigned long long e, long long i, bool there) {
-        if (there && (unsigned)(e >> 42) == prefix) {
-            const unsigned at = atomicAdd(&found, 1u);
+        const bool hit = there && (unsigned)(e >> 42) == prefix;
+        const unsigned long long hits = __ballot(hit);
+        if (!hits) return;
+        // (one addition per wave: equal keys come by the thousand)
+        const int leader = __ffsll((long long)hits) - 1, lane = threadIdx.x & 63;
+        unsigned at = 0;
+        if (lane == leader) at = atomicAdd(&found, (unsigned)__popcll(hits));
+        at = (unsigned)__builtin_amdgcn_readlane((int)at, leader) + (unsigned)__popcll(hits & ((1ull << lane) - 1ull));
+        if (hit) {
             if (at < (unsigned)kSelThreads) index[at] = (unsigned)i;
+            high = e > high ? e : high;
+            not_low = ~e > not_low ? ~e : not_low;
         }
     });
+    if (__any(not_low != 0ull)) {
+        for (int d = 32; d > 0; d >>= 1) {
+            const unsigned long long oh = __shfl_xor(high, d), ol = __shfl_xor(not_low, d);
+            high = oh > high ? oh : high;
+            not_low = ol > not_low ? ol : not_low;
+        }
+        if ((threadIdx.x & 63) == 0) {
+            atomicMax(&ends[0], high);
+            atomicMax(&ends[1], not_low);
+        }
+    }
     __syncthreads();
     // (more than a workgroup can hold: the list counts as overflown)
     const unsigned m = found;
     if (m == 0) return;
+    if (threadIdx.x < 2) st->ends[blockIdx.x][threadIdx.x] = ends[threadIdx.x];
     if (threadIdx.x == 0) at0 = atomicAdd(&st->listed, m <= (unsigned)kSelThreads ? m : (unsigned)kListCap + 1u);
     __syncthreads();
     const unsigned at = at0 + threadIdx.x;
@@ -510,9 +623,9 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const unsign
 template <int PER>
 __device__ __forceinline__ void block_rank(const unsigned long long (&key)[PER], unsigned (&late)[PER],
                                            unsigned long long base, int bits, unsigned k, uint4v* slots,
-                                           unsigned long long* kth, unsigned* last_index) {
+                                           unsigned long long* ends, unsigned long long* kth, unsigned* last_index) {
     unsigned turn = 0, above = 0;
-    const unsigned long long t = block_kth(key, base, bits, k, slots, turn);
+    const unsigned long long t = block_kth(key, base, bits, k, slots, turn, ends);
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         above += (unsigned)__popcll(__ballot(key[j] > t));
@@ -520,18 +633,34 @@ __device__ __forceinline__ void block_rank(const unsigned long long (&key)[PER],
     }
     above = block_total(above, slots, turn);
     *kth = t;
-    *last_index = ~block_kth(late, 0u, 32, k - above, slots, turn);
+    unsigned first_late = 0u;
+    block_bits(late, first_late, 32, 0, k - above, slots, turn);
+    *last_index = ~first_late;
 }
 
 // One workgroup: the k-th largest among the gathered keys, equal ones by index.
 __global__ __launch_bounds__(kSelThreads) void select_finish_kernel(unsigned k, SelectState* st) {
     __shared__ unsigned scratch[18];
     __shared__ uint4v slots[8];
+    __shared__ unsigned long long ends[2];
     unsigned rank;
     const unsigned prefix = first_bits(st, k, scratch, &rank);
     const unsigned m = st->listed;
     if (m > (unsigned)kListCap) {
-        if (threadIdx.x == 0) st->slow = 1u;
+        // (workgroups that found none have left zeros)
+        unsigned long long high = 0, not_low = 0;
+        if (threadIdx.x < kPassGrid) {
+            high = st->ends[threadIdx.x][0];
+            not_low = st->ends[threadIdx.x][1];
+        }
+        block_ends(high, not_low, ends, &high, &not_low);
+        if (threadIdx.x == 0) {
+            if (high == ~not_low) {
+                st->threshold = high;
+                st->ties_kept = rank;
+            }
+            st->slow = high == ~not_low ? 2u : 1u;
+        }
         return;
     }
     constexpr int PER = kListCap / kSelThreads;
@@ -545,66 +674,176 @@ __global__ __launch_bounds__(kSelThreads) void select_finish_kernel(unsigned k, 
     }
     unsigned long long t;
     unsigned last;
-    block_rank(key, late, (unsigned long long)prefix << 42, 42, rank, slots, &t, &last);
+    block_rank(key, late, (unsigned long long)prefix << 42, 42, rank, slots, ends, &t, &last);
     if (threadIdx.x == 0) {
         st->threshold = t;
         st->last_index = last;
     }
 }
 
+// The index of the rank-th (from 1) of the PER * kSelThreads keys that is equal to t.  `counts` is PER * 16 words of LDS,
+// `found` one.
+template <int PER>
+__device__ __forceinline__ unsigned nth_equal(const unsigned long long* __restrict__ key, int n, unsigned long long t,
+                                              unsigned rank, unsigned* counts, unsigned* found) {
+    constexpr int WAVES = kSelThreads / 64, EACH = PER * WAVES / 64;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto equal = [&](int i) { return key[i < n ? i : n - 1] == t && i < n; };
+#pragma unroll 4
+    for (int j = 0; j < PER; ++j) {
+        const unsigned c = (unsigned)__popcll(__ballot(equal(j * kSelThreads + (int)threadIdx.x)));
+        if (lane == 0) counts[j * WAVES + wave] = c;
+    }
+    __syncthreads();
+    unsigned c[EACH], sum = 0;                                // (every wave works this out for itself)
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) sum += c[q] = counts[lane * EACH + q];
+    unsigned incl = sum;
+#pragma unroll
+    for (int d = 1; d < 64; d <<= 1) {
+        const unsigned o = __shfl_up(incl, d);
+        if (lane >= d) incl += o;
+    }
+    unsigned before = incl - sum, at = ~0u, left = 0;
+#pragma unroll
+    for (int q = 0; q < EACH; ++q) {
+        if (before < rank && rank <= before + c[q]) {
+            at = (unsigned)(lane * EACH + q);
+            left = rank - before;
+        }
+        before += c[q];
+    }
+    const int lead = __ffsll((long long)__ballot(at != ~0u)) - 1;     // (one lane has it: there are `rank` of them)
+    at = __shfl(at, lead);
+    left = __shfl(left, lead);
+    if ((int)(at % WAVES) == wave) {
+        const int i = (int)(at / WAVES) * kSelThreads + (int)threadIdx.x;
+        const bool hit = equal(i);
+        const unsigned long long hits = __ballot(hit);
+        if (hit && (unsigned)__popcll(hits & ((1ull << lane) - 1ull)) + 1u == left) *found = (unsigned)i;
+    }
+    __syncthreads();
+    return *found;
+}
+
 // kSmallN < n <= kMidN: one workgroup ranks the keys that norm_key_kernel left, from registers.  Their leading 19 bits
 // are counted as a distance from the largest key's -- 256 bins an octave over the 16 octaves below it, everything
-// smaller in the last bin -- and only the keys that share the k-th largest's bin are ranked bit by bit; where those do
-// not fit the list (equal norms by the thousand), all keys are.  The radix selection's nine launches took 52 us of an iteration at
-// 12607 fp16 kernels (46 us with a library's sort); two launches take 23 us.
+// smaller in the last bin -- and only the keys that share the k-th largest's bin are ranked bit by bit.  Where those do
+// not fit the list (norms that are equal or nearly so by the thousand), their own bits below what they share are
+// counted, 12 at a time, until the rest fits or is all the same.  The radix selection's ten launches took 52 us of an
+// iteration at 12607 fp16 kernels (46 us with a library's sort); two launches take 23 us.
 template <int PER>
 __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned long long* __restrict__ src, int n,
                                                                  unsigned k, uint8_t* __restrict__ mask) {
-    constexpr int DIST = 4096, LIST = kListCap / kSelThreads, LOW = 44;
-    __shared__ unsigned hist[DIST], scratch[18], listed;
-    __shared__ unsigned long long list_key[kListCap], wave_max[kSelThreads / 64];
+    constexpr int DIST = 4096, LIST = kListCap / kSelThreads, LOW = 44, REST = 32;
+    __shared__ __attribute__((aligned(16))) unsigned hist[DIST];
+    __shared__ unsigned scratch[18], wave_max[kSelThreads / 64], listed;
+    __shared__ unsigned long long list_key[kListCap], ends[2];
     __shared__ unsigned list_late[kListCap];
     __shared__ uint4v slots[8];
-    unsigned long long key[PER], top = 0;
+    // (of a key the leading half, the rest is read where that does not decide: whole keys are 64 of the 128 registers.
+    // Places behind the last kernel hold 0, like kernels without weight.  Loads without a branch around each, which would
+    // wait for it)
+    const unsigned* const halves = reinterpret_cast<const unsigned*>(src);
+    unsigned key[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         const int i = j * kSelThreads + (int)threadIdx.x;
-        key[j] = i < n ? src[i] : 0ull;
+        key[j] = halves[2 * (i < n ? i : n - 1) + 1];
+        if (i >= n) key[j] = 0u;
     }
     for (int b = threadIdx.x; b < DIST; b += kSelThreads) hist[b] = 0u;
     if (threadIdx.x == 0) listed = 0u;
+    unsigned top = 0;
 #pragma unroll
     for (int j = 0; j < PER; ++j) top = key[j] > top ? key[j] : top;
-    for (int d = 32; d > 0; d >>= 1) {
-        const unsigned long long o = __shfl_xor(top, d);
-        top = o > top ? o : top;
-    }
+    for (int d = 32; d > 0; d >>= 1) top = max(top, (unsigned)__shfl_xor(top, d));
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = top;
     __syncthreads();
-    for (int q = 0; q < kSelThreads / 64; ++q) top = wave_max[q] > top ? wave_max[q] : top;
-    const unsigned first = (unsigned)(top >> LOW);            // (19 bits)
-    auto bin = [&](unsigned long long e) {                    // larger keys, larger bins
-        const unsigned d = first - (unsigned)(e >> LOW);
+    for (int q = 0; q < kSelThreads / 64; ++q) top = max(top, wave_max[q]);
+    const unsigned first = top >> (LOW - REST);               // (19 bits)
+    auto bin = [&](unsigned e) {                              // larger keys, larger bins
+        const unsigned d = first - (e >> (LOW - REST));
         return d < (unsigned)DIST ? (unsigned)DIST - 1u - d : 0u;
     };
+    bool crowd = false;                                       // (a look at every eighth: 2 us at 32768 if at each)
 #pragma unroll
-    for (int j = 0; j < PER; ++j)
-        if (j * kSelThreads + (int)threadIdx.x < n) atomicAdd(&hist[bin(key[j])], 1u);
+    for (int j = 0; j < PER; ++j) {
+        if (j * kSelThreads >= n) continue;
+        const unsigned b = bin(key[j]);
+        if (j % 8 == 0) crowd = __popcll(__ballot(b == (unsigned)__builtin_amdgcn_readfirstlane((int)b))) >= 16;
+        if (crowd) add_digit(hist, true, b);
+        else atomicAdd(&hist[b], 1u);
+    }
     __syncthreads();
     unsigned digit, rank;
     find_digit<DIST>(hist, 1, k, scratch, &digit, &rank);
-    const bool fits = hist[digit] <= (unsigned)kListCap;
-    unsigned long long t;
-    unsigned last;
+    // the candidates are the keys in [low, high]; those above are kept
+    bool fits = hist[digit] <= (unsigned)kListCap;
+    unsigned long long low, high;
+    int bits;                                                 // in which the candidates may differ
+    if (digit == 0) {                                         // (the last bin: everything that far below the largest)
+        low = 0ull;
+        high = (unsigned long long)(first - (unsigned)DIST + 1u) << LOW | ((1ull << LOW) - 1ull);
+        bits = 63;
+    } else {
+        low = (unsigned long long)(first - ((unsigned)DIST - 1u - digit)) << LOW;
+        high = low | ((1ull << LOW) - 1ull);
+        bits = LOW;
+    }
+    unsigned long long t = 0ull;
+    unsigned last = 0u;
+    // (the places' numbers and which of them exist, worked out anew for each of the loops below: kept from the first loop on
+    // they are 32 vector and 64 scalar registers, and the kernel spills.  A form that did gave wrong marks: the compiler
+    // had put copies of the keys' registers at the end of a branch that some waves do not take, in front of the
+    // instruction that brings those waves back)
+    int thread = (int)threadIdx.x;
+    auto anew = [&] { asm volatile("" : "+v"(thread), "+s"(n)); };
+    anew();
+    while (!fits) {                                           // (uniform; 12 bits less each time, at most six times)
+        unsigned long long h = 0, l = 0;
+#pragma unroll 8
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * kSelThreads + thread;
+            const unsigned long long e = src[i < n ? i : n - 1];
+            if (i < n && e >= low && e <= high) {
+                h = e > h ? e : h;
+                l = ~e > l ? ~e : l;
+            }
+        }
+        unsigned long long not_low;
+        block_ends(h, l, ends, &high, &not_low);
+        low = ~not_low;
+        if (low == high) break;
+        bits = 64 - __clzll(low ^ high);
+        const int shift = bits > 12 ? bits - 12 : 0;
+        for (int b = threadIdx.x; b < DIST; b += kSelThreads) hist[b] = 0u;
+        __syncthreads();
+#pragma unroll 8
+        for (int j = 0; j < PER; ++j) {
+            const int i = j * kSelThreads + thread;
+            const unsigned long long e = src[i < n ? i : n - 1];
+            add_digit(hist, i < n && e >= low && e <= high, (unsigned)(e >> shift) & (unsigned)(DIST - 1));
+        }
+        __syncthreads();
+        find_digit<DIST>(hist, 1, rank, scratch, &digit, &rank);
+        fits = hist[digit] <= (unsigned)kListCap;
+        low = (low >> bits << bits) | (unsigned long long)digit << shift;
+        high = low | ((1ull << shift) - 1ull);
+        bits = shift;
+        __syncthreads();
+    }
+    anew();
     if (fits) {                                               // (uniform)
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
-            const int i = j * kSelThreads + (int)threadIdx.x;
-            if (i < n && bin(key[j]) == digit) {
-                const unsigned at = atomicAdd(&listed, 1u);
-                list_key[at] = key[j];
-                list_late[at] = ~(unsigned)i;
-            }
+            const int i = j * kSelThreads + thread;
+            if (key[j] < (unsigned)(low >> REST) || key[j] > (unsigned)(high >> REST) || i >= n) continue;
+            const unsigned long long e = src[i];
+            if (e < low || e > high) continue;
+            const unsigned at = atomicAdd(&listed, 1u);
+            list_key[at] = e;
+            list_late[at] = ~(unsigned)i;
         }
         __syncthreads();
         const unsigned m = listed;
@@ -616,57 +855,48 @@ __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned 
             some[j] = at < m ? list_key[at] : 0ull;
             late[j] = at < m ? list_late[at] : 0u;
         }
-        // (the last bin's keys share no leading bits)
-        const bool whole = digit == 0;
-        const unsigned long long base = (unsigned long long)(first - ((unsigned)DIST - 1u - digit)) << LOW;
-        block_rank(some, late, whole ? 0ull : base, whole ? 63 : LOW, rank, slots, &t, &last);
+        block_rank(some, late, low, bits, rank, slots, ends, &t, &last);
     } else {
-        unsigned late[PER];
-#pragma unroll
-        for (int j = 0; j < PER; ++j) {
-            const int i = j * kSelThreads + (int)threadIdx.x;
-            late[j] = i < n ? ~(unsigned)i : 0u;
-        }
-        block_rank(key, late, 0ull, 63, k, slots, &t, &last);
+        t = high;
+        last = nth_equal<PER>(src, n, t, rank, hist, scratch);
     }
+    anew();
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int i = j * kSelThreads + (int)threadIdx.x;
-        if (i < n) mask[i] = key[j] > t || (key[j] == t && (unsigned)i <= last) ? 1 : 0;
+        const int i = j * kSelThreads + thread;
+        if (i >= n) continue;
+        bool keep = key[j] > (unsigned)(t >> REST);
+        if (key[j] == (unsigned)(t >> REST)) {
+            const unsigned long long e = src[i];
+            keep = e > t || (e == t && (unsigned)i <= last);
+        }
+        mask[i] = keep ? 1 : 0;
     }
 }
 
-// The bits below the first 21, 14 at a time, where too many keys share those.
+// The bits below the first 21, 14 at a time, where too many keys share those: what is known of the k-th largest after
+// `passes` of them, from what the pass before has left and its counts.
 __device__ __forceinline__ unsigned long long slow_prefix(const SelectState* st, unsigned k, int passes, unsigned* scratch,
                                                           unsigned* rank) {
-    unsigned long long prefix = first_bits(st, k, scratch, rank);
-    for (int p = 0; p < passes; ++p) {
-        unsigned digit;
-        find_digit<kSlowBins>(st->slow_hist[p], 1, *rank, scratch, &digit, rank);
-        prefix = prefix << kSlowBits | digit;
-    }
-    return prefix;
+    if (passes == 0) return first_bits(st, k, scratch, rank);
+    unsigned digit;
+    find_digit<kSlowBins>(st->slow_hist[passes - 1], 1, st->prefix_rank[passes - 1], scratch, &digit, rank);
+    return st->prefix[passes - 1] << kSlowBits | digit;
 }
 __global__ __launch_bounds__(kSelThreads) void select_slow_kernel(const unsigned long long* __restrict__ key, long long n,
                                                                   unsigned k, int pass, SelectState* st) {
-    if (!st->slow) return;
+    if (st->slow != 1u) return;
     __shared__ unsigned hist[kSlowBins], scratch[18];
     for (int b = threadIdx.x; b < kSlowBins; b += kSelThreads) hist[b] = 0u;
     unsigned rank;
     const unsigned long long prefix = slow_prefix(st, k, pass, scratch, &rank);
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        st->prefix[pass] = prefix;
+        st->prefix_rank[pass] = rank;
+    }
     const int top = 42 - kSlowBits * pass, low = top - kSlowBits;
     for_keys(key, n, [&](unsigned long long e, long long, bool there) {
-        // (equal keys by the thousand are what brings a call here: a wave whose hits agree adds once)
-        const bool hit = there && (e >> top) == prefix;
-        const unsigned d = (unsigned)(e >> low) & (unsigned)(kSlowBins - 1);
-        const unsigned long long hits = __ballot(hit);
-        if (!hits) return;
-        const unsigned first = __shfl(d, __ffsll((long long)hits) - 1);
-        if (__ballot(hit && d == first) == hits) {
-            if ((threadIdx.x & 63) == 0) atomicAdd(&hist[first], (unsigned)__popcll(hits));
-        } else if (hit) {
-            atomicAdd(&hist[d], 1u);
-        }
+        add_digit(hist, there && (e >> top) == prefix, (unsigned)(e >> low) & (unsigned)(kSlowBins - 1));
     });
     __syncthreads();
     for (int b = threadIdx.x; b < kSlowBins; b += kSelThreads)
@@ -684,9 +914,10 @@ __global__ __launch_bounds__(kSelThreads) void select_ties_kernel(const unsigned
     __shared__ unsigned scratch[18];
     __shared__ uint4v slots[8];
     unsigned rank, turn = 0;
-    const unsigned long long t = slow_prefix(st, k, 3, scratch, &rank);
+    const bool known = st->slow == 2u;
+    const unsigned long long t = known ? st->threshold : slow_prefix(st, k, 3, scratch, &rank);
     const long long run = run_length(n);
-    for (int r = blockIdx.x; r < kRuns; r += gridDim.x) {
+    for (int r = blockIdx.x; r < kRuns && (long long)r * run < n; r += gridDim.x) {
         const long long first = (long long)r * run;
         unsigned c = 0;
         for (long long i = first + threadIdx.x; i < first + run && i - threadIdx.x < n; i += kSelThreads)
@@ -694,7 +925,7 @@ __global__ __launch_bounds__(kSelThreads) void select_ties_kernel(const unsigned
         c = block_total(c, slots, turn);
         if (threadIdx.x == 0) st->run_ties[r] = c;
     }
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
+    if (threadIdx.x == 0 && blockIdx.x == 0 && !known) {
         st->threshold = t;
         st->ties_kept = rank;
     }
@@ -728,7 +959,7 @@ __global__ __launch_bounds__(kSelThreads) void mark_kept_kernel(const unsigned l
     unsigned turn = 0;
     const unsigned ties_kept = st->ties_kept;
     const long long run = run_length(n);
-    for (int r = blockIdx.x; r < kRuns; r += gridDim.x) {
+    for (int r = blockIdx.x; r < kRuns && (long long)r * run < n; r += gridDim.x) {
         unsigned before = 0;
         for (int q = threadIdx.x; q < r; q += kSelThreads) before += st->run_ties[q];
         for (int d = 32; d > 0; d >>= 1) before += __shfl_down(before, d);
@@ -828,17 +1059,18 @@ extern "C" int pconv_select_connectivity_device(const void* w, int dtype, long l
                        reinterpret_cast<unsigned*>(state));
     PCONV_NORMS(true, state);
 #undef PCONV_NORMS
-    // (128 workgroups read 13 MB of keys in 4 us, and their counts are half as many additions in memory as 256's)
-    const dim3 pass_grid((unsigned)std::min<long long>((n + kAhead * kSelThreads - 1) / (kAhead * kSelThreads), 128));
+    const dim3 pass_grid((unsigned)std::min<long long>((n + kAhead * kSelThreads - 1) / (kAhead * kSelThreads), kPassGrid));
     hipLaunchKernelGGL(select_count_kernel, pass_grid, sel, 0, st, key, n, k, state);
     hipLaunchKernelGGL(select_gather_kernel, pass_grid, sel, 0, st, key, n, k, state);
     hipLaunchKernelGGL(select_finish_kernel, dim3(1), sel, 0, st, k, state);
     for (int p = 0; p < 3; ++p) hipLaunchKernelGGL(select_slow_kernel, pass_grid, sel, 0, st, key, n, k, p, state);
-    hipLaunchKernelGGL(select_ties_kernel, pass_grid, sel, 0, st, key, n, k, state);
+    // (a run at a time where equal keys are ranked: one workgroup a run as far as they go)
+    const dim3 run_grid((unsigned)std::min<long long>((n + kSelThreads - 1) / kSelThreads, kPassGrid));
+    hipLaunchKernelGGL(select_ties_kernel, run_grid, sel, 0, st, key, n, k, state);
     if (n % 4 == 0 && reinterpret_cast<uintptr_t>(mask) % 4 == 0)
-        hipLaunchKernelGGL(mark_kept_kernel<true>, pass_grid, sel, 0, st, key, n, state, mask);
+        hipLaunchKernelGGL(mark_kept_kernel<true>, run_grid, sel, 0, st, key, n, state, mask);
     else
-        hipLaunchKernelGGL(mark_kept_kernel<false>, pass_grid, sel, 0, st, key, n, state, mask);
+        hipLaunchKernelGGL(mark_kept_kernel<false>, run_grid, sel, 0, st, key, n, state, mask);
     PCONV_HIP(hipGetLastError());
     return PCONV_OK;
 }
