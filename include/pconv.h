@@ -127,10 +127,21 @@ int pconv_packed_stats(const pconv_packed* p, int* F, int* C, int* K, int* dtype
  * tiling (waves, filters_per_wave) this returns the mean number of kept kernels per wave and chunk and the mean,
  * over workgroups and chunks, of the maximum over the waves; their ratio is the share of the multiply phase that an
  * average wave spends working.  balanced = 0: channels staged in their own order; 1: in the balanced order computed
- * at pack time (PCONV_EUNSUPPORTED if the handle has none for this tiling).
+ * at pack time (pconv_packed_order; PCONV_EUNSUPPORTED if the handle has none for this tiling).
  */
 int pconv_packed_balance(const pconv_packed* p, int waves, int filters_per_wave, int balanced, double* mean_per_wave,
                          double* mean_of_max);
+
+/*
+ * The balanced staging order itself, as the kernels of the tiling (waves, filters_per_wave, channels staged per chunk)
+ * read it: for every group of waves * filters_per_wave filters (in the packed order) the channel at each position of its
+ * chunks, 0xFFFFFFFF where there is none.  It is found on the device for layers of up to 2048 channels and on the host for
+ * larger ones and for host-only handles, by the same rule; a handle with a device copy is asked for the device's.  Tilings:
+ * 16x2, 16x1 and 8x1 with 32 channels, 16x2 and 16x1 with 16; PCONV_EUNSUPPORTED for another.
+ *   order_out  host, uint32_t[*positions], or NULL to learn *positions
+ */
+int pconv_packed_order(const pconv_packed* p, int waves, int filters_per_wave, int channels, uint32_t* order_out,
+                       size_t* positions);
 
 /*
  * Introspection of the stride-2 path.  A stride-2 layer runs as a stride-1 layer over the four row/column parity

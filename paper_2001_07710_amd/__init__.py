@@ -69,6 +69,8 @@ def _load():
                                        ctypes.POINTER(ctypes.c_size_t)]
     lib.pconv_packed_balance.argtypes = [vp, i, i, i, ctypes.POINTER(ctypes.c_double), ctypes.POINTER(ctypes.c_double)]
     lib.pconv_packed_balance.restype = i
+    lib.pconv_packed_order.argtypes = [vp, i, i, i, vp, ctypes.POINTER(ctypes.c_size_t)]
+    lib.pconv_packed_order.restype = i
     lib.pconv_packed_parity_form.argtypes = [vp, i, ctypes.POINTER(vp)]
     lib.pconv_packed_library.argtypes = [vp, vp]
     lib.pconv_free.argtypes = [vp]
@@ -241,6 +243,16 @@ def packed_balance(p: Packed, waves: int, filters_per_wave: int, balanced: bool)
     _check(_load().pconv_packed_balance(p.handle, waves, filters_per_wave, int(balanced), ctypes.byref(a),
                                         ctypes.byref(b)), "pconv_packed_balance")
     return a.value, b.value
+
+
+def packed_order(p: Packed, waves: int, filters_per_wave: int, channels: int) -> np.ndarray:
+    """Channel at every position of the balanced staging order, [group][position], 0xFFFFFFFF where there is none."""
+    n = ctypes.c_size_t()
+    _check(_load().pconv_packed_order(p.handle, waves, filters_per_wave, channels, None, ctypes.byref(n)), "pconv_packed_order")
+    out = np.empty(n.value, dtype=np.uint32)
+    _check(_load().pconv_packed_order(p.handle, waves, filters_per_wave, channels, _hp(out), ctypes.byref(n)), "pconv_packed_order")
+    groups = -(-p.F // (waves * filters_per_wave))
+    return out.reshape(groups, -1)
 
 
 def packed_parity_form(p: Packed, pad: int) -> Packed:

@@ -508,6 +508,12 @@ int upload_packed(pconv_packed* p) {
     return PCONV_OK;
 }
 
+int download_order(const BalancedLayout& b, std::vector<uint32_t>* perm) {
+    perm->assign((size_t)b.n_groups * b.n_chunks * b.cc, kNoChannel);
+    PCONV_HIP(hipMemcpy(perm->data(), b.d_perm, perm->size() * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    return PCONV_OK;
+}
+
 void release_device(pconv_packed* p) {
     for (MfmaWeights& m : p->mfma) {
         m.d_w = nullptr;

@@ -729,6 +729,34 @@ extern "C" int pconv_packed_import(const uint32_t* filter_order, const uint32_t*
     }
 }
 
+// The balanced order of one tiling: as it lies on the device, or as it was or would be found on the host.
+static int staging_order(const pconv_packed* p, const pconv::BalancedLayout& b, std::vector<uint32_t>* perm) {
+    if (b.d_perm) return pconv::download_order(b, perm);
+    pconv::BalancedLayout found = b;
+    if (found.perm.empty()) find_balanced(p, &found);
+    *perm = found.perm;
+    return PCONV_OK;
+}
+
+extern "C" int pconv_packed_order(const pconv_packed* p, int waves, int filters_per_wave, int channels, uint32_t* order_out,
+                                  size_t* positions) {
+    if (!p) return PCONV_EINVAL;
+    for (const pconv::BalancedLayout& b : p->balanced) {
+        if (b.fw != waves || b.nf != filters_per_wave || b.cc != channels) continue;
+        if (positions) *positions = (size_t)b.n_groups * b.n_chunks * b.cc;
+        if (!order_out) return PCONV_OK;
+        try {
+            std::vector<uint32_t> perm;
+            if (int rc = staging_order(p, b, &perm)) return rc;
+            std::copy(perm.begin(), perm.end(), order_out);
+        } catch (const std::bad_alloc&) {
+            return PCONV_ENOMEM;
+        }
+        return PCONV_OK;
+    }
+    return PCONV_EUNSUPPORTED;
+}
+
 extern "C" int pconv_packed_balance(const pconv_packed* p, int waves, int filters_per_wave, int balanced,
                                     double* mean_per_wave, double* mean_of_max) {
     if (!p || !mean_per_wave || !mean_of_max) return PCONV_EINVAL;
@@ -738,12 +766,18 @@ extern "C" int pconv_packed_balance(const pconv_packed* p, int waves, int filter
     for (const pconv::BalancedLayout& b : p->balanced)
         if (b.fw == waves && b.nf == filters_per_wave && b.cc == cc) bl = &b;
     if (balanced && !bl) return PCONV_EUNSUPPORTED;
-    pconv::BalancedLayout found;
-    if (balanced && bl->pos_of.empty()) {                    // (the order is on the device only: found again)
+    std::vector<uint32_t> pos_of;                            // [group][C]: position of a channel in its group's order
+    if (balanced) {
         try {
-            found = *bl;
-            find_balanced(p, &found);
-            bl = &found;
+            std::vector<uint32_t> perm;
+            if (int rc = staging_order(p, *bl, &perm)) return rc;
+            const int npos = bl->n_chunks * cc;
+            pos_of.assign((size_t)bl->n_groups * p->C, 0);
+            for (size_t at = 0; at < perm.size(); ++at)
+                if (perm[at] != pconv::kNoChannel) {
+                    if (perm[at] >= (uint32_t)p->C) return PCONV_ESTATE;
+                    pos_of[at / npos * p->C + perm[at]] = (uint32_t)(at % npos);
+                }
         } catch (const std::bad_alloc&) {
             return PCONV_ENOMEM;
         }
@@ -758,7 +792,7 @@ extern "C" int pconv_packed_balance(const pconv_packed* p, int waves, int filter
     }
     for (int i = 0; i < F; ++i)
         for (uint32_t e = p->grp_ptr[(size_t)i * p->K]; e < p->grp_ptr[(size_t)(i + 1) * p->K]; ++e) {
-            const uint32_t at = balanced ? bl->pos_of[(size_t)(i / fg) * p->C + p->cin[e]] : p->cin[e];
+            const uint32_t at = balanced ? pos_of[(size_t)(i / fg) * p->C + p->cin[e]] : p->cin[e];
             ++counts[(size_t)i * nch + at / cc];
         }
     auto count = [&](int pos, int k) -> uint32_t { return counts[(size_t)pos * nch + k]; };

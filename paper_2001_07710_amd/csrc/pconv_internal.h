@@ -39,7 +39,7 @@ struct BalancedLayout {
     int fw = 0, nf = 0, cc = 0;
     int n_groups = 0, n_chunks = 0;
     // the order itself is found on the device (order_channels_kernel) for layers of at most kOrderChannels channels, whose
-    // two vectors here stay empty, and on the host by find_balanced() for larger ones and for introspection
+    // two vectors here stay empty, and on the host by find_balanced() for larger ones and for host-only handles
     std::vector<uint32_t> perm;      // [n_groups][n_chunks*cc]: channel staged at each position, 0xFFFFFFFF = none
     std::vector<uint16_t> pos_of;    // [n_groups][C]: position of a channel in its group's order (channels it stages)
     // on the device only, made there from the canonical arrays and pos_of (build_entries_kernel):
@@ -198,6 +198,8 @@ int launch_mfma_arrange(const void* w_oihw, void* out, int F, int C, int mt, voi
 size_t mfma_weight_bytes(int F, int C, int mt, int n_taps);
 // implemented in pconv_device.hip
 int upload_packed(pconv_packed* p);
+// the order that the kernels read for a tiling of an uploaded layer (a synchronous copy)
+int download_order(const BalancedLayout& b, std::vector<uint32_t>* perm);
 void release_device(pconv_packed* p);
 void set_hip_error(const char* what, int hip_code);
 }  // namespace pconv

@@ -22,6 +22,7 @@ int oracle_maxpool2x2(const float* x, long planes, int H, int W, float* y);
 
 namespace pconv {
 int upload_packed(pconv_packed*) { return PCONV_EHIP; }
+int download_order(const BalancedLayout&, std::vector<uint32_t>*) { return PCONV_EHIP; }
 void release_device(pconv_packed*) {}
 void set_hip_error(const char*, int) {}
 }  // namespace pconv
@@ -66,6 +67,11 @@ static int one_layer(int F, int C, int K, double keep, int dtype) {
     CHECK(pconv_packed_stats(p, &f2, &c2, &k2, &d2, &n_kept) == PCONV_OK && f2 == F && c2 == C && k2 == K && d2 == dtype);
     double mean = 0, mx = 0;
     (void)pconv_packed_balance(p, 16, 2, 1, &mean, &mx);
+    size_t positions = 0;
+    CHECK(pconv_packed_order(p, 16, 1, 16, nullptr, &positions) == PCONV_OK);
+    std::vector<uint32_t> staged(positions);
+    CHECK(pconv_packed_order(p, 16, 1, 16, staged.data(), &positions) == PCONV_OK);
+    CHECK(pconv_packed_order(p, 16, 1, 8, nullptr, &positions) == PCONV_EUNSUPPORTED);
     for (int pad = 0; pad < 2; ++pad) {
         pconv_packed* q = nullptr;
         CHECK(pconv_packed_parity_form(p, pad, &q) == PCONV_OK);
