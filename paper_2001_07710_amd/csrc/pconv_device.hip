@@ -2784,7 +2784,15 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
             // four at 7x7 -- and costs the round trip of MT x NT floats per part otherwise: the 64 -> 64 layer at
             // 56x56 goes from 17 to 53 us in two parts.  The estimate carries both.  Not asked for, the choice is
             // between 1, 2 and, at stride 1, 4 parts: more lost on every shape measured.)
-            for (int ks = 1; ks <= 16; ks *= 2)
+            // (the weights kept for this shape's tile height say whether its tiles have channel lists)
+            for (const MfmaWeights& m : wp->mfma)
+                if (m.mt == mfma_shape_height(sh) && m.groups == a.groups) {
+                    a.d_clist = m.d_clist; a.d_tinfo = m.d_tinfo;
+                    a.min_blocks = m.min_blocks; a.total_blocks = m.total_blocks;
+                }
+            for (int ks = 1; ks <= 16; ks *= 2) {
+                double us[2] = {-1.0, -1.0};
+                bool estimated = false;
                 for (int sp = 0; sp <= (ks > 1 ? 1 : 0); ++sp) {
                     // sp = 1: the parts are added by a second kernel, which lets more of them pay: up to 8 (layers
                     // of one or two taps, whose blocks are too short to hide their loads: 16); added by the last
@@ -2792,18 +2800,13 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
                     if (want_reduce && ks > 1 && sp != want_reduce - 1) continue;
                     const int most = a.n_taps <= 2 ? 16 : sp ? 8 : stride == 2 ? 2 : 4;
                     if (want_splits ? ks != want_splits : ks > most) continue;
-                    // (the weights kept for this shape's tile height say whether its tiles have channel lists)
-                    for (const MfmaWeights& m : wp->mfma)
-                        if (m.mt == mfma_shape_height(sh) && m.groups == a.groups) {
-                            a.d_clist = m.d_clist; a.d_tinfo = m.d_tinfo;
-                            a.min_blocks = m.min_blocks; a.total_blocks = m.total_blocks;
-                        }
-                    a.second_pass = sp;
-                    const double t = mfma_estimate_us(a, sh, ks);
-                    if (t >= 0.0 && (best_us < 0.0 || t < best_us)) {
-                        best_us = t; a.shape = sh; a.splits = ks; best_sp = sp;
+                    if (!estimated) mfma_estimate_us(a, sh, ks, us);
+                    estimated = true;
+                    if (us[sp] >= 0.0 && (best_us < 0.0 || us[sp] < best_us)) {
+                        best_us = us[sp]; a.shape = sh; a.splits = ks; best_sp = sp;
                     }
                 }
+            }
         }
         a.second_pass = best_sp;
         // ... or the kernel for layers of few tiles, whose waves share a tile's channel blocks (channel_splits: how many)
@@ -2825,8 +2828,8 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
                 if (want_shape && sh != want_shape - kMfmaShapes - 1) continue;
                 MfmaConv one = base;
                 one.splits = want_shape ? want_splits : 0;
-                const double t = small_estimate_us(&one, sh);
-                if (t >= 0.0 && (bar_us < 0.0 || t < bar_us)) {
+                const double t = small_estimate_us(&one, sh, bar_us >= 0.0 ? bar_us : 1e30);
+                if (t >= 0.0) {
                     best_us = bar_us = t;
                     small_shape = sh;
                     small = one;
@@ -3193,8 +3196,9 @@ extern "C" int pconv_dense_conv3x3(const void* x, void* y, const void* w, const 
         a.stride = stride; a.pad = pad; a.relu = relu;
         double best_us = -1.0;
         for (int sh = 1; sh <= kMfmaShapes; ++sh) {
-            const double t = mfma_estimate_us(a, sh, 1);
-            if (t >= 0.0 && (best_us < 0.0 || t < best_us)) { best_us = t; a.shape = sh; }
+            double us[2];
+            mfma_estimate_us(a, sh, 1, us);
+            if (us[0] >= 0.0 && (best_us < 0.0 || us[0] < best_us)) { best_us = us[0]; a.shape = sh; }
         }
         a.splits = 1;
         const int mt = a.shape ? mfma_shape_height(a.shape) : 128;

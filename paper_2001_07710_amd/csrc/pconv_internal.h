@@ -92,7 +92,7 @@ struct Choice {
     int kernel = 0;                   // 0: vector kernels, 1: matrix-core kernel, 2: matrix-core kernel for few tiles
     int shape = 0, splits = 0, second_pass = 0, tile_w = 0, tile_lw = 0;
 };
-constexpr int kChoices = 16;
+constexpr int kChoices = 64;               // (a program with more sizes than this pays the search on every call)
 
 }  // namespace pconv
 
@@ -184,14 +184,15 @@ constexpr int kMfmaTileHeights[2] = {128, 64};
 constexpr int kOneByOneGroups = 4;       // channel ranges per block of the second copy of a 1x1 layer's weights
 int compute_units();        // of the current device
 int mfma_shape_height(int shape);
-// estimated run time in microseconds of shape `shape` with `splits` workgroups per tile, negative if it cannot run
-double mfma_estimate_us(const MfmaConv& a, int shape, int splits);
+// estimated run time in microseconds of shape `shape` with `splits` workgroups per tile, whose parts the last to arrive
+// adds (us[0]) or a second kernel (us[1]); negative if it cannot run
+void mfma_estimate_us(const MfmaConv& a, int shape, int splits, double us[2]);
 // workspace that a launch with a.shape and a.splits > 1 needs
 int mfma_workspace(const MfmaConv& a, size_t* floats, size_t* counters);
 int launch_mfma_conv(const MfmaConv& a, void* stream);
 // implemented in pconv_small.hip: the matrix-core kernel for layers of few tiles, shapes 0..kSmallShapes-1
-// (chosen: tile_w, tile_lw and splits of *a are set to what the estimate is for)
-double small_estimate_us(MfmaConv* a, int shape);
+// (chosen: tile_w, tile_lw and splits of *a are set to what the estimate is for; -1 also where it is not below `bar`)
+double small_estimate_us(MfmaConv* a, int shape, double bar);
 int launch_small_conv(const MfmaConv& a, int shape, void* stream);
 // dense fp16 weights OIHW on the device -> MfmaWeights order for tile height mt, all nine taps (the dense baseline)
 int launch_mfma_arrange(const void* w_oihw, void* out, int F, int C, int mt, void* stream);

@@ -1177,15 +1177,16 @@ int mfma_shape_height(int shape) {
 // cannot take it.  Rounds of resident workgroups times (a fixed part + channel blocks x time per block).  The block
 // times are measured ones (MI355X, VGG-16 and ResNet-50 shapes); while a workgroup has its compute unit to itself a
 // block cannot take less than the round trip of the loads that fetch the next one.
-double mfma_estimate_us(const MfmaConv& a0, int shape, int splits) {
-    if (shape < 1 || shape > kMfmaShapes) return -1.0;
+void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
+    us[0] = us[1] = -1.0;
+    if (shape < 1 || shape > kMfmaShapes) return;
     MfmaConv a = a0;
     a.mt = mfma_shape_height(shape);
     a.splits = splits;
     MfmaParams p;
     int lw = 0, ki = 0, grid = 0;
     size_t lds = 0;
-    if (!plan(a, shape - 1, a.rows, &p, &lw, &ki, &lds, &grid)) return -1.0;
+    if (!plan(a, shape - 1, a.rows, &p, &lw, &ki, &lds, &grid)) return;
     const long long tiles = (long long)p.tiles_n * p.tiles_m * p.KS;
     // the shapes whose waves keep within half the registers leave room for a second workgroup on a compute unit, if
     // the LDS fits twice
@@ -1227,8 +1228,8 @@ double mfma_estimate_us(const MfmaConv& a0, int shape, int splits) {
     // (fitted to ResNet-50's 14 x 14 and 7 x 7 layers at batch 32 in 2, 4 and 8 parts)
     // (second pass: a launch, and the parts written once and read once -- fitted to ResNet-50's 3x3 and 1x1 layers
     // at batch 32: 4.5 TB/s, the parts of such layers staying in the memory-side cache)
-    const double split_us = p.KS <= 1 ? 0.0 : a.second_pass ? 4.0 + 2.0 * part_bytes / 4.5e6
-                                                             : 4.0 + 1.5 * (p.KS - 1) + part_bytes / 1.8e6;
+    const double split_us[2] = {p.KS <= 1 ? 0.0 : 4.0 + 1.5 * (p.KS - 1) + part_bytes / 1.8e6,
+                                p.KS <= 1 ? 0.0 : 4.0 + 2.0 * part_bytes / 4.5e6};
     if (p.nt < 9) block_us *= (double)std::max(p.nt, 1) / 9.0;
     // A 1x1 layer with channel ranges in the place of taps multiplies for a fraction of the time that staging a
     // block takes its waves: 8 ki load instructions per lane and block with their address arithmetic, transposition
@@ -1237,9 +1238,10 @@ double mfma_estimate_us(const MfmaConv& a0, int shape, int splits) {
     // compute unit, and lost on every one of those layers: they are priced out of the automatic choice.
     if (a.groups > 1) {
         const double staged_us = 0.8 + 0.1 * 8.0 * ki;
-        return (rounds * (8.0 + blocks * staged_us) + split_us) * (shape == 3 ? 1.0 : 2.0);
+        for (int sp = 0; sp < 2; ++sp) us[sp] = (rounds * (8.0 + blocks * staged_us) + split_us[sp]) * (shape == 3 ? 1.0 : 2.0);
+        return;
     }
-    return rounds * (tile_us + blocks * std::max(block_us, floor_us)) + split_us;
+    for (int sp = 0; sp < 2; ++sp) us[sp] = rounds * (tile_us + blocks * std::max(block_us, floor_us)) + split_us[sp];
 }
 
 int mfma_workspace(const MfmaConv& a, size_t* floats, size_t* counters) {

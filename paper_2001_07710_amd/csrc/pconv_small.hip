@@ -417,7 +417,7 @@ int pieces_for(int lw, long long need) {
 }
 
 // The launch of one shape: tile, load width and waves with the smallest estimated time; false if the shape cannot take
-// the layer.
+// the layer in less than `bar` microseconds.
 //
 // The estimate (microseconds, fitted to ResNet-50's layers at batch 1 to 64 and some sixty ragged ones, inputs not in the
 // L2): a workgroup takes a fixed time (first loads, the sums through LDS), up to twice as long when the compute unit is
@@ -429,7 +429,7 @@ int pieces_for(int lw, long long need) {
 // random layers took 1.16, 1.28 and 1.3 times as long in the three shapes, and that is asked of them.  (Without it, one
 // in fifty was slower than the vector or tile kernel it was chosen over: four patterns of eight taps, 432 -> 16 channels
 // at 224 x 224, batch 1: 31.9 -> 52.6 us.)
-bool plan(const MfmaConv& a, int shape, SmallPlan* out) {
+bool plan(const MfmaConv& a, int shape, double bar, SmallPlan* out) {
     const SmallShape& sh = kSmall[shape];
     const int M = sh.af * 32, PX = sh.bf * 32;
     if (a.groups > 1 || a.n_taps < 1 || a.n_taps > 9) return false;
@@ -455,18 +455,24 @@ bool plan(const MfmaConv& a, int shape, SmallPlan* out) {
     const long long plane = 2ll * a.H * a.W;
     const double crowded = a.nhwc || ext != 1 || s != 1 || a.C < 64 ? 1.0 : plane % 2048 == 0 ? 4.0 : plane % 512 == 0 ? 2.0 : 1.0;
     SmallPlan best{};
-    best.us = -1.0;
+    best.us = bar;
+    bool found = false;
     const int cus = compute_units();
-    for (int tw = a.tile_w > 0 ? a.tile_w : 1; tw <= (a.tile_w > 0 ? a.tile_w : std::min(PX, a.Wo)); ++tw) {
-        // (columns cut evenly, so that the last tile of a row is not nearly empty)
+    const double out_us = (double)a.N * a.F * a.Ho * a.Wo * 2.0 / 4e6, step_weights = sh.af * 1024.0 * a.n_taps * nb;
+    for (int tw = a.tile_w > 0 ? a.tile_w : std::min(PX, a.Wo); tw > 0; tw = a.tile_w > 0 ? 0 : tw - 1) {
+        // (columns cut evenly, so that the last tile of a row is not nearly empty: the least width that makes as many tiles
+        // of a row, then the next narrower one)
         const int nx = (a.Wo + tw - 1) / tw;
-        if ((a.Wo + nx - 1) / nx != tw) continue;
+        tw = (a.Wo + nx - 1) / nx;
         int th = std::min(PX / tw, a.Ho);
         const int ny = (a.Ho + th - 1) / th;
         th = (a.Ho + ny - 1) / ny;
         const int rs = ext == 1 ? s : 1, rows = ext == 1 ? th : (th - 1) * s + ext;
         const long long tiles = (long long)tiles_m * nx * ny * a.N;
         if (tiles > 0x7FFFFFF0) continue;
+        // (what no load width and no number of waves can make up for: a first call of a size pays for the search)
+        const double busy_least = kFixedUs[shape] + (double)tiles * steps * kStepUs[shape][nb > 1] / ((double)cus * kWavesPerCu[shape][nb > 1]);
+        if (taps_cost * (3.0 + std::max(busy_least, (double)tiles * steps * step_weights / 16e6 + out_us)) > best.us) continue;
         for (int lw = a.nhwc ? 0 : 4; lw >= 0; lw = lw == 4 ? 2 : lw == 2 ? 1 : -1) {
             if (a.tile_w > 0 && lw != a.tile_lw) continue;
             const int piece = lw ? lw : 1;
@@ -487,9 +493,10 @@ bool plan(const MfmaConv& a, int shape, SmallPlan* out) {
             // a wave's step: bytes it fetches, and the instructions that take them
             // (a row of the patch comes in whole memory lines; the rows of a 1x1 layer are one run of pixels)
             const double row_bytes = ext == 1 && s == 1 ? pw * 2.0 : 64.0 + pw * cs * 2.0;
-            const double fetched = sh.af * 1024.0 * a.n_taps * nb + crowded * rows * row_bytes * 16.0 * nb;
+            const double fetched = step_weights + crowded * rows * row_bytes * 16.0 * nb;
             const int loads = (a.nhwc ? ki : 8 * ki) + sh.af * a.n_taps * nb;
-            const double traffic_us = (double)tiles * steps * fetched / 16e6 + (double)a.N * a.F * a.Ho * a.Wo * 2.0 / 4e6;
+            const double traffic_us = (double)tiles * steps * fetched / 16e6 + out_us;
+            if (taps_cost * (3.0 + std::max(busy_least, traffic_us)) > best.us) continue;
             for (int waves = 8; waves >= 1; waves /= 2) {
                 if (a.splits ? waves != a.splits : waves > steps && waves > 1) continue;
                 const size_t stage = (size_t)rows * row_slots * 32 * nb * waves;
@@ -504,8 +511,10 @@ bool plan(const MfmaConv& a, int shape, SmallPlan* out) {
                 const double busy = rounds * (kFixedUs[shape] * (1.0 + on_cu / 16.0) + 0.1 * waves +
                                               (steps + waves - 1) / waves * std::max(kStepUs[shape][nb > 1], on_cu * loads * 0.006));
                 const double us = taps_cost * (3.0 + std::max(busy, traffic_us) + 0.15 * std::min(busy, traffic_us));
-                if (best.us >= 0.0 && us >= best.us) continue;
+                // (of equal ones the narrowest tile, then the widest loads and the most waves)
+                if (us > best.us || (us == best.us && (!found || best.p.TW == tw))) continue;
                 best.us = us;
+                found = true;
                 SmallParams p{};
                 p.TH = th; p.TW = tw; p.tiles_x = nx; p.tiles_y = ny; p.tiles = (int)tiles;
                 p.rs = rs; p.cs = cs;
@@ -520,7 +529,7 @@ bool plan(const MfmaConv& a, int shape, SmallPlan* out) {
             }
         }
     }
-    if (best.us < 0.0) return false;
+    if (!found) return false;
     SmallParams& p = best.p;
     p.x = static_cast<const unsigned char*>(a.x);
     p.y = static_cast<_Float16*>(a.y);
@@ -581,9 +590,9 @@ int launch_shape(const SmallPlan& pl, hipStream_t st) {
 
 }  // namespace
 
-double small_estimate_us(MfmaConv* a, int shape) {
+double small_estimate_us(MfmaConv* a, int shape, double bar) {
     SmallPlan pl;
-    if (shape < 0 || shape >= kSmallShapes || !plan(*a, shape, &pl)) return -1.0;
+    if (shape < 0 || shape >= kSmallShapes || !plan(*a, shape, bar, &pl)) return -1.0;
     a->tile_w = pl.p.TW;
     a->tile_lw = pl.lw;
     a->splits = pl.waves;
@@ -592,7 +601,7 @@ double small_estimate_us(MfmaConv* a, int shape) {
 
 int launch_small_conv(const MfmaConv& a, int shape, void* stream) {
     SmallPlan pl;
-    if (shape < 0 || shape >= kSmallShapes || !plan(a, shape, &pl)) return PCONV_EUNSUPPORTED;
+    if (shape < 0 || shape >= kSmallShapes || !plan(a, shape, 1e30, &pl)) return PCONV_EUNSUPPORTED;
     hipStream_t st = static_cast<hipStream_t>(stream);
     switch (shape) {
         case 0: return launch_shape<1, 1>(pl, st);

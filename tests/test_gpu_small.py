@@ -134,22 +134,71 @@ def test_1x1_layers(case, nhwc):
 
 
 def test_the_choice_is_the_same_on_every_call():
-    """The handle keeps what the automatic choice came to; results are bit-equal from call to call, also when more sizes
-    than it keeps come by in between."""
+    """The handle keeps what the automatic choice came to; results are bit-equal from call to call, on a call that finds its
+    size kept and on one that does not because more sizes than the handle keeps have come by in between."""
     spec = L.LayerSpec(cfg=39, idx=1, name="choice", N=1, C=64, F=48, H=14, W=14, dtype="f16", K=8, keep=0.3)
     layer = GpuLayer(spec)
     x = L.gen_activations(spec)
     first = layer.run(x, True)
     for round_ in range(2):
-        for h in range(3, 24):
+        assert np.array_equal(layer.run(x, True).view(np.uint16), first.view(np.uint16))      # (kept)
+        for h in range(3, 73):                               # (70 sizes, the handle keeps 64)
             sub = L.shrink(spec, H=h, W=h + 1)
             layer.spec = sub
             xs = L.gen_activations(sub)
             a = layer.run(xs, True)
-            assert rel_err(a, layer.oracle(xs, True)) <= TOL["f16"]
+            assert np.array_equal(layer.run(xs, True).view(np.uint16), a.view(np.uint16))     # (kept)
+            if h < 24:
+                assert rel_err(a, layer.oracle(xs, True)) <= TOL["f16"]
         layer.spec = spec
-        assert np.array_equal(layer.run(x, True).view(np.uint16), first.view(np.uint16))
+        assert np.array_equal(layer.run(x, True).view(np.uint16), first.view(np.uint16))      # (found again)
     layer.free()
+
+
+@pytest.mark.parametrize("outcome,N,C,F,H,W,pad", [("few", 1, 64, 48, 14, 14, 1), ("few", 2, 256, 40, 9, 11, 0), ("tile", 8, 512, 512, 28, 28, 1),
+                                                   ("vector", 1, 227, 16, 224, 224, 0)])
+def test_a_kept_choice_runs_the_launch_it_was_made_for(outcome, N, C, F, H, W, pad):
+    """Every outcome of the choice, made and then found again, with other layouts and alignments of the same size in between."""
+    import torch
+    say("kept choice", outcome, N, C, F, H, W)
+    r = np.random.default_rng(C)
+    lib = np.array([0x1B, 0x36, 0xB1, 0x72], dtype=np.uint16)           # (eight taps)
+    p = pc.pack((r.standard_normal((F, C, 3, 3)) * np.sqrt(2.0 / (9 * C))).astype(np.float16), lib,
+                r.integers(0, 4, (F, C)).astype(np.uint8), (r.random((F, C)) < 0.2).astype(np.uint8))
+    kernel, shape = pc.conv3x3_choice(p, N, H, W, 1, pad)
+    assert {"few": kernel == M and shape >= 5, "tile": kernel == M and shape < 5, "vector": kernel != M}[outcome]
+    Ho, Wo = H + 2 * pad - 2, W + 2 * pad - 2
+    g = torch.Generator(device="cuda").manual_seed(C)
+    x = torch.randn((N, C, H, W), generator=g, device="cuda").half()
+    bias = torch.randn((F,), generator=g, device="cuda")
+    st = torch.cuda.current_stream().cuda_stream
+    want = torch.empty((N, F, Ho, Wo), dtype=torch.float16, device="cuda")
+    pc.conv3x3_tuned(x, want, p, bias, N, H, W, 1, pad, 0, st, kernel=pc.KERNEL_GENERIC)
+    want = want.cpu().numpy()
+
+    def run(x_shift=0, y_shift=0, nhwc=False):
+        xs = x.permute(0, 2, 3, 1).contiguous() if nhwc else x
+        xb = torch.zeros(xs.numel() + x_shift, dtype=torch.float16, device="cuda")
+        xb[x_shift:] = xs.reshape(-1)
+        yb = torch.full((N * F * Ho * Wo + y_shift + 64,), -777.0, dtype=torch.float16, device="cuda")
+        pc.conv3x3(xb[x_shift:], yb[y_shift:], p, bias, N, H, W, 1, pad, pc.FLAG_NHWC if nhwc else 0, st)
+        torch.cuda.synchronize()
+        y = yb.cpu().numpy()
+        n = N * F * Ho * Wo
+        assert np.all(y[:y_shift] == -777.0) and np.all(y[y_shift + n:] == -777.0)
+        y = y[y_shift:y_shift + n]
+        y = y.reshape(N, Ho, Wo, F).transpose(0, 3, 1, 2) if nhwc else y.reshape(N, F, Ho, Wo)
+        assert rel_err(y, want) <= TOL["f16"]
+        return np.ascontiguousarray(y).view(np.uint16)
+
+    forms = [dict(), dict(x_shift=1), dict(x_shift=2, y_shift=1), dict(y_shift=2), dict(x_shift=4, y_shift=4)]
+    if C % 8 == 0 and pad == 1:
+        forms.append(dict(nhwc=True))
+    made = [run(**f) for f in forms]
+    for round_ in range(2):
+        for f, m in zip(forms, made):
+            assert np.array_equal(run(**f), m), f
+    p.free()
 
 
 @pytest.mark.parametrize("case", [(512, 40, 7, 7), (500, 33, 7, 9), (700, 24, 5, 5)])
