@@ -116,10 +116,10 @@ struct KernelList {
     std::vector<unsigned char> w4;    // the kept weights, taps ascending, four of the storage type (missing ones zero)
 };
 
-// From a dense tensor, pattern ids and a mask.  The channel scan has no branch per kernel: every channel is written,
-// the kept ones advance.
+// From a dense tensor (of any alignment), pattern ids and a mask.  The channel scan has no branch per kernel: every channel
+// is written, the kept ones advance.
 template <typename E>
-void list_kernels(const E* w, int F, int C, const uint16_t* lib, int K, const uint8_t* pid, const uint8_t* mask,
+void list_kernels(const unsigned char* w, int F, int C, const uint16_t* lib, int K, const uint8_t* pid, const uint8_t* mask,
                   KernelList* out) {
     std::vector<int> taps((size_t)K * 4, -1);
     for (int j = 0; j < K; ++j) {
@@ -153,10 +153,12 @@ void list_kernels(const E* w, int F, int C, const uint16_t* lib, int K, const ui
             const size_t fc = (size_t)f * C + out->c[e];
             const int j = pid[fc];
             out->pid[e] = (uint8_t)j;
-            const E* k9 = w + fc * 9;
+            const unsigned char* k9 = w + fc * 9 * sizeof(E);
             for (int q = 0; q < 4; ++q) {
                 const int t = taps[(size_t)j * 4 + q];
-                w4[e * 4 + q] = t >= 0 ? k9[t] : (E)0;
+                E v = 0;
+                if (t >= 0) std::memcpy(&v, k9 + (size_t)t * sizeof(E), sizeof(E));
+                w4[e * 4 + q] = v;
             }
         }
     }
@@ -427,10 +429,11 @@ static int pack_impl(const void* w_oihw, int dtype, int F, int C, const uint16_t
         if (mask[i] && pid[i] >= K) return PCONV_EPATTERN;
     try {
         KernelList list;
+        const unsigned char* wb = static_cast<const unsigned char*>(w_oihw);
         if (dtype == PCONV_F16)
-            list_kernels(static_cast<const uint16_t*>(w_oihw), F, C, lib, K, pid, mask, &list);
+            list_kernels<uint16_t>(wb, F, C, lib, K, pid, mask, &list);
         else
-            list_kernels(static_cast<const uint32_t*>(w_oihw), F, C, lib, K, pid, mask, &list);
+            list_kernels<uint32_t>(wb, F, C, lib, K, pid, mask, &list);
         return pack_list(list, dtype, F, C, lib, K, flags, want_mfma, one_by_one, out);
     } catch (const std::bad_alloc&) {
         return PCONV_ENOMEM;

@@ -7,6 +7,7 @@
 #include <cstdint>
 #include <cstdio>
 #include <cstdlib>
+#include <cstring>
 #include <vector>
 
 #include "pconv.h"
@@ -54,7 +55,11 @@ static int one_layer(int F, int C, int K, double keep, int dtype) {
     std::vector<uint16_t> wh((size_t)F * C * 9);
     for (size_t i = 0; i < wh.size(); ++i) wh[i] = (uint16_t)(0x3000u + (i * 37u) % 0x0800u);   // finite fp16 patterns
     pconv_packed* p = nullptr;
-    const void* wptr = dtype == PCONV_F16 ? (const void*)wh.data() : (const void*)w.data();
+    // (weights may lie at any address)
+    const size_t bytes = (size_t)F * C * 9 * (dtype == PCONV_F16 ? 2 : 4);
+    std::vector<unsigned char> shifted(bytes + 1);
+    std::memcpy(&shifted[1], dtype == PCONV_F16 ? (const void*)wh.data() : (const void*)w.data(), bytes);
+    const void* wptr = &shifted[1];
     CHECK(pconv_pack(wptr, dtype, F, C, lib.data(), K, pid.data(), mask.data(), PCONV_PACK_HOST_ONLY, &p) == PCONV_OK);
     size_t n_kept = 0;
     CHECK(pconv_packed_export(p, nullptr, nullptr, nullptr, nullptr, &n_kept) == PCONV_OK);
