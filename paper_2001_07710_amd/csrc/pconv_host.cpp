@@ -394,21 +394,19 @@ int pack_list(const KernelList& list, int dtype, int F, int C, const uint16_t* l
                     plan_mfma_weights(p, pconv::kMfmaTileHeights[h], pconv::kOneByOneGroups, &p->mfma[(size_t)(nh + h)]);
             }
         }
+        const int rc = flags & PCONV_PACK_HOST_ONLY ? PCONV_OK : pconv::upload_packed(p);
+        if (rc == PCONV_OK) {
+            *out = p;
+            return PCONV_OK;
+        }
+        pconv::release_device(p);
+        delete p;
+        return rc;
     } catch (const std::bad_alloc&) {
+        pconv::release_device(p);
         delete p;
         return PCONV_ENOMEM;
     }
-
-    if (!(flags & PCONV_PACK_HOST_ONLY)) {
-        const int rc = pconv::upload_packed(p);
-        if (rc != PCONV_OK) {
-            pconv::release_device(p);
-            delete p;
-            return rc;
-        }
-    }
-    *out = p;
-    return PCONV_OK;
 }
 
 }  // namespace

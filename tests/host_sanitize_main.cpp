@@ -8,6 +8,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <new>
 #include <vector>
 
 #include "pconv.h"
@@ -22,7 +23,8 @@ int oracle_maxpool2x2(const float* x, long planes, int H, int W, float* y);
 }
 
 namespace pconv {
-int upload_packed(pconv_packed*) { return PCONV_EHIP; }
+// (out of memory at the last: packing must leave nothing behind)
+int upload_packed(pconv_packed*) { throw std::bad_alloc(); }
 int download_order(const BalancedLayout&, std::vector<uint32_t>*) { return PCONV_EHIP; }
 void release_device(pconv_packed*) {}
 void set_hip_error(const char*, int) {}
@@ -61,6 +63,8 @@ static int one_layer(int F, int C, int K, double keep, int dtype) {
     std::memcpy(&shifted[1], dtype == PCONV_F16 ? (const void*)wh.data() : (const void*)w.data(), bytes);
     const void* wptr = &shifted[1];
     CHECK(pconv_pack(wptr, dtype, F, C, lib.data(), K, pid.data(), mask.data(), PCONV_PACK_HOST_ONLY, &p) == PCONV_OK);
+    pconv_packed* none = nullptr;
+    CHECK(pconv_pack(wptr, dtype, F, C, lib.data(), K, pid.data(), mask.data(), 0, &none) == PCONV_ENOMEM && !none);
     size_t n_kept = 0;
     CHECK(pconv_packed_export(p, nullptr, nullptr, nullptr, nullptr, &n_kept) == PCONV_OK);
     std::vector<uint32_t> order((size_t)F), ptr((size_t)F * K + 1);
