@@ -941,8 +941,11 @@ int persistent_grid(const void* kern, int threads, size_t lds, long long ntiles,
     if (known >> 8 == lds && known) {
         per_cu = (int)(known & 255u);
     } else {
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds) != hipSuccess || per_cu < 1) per_cu = 1;
-        resident.store((unsigned)(lds << 8) | (unsigned)std::min(per_cu, 255), std::memory_order_relaxed);
+        // (an answer is kept, the lack of one is not)
+        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, threads, lds) != hipSuccess || per_cu < 1)
+            per_cu = 1;
+        else
+            resident.store((unsigned)(lds << 8) | (unsigned)std::min(per_cu, 255), std::memory_order_relaxed);
     }
     const long long at_once = (long long)compute_units() * per_cu / 8 * 8;
     return (int)std::max<long long>(8, std::min<long long>((ntiles + 7) / 8 * 8, at_once));
