@@ -741,22 +741,31 @@ __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned 
     __shared__ unsigned long long list_key[kListCap], ends[2];
     __shared__ unsigned list_late[kListCap];
     __shared__ uint4v slots[8];
-    // (of a key the leading half, the rest is read where that does not decide: whole keys are 64 of the 128 registers.
-    // Places behind the last kernel hold 0, like kernels without weight.  Loads without a branch around each, which would
-    // wait for it)
-    const unsigned* const halves = reinterpret_cast<const unsigned*>(src);
-    unsigned key[PER];
+    // (the places' numbers and which of them exist, worked out anew for each of the loops: kept from the first one on
+    // they are 32 vector and 64 scalar registers, and the kernel spills.  A form that did gave wrong marks: the compiler
+    // had put copies of the keys' registers at the end of a branch that some waves do not take, in front of the
+    // instruction that brings those waves back)
+    int thread = (int)threadIdx.x;
+    auto anew = [&] { asm volatile("" : "+v"(thread), "+s"(n)); };
+    // (places behind the last kernel hold 0, like kernels without weight; a row of places is loaded by all lanes or not at
+    // all: behind a branch of its own each load would be waited for)
+    unsigned long long key[PER];
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
-        const int i = j * kSelThreads + (int)threadIdx.x;
-        key[j] = halves[2 * (i < n ? i : n - 1) + 1];
-        if (i >= n) key[j] = 0u;
+        const int i = j * kSelThreads + thread;
+        key[j] = 0ull;
+        if (j * kSelThreads < n) key[j] = src[i < n ? i : n - 1];
     }
+    anew();
+    const bool partial = thread >= (n & (kSelThreads - 1));      // of the lanes of the last row, if that is not full
+#pragma unroll
+    for (int j = 0; j < PER; ++j)
+        if (n - j * kSelThreads < kSelThreads && n > j * kSelThreads) key[j] = partial ? 0ull : key[j];
     for (int b = threadIdx.x; b < DIST; b += kSelThreads) hist[b] = 0u;
     if (threadIdx.x == 0) listed = 0u;
     unsigned top = 0;
 #pragma unroll
-    for (int j = 0; j < PER; ++j) top = key[j] > top ? key[j] : top;
+    for (int j = 0; j < PER; ++j) top = max(top, (unsigned)(key[j] >> REST));
     for (int d = 32; d > 0; d >>= 1) top = max(top, (unsigned)__shfl_xor(top, d));
     if ((threadIdx.x & 63) == 0) wave_max[threadIdx.x >> 6] = top;
     __syncthreads();
@@ -766,11 +775,12 @@ __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned 
         const unsigned d = first - (e >> (LOW - REST));
         return d < (unsigned)DIST ? (unsigned)DIST - 1u - d : 0u;
     };
+    anew();
     bool crowd = false;                                       // (a look at every eighth: 2 us at 32768 if at each)
 #pragma unroll
     for (int j = 0; j < PER; ++j) {
         if (j * kSelThreads >= n) continue;
-        const unsigned b = bin(key[j]);
+        const unsigned b = bin((unsigned)(key[j] >> REST));
         if (j % 8 == 0) crowd = __popcll(__ballot(b == (unsigned)__builtin_amdgcn_readfirstlane((int)b))) >= 16;
         if (crowd) add_digit(hist, true, b);
         else atomicAdd(&hist[b], 1u);
@@ -793,12 +803,6 @@ __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned 
     }
     unsigned long long t = 0ull;
     unsigned last = 0u;
-    // (the places' numbers and which of them exist, worked out anew for each of the loops below: kept from the first loop on
-    // they are 32 vector and 64 scalar registers, and the kernel spills.  A form that did gave wrong marks: the compiler
-    // had put copies of the keys' registers at the end of a branch that some waves do not take, in front of the
-    // instruction that brings those waves back)
-    int thread = (int)threadIdx.x;
-    auto anew = [&] { asm volatile("" : "+v"(thread), "+s"(n)); };
     anew();
     while (!fits) {                                           // (uniform; 12 bits less each time, at most six times)
         unsigned long long h = 0, l = 0;
@@ -838,11 +842,9 @@ __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned 
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
             const int i = j * kSelThreads + thread;
-            if (key[j] < (unsigned)(low >> REST) || key[j] > (unsigned)(high >> REST) || i >= n) continue;
-            const unsigned long long e = src[i];
-            if (e < low || e > high) continue;
+            if (key[j] < low || key[j] > high || i >= n) continue;
             const unsigned at = atomicAdd(&listed, 1u);
-            list_key[at] = e;
+            list_key[at] = key[j];
             list_late[at] = ~(unsigned)i;
         }
         __syncthreads();
@@ -865,11 +867,7 @@ __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned 
     for (int j = 0; j < PER; ++j) {
         const int i = j * kSelThreads + thread;
         if (i >= n) continue;
-        bool keep = key[j] > (unsigned)(t >> REST);
-        if (key[j] == (unsigned)(t >> REST)) {
-            const unsigned long long e = src[i];
-            keep = e > t || (e == t && (unsigned)i <= last);
-        }
+        const bool keep = key[j] > t || (key[j] == t && (unsigned)i <= last);
         mask[i] = keep ? 1 : 0;
     }
 }
