@@ -202,6 +202,12 @@ void pconv_free(pconv_packed* p);
  *   stream  a hipStream_t passed as void* (NULL = the default stream)
  * Launch errors are returned; execution errors surface at the caller's next synchronisation.  N = 0 is a no-op.
  *
+ * Non-finite activations.  The vector kernels (fp32 storage) skip pruned weights: an infinity or NaN reaches the outputs
+ * whose kept weights meet it.  The matrix-core kernels multiply by the zeros that stand for them: there it makes NaN of
+ * every output whose window (1x1 layers: whose pixel) holds it.  With fp16 storage the automatic choice takes the one or
+ * the other by the call's sizes, also for single images; a caller that has to keep such values apart forces a vector
+ * kernel (pconv_conv3x3_tuned).
+ *
  * Channel-minor layout.  With PCONV_FLAG_NHWC x is dtype[N][H][W][C] and y dtype[N][Ho][Wo][F]: the order in which the
  * matrix-core kernel keeps activations on chip, so they travel from memory to LDS without passing registers.  fp16
  * storage only, C and F multiples of 8 (pad a three-channel input to eight), x and y aligned to 16 bytes, and a layer

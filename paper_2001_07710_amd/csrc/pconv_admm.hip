@@ -221,8 +221,8 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const T* __restrict__ 
 // finds the k-th largest among them; the last pass compares every key with it.  Every pass works out the position of
 // the k-th largest from the counts of the passes before it, redundantly in each workgroup, so that nothing waits for
 // anything but the end of the kernel before.  Where more keys share 21 bits than the list holds -- many equal norms:
-// kernels pruned to zero already -- three more counting passes of 14 bits settle the rest of the key, and equal keys
-// are ranked by index through counts per run of kernels; those passes return at once otherwise.
+// kernels pruned to zero already -- and are not all the same, three more counting passes of 14 bits settle the rest of the
+// key; equal keys are ranked by index through counts per run of kernels.  Those passes return at once otherwise.
 // 1.6 million fp32 kernels: 300 us with a 64-bit radix sort of (norm, index) pairs, whose eight passes move the pairs
 // through memory and back; 55 us so, of which 15 read the weights (59 MB at the rate of a copy).
 constexpr int kSelThreads = 1024;

@@ -48,7 +48,7 @@ void set_hip_error(const char* what, int hip_code) {
 
 // What the host hands over is small: the canonical arrays, the staging orders and the channel lists.  The layouts the
 // kernels read -- the entries once per tiling, the matrix-core weights once per tile height, ten to twenty times as many
-// bytes -- are made from them here, so a layer is one allocation, one copy and three short kernels (256 -> 256 channels,
+// bytes -- are made from them here, so a layer is one allocation, one copy and four short kernels (256 -> 256 channels,
 // fp16: the copy is 0.5 MB, not 6; with the host side of packing, 5.8 -> 0.7 ms).
 
 // The entries of the layer for up to kMaxLayouts staging orders: workgroup (i, l) is one wave that brings the entries of
@@ -135,7 +135,7 @@ __global__ __launch_bounds__(64) void build_entries_kernel(const EntryParams p) 
 // host's find_balanced(): channels by decreasing number of users go, one after the other, into the chunk where the busiest
 // wave stays least busy.  A chain of C short steps per filter group, and the groups are independent: one wave per group
 // and tiling, a lane per chunk (NBLK chunks), a step some 400 clocks of register arithmetic and one minimum over the lanes
-// -- 256 -> 256 channels: 50 us for the five tilings side by side, 210 us on three host threads.
+// -- 256 -> 256 channels: 75 us for the five tilings side by side, 210 us on three host threads.
 struct OrderLayout {
     uint32_t* perm;
     uint16_t* pos_of;

@@ -355,7 +355,8 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                 // (with channel ranges in the place of taps: the same positions of every range, each range into its
                 // own part of the stage, 2 P pieces long.  A layer of nine taps has no ranges, and its loads sit in the
                 // straight run of code between the MFMAs: a loop there, even one that runs once, costs 1,100 spilled
-                // scalars in the 128 x 448 tile -- 128 -> 128 channels at 112 x 112, batch 64: 8,270 us with the loop)
+                // scalars in the 128 x 448 tile -- 128 -> 128 channels at 112 x 112, batch 64: 8,300 us with the loop, 198 to 215
+                // without.  A layer that misses a tap runs the form below with its loop and run-time number of taps: 255 us)
                 const int ranges = FULL ? 1 : p.groups;
                 for (int t = 0; t < ranges; ++t)
                     __builtin_amdgcn_raw_ptr_buffer_load_lds(
