@@ -2816,12 +2816,7 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
         // kernel's leaves out some 6 us (measured on layers of few blocks), and so does what the vector kernels are
         // compared with below -- there the tile kernel stands with its own number.
         const double tile_us = best_us;
-        // (layers of two to eight taps: like the other kernel's estimate, this one's is of nine, scaled down, and the form
-        // that runs has a run-time number of taps; 4,500 such layers took 1.15 times the sum in the mean.  1.1 is asked: 128 ->
-        // 128 at 56 x 56, stride 2, batch 32, needs 1.08 -- 27.1 us there, 28.6 here --, 320 -> 96 at 32 x 32, batch 34, less
-        // than 1.13 -- 65 against 57)
-        const double taps_cost = a.kext == 3 && a.n_taps > 1 && a.n_taps < 9 ? 1.1 : 1.0;
-        double bar_us = tile_us >= 0.0 ? (tile_us + 6.0) * taps_cost : -1.0;
+        double bar_us = tile_us >= 0.0 ? tile_us + 6.0 : -1.0;
         if (!known && (want_shape == 0 ? !forced || (nhwc && all_auto) : want_shape > kMfmaShapes) && use_weights(wp, 64, 1, &small)) {
             const MfmaConv base = small;
             for (int sh = 0; sh < kSmallShapes; ++sh) {

@@ -254,18 +254,6 @@ def test_layers_whose_patterns_leave_out_a_tap_are_priced_as_such(case):
     p.free()
 
 
-def test_both_matrix_core_kernels_are_priced_for_a_tap_left_out():
-    """128 -> 128 at 56 x 56, stride 2, batch 32, eight taps: 27.1 us in the kernel for few tiles, 28.6 in the tile kernel."""
-    say("a tap left out, both kernels")
-    r = np.random.default_rng(3)
-    w = (r.standard_normal((128, 128, 3, 3)) * 0.04).astype(np.float16)
-    p = pc.pack(w, np.array([0x1B, 0x36, 0xB1, 0x72], dtype=np.uint16), r.integers(0, 4, (128, 128)).astype(np.uint8),
-                (r.random((128, 128)) < 0.3).astype(np.uint8))
-    kernel, shape = pc.conv3x3_choice(p, 32, 56, 56, 2, 1)
-    assert kernel == M and shape >= 5
-    p.free()
-
-
 @pytest.mark.parametrize("case", [(2, 1844, 96, 224, 224, 0.35), (1, 1104, 219, 224, 224, 0.5), (17, 1680, 768, 32, 32, 0.3),
                                   (1, 419, 208, 224, 224, 0.28), (11, 1082, 114, 32, 32, 0.28)])
 def test_1x1_layers_whose_planes_crowd_the_cache_are_priced_as_such(case):
