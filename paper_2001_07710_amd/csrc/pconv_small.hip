@@ -424,11 +424,7 @@ int pieces_for(int lw, long long need) {
 // full, and a time per step of its waves: the round trip of the next step's loads, or what the load instructions of all
 // waves on the compute unit take at one per 6 ns.  As many workgroups as registers and LDS allow share a compute unit, the
 // rest waits for another round.  A full device is also bound by what its waves fetch from the L2, their weights above
-// all: about 16 TB/s.  Layers of two to eight taps run the form whose number of taps is not known to the compiler
-// (NT = 0: more scalars than registers, loads that wait sooner): against this estimate, fitted to nine taps, 4,400 such
-// random layers took 1.16, 1.28 and 1.3 times as long in the three shapes, and that is asked of them.  (Without it, one
-// in fifty was slower than the vector or tile kernel it was chosen over: four patterns of eight taps, 432 -> 16 channels
-// at 224 x 224, batch 1: 31.9 -> 52.6 us.)
+// all: about 16 TB/s.
 bool plan(const MfmaConv& a, int shape, double bar, SmallPlan* out) {
     const SmallShape& sh = kSmall[shape];
     const int M = sh.af * 32, PX = sh.bf * 32;
@@ -444,8 +440,6 @@ bool plan(const MfmaConv& a, int shape, double bar, SmallPlan* out) {
     const int wtiles = (a.F + 63) / 64, blocks = a.d_clist ? (a.total_blocks + wtiles - 1) / wtiles : (a.C + 15) / 16;
     const int steps = (blocks + nb - 1) / nb;
     static const double kFixedUs[kSmallShapes] = {1.4, 2.2, 4.4}, kStepUs[kSmallShapes][2] = {{0.55, 0.35}, {0.8, 0.6}, {1.2, 0.9}};
-    static const double kSomeTaps[kSmallShapes] = {1.16, 1.28, 1.3};
-    const double taps_cost = a.n_taps == 1 || a.n_taps == 9 ? 1.0 : kSomeTaps[shape];
     static const int kWavesPerCu[kSmallShapes][2] = {{16, 16}, {12, 16}, {8, 16}};
     // (a step of a 1x1 layer reads one short run from each of 64 planes: planes a multiple of 512 or of 2048 bytes apart
     // fall on few of the L2's channels, and the activations come at half or a quarter of the rate.  3,200 random layers,
@@ -472,7 +466,7 @@ bool plan(const MfmaConv& a, int shape, double bar, SmallPlan* out) {
         if (tiles > 0x7FFFFFF0) continue;
         // (what no load width and no number of waves can make up for: a first call of a size pays for the search)
         const double busy_least = kFixedUs[shape] + (double)tiles * steps * kStepUs[shape][nb > 1] / ((double)cus * kWavesPerCu[shape][nb > 1]);
-        if (taps_cost * (3.0 + std::max(busy_least, (double)tiles * steps * step_weights / 16e6 + out_us)) > best.us) continue;
+        if (3.0 + std::max(busy_least, (double)tiles * steps * step_weights / 16e6 + out_us) > best.us) continue;
         for (int lw = a.nhwc ? 0 : 4; lw >= 0; lw = lw == 4 ? 2 : lw == 2 ? 1 : -1) {
             if (a.tile_w > 0 && lw != a.tile_lw) continue;
             const int piece = lw ? lw : 1;
@@ -496,7 +490,7 @@ bool plan(const MfmaConv& a, int shape, double bar, SmallPlan* out) {
             const double fetched = step_weights + crowded * rows * row_bytes * 16.0 * nb;
             const int loads = (a.nhwc ? ki : 8 * ki) + sh.af * a.n_taps * nb;
             const double traffic_us = (double)tiles * steps * fetched / 16e6 + out_us;
-            if (taps_cost * (3.0 + std::max(busy_least, traffic_us)) > best.us) continue;
+            if (3.0 + std::max(busy_least, traffic_us) > best.us) continue;
             for (int waves = 8; waves >= 1; waves /= 2) {
                 if (a.splits ? waves != a.splits : waves > steps && waves > 1) continue;
                 const size_t stage = (size_t)rows * row_slots * 32 * nb * waves;
@@ -510,7 +504,7 @@ bool plan(const MfmaConv& a, int shape, double bar, SmallPlan* out) {
                 const double on_cu = std::min((double)resident, std::max<double>(tiles, cus)) / cus * waves;
                 const double busy = rounds * (kFixedUs[shape] * (1.0 + on_cu / 16.0) + 0.1 * waves +
                                               (steps + waves - 1) / waves * std::max(kStepUs[shape][nb > 1], on_cu * loads * 0.006));
-                const double us = taps_cost * (3.0 + std::max(busy, traffic_us) + 0.15 * std::min(busy, traffic_us));
+                const double us = 3.0 + std::max(busy, traffic_us) + 0.15 * std::min(busy, traffic_us);
                 // (of equal ones the narrowest tile, then the widest loads and the most waves)
                 if (us > best.us || (us == best.us && (!found || best.p.TW == tw))) continue;
                 best.us = us;
