@@ -8,7 +8,7 @@
 // layout v_mfma_f32_32x32x16_f16 wants: a lane's operand is 8 consecutive pixels of one filter (or channel), 16
 // contiguous bytes.  No transposition anywhere.
 //
-// Tile.  A workgroup of four waves owns 64 filters x 64 channels x 9 taps (a wave: 32 x 32 x 9, 144 accumulators)
+// Tile.  A workgroup owns 64 filters x 64 channels x 9 taps (four of its waves: 32 x 32 x 9 each, 144 accumulators)
 // and walks over chunks of the pixels: R output rows x Gc groups of 8 columns of one image.  Per chunk it stages
 //   x   [input row r'][group g][channel][8 pixels]            rows oy0-1 .. oy0+R, one 16-byte piece per (channel, r', g)
 //   dy  [row r][group j][filter][8 pixels]                    groups one left and one right more than x has
@@ -17,13 +17,16 @@
 // kernel row share one read of x: the sum over ox of dy[ox] * x[ox+kx-1] is the sum over x's own columns ox' of
 // dy[ox'+1-kx] * x[ox'], so kx = 1 multiplies x with dy's group as it is, and kx = 0 / 2 with the same eight pixels of
 // dy moved by one with the first / last pixel of the neighbouring group (eight v_alignbyte_b32 per K step of nine
-// MFMAs).  Those neighbour words are staged a second time, 8 bytes per (row, group, filter) side by side over the
-// filters, so that dy is one 128-bit and one 64-bit read free of bank conflicts.  Zero padding is nothing but dy's
-// zero halo: columns beyond the image, rows beyond it, filters beyond F and channels beyond C are loads at an
-// offset outside the buffer descriptor.  The loads of the next chunk are in flight, in registers, while the current
-// one is multiplied.  (First version: the shifts on the x side, three per kernel row -- 24 vector instructions, seven
-// LDS reads and a dozen of address arithmetic per nine MFMAs, and the one wave a SIMD has here cannot issue that many
-// beside its MFMAs: 19 to 26 % of the matrix cores' rate.)
+// MFMAs).  Zero padding is nothing but dy's zero halo: columns beyond the image, rows beyond it, filters beyond F and
+// channels beyond C are loads at an offset outside the buffer descriptor.
+//
+// Waves.  What bounded the first forms was that nothing overlapped: with one wave per SIMD that both stages and
+// multiplies, the address arithmetic of 20 pieces, the wait for their loads, the LDS writes and two barriers added up
+// with the MFMAs (matrix cores busy 29 % of the time).  So four waves, one per SIMD, do nothing but multiply, and four
+// others, their neighbours on the SIMDs, nothing but stage: while chunk k is multiplied out of one half of the LDS they
+// write chunk k + 1, whose loads were issued a chunk's time ago, into the other, and issue the loads of chunk k + 2.
+// One barrier per chunk.  128 -> 128 channels at 112 x 112, batch 64: 341 -> 217 us, where the MFMAs alone, without
+// loads and LDS reads, take 150 (the clock sinks to 1.95 GHz under them); 512 -> 512 at 28 x 28: 411 -> 258, at 14 x 14 179 -> 110.
 //
 // The pixels are split over S workgroups per tile; each writes its 9 x 64 x 64 partial sums to the workspace, a second
 // kernel adds the S parts in order, and a third gathers the sums of the kept weights into the canonical entry order
@@ -32,9 +35,11 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <type_traits>
 
 #include "pconv_backward.h"
 #include "pconv_internal.h"
+#include "pconv_mfma_util.h"
 
 namespace pconv {
 
@@ -49,15 +54,9 @@ namespace pconv {
 
 namespace {
 
-typedef _Float16 half8 __attribute__((ext_vector_type(8)));
-typedef float float16v __attribute__((ext_vector_type(16)));
-typedef unsigned uint4v __attribute__((ext_vector_type(4)));
-typedef unsigned uint2v __attribute__((ext_vector_type(2)));
-
-constexpr uint32_t kInvalid = 0x80000000u;
 constexpr int kPitch = 64 * 16 + 16;          // bytes from one (row, group) of a staged operand to the next
-constexpr int kPitchE = 64 * 8 + 8;           // the same for the neighbour words of dy (8 bytes per filter)
-constexpr int kMaxX = 12, kMaxD = 10;         // 16-byte pieces per thread and chunk, at most: x, dy
+constexpr int kMaxSlots = 78;                 // (row, group) slots of a chunk, x and dy together: two chunks in 160 KB;
+                                              // 64 / 256 of them 16-byte pieces per staging thread, 20 at most
 constexpr int kTile = 64;
 
 struct GwParams {
@@ -70,13 +69,10 @@ struct GwParams {
     int chunks;               // N * nrb * ncb
     int S;                    // workgroups per tile
     int tiles_c, tiles;       // channel tiles; all tiles
-    int npx, npd;             // pieces per thread: x, dy
+    int slots_x, slots;       // (row, group) slots of a chunk: x's, and with dy's behind them
     unsigned x_img_bytes, dy_img_bytes;
+    FastDiv div_Gc, div_NJ;
 };
-
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_rsrc(const void* base, uint32_t bytes) {
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
-}
 
 // eight consecutive fp16 elements from byte offset `off` (kInvalid: zeros), LW elements per load
 template <int LW>
@@ -102,95 +98,87 @@ __device__ __forceinline__ uint4v load8(__amdgpu_buffer_rsrc_t r, const uint32_t
     return v;
 }
 
-template <int LW>
-__global__ __launch_bounds__(256, 1) void grad_weight_kernel(const GwParams p) {
+// NP: pieces per staging thread and chunk, at most (8, 12, 16 or 20)
+template <int LW, int NP>
+__global__ __launch_bounds__(512, 2) void grad_weight_kernel(const GwParams p) {
     extern __shared__ __align__(16) unsigned char lds[];
-    const int tid = threadIdx.x, lane = tid & 63;
-    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int wf = wave >> 1, wc = wave & 1, li = lane & 31, lk = lane >> 5;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int tile = (int)blockIdx.x / p.S, split = (int)blockIdx.x - tile * p.S;
     const int tf = tile / p.tiles_c, tc = tile - tf * p.tiles_c;
     const int R = p.R, Gc = p.Gc, NJ = p.NJ, H = p.H, W = p.W;
-    unsigned char* const dyL = lds;                               // [r][j < NJ][filter][8 pixels]
-    unsigned char* const eL = dyL + R * NJ * kPitch;              // [r][j][filter]{left neighbours, right neighbours}
-    unsigned char* const xL = eL + R * NJ * kPitchE;              // [r' < R + 2][g < Gc][channel][8 pixels]
+    const int buf_bytes = p.slots * kPitch;       // a staged chunk: x [r' < R + 2][g < Gc], then dy [r][j < NJ]
+    // this workgroup's chunks: neighbours in the image, so that the rows two chunks share are still in the L2
+    const int c0 = (int)((long long)split * p.chunks / p.S), c1 = (int)((long long)(split + 1) * p.chunks / p.S);
 
-    // ---- this thread's pieces of a chunk (the same for every chunk): where they go in LDS, and where they come
-    // from relative to the chunk's first output row and column
-    int xl[kMaxX], xrel[kMaxX], xrg[kMaxX];      // xrg: row r' | group g << 8
-    int dl[kMaxD], drel[kMaxD], drj[kMaxD];      // drj: row r | group j << 8
+    if (wave >= 4) {
+        // ---- staging.  This thread's pieces of a chunk (the same for every chunk): where they go in LDS, and where they
+        // come from relative to the chunk's first output row and column.  A wave's 64 pieces are all of x or all of dy.
+        // (Loads and LDS writes are unconditional -- a piece that is not there is a load outside the descriptor and a
+        // write behind the two chunks -- because a branch around them makes the compiler wait for every load at once.)
+        const int ltid = (int)threadIdx.x - 256, first = (wave - 4) * 64;
+        int to[NP], rel[NP], rc[NP];              // rc: relative row + 1 | (relative column + 8) << 16
 #pragma unroll
-    for (int i = 0; i < kMaxX; ++i) {
-        const int idx = tid + i * 256;
-        const int g = idx % Gc, q = idx / Gc, c = q & 63, r = q >> 6;
-        const int chan = tc * kTile + c;
-        const bool ok = r < R + 2 && chan < p.C;
-        xl[i] = r < R + 2 ? (r * Gc + g) * kPitch + c * 16 : -1;
-        xrel[i] = ok ? (chan * H * W + (r - 1) * W + g * 8) * 2 : (int)kInvalid;
-        xrg[i] = r | (g << 8);
-    }
-#pragma unroll
-    for (int i = 0; i < kMaxD; ++i) {
-        const int idx = tid + i * 256;
-        const int j = idx % NJ, q = idx / NJ, f = q & 63, r = q >> 6;
-        const int filt = tf * kTile + f;
-        const bool ok = r < R && filt < p.F;
-        dl[i] = r < R ? (r * NJ + j) * kPitch + f * 16 : -1;
-        drel[i] = ok ? (filt * H * W + r * W + (j - 1) * 8) * 2 : (int)kInvalid;
-        drj[i] = r | (j << 8);
-    }
-
-    uint4v xs[kMaxX], ds[kMaxD];
-    auto fetch = [&](int chunk) {
-        const int cb = chunk % p.ncb, q = chunk / p.ncb, rb = q % p.nrb, n = q / p.nrb;
-        const int oy0 = rb * R, col0 = cb * Gc * 8;
-        const __amdgpu_buffer_rsrc_t xr = make_rsrc(p.x + (size_t)n * p.x_img_bytes, p.x_img_bytes);
-        const __amdgpu_buffer_rsrc_t dr = make_rsrc(p.dy + (size_t)n * p.dy_img_bytes, p.dy_img_bytes);
-        const int shift = (oy0 * W + col0) * 2;
-#pragma unroll
-        for (int i = 0; i < kMaxX; ++i) {
-            if (i < p.npx) {
-                const int iy = oy0 + (xrg[i] & 255) - 1, col = col0 + (xrg[i] >> 8) * 8;
-                const bool row_ok = xrel[i] != (int)kInvalid && iy >= 0 && iy < H;
-                uint32_t off[8 / LW];
-#pragma unroll
-                for (int u = 0; u < 8 / LW; ++u)
-                    off[u] = (row_ok && col + u * LW < W) ? (uint32_t)(xrel[i] + shift + u * LW * 2) : kInvalid;
-                xs[i] = load8<LW>(xr, off);
-            }
+        for (int i = 0; i < NP; ++i) {
+            const int id = ltid + i * 256;
+            const bool is_x = id < p.slots_x * 64;
+            const int at = is_x ? id : id - p.slots_x * 64;
+            const int groups = is_x ? Gc : NJ;
+            const int q = (int)fastdiv((unsigned)at, is_x ? p.div_Gc : p.div_NJ), g = at - q * groups, c = q & 63, r = q >> 6;
+            const int chan = (is_x ? tc : tf) * kTile + c;
+            const int row = is_x ? r - 1 : r, col = is_x ? g * 8 : (g - 1) * 8;
+            const bool there = id < p.slots * 64;
+            to[i] = there ? ((is_x ? 0 : p.slots_x) + r * groups + g) * kPitch + c * 16 : 2 * buf_bytes + lane * 16;
+            rel[i] = (chan * H * W + row * W + col) * 2;
+            rc[i] = there && chan < (is_x ? p.C : p.F) ? (row + 1) | ((col + 8) << 16) : 0x7FFF;     // (a row beyond any image)
         }
+        uint4v v[NP];
+        // One chunk on: piece by piece, what has arrived is written into half `buf` and its register asks for the same piece
+        // of the chunk after, so that every load has a whole chunk's time to come back.  (All writes first and then all
+        // loads, the last loads' round trip was waited for in every chunk: 222 -> 217 us at 128 -> 128, 112 x 112.)
+        auto move_on = [&](auto write_, auto load_, int buf, int chunk) {
+            const int cb = chunk % p.ncb, q = chunk / p.ncb, rb = q % p.nrb, n = q / p.nrb;
+            const int oy0 = rb * R - 1, col0 = cb * Gc * 8 - 8;                        // (matches rc's offsets)
+            const __amdgpu_buffer_rsrc_t xr = make_rsrc(p.x + (size_t)n * p.x_img_bytes, p.x_img_bytes);
+            const __amdgpu_buffer_rsrc_t dr = make_rsrc(p.dy + (size_t)n * p.dy_img_bytes, p.dy_img_bytes);
+            const int shift = (rb * R * W + cb * Gc * 8) * 2;
+            // (which pieces are x's and which are there at all: asked anew for each chunk.  As conditions that do not
+            // change the compiler would keep 2 NP of them, in more scalar registers than there are)
+            int first_now = first;
+            asm volatile("" : "+s"(first_now));
 #pragma unroll
-        for (int i = 0; i < kMaxD; ++i) {
-            if (i < p.npd) {
-                const int oy = oy0 + (drj[i] & 255), col = col0 + ((drj[i] >> 8) - 1) * 8;
-                const bool row_ok = drel[i] != (int)kInvalid && oy < H;
-                uint32_t off[8 / LW];
+            for (int i = 0; i < NP; ++i) {
+                if constexpr (decltype(write_)::value)
+                    *reinterpret_cast<uint4v*>(lds + to[i] + (first_now + i * 256 < p.slots * 64 ? buf * buf_bytes : 0)) = v[i];
+                if constexpr (decltype(load_)::value) {
+                    const bool row_ok = (unsigned)(oy0 + (rc[i] & 0xFFFF)) < (unsigned)H;
+                    const int col = col0 + (rc[i] >> 16);
+                    uint32_t off[8 / LW];
 #pragma unroll
-                for (int u = 0; u < 8 / LW; ++u) {
-                    const int cc = col + u * LW;
-                    off[u] = (row_ok && cc >= 0 && cc < W) ? (uint32_t)(drel[i] + shift + u * LW * 2) : kInvalid;
+                    for (int u = 0; u < 8 / LW; ++u)
+                        off[u] = row_ok && (unsigned)(col + u * LW) < (unsigned)W ? (uint32_t)(rel[i] + shift + u * LW * 2) : kInvalid;
+                    v[i] = load8<LW>(first_now + i * 256 < p.slots_x * 64 ? xr : dr, off);
                 }
-                ds[i] = load8<LW>(dr, off);
+                __builtin_amdgcn_sched_barrier(0);
             }
+        };
+        if (c0 >= c1) return;
+        const std::true_type yes;
+        const std::false_type no;
+        move_on(no, yes, 0, c0);
+        int chunk = c0;
+        for (; chunk + 1 < c1; ++chunk) {
+            move_on(yes, yes, (chunk - c0) & 1, chunk + 1);
+            __syncthreads();
         }
-    };
-    auto stage = [&]() {
-#pragma unroll
-        for (int i = 0; i < kMaxX; ++i)
-            if (i < p.npx && xl[i] >= 0) *reinterpret_cast<uint4v*>(xL + xl[i]) = xs[i];
-#pragma unroll
-        for (int i = 0; i < kMaxD; ++i)
-            if (i < p.npd && dl[i] >= 0) {
-                *reinterpret_cast<uint4v*>(dyL + dl[i]) = ds[i];
-                // this piece's last two pixels are the left neighbours of the group to its right, its first two the
-                // right neighbours of the group to its left (only groups 1 .. Gc are ever multiplied)
-                const int j = drj[i] >> 8;
-                const int e = (dl[i] / kPitch) * kPitchE + ((dl[i] % kPitch) >> 1);
-                if (j < NJ - 1) *reinterpret_cast<unsigned*>(eL + e + kPitchE) = ds[i].w;
-                if (j >= 1) *reinterpret_cast<unsigned*>(eL + e - kPitchE + 4) = ds[i].x;
-            }
-    };
+        move_on(yes, no, (chunk - c0) & 1, 0);
+        __syncthreads();
+        __syncthreads();      // (the one in front of the last chunk's last step)
+        return;
+    }
 
+    // ---- multiplying
+    const int wf = wave >> 1, wc = wave & 1, li = lane & 31, lk = lane >> 5;
     float16v acc[3][3];
 #pragma unroll
     for (int ky = 0; ky < 3; ++ky)
@@ -200,114 +188,133 @@ __global__ __launch_bounds__(256, 1) void grad_weight_kernel(const GwParams p) {
             for (int i = 0; i < 16; ++i) acc[ky][kx][i] = 0.f;
 
     const int nk = R * Gc / 2;                  // K steps of 16 pixels per chunk (R*Gc is even)
-    const int a_lane = (wf * 32 + li) * 16, b_lane = (wc * 32 + li) * 16;
+    const int a_lane = p.slots_x * kPitch + (wf * 32 + li) * 16, b_lane = (wc * 32 + li) * 16;
     // This half-wave's items are lk, lk + 2, ...; item = r*Gc + g.  x has no halo groups, so an item's x slot is the
     // item number plus ky rows; its dy slot is r*NJ + g + 1, which skips the two halo groups at every row end.
     const bool one_group = Gc == 1;             // (then every item is a row of its own: three dy slots per item)
-    const int a_slot0 = one_group ? lk * 3 + 1 : lk + 1;
+    const int a_off0 = (one_group ? lk * 3 + 1 : lk + 1) * kPitch + a_lane, b_off0 = lk * kPitch + b_lane;
     const int row_b = Gc * kPitch;
-    struct RawA {
+    if (c0 < c1) {
+        // The K steps of all chunks are one sequence, software-pipelined: while a step's nine MFMAs run, the next step's
+        // operands are read from LDS and shifted, a few instructions behind each MFMA, so that the wave never has more to
+        // issue than an MFMA takes.  The barrier between two chunks stands in front of a chunk's last step, whose operands
+        // are in registers by then: what it lets pass are the reads of the next chunk's first step.
+        // The shifts by one pixel are made on the dy side: the sum over ox of dy[ox] * x[ox + kx - 1] is the sum over x's
+        // own columns ox' of dy[ox' + 1 - kx] * x[ox'], so one read of x per kernel row serves its three taps, and dy is
+        // read once per step and moved left and right by one pixel with its neighbour words (eight v_alignbyte_b32 per
+        // nine MFMAs; with the shifts on the x side it was 24 vector instructions per step).
+        const unsigned char *a_at = lds + a_off0, *b_at = lds + b_off0;
         uint4v cur;
-        uint2v nb;
-    };
-    auto read_a = [&](int slot) {
-        RawA w;
-        w.cur = *reinterpret_cast<const uint4v*>(dyL + slot * kPitch + a_lane);
-        w.nb = *reinterpret_cast<const uint2v*>(eL + slot * kPitchE + (a_lane >> 1));
-        return w;
-    };
-    auto read_b = [&](int off, int ky) { return *reinterpret_cast<const half8*>(xL + off + ky * row_b); };
-
-    int chunk = split;
-    if (chunk < p.chunks) fetch(chunk);
-    while (chunk < p.chunks) {
-        stage();
-        __syncthreads();
-        const int next = chunk + p.S;
-        if (next < p.chunks) fetch(next);
-        // The operands of a K step are requested one step ahead, each as soon as its registers are free, so the LDS
-        // has nine MFMAs' time to answer.  The shifts by one pixel are made on the dy side: the sum over ox of
-        // dy[ox] * x[ox + kx - 1] is the sum over x's own columns ox' of dy[ox' + 1 - kx] * x[ox'], so one read of x
-        // per kernel row serves its three taps, and dy is read once per step and moved left and right by one pixel
-        // with its neighbour words (eight v_alignbyte_b32 per nine MFMAs; with the shifts on the x side it was 24
-        // vector instructions per step, and a single wave per SIMD cannot issue that many beside its MFMAs).
-        int g = lk, a_slot = a_slot0, b_off = lk * kPitch + b_lane;
-        RawA ra = read_a(a_slot);
-        half8 b[3];
-#pragma unroll
-        for (int ky = 0; ky < 3; ++ky) b[ky] = read_b(b_off, ky);
-        for (int k = 0; k < nk; ++k) {
-            // the items after these (behind the last: the first again, whose operands are read and not used)
-            g += 2;
-            const bool wrap = g >= Gc;
-            g = wrap ? g - Gc : g;
-            a_slot += one_group ? 6 : wrap ? 4 : 2;
-            b_off += 2 * kPitch;
-            if (k + 1 == nk) {
-                g = lk;
-                a_slot = a_slot0;
-                b_off = lk * kPitch + b_lane;
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            const uint4v cur = ra.cur;
-            const unsigned l0 = __builtin_amdgcn_alignbyte(cur.x, ra.nb.x, 2);
+        unsigned left, right;                   // the neighbouring groups' last and first two pixels
+        auto read_a = [&] {
+            cur = *reinterpret_cast<const uint4v*>(a_at);
+            left = *reinterpret_cast<const unsigned*>(a_at - kPitch + 12);
+            right = *reinterpret_cast<const unsigned*>(a_at + kPitch);
+        };
+        half8 a[2][3], b[3];                    // [kx]: dy at columns ox' + 1, ox', ox' - 1
+        auto shift_a = [&](half8 (&to)[3]) {
+            const unsigned l0 = __builtin_amdgcn_alignbyte(cur.x, left, 2);
             const unsigned l1 = __builtin_amdgcn_alignbyte(cur.y, cur.x, 2);
             const unsigned l2 = __builtin_amdgcn_alignbyte(cur.z, cur.y, 2);
             const unsigned l3 = __builtin_amdgcn_alignbyte(cur.w, cur.z, 2);
-            const unsigned r3 = __builtin_amdgcn_alignbyte(ra.nb.y, cur.w, 2);
-            const half8 a2 = __builtin_bit_cast(half8, uint4v{l0, l1, l2, l3});      // dy at column ox' - 1: tap kx = 2
-            const half8 a1 = __builtin_bit_cast(half8, cur);                          // ox': kx = 1
-            const half8 a0 = __builtin_bit_cast(half8, uint4v{l1, l2, l3, r3});      // ox' + 1: kx = 0
-            ra = read_a(a_slot);
+            const unsigned r3 = __builtin_amdgcn_alignbyte(right, cur.w, 2);
+            to[2] = __builtin_bit_cast(half8, uint4v{l0, l1, l2, l3});
+            to[1] = __builtin_bit_cast(half8, cur);
+            to[0] = __builtin_bit_cast(half8, uint4v{l1, l2, l3, r3});
+            asm volatile("" : "+v"(to[0]), "+v"(to[2]));       // (made here, not where the next step first needs them)
+        };
+        __builtin_amdgcn_s_setprio(1);
+        __syncthreads();
+        read_a();
+#pragma unroll
+        for (int ky = 0; ky < 3; ++ky) b[ky] = *reinterpret_cast<const half8*>(b_at + ky * row_b);
+        shift_a(a[0]);
+        int g = lk, k = 0, buf = 0;
+        auto step = [&](auto set_) {
+            constexpr int set = decltype(set_)::value;
+            g += 2;
+            const bool wrap = g >= Gc;
+            g = wrap ? g - Gc : g;
+            a_at += (one_group ? 6 : wrap ? 4 : 2) * kPitch;
+            b_at += 2 * kPitch;
+            if (++k == nk) {
+                __syncthreads();
+                k = 0;
+                g = lk;
+                buf = buf_bytes - buf;
+                a_at = lds + buf + a_off0;
+                b_at = lds + buf + b_off0;
+            }
+            read_a();
 #pragma unroll
             for (int ky = 0; ky < 3; ++ky) {
-                __builtin_amdgcn_sched_barrier(0);
-                acc[ky][0] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a0, b[ky], acc[ky][0], 0, 0, 0);
-                acc[ky][1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a1, b[ky], acc[ky][1], 0, 0, 0);
-                acc[ky][2] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a2, b[ky], acc[ky][2], 0, 0, 0);
-                b[ky] = read_b(b_off, ky);
+#pragma unroll
+                for (int kx = 0; kx < 3; ++kx) {
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[ky][kx] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[set][kx], b[ky], acc[ky][kx], 0, 0, 0);
+                }
+                b[ky] = *reinterpret_cast<const half8*>(b_at + ky * row_b);
+                if (ky == 1) shift_a(a[set ^ 1]);
             }
+            __builtin_amdgcn_sched_barrier(0);
+        };
+        const long long steps = (long long)(c1 - c0) * nk;
+        for (long long i = 0; i + 1 < steps; i += 2) {
+            step(std::integral_constant<int, 0>{});
+            step(std::integral_constant<int, 1>{});
         }
-        __builtin_amdgcn_sched_barrier(0);
-        __syncthreads();
-        chunk = next;
+        if (steps & 1) step(std::integral_constant<int, 0>{});
     }
 
-    // ---- partial sums: ws[split][tile][tap][filter in tile][channel in tile]; accumulator row i of a 32 x 32 block
-    // is filter (i/4)*8 + (lane/32)*4 + i%4, its column (lane%32) the channel
-    float* const out = p.ws + ((size_t)split * p.tiles + tile) * (9 * kTile * kTile);
+    // ---- partial sums: ws[split][tile][tap][wave][filter of the wave's 32][channel].  Accumulator row i of a 32 x 32 block
+    // is filter (i/4)*8 + (lane/32)*4 + i%4, its column (lane%32) the channel; through a part of the LDS that no other
+    // wave touches (all operands are in registers since the last barrier), so that every store is 1 KB in one piece.
+    // (Straight from the registers, 128 bytes a row, the stores of a layer of a few chunks took as long as its MFMAs.)
+    constexpr int kRow = 36;
+    static_assert(4 * 32 * kRow * 4 <= 2 * 10 * kPitch, "a chunk has ten slots at least");
+    float* const turn = reinterpret_cast<float*>(lds) + wave * 32 * kRow;
+    float4v* const out = reinterpret_cast<float4v*>(p.ws + ((size_t)split * p.tiles + tile) * (9 * kTile * kTile));
 #pragma unroll
-    for (int ky = 0; ky < 3; ++ky)
+    for (int t = 0; t < 9; ++t) {
+        // (lanes read what other lanes of the wave wrote; the hardware takes a wave's LDS accesses in order)
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-        for (int kx = 0; kx < 3; ++kx)
+        for (int i = 0; i < 16; ++i) turn[((i >> 2) * 8 + lk * 4 + (i & 3)) * kRow + li] = acc[t / 3][t % 3][i];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
 #pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int f = wf * 32 + (i >> 2) * 8 + lk * 4 + (i & 3), c = wc * 32 + li;
-                out[((ky * 3 + kx) * kTile + f) * kTile + c] = acc[ky][kx][i];
-            }
+        for (int q = 0; q < 4; ++q)
+            out[((t * 4 + wave) * 4 + q) * 64 + lane] =
+                *reinterpret_cast<const float4v*>(turn + (q * 8 + (lane >> 3)) * kRow + (lane & 7) * 4);
+    }
+}
+
+// Where in a tile's part the sum of tap t for filter f and channel c of the tile lies
+__device__ __forceinline__ int part_index(int t, int f, int c) {
+    return ((t * 4 + (f >> 5) * 2 + (c >> 5)) * 32 + (f & 31)) * 32 + (c & 31);
 }
 
 // The S parts of every tile added into part 0, in order: a dense pass, four neighbouring sums per thread, so the parts
 // are read at the rate of a copy.  (Summed inside the gather below instead, one scattered 4-byte read per part and kept
 // weight, the parts of a layer with a single tile -- 256 of them -- took 90 us.)
 __global__ __launch_bounds__(256) void grad_weight_reduce_kernel(float* __restrict__ ws, long long n4, long long part4, int S,
-                                                                 int step, int cnt) {
-    // group blockIdx.y: parts (group*cnt + s)*step, s < cnt, as far as there are parts, added into the group's first
-    typedef float float4v __attribute__((ext_vector_type(4)));
+                                                                 int cnt) {
+    // group blockIdx.y: parts group*cnt + s, s < cnt, as far as there are parts, added into the group's first
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     float4v* const w4 = reinterpret_cast<float4v*>(ws);
-    const long long first = (long long)blockIdx.y * cnt * step;
+    const long long first = (long long)blockIdx.y * cnt;
     float4v sum = w4[first * part4 + i];
-    for (int s = 1; s < cnt && first + (long long)s * step < S; ++s) sum += w4[(first + (long long)s * step) * part4 + i];
+    for (int s = 1; s < cnt && first + s < S; ++s) sum += w4[(first + s) * part4 + i];
     w4[first * part4 + i] = sum;
 }
 
-// dw4[e][q] = sum over the S parts, in order, of the partial sum of entry e's filter and channel at the q-th tap of
-// its pattern
+// dw4[e][q] = sum over the parts that are left, in order, of the partial sum of entry e's filter and channel at the
+// q-th tap of its pattern.  `stride`: floats from one of them to the next.
 __global__ __launch_bounds__(256) void grad_weight_gather_kernel(const float* __restrict__ ws, const uint32_t* __restrict__ canon,
-                                                                 float* __restrict__ dw4, long long n4, int S, int tiles,
-                                                                 int tiles_c) {
+                                                                 float* __restrict__ dw4, long long n4, int parts,
+                                                                 size_t stride, int tiles_c) {
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
     const long long e = i >> 2;
@@ -322,8 +329,8 @@ __global__ __launch_bounds__(256) void grad_weight_gather_kernel(const float* __
     float sum = 0.f;
     if (t >= 0) {
         const int tile = (int)(f / kTile) * tiles_c + (int)(c / kTile);
-        const size_t at = ((size_t)tile * 9 + t) * (kTile * kTile) + (f % kTile) * kTile + (c % kTile);
-        for (int s = 0; s < S; ++s) sum += ws[(size_t)s * tiles * (9 * kTile * kTile) + at];
+        const float* at = ws + (size_t)tile * (9 * kTile * kTile) + part_index(t, f % kTile, c % kTile);
+        for (int s = 0; s < parts; ++s, at += stride) sum += *at;
     }
     dw4[i] = sum;
 }
@@ -336,12 +343,12 @@ bool plan(const pconv_packed* p, int N, int H, int W, GwParams* out, int* lw, si
     g.ncb = (Gp + 7) / 8;
     g.Gc = (Gp + g.ncb - 1) / g.ncb;
     g.NJ = g.Gc + 2;
-    // rows per chunk: even (a K step is two items), as many as the pieces per thread allow, evened out over the image
-    int R = 2;
-    while (R + 2 <= 254 && ((R + 4) * g.Gc * 64 + 255) / 256 <= kMaxX && ((R + 2) * g.NJ * 64 + 255) / 256 <= kMaxD) R += 2;
-    if (((R + 2) * g.Gc * 64 + 255) / 256 > kMaxX || (R * g.NJ * 64 + 255) / 256 > kMaxD) return false;
+    // rows per chunk: as many as two chunks leave room for in LDS, evened out over the image; a K step is two items, so
+    // rows x groups is even
+    const int even = g.Gc % 2 ? 2 : 1;
+    int R = (kMaxSlots - 2 * g.Gc) / (g.Gc + g.NJ) / even * even;
     int nrb = (H + R - 1) / R;
-    R = std::min(R, ((H + nrb - 1) / nrb + 1) / 2 * 2);
+    R = ((H + nrb - 1) / nrb + even - 1) / even * even;
     nrb = (H + R - 1) / R;
     g.R = R;
     g.nrb = nrb;
@@ -352,15 +359,16 @@ bool plan(const pconv_packed* p, int N, int H, int W, GwParams* out, int* lw, si
     g.tiles = g.tiles_c * ((p->F + kTile - 1) / kTile);
     const int cus = compute_units();
     g.S = (int)std::max<long long>(1, std::min<long long>(chunks, (cus + g.tiles - 1) / g.tiles));
-    g.npx = ((R + 2) * g.Gc * 64 + 255) / 256;
-    g.npd = (R * g.NJ * 64 + 255) / 256;
+    g.div_Gc = make_fastdiv((unsigned)g.Gc);
+    g.div_NJ = make_fastdiv((unsigned)g.NJ);
+    g.slots_x = (R + 2) * g.Gc;
+    g.slots = g.slots_x + R * g.NJ;
     const unsigned long long ximg = (unsigned long long)p->C * H * W * 2ull, dimg = (unsigned long long)p->F * H * W * 2ull;
     if (ximg >= 0x7FFFFFFFull || dimg >= 0x7FFFFFFFull) return false;
     g.x_img_bytes = (unsigned)ximg;
     g.dy_img_bytes = (unsigned)dimg;
     *lw = W % 8 == 0 ? 8 : W % 4 == 0 ? 4 : W % 2 == 0 ? 2 : 1;
-    *lds = (size_t)(R * g.NJ + (R + 2) * g.Gc) * kPitch + (size_t)R * g.NJ * kPitchE;
-    if (*lds > 160 * 1024) return false;
+    *lds = 2 * (size_t)g.slots * kPitch + 64 * 16;
     *ws_floats = (size_t)g.S * g.tiles * 9 * kTile * kTile;
     *out = g;
     return true;
@@ -420,33 +428,31 @@ extern "C" int pconv_conv3x3_grad_weight(const void* x, const void* dy, const pc
     g.N = N;
     if (N == 0) g.chunks = 0;          // (no pixels: the workgroups write zeros, the gather adds them)
     const dim3 grid((unsigned)(g.tiles * g.S));
-#define PCONV_GW_CASE(LWv)                                                                                              \
-    if (lw == LWv) {                                                                                                    \
-        auto kern = grad_weight_kernel<LWv>;                                                                            \
-        if (lds > 64 * 1024)                                                                                            \
-            PCONV_HIP(hipFuncSetAttribute((const void*)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));    \
-        hipLaunchKernelGGL(kern, grid, dim3(256), lds, st, g);                                                          \
+    const int np = std::max(2, (g.slots + 15) / 16) * 4;         // (pieces: rounded up to what the kernel is built for)
+#define PCONV_GW_CASE(LWv, NPv)                                                                                         \
+    if (lw == LWv && np == NPv) {                                                                                       \
+        auto kern = grad_weight_kernel<LWv, NPv>;                                                                       \
+        static LdsAllowance allowed;                                                                                    \
+        if (lds > 64 * 1024) PCONV_HIP(allowed.ask((const void*)kern));                                                 \
+        hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, g);                                                          \
     }
-    PCONV_GW_CASE(8) PCONV_GW_CASE(4) PCONV_GW_CASE(2) PCONV_GW_CASE(1)
+#define PCONV_GW_CASES(NPv) PCONV_GW_CASE(8, NPv) PCONV_GW_CASE(4, NPv) PCONV_GW_CASE(2, NPv) PCONV_GW_CASE(1, NPv)
+    PCONV_GW_CASES(8) PCONV_GW_CASES(12) PCONV_GW_CASES(16) PCONV_GW_CASES(20)
+#undef PCONV_GW_CASES
 #undef PCONV_GW_CASE
     PCONV_HIP(hipGetLastError());
+    // (groups of 16 consecutive parts, so that there are workgroups enough and the parts are read at the rate of a copy;
+    // the groups' sums, 16 at most, the gather adds itself: a second such pass cost a launch, 4.5 us, and saved it 1)
+    const int group = 16, groups = (g.S + group - 1) / group;
+    const size_t part = (size_t)g.tiles * 9 * kTile * kTile;
     if (g.S > 1) {
-        const long long part4 = (long long)g.tiles * 9 * kTile * kTile / 4;
-        // (in two levels where there are many parts, so that the first level has workgroups enough: groups of 16
-        // consecutive parts, then the groups' sums; the order of the additions is fixed either way)
-        const unsigned blocks = (unsigned)((part4 + 255) / 256);
-        const int groups = g.S > 16 ? (g.S + 15) / 16 : 1;
-        if (groups > 1) {
-            hipLaunchKernelGGL(grad_weight_reduce_kernel, dim3(blocks, (unsigned)groups), dim3(256), 0, st,
-                               static_cast<float*>(workspace), part4, part4, g.S, 1, 16);
-            PCONV_HIP(hipGetLastError());
-        }
-        hipLaunchKernelGGL(grad_weight_reduce_kernel, dim3(blocks, 1u), dim3(256), 0, st, static_cast<float*>(workspace),
-                           part4, part4, g.S, groups > 1 ? 16 : 1, groups > 1 ? groups : g.S);
+        const long long part4 = (long long)(part / 4);
+        hipLaunchKernelGGL(grad_weight_reduce_kernel, dim3((unsigned)((part4 + 255) / 256), (unsigned)groups), dim3(256), 0, st,
+                           static_cast<float*>(workspace), part4, part4, g.S, group);
         PCONV_HIP(hipGetLastError());
     }
     hipLaunchKernelGGL(grad_weight_gather_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st,
-                       static_cast<const float*>(workspace), p->d_canon, dw4, n4, 1, g.tiles, g.tiles_c);
+                       static_cast<const float*>(workspace), p->d_canon, dw4, n4, groups, part * group, g.tiles_c);
     PCONV_HIP(hipGetLastError());
     return PCONV_OK;
 }

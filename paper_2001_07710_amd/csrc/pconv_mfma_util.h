@@ -1,4 +1,4 @@
-// Device helpers shared by the matrix-core kernels of libpconv (pconv_mfma.hip, pconv_small.hip).
+// Device helpers shared by the matrix-core kernels of libpconv (pconv_mfma.hip, pconv_small.hip, pconv_backward.hip).
 #pragma once
 
 #include <hip/hip_runtime.h>

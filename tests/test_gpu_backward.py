@@ -88,6 +88,16 @@ GW = [  # N, C, F, H, W
 ]
 
 
+# chunk geometry of the weight gradient (rows x groups of a chunk, chunks per workgroup, groups of parts)
+GW += [
+    (1, 16, 16, 7, 64),       # eight groups, so an odd number of rows per chunk: three, three and one
+    (2, 16, 16, 40, 8),       # one group, rows made even; 16-byte loads
+    (17, 16, 16, 2, 16),      # fewest pieces per staging thread; 17 parts: a group of sixteen and one of one
+    (300, 16, 16, 1, 8),      # more chunks than parts: workgroups of one and of two chunks, one K step each
+    (1, 64, 64, 23, 56),      # a chunk that fills its half of the LDS (78 slots), last row block ragged
+]
+
+
 @pytest.mark.parametrize("case", GW, ids=[f"n{c[0]}c{c[1]}f{c[2]}h{c[3]}w{c[4]}" for c in GW])
 def test_masked_weight_gradient(case):
     N, C, F, H, W = case
