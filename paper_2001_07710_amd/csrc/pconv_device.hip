@@ -48,8 +48,9 @@ void set_hip_error(const char* what, int hip_code) {
 
 // What the host hands over is small: the canonical arrays, the staging orders and the channel lists.  The layouts the
 // kernels read -- the entries once per tiling, the matrix-core weights once per tile height, ten to twenty times as many
-// bytes -- are made from them here, so a layer is one allocation, one copy and four short kernels (256 -> 256 channels,
-// fp16: the copy is 0.5 MB, not 6; with the host side of packing, 5.8 -> 0.7 ms).
+// bytes -- are made from them here, so a layer is one allocation, one copy and two kernels (256 -> 256 channels, fp16: the
+// copy is 0.5 MB, not 6).  The first finds the staging orders and clears the matrix-core weights, the second needs what
+// the first leaves: it brings the entries into those orders and puts the kept weights into the cleared copies.
 
 // The entries of the layer for up to kMaxLayouts staging orders: workgroup (i, l) is one wave that brings the entries of
 // filter position i into the order of layout l, by chunk of staged channels, inside a chunk in canonical order (pattern,
@@ -70,10 +71,8 @@ struct EntryParams {
     int F, C, f16;
     EntryLayout lay[kMaxLayouts];
 };
-__global__ __launch_bounds__(64) void build_entries_kernel(const EntryParams p) {
-    extern __shared__ uint32_t at[];
-    const EntryLayout& l = p.lay[blockIdx.y];
-    const int i = blockIdx.x, lane = threadIdx.x;
+__device__ void build_entries(const EntryParams& p, const EntryLayout& l, int i, uint32_t* at) {
+    const int lane = threadIdx.x;
     const uint32_t e0 = p.row[i], e1 = p.row[i + 1];
     const uint16_t* pos_of = l.pos_of ? l.pos_of + (size_t)(i / l.fg) * p.C : nullptr;
     auto position = [&](uint32_t c) { return pos_of ? (uint32_t)pos_of[c] : c; };
@@ -133,9 +132,11 @@ __global__ __launch_bounds__(64) void build_entries_kernel(const EntryParams p) 
 
 // The staging orders of the layer's tilings (see BalancedLayout), by the same greedy rule and with the same result as the
 // host's find_balanced(): channels by decreasing number of users go, one after the other, into the chunk where the busiest
-// wave stays least busy.  A chain of C short steps per filter group, and the groups are independent: one wave per group
-// and tiling, a lane per chunk (NBLK chunks), a step some 400 clocks of register arithmetic and one minimum over the lanes
-// -- 256 -> 256 channels: 75 us for the five tilings side by side, 210 us on three host threads.
+// wave stays least busy.  A chain of C steps per filter group, and the groups are independent: one wave per group and
+// tiling.  What bounds the kernel is the length of one step, all of it dependent register arithmetic of a single wave, so
+// four lanes share a chunk, four of the 16 waves' loads each: one packed add and maximum per lane, two exchanges inside the
+// quad, and a minimum over 16 quads.  256 -> 256 channels, five tilings side by side: 34 us; with a lane per chunk, which
+// adds and compares four words and takes its minimum over 64 lanes, 75; on three host threads 210.
 struct OrderLayout {
     uint32_t* perm;
     uint16_t* pos_of;
@@ -145,19 +146,26 @@ struct OrderParams {
     const uint32_t* canon;
     const uint32_t* row;
     int F, C;
+    int groups;               // of the tiling with the most; workgroup b < n_order is group b % groups of tiling b / groups
+    unsigned n_order, n_clear;
+    uint4* clear;             // the workgroups behind those clear this
+    size_t clear_quads;
     OrderLayout lay[kMaxLayouts];
 };
-// smallest value of the wave's lanes
-__device__ __forceinline__ uint32_t wave_min(uint32_t v) {
+// smallest value of the wave's lanes, the four of a quad being equal
+__device__ __forceinline__ uint32_t wave_min_of_quads(uint32_t v) {
 #define PCONV_DPP_MIN(ctrl) v = min(v, (uint32_t)__builtin_amdgcn_update_dpp(-1, (int)v, ctrl, 0xF, 0xF, false))
-    PCONV_DPP_MIN(0x111);   // row_shr:1, 2, 4, 8
-    PCONV_DPP_MIN(0x112);
-    PCONV_DPP_MIN(0x114);
+    PCONV_DPP_MIN(0x114);   // row_shr:4, 8
     PCONV_DPP_MIN(0x118);
     PCONV_DPP_MIN(0x142);   // row_bcast:15
     PCONV_DPP_MIN(0x143);   // row_bcast:31
 #undef PCONV_DPP_MIN
     return (uint32_t)__builtin_amdgcn_readlane((int)v, 63);
+}
+// (one wave: the hardware takes its LDS accesses in order, what is left is to hold the compiler to it)
+__device__ __forceinline__ void wave_sync() {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
 }
 // Stable counting sort of the wave's channels: fn(c) -> bin (negative: left out) of fewer than 2^bits bins; at[] are the
 // bins' cursors, place(c, cursor value) is called for every channel, channels ascending inside a bin.
@@ -173,58 +181,116 @@ __device__ __forceinline__ void place_channels(int C, int bits, uint32_t* at, Bi
         }
         const uint32_t rank = (uint32_t)__popcll(same & ((1ull << lane) - 1ull));
         const uint32_t d = k >= 0 ? at[k] + rank : 0u;
-        __syncthreads();
+        wave_sync();
         if (k >= 0) {
             if (rank + 1 == (uint32_t)__popcll(same)) at[k] = d + 1;
             place(c, d);
         }
-        __syncthreads();
+        wave_sync();
     }
 }
-template <int NBLK>
-__global__ __launch_bounds__(64) void order_channels_kernel(const OrderParams p) {
+// The greedy chain: chunk[c] for the n_used channels of order[].  Up to 16 * NB chunks: lane i holds, of chunks i/4,
+// i/4 + 16, ..., the loads of waves 4*(i%4) .. +3 in the bytes of a word.
+template <int NB>
+__device__ __forceinline__ void choose_chunks(const OrderLayout& l, const uint32_t* uses, const uint16_t* order,
+                                              const uint8_t* weight, uint16_t* chunk, uint4* batch, int n_used) {
+    const int lane = threadIdx.x, slot = lane >> 2;
+    constexpr uint32_t kFull = 1u << 31;        // of a chunk's total: takes no more channels (a key is less than 2^30)
+    uint32_t load[NB], total[NB];               // total: kernels << 12 | number of the chunk
+    int room[NB];                               // channels that still fit, less one
+#pragma unroll
+    for (int b = 0; b < NB; ++b) {
+        const int k = b * 16 + slot;
+        load[b] = 0u;
+        total[b] = (uint32_t)k | (k < l.nch ? 0u : kFull);
+        room[b] = (1 << l.cc_shift) - 1;
+    }
+    // 64 channels at a time: lane i holds the i-th one's number and weight; the words of kernels per wave go through LDS,
+    // from where a lane has its quarter of the next eight channels' at hand before it needs them
+    const uint32_t* const quarter = reinterpret_cast<const uint32_t*>(batch) + (lane & 3);
+    for (int r0 = 0; r0 < n_used; r0 += 64) {
+        const bool there = r0 + lane < n_used;
+        const uint32_t mine = there ? order[r0 + lane] : 0u, my_weight = there ? (uint32_t)weight[mine] << 12 : 0u;
+        uint32_t my_chunk = 0;
+        wave_sync();
+        batch[lane] = reinterpret_cast<const uint4*>(uses)[mine];
+        wave_sync();
+        auto step = [&](uint32_t u, int i) {
+            const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)my_weight, i);
+            uint32_t key = ~0u;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
+                const uint32_t v = load[b] + u;
+                const ushort2v m = __builtin_elementwise_max(__builtin_bit_cast(ushort2v, v & 0x00FF00FFu),
+                                                             __builtin_bit_cast(ushort2v, v >> 8 & 0x00FF00FFu));
+                uint32_t most = max((uint32_t)m.x, (uint32_t)m.y);
+                most = max(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0xB1, 0xF, 0xF, false));  // lane ^ 1
+                most = max(most, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)most, 0x4E, 0xF, 0xF, false));  // lane ^ 2
+                key = min(key, total[b] + (most << 23));
+            }
+            const uint32_t best = wave_min_of_quads(key) & 0xFFFu;
+#pragma unroll
+            for (int b = 0; b < NB; ++b) {
+                const bool hit = best == (uint32_t)(b * 16 + slot);
+                load[b] += hit ? u : 0u;
+                room[b] -= hit ? 1 : 0;
+                total[b] = (total[b] + (hit ? wt : 0u)) | ((uint32_t)room[b] & kFull);
+            }
+            my_chunk = lane == i ? best : my_chunk;
+        };
+        const int count = min(64, n_used - r0);
+        int i = 0;
+        for (; i + 8 <= count; i += 8) {
+            uint32_t u[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) u[k] = quarter[(i + k) * 4];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) step(u[k], i + k);
+        }
+        for (; i < count; ++i) step(quarter[i * 4], i);
+        if (there) chunk[mine] = (uint16_t)my_chunk;
+    }
+}
+__global__ __launch_bounds__(256) void order_channels_kernel(const OrderParams p) {
     extern __shared__ __align__(16) unsigned char order_lds[];
-    const OrderLayout& l = p.lay[blockIdx.y];
-    const int g = blockIdx.x, lane = threadIdx.x, C = p.C;
+    const int tid = threadIdx.x, lane = tid & 63, C = p.C;
+    if (blockIdx.x >= p.n_order) {
+        for (size_t i = (size_t)(blockIdx.x - p.n_order) * 256 + tid; i < p.clear_quads; i += (size_t)p.n_clear * 256)
+            p.clear[i] = uint4{0u, 0u, 0u, 0u};
+        return;
+    }
+    const OrderLayout& l = p.lay[blockIdx.x / p.groups];
+    const int g = blockIdx.x % p.groups;
     if (g >= l.groups) return;
-    uint32_t* const uses = reinterpret_cast<uint32_t*>(order_lds);              // [C][16] bytes: kernels per wave
+    uint4* const batch = reinterpret_cast<uint4*>(order_lds);                   // [64] the channels under way
+    uint32_t* const uses = reinterpret_cast<uint32_t*>(batch + 64);             // [C][16] bytes: kernels per wave
     uint16_t* const order = reinterpret_cast<uint16_t*>(uses + (size_t)C * 4);  // [C]
     uint16_t* const chunk = order + C;                                          // [C]
     uint8_t* const weight = reinterpret_cast<uint8_t*>(chunk + C);              // [C]
-    uint32_t* const at = reinterpret_cast<uint32_t*>(order_lds + ((size_t)C * 21 + 15) / 16 * 16);    // [max(64, nch)]
+    uint32_t* const at = reinterpret_cast<uint32_t*>(order_lds + 1024 + ((size_t)C * 21 + 15) / 16 * 16);    // [max(64, nch)]
     const int npos = l.nch << l.cc_shift;
-    for (int i = lane; i < C * 4; i += 64) uses[i] = 0u;
-    for (int i = lane; i < npos; i += 64) l.perm[(size_t)g * npos + i] = kNoChannel;
-    const int i0 = g * l.fg, i1 = min(p.F, i0 + l.fg);
-    // (all entries of the group in one run, eight loads at a time, an entry's filter by bisection: filter by filter this was
-    // half the kernel, one trip to memory after the other)
-    if (lane <= i1 - i0) at[lane] = p.row[i0 + lane];                           // (at most 33 rows)
+    for (int i = tid; i < C * 4; i += 256) uses[i] = 0u;
+    for (int i = tid; i < npos; i += 256) l.perm[(size_t)g * npos + i] = kNoChannel;
+    if (tid < 64) at[tid] = 0u;
     __syncthreads();
-    const uint32_t e0 = at[0], e1 = at[i1 - i0];
-    for (uint32_t first = e0; first < e1; first += 64 * 8) {
-        uint32_t cm[8];
+    // counting, by all four waves: eight lanes per filter (32 of them at most), eight loads of each under way.  (By one wave
+    // over the group's entries in one run, every entry's filter found by bisection, it took as long as the chain.)
+    const int row = g * l.fg + (tid >> 3);
+    if (row < min(p.F, (g + 1) * l.fg)) {
+        const int w = (tid >> 3) % l.fw;
+        const uint32_t e1 = p.row[row + 1];
+        for (uint32_t first = p.row[row] + (tid & 7); first < e1; first += 64) {
+            uint32_t cm[8];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const uint32_t e = first + k * 64 + lane;
-            cm[k] = e < e1 ? p.canon[2 * (size_t)e + 1] : 0u;
-        }
+            for (int k = 0; k < 8; ++k) cm[k] = first + k * 8 < e1 ? p.canon[2 * (size_t)(first + k * 8) + 1] : 0u;
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const uint32_t e = first + k * 64 + lane;
-            if (e >= e1) continue;
-            int lo = 0, hi = i1 - i0;                                           // at[lo] <= e < at[hi]
-            while (hi - lo > 1) {
-                const int mid = (lo + hi) >> 1;
-                if (at[mid] <= e) lo = mid; else hi = mid;
-            }
-            const int w = lo % l.fw;
-            atomicAdd(&uses[(cm[k] & 0xFFFFu) * 4 + (w >> 2)], 1u << (w & 3) * 8);
+            for (int k = 0; k < 8; ++k)
+                if (first + k * 8 < e1) atomicAdd(&uses[(cm[k] & 0xFFFFu) * 4 + (w >> 2)], 1u << (w & 3) * 8);
         }
     }
     __syncthreads();
-    at[lane] = 0u;
-    __syncthreads();
-    for (int c = lane; c < C; c += 64) {
+    for (int c = tid; c < C; c += 256) {
         uint32_t n = 0;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -235,6 +301,7 @@ __global__ __launch_bounds__(64) void order_channels_kernel(const OrderParams p)
         atomicAdd(&at[32 - n], 1u);
     }
     __syncthreads();
+    if (tid >= 64) return;                                                      // the rest is one wave's
     {   // bins are 32 - weight: most users first
         uint32_t incl = lane <= 32 ? at[lane] : 0u;
         const uint32_t own = incl;
@@ -243,70 +310,25 @@ __global__ __launch_bounds__(64) void order_channels_kernel(const OrderParams p)
             const uint32_t o = __shfl_up(incl, d);
             if (lane >= d) incl += o;
         }
-        __syncthreads();
+        wave_sync();
         at[lane] = incl - own;
     }
-    __syncthreads();
+    wave_sync();
     const int n_used = (int)at[32];                                             // (where the unused ones begin)
     place_channels(C, 6, at, [&](int c) { return weight[c] ? 32 - (int)weight[c] : -1; },
                    [&](int c, uint32_t d) { order[d] = (uint16_t)c; });
-    // the chunks: kernels per wave in bytes, and users << 12 | number of the chunk
-    uint32_t load[NBLK][4], total[NBLK], room[NBLK];
-#pragma unroll
-    for (int b = 0; b < NBLK; ++b) {
-        const int k = b * 64 + lane;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) load[b][q] = 0u;
-        total[b] = (uint32_t)k;
-        room[b] = k < l.nch ? 1u << l.cc_shift : 0u;
-    }
-    __syncthreads();
-    // 64 channels at a time: lane i holds the i-th one's numbers, from where they are broadcast as scalars (from LDS, each
-    // step would wait for two dependent reads)
-    for (int r0 = 0; r0 < n_used; r0 += 64) {
-        const bool there = r0 + lane < n_used;
-        const uint32_t mine = there ? order[r0 + lane] : 0u, my_weight = there ? (uint32_t)weight[mine] << 12 : 0u;
-        uint32_t my_uses[4], my_chunk = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) my_uses[q] = there ? uses[mine * 4 + q] : 0u;
-        const int count = min(64, n_used - r0);
-        for (int i = 0; i < count; ++i) {
-            uint32_t u[4];
-#pragma unroll
-            for (int q = 0; q < 4; ++q) u[q] = (uint32_t)__builtin_amdgcn_readlane((int)my_uses[q], i);
-            const uint32_t wt = (uint32_t)__builtin_amdgcn_readlane((int)my_weight, i);
-            uint32_t key = ~0u;
-#pragma unroll
-            for (int b = 0; b < NBLK; ++b) {
-                typedef unsigned short ushort2v __attribute__((ext_vector_type(2)));
-                ushort2v m[4];                                                  // maxima of the 16 bytes, in halves
-#pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const uint32_t v = load[b][q] + u[q];
-                    m[q] = __builtin_elementwise_max(__builtin_bit_cast(ushort2v, v & 0x00FF00FFu),
-                                                     __builtin_bit_cast(ushort2v, v >> 8 & 0x00FF00FFu));
-                }
-                const ushort2v m2 = __builtin_elementwise_max(__builtin_elementwise_max(m[0], m[1]), __builtin_elementwise_max(m[2], m[3]));
-                const uint32_t most = max((uint32_t)m2.x, (uint32_t)m2.y);
-                key = min(key, room[b] ? total[b] + (most << 23) : ~0u);
-            }
-            const uint32_t best = wave_min(key) & 0xFFFu;
-#pragma unroll
-            for (int b = 0; b < NBLK; ++b) {
-                const bool hit = best == (uint32_t)(b * 64 + lane);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) load[b][q] += hit ? u[q] : 0u;
-                total[b] += hit ? wt : 0u;
-                room[b] -= hit ? 1u : 0u;
-            }
-            my_chunk = lane == i ? best : my_chunk;
-        }
-        if (there) chunk[mine] = (uint16_t)my_chunk;
-    }
-    __syncthreads();
+    if (l.nch <= 16)
+        choose_chunks<1>(l, uses, order, weight, chunk, batch, n_used);
+    else if (l.nch <= 32)
+        choose_chunks<2>(l, uses, order, weight, chunk, batch, n_used);
+    else if (l.nch <= 64)
+        choose_chunks<4>(l, uses, order, weight, chunk, batch, n_used);
+    else
+        choose_chunks<8>(l, uses, order, weight, chunk, batch, n_used);
+    wave_sync();
     // positions: the channels of a chunk in ascending order
     for (int k = lane; k < l.nch; k += 64) at[k] = (uint32_t)k << l.cc_shift;
-    __syncthreads();
+    wave_sync();
     int bits = 0;
     while ((1 << bits) < l.nch) ++bits;
     place_channels(C, bits, at, [&](int ch) { return weight[ch] ? (int)chunk[ch] : -1; },
@@ -316,7 +338,7 @@ __global__ __launch_bounds__(64) void order_channels_kernel(const OrderParams p)
                    });
 }
 
-// The matrix-core weights of the layer (see MfmaWeights), cleared beforehand: one thread per kept kernel and copy.
+// The matrix-core weights of the layer (see MfmaWeights), cleared beforehand: one thread per kept kernel e and copy.
 struct ScatterCopy {
     uint16_t* w;
     const uint16_t* pos_of;   // null: no channel lists
@@ -331,10 +353,7 @@ struct ScatterParams {
     int C;
     ScatterCopy copy[4];
 };
-__global__ __launch_bounds__(256) void scatter_weights_kernel(const ScatterParams p) {
-    const unsigned e = blockIdx.x * 256u + threadIdx.x;
-    if (e >= p.n_kept) return;
-    const ScatterCopy& m = p.copy[blockIdx.y];
+__device__ __forceinline__ void scatter_weights(const ScatterParams& p, const ScatterCopy& m, unsigned e) {
     const uint32_t f = p.canon[2 * (size_t)e], cm = p.canon[2 * (size_t)e + 1], mask = cm >> 16;
     uint32_t c = cm & 0xFFFFu;
     const uint32_t tile = f / (uint32_t)m.mt, fl = f - tile * (uint32_t)m.mt;
@@ -355,8 +374,17 @@ __global__ __launch_bounds__(256) void scatter_weights_kernel(const ScatterParam
     }
 }
 
-__global__ __launch_bounds__(256) void clear_kernel(uint4* p, size_t n) {
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) p[i] = uint4{0u, 0u, 0u, 0u};
+// Everything that needs the staging orders and the cleared weights, in workgroups of one wave.  gridDim.x is F; the first
+// `n_layouts` rows of the grid build the entries of a layout each, behind them come `rows` for every copy of the weights.
+__global__ __launch_bounds__(64) void build_layouts_kernel(const EntryParams p, const ScatterParams s, int n_layouts, int rows) {
+    extern __shared__ uint32_t layouts_at[];
+    const int y = blockIdx.y - n_layouts;
+    if (y < 0) {
+        build_entries(p, p.lay[blockIdx.y], (int)blockIdx.x, layouts_at);
+    } else {
+        const unsigned long long e = ((unsigned long long)(y % rows) * gridDim.x + blockIdx.x) * 64 + threadIdx.x;
+        if (e < s.n_kept) scatter_weights(s, s.copy[y / rows], (unsigned)e);
+    }
 }
 
 int upload_packed(pconv_packed* p) {
@@ -438,54 +466,50 @@ int upload_packed(pconv_packed* p) {
                          reinterpret_cast<uint16_t*>(base + at_pos[t]), log2_of(b.cc), b.n_chunks, b.fw * b.nf};
         most_chunks = std::max(most_chunks, b.n_chunks);
     }
-    if (order_here && nl) {
-        OrderParams op{};
-        op.canon = ep.canon;
-        op.row = ep.row;
-        op.F = p->F;
-        op.C = p->C;
-        int most_groups = 0;
-        for (size_t t = 0; t < nl; ++t) {
-            const BalancedLayout& b = p->balanced[t];
-            op.lay[t] = {reinterpret_cast<uint32_t*>(base + at_perm[t]), reinterpret_cast<uint16_t*>(base + at_pos[t]), b.fw,
-                         b.fw * b.nf, log2_of(b.cc), b.n_chunks, b.n_groups};
-            most_groups = std::max(most_groups, b.n_groups);
-        }
-        const size_t lds = ((size_t)p->C * 21 + 15) / 16 * 16 + (size_t)std::max(64, most_chunks) * sizeof(uint32_t);
-        const dim3 grid((unsigned)most_groups, (unsigned)nl);
-        if (most_chunks <= 64)
-            hipLaunchKernelGGL(order_channels_kernel<1>, grid, dim3(64), lds, 0, op);
-        else
-            hipLaunchKernelGGL(order_channels_kernel<2>, grid, dim3(64), lds, 0, op);
+    OrderParams op{};
+    op.canon = ep.canon;
+    op.row = ep.row;
+    op.F = p->F;
+    op.C = p->C;
+    op.groups = 1;
+    for (size_t t = 0; t < nl && order_here; ++t) {
+        const BalancedLayout& b = p->balanced[t];
+        op.lay[t] = {reinterpret_cast<uint32_t*>(base + at_perm[t]), reinterpret_cast<uint16_t*>(base + at_pos[t]), b.fw,
+                     b.fw * b.nf, log2_of(b.cc), b.n_chunks, b.n_groups};
+        op.groups = std::max(op.groups, b.n_groups);
+        op.n_order = (unsigned)(t + 1);
+    }
+    op.n_order *= (unsigned)op.groups;
+    op.clear = reinterpret_cast<uint4*>(base + copied);
+    op.clear_quads = (cleared - copied) / 16;
+    op.n_clear = (unsigned)std::min<size_t>((op.clear_quads + 255) / 256, 1024);
+    if (op.n_order + op.n_clear) {
+        const size_t lds = op.n_order ? 1024 + ((size_t)p->C * 21 + 15) / 16 * 16 + (size_t)std::max(64, most_chunks) * sizeof(uint32_t) : 0;
+        hipLaunchKernelGGL(order_channels_kernel, dim3(op.n_order + op.n_clear), dim3(256), lds, 0, op);
         PCONV_HIP(hipGetLastError());
     }
-    hipLaunchKernelGGL(build_entries_kernel, dim3((unsigned)p->F, (unsigned)(nl + 1)), dim3(64), most_chunks * sizeof(uint32_t), 0, ep);
+    ScatterParams sp{};
+    sp.canon = ep.canon;
+    sp.w4 = reinterpret_cast<uint16_t*>(base + at_w4);
+    sp.n_kept = (unsigned)n;
+    sp.C = p->C;
+    for (size_t t = 0; t < nm; ++t) {
+        const MfmaWeights& m = p->mfma[t];
+        ScatterCopy& c = sp.copy[t];
+        c.w = reinterpret_cast<uint16_t*>(base + at_mw[t]);
+        c.pos_of = m.clist.empty() ? nullptr : reinterpret_cast<uint16_t*>(base + at_mpos[t]);
+        c.tinfo = m.clist.empty() ? nullptr : reinterpret_cast<uint32_t*>(base + at_tinfo[t]);
+        c.mt = m.mt;
+        c.n_cblocks = m.n_cblocks;
+        c.nt = m.n_taps;
+        c.groups = m.groups;
+        c.group_channels = p->C / m.groups;
+        std::memcpy(c.slot_of, m.slot_of, sizeof(m.slot_of));
+    }
+    const int rows = (int)std::max<size_t>(1, (n + (size_t)p->F * 64 - 1) / ((size_t)p->F * 64));
+    hipLaunchKernelGGL(build_layouts_kernel, dim3((unsigned)p->F, (unsigned)(nl + 1 + (n ? nm * rows : 0))), dim3(64),
+                       most_chunks * sizeof(uint32_t), 0, ep, sp, (int)nl + 1, rows);
     PCONV_HIP(hipGetLastError());
-    if (nm) {
-        const size_t quads = (cleared - copied) / 16;
-        hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<size_t>((quads + 255) / 256, 4096)), dim3(256), 0, 0,
-                           reinterpret_cast<uint4*>(base + copied), quads);
-        ScatterParams sp{};
-        sp.canon = ep.canon;
-        sp.w4 = reinterpret_cast<uint16_t*>(base + at_w4);
-        sp.n_kept = (unsigned)n;
-        sp.C = p->C;
-        for (size_t t = 0; t < nm; ++t) {
-            const MfmaWeights& m = p->mfma[t];
-            ScatterCopy& c = sp.copy[t];
-            c.w = reinterpret_cast<uint16_t*>(base + at_mw[t]);
-            c.pos_of = m.clist.empty() ? nullptr : reinterpret_cast<uint16_t*>(base + at_mpos[t]);
-            c.tinfo = m.clist.empty() ? nullptr : reinterpret_cast<uint32_t*>(base + at_tinfo[t]);
-            c.mt = m.mt;
-            c.n_cblocks = m.n_cblocks;
-            c.nt = m.n_taps;
-            c.groups = m.groups;
-            c.group_channels = p->C / m.groups;
-            std::memcpy(c.slot_of, m.slot_of, sizeof(m.slot_of));
-        }
-        if (n) hipLaunchKernelGGL(scatter_weights_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)nm), dim3(256), 0, 0, sp);
-        PCONV_HIP(hipGetLastError());
-    }
     PCONV_HIP(hipStreamSynchronize(0));
 
     p->d_canon = reinterpret_cast<uint32_t*>(base + at_canon);

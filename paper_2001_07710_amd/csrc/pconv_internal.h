@@ -42,7 +42,7 @@ struct BalancedLayout {
     // two vectors here stay empty, and on the host by find_balanced() for larger ones and for host-only handles
     std::vector<uint32_t> perm;      // [n_groups][n_chunks*cc]: channel staged at each position, 0xFFFFFFFF = none
     std::vector<uint16_t> pos_of;    // [n_groups][C]: position of a channel in its group's order (channels it stages)
-    // on the device only, made there from the canonical arrays and pos_of (build_entries_kernel):
+    // on the device only, made there from the canonical arrays and pos_of (build_layouts_kernel):
     DevEntry* d_ent = nullptr;       // [n_kept]; DevEntry::c is the POSITION of the channel in the staging order
     uint32_t* d_eptr = nullptr;      // [F*n_chunks + 1]: entries of (filter position i, chunk k)
     uint32_t* d_perm = nullptr;
@@ -63,7 +63,7 @@ struct MfmaWeights {
     uint8_t taps[9] = {};             // tap index t = 3*ky + kx of every tap slot, ascending
     int8_t slot_of[9] = {};           // tap slot of every tap, -1: the tap does not occur
     size_t elements = 0;              // of w
-    void* d_w = nullptr;              // on the device only, made there from the canonical arrays (scatter_weights_kernel)
+    void* d_w = nullptr;              // on the device only, made there from the canonical arrays (build_layouts_kernel)
     size_t bytes() const { return elements * sizeof(uint16_t); }
     // Channel lists (empty: every filter tile takes the channels in their own order, n_cblocks blocks each).  Where
     // the filters of a tile keep only part of the input channels -- connectivity pruning that removes the same

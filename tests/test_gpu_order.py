@@ -1,6 +1,6 @@
 """The staging orders that the vector kernels read are found on the device; the rule is the host's, to the last tie: element for
-element the same, for every tiling, on both sides of the channel counts where the device's search takes a second block of
-chunks, with groups that are not full and filters that keep nothing."""
+element the same, for every tiling, on both sides of the channel counts where the device's search takes two, four or eight
+blocks of chunks, with groups that are not full and filters that keep nothing."""
 import numpy as np
 import pytest
 
@@ -14,6 +14,7 @@ NONE = 0xFFFFFFFF
 
 
 @pytest.mark.parametrize("C,F,keep", [(1, 1, 1.0), (3, 70, 1.0), (31, 16, 0.5), (100, 72, 0.4), (256, 33, 0.3), (1008, 47, 0.2),
+                                      (257, 17, 0.3), (512, 40, 0.25), (513, 16, 0.3),
                                       (1024, 16, 0.3), (1025, 40, 0.25), (1040, 33, 0.02), (2048, 65, 0.3), (2049, 32, 0.1)])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 def test_the_orders_on_the_device_are_the_hosts(C, F, keep, dtype):
