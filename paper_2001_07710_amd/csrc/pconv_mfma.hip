@@ -140,7 +140,7 @@ struct TileGeo {
 // descriptor and arrive as zeros, which is the padding): no staging registers, no byte permutes, no LDS writes.  The
 // epilogue turns 32 pixels at a time through a wave-private LDS window so that whole runs of a pixel's filters are
 // stored.
-template <int AF, int BF, int WM, int WN, int LW, int KI, bool FULL, bool NHWC>
+template <int AF, int BF, int WM, int WN, int LW, int KI, bool FULL, bool NHWC, bool PIPE = false>
 __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 1) void mfma_conv_kernel(const MfmaParams p) {
     constexpr int kItems = NHWC ? 0 : KI;
     constexpr int kAL = NHWC ? 12 : 0;      // NHWC: wave-wide activation loads per wave and block, at most
@@ -167,7 +167,9 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
         w0 = (late ? (nwg >> 1) : 0u) + (blockIdx.x & 7u) * half_per + (blockIdx.x >> 4);
     }
     // (a work item is a tile, or one of the KS parts of a tile's channel blocks; the parts of a tile are neighbours)
-    const unsigned ntiles = (unsigned)p.tiles_n * (unsigned)p.tiles_m * (unsigned)p.KS;
+    const int KS = PIPE ? 1 : p.KS;
+    const unsigned* const clist = PIPE ? nullptr : p.clist;
+    const unsigned ntiles = (unsigned)p.tiles_n * (unsigned)p.tiles_m * (unsigned)KS;
     if (w0 >= ntiles) return;
     if (late)
         for (int i = 0; i < p.stagger; ++i) __builtin_amdgcn_s_sleep(32);      // 2048 clocks each
@@ -179,19 +181,19 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
 
     auto geometry = [&](unsigned item) {
         TileGeo g;
-        const unsigned T = fastdiv(item, p.div_KS);
+        const unsigned T = PIPE ? item : fastdiv(item, p.div_KS);
         g.tile = (int)T;
-        g.split = (int)(item - T * (unsigned)p.KS);
+        g.split = (int)(item - T * (unsigned)KS);
         const unsigned tn = fastdiv(T, p.div_tiles_m);
         g.tm = (int)(T - tn * (unsigned)p.tiles_m);
         int blocks = p.CB;
         g.wb = g.tm * p.CB;
-        if (p.clist) {
+        if (clist) {
             blocks = (int)__builtin_amdgcn_readfirstlane(p.tinfo[2 * g.tm]);
             g.wb = (int)__builtin_amdgcn_readfirstlane(p.tinfo[2 * g.tm + 1]);
         }
-        g.cb0 = g.split * blocks / p.KS;
-        g.cb1 = (g.split + 1) * blocks / p.KS;
+        g.cb0 = g.split * blocks / KS;
+        g.cb1 = (g.split + 1) * blocks / KS;
         const int R0 = (int)tn * p.R;
         g.Rv = min(p.R, p.N * Ho - R0);
         g.n0 = (int)fastdiv((unsigned)R0, p.div_Ho);
@@ -280,7 +282,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                 }
             }
         }
-        const int slots_all = g.used_slots * p.groups;         // (with channel ranges: the row slots of every range)
+        const int slots_all = g.used_slots * (PIPE ? 1 : p.groups);         // (with channel ranges: the row slots of every range)
         const float inv_slots = 1.0f / (float)slots_all;
 #pragma unroll
         for (int i = 0; i < kItems; ++i) {
@@ -295,7 +297,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
             const unsigned it = (unsigned)(ltid + i * HALF);
             const unsigned gg = (unsigned)(((float)it + 0.5f) * inv_slots);
             unsigned sl = it - gg * (unsigned)slots_all, range = 0;
-            while (sl >= (unsigned)g.used_slots) {              // (at most groups - 1 times)
+            while (!PIPE && sl >= (unsigned)g.used_slots) {              // (at most groups - 1 times)
                 sl -= (unsigned)g.used_slots;
                 ++range;
             }
@@ -342,7 +344,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
 #pragma unroll
         for (int ch = 0; ch < 8; ++ch) {
             chans[ch] = cb * 16 + kbs * 8 + ch;
-            if (p.clist) chans[ch] = (int)__builtin_amdgcn_readfirstlane(p.clist[(stage_wb + cb) * 16 + kbs * 8 + ch]);
+            if (clist) chans[ch] = (int)__builtin_amdgcn_readfirstlane(clist[(stage_wb + cb) * 16 + kbs * 8 + ch]);
         }
     };
     auto issue_one = [&](int cb, int buf, int j) {
@@ -728,6 +730,147 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
         return true;
     };
 
+    // ---- PIPE: all K steps as one sequence.  The loop below ends every block with a wait for the next block's loads, their
+    // interleaving, LDS writes and a barrier, and begins it with the latency of its first operands, all of it exposed where
+    // one wave has the SIMD to itself (1,650 clocks of 5,900 a block).  Here the activations are loaded two blocks ahead: a
+    // block's first taps ask for the next block's weights, which go to LDS by themselves; taps 5 and on write the next
+    // block's activations, a block's time after they were asked for, and ask for those of the block after into the same
+    // registers.  The barrier stands in front of the last tap, whose operands are in registers by then, and the next
+    // block's first operands are read behind it.  Tiles of two blocks or more, without channel lists or splits (the host
+    // sees to it), so the block two ahead is in this tile or the next.
+    if constexpr (PIPE) {
+        unsigned T = w0, Tl = w0;                               // the tile that is multiplied, and that is loaded
+        TileGeo gc = geometry(T), gl = gc;
+        int lcb = 0, bias_l = 0;
+        bool l_on = true;
+        stage_descriptors(gl);
+        stage_bias(gl.tm, 0);
+        auto load_act = [&](int j) {
+            const int i = j >> 3;
+            const unsigned chan = (unsigned)(lcb * 16 + kbs * 8 + (j & 7));
+            const bool there = chan < (unsigned)p.C;
+            const __amdgpu_buffer_rsrc_t xr =
+                make_rsrc(reinterpret_cast<const void*>(((unsigned long long)xb_hi << 32) | xb_lo), x_records);
+            stg[i][j & 7].load(xr, there && l_on ? goff[i] : kInvalid, there ? chan * p.chan_bytes : 0u);
+        };
+        int wblock = gl.wb;                                     // the next block's weights, and where its activations go
+        bool w_on = true;
+        int to[KI];
+        // (no branch between the MFMAs: behind the last block the loads are outside the descriptor and leave zeros, and a
+        // piece that is not there is written to the wave's window, which nothing else uses meanwhile)
+        static_assert(9 * 2 * MT == WPIECES * NTH, "nine taps' weights are whole loads");
+        auto load_weights = [&](int buf, int j) {
+            const int first = (j * NW + wave) * 64;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_ptr)(ldsA + buf * p.a_bytes + first * 16), 16,
+                                                     w_on ? (first + lane) * 16 : (int)kInvalid, wblock * p.a_bytes, 0, 0);
+        };
+        const int spare = (int)(reinterpret_cast<unsigned char*>(win_fixed) - lds) + lane * 16;
+        auto place_act = [&](int buf) {
+#pragma unroll
+            for (int i = 0; i < KI; ++i)
+                to[i] = loff[i] < 0 ? spare : (int)(ldsB - lds) + buf * 2 * p.plane_bytes + loff[i];
+        };
+        auto write_act = [&](int i, int px) {
+            uint4v v;
+            v.x = interleave(stg[i][0].dword(px >> 1), stg[i][1].dword(px >> 1), px & 1);
+            v.y = interleave(stg[i][2].dword(px >> 1), stg[i][3].dword(px >> 1), px & 1);
+            v.z = interleave(stg[i][4].dword(px >> 1), stg[i][5].dword(px >> 1), px & 1);
+            v.w = interleave(stg[i][6].dword(px >> 1), stg[i][7].dword(px >> 1), px & 1);
+            *reinterpret_cast<uint4v*>(lds + to[i] + px * 16) = v;
+        };
+#pragma unroll
+        for (int j = 0; j < 8 * KI; ++j) load_act(j);
+#pragma unroll
+        for (int j = 0; j < WPIECES; ++j) load_weights(0, j);
+        place_act(0);
+#pragma unroll
+        for (int i = 0; i < KI; ++i)
+#pragma unroll
+            for (int px = 0; px < LW; ++px) write_act(i, px);
+        lcb = 1;
+        __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
+#pragma unroll
+        for (int j = 0; j < 8 * KI; ++j) load_act(j);
+        __syncthreads();
+        compute_descriptors(gc);
+        start_acc(gc, 0);
+        int buf = 0, bias_slot = 0;
+        half8 fa[2][AF], fb[BF];
+#pragma unroll
+        for (int af = 0; af < AF; ++af) fa[0][af] = *reinterpret_cast<const half8*>(ldsA + aoff + af * 512);
+#pragma unroll
+        for (int bf = 0; bf < BF; ++bf) fb[bf] = *reinterpret_cast<const half8*>(ldsB + boff[bf] + p.tap_off[0]);
+        for (;;) {
+            for (int cb = 0; cb < p.CB; ++cb) {
+                // the block that follows this one is the one loaded last; on to the one behind that
+                const int nbuf = buf ^ 1;
+                wblock = gl.wb + lcb;
+                w_on = l_on;
+                place_act(nbuf);
+                if (++lcb == p.CB) {
+                    lcb = 0;
+                    Tl += nwg;
+                    l_on = Tl < ntiles;
+                    if (l_on) {
+                        gl = geometry(Tl);
+                        stage_descriptors(gl);
+                        bias_l = bias_l == 2 ? 0 : bias_l + 1;
+                        stage_bias(gl.tm, bias_l);
+                    }
+                }
+                int here[BF];                                    // this block's pixels; boff is the next block's from here on
+#pragma unroll
+                for (int bf = 0; bf < BF; ++bf) here[bf] = boff[bf];
+                // (the last block told from the others where the compiler cannot see it: it would split it off the loop, in a
+                // second copy whose accumulators lie in other registers -- 450 moves a tile)
+                int next_cb = cb + 1;
+                asm volatile("" : "+s"(next_cb));
+                if (next_cb == p.CB) compute_descriptors(gl);
+                constexpr int WRITES = KI * LW, LOADS = 8 * KI;
+#pragma unroll
+                for (int ts = 0; ts < 9; ++ts) {
+                    if (ts == 8) {
+                        // (the next block's weights have arrived: behind them only its successor's activations are under way)
+                        __builtin_amdgcn_sched_barrier(0);
+                        __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15) | (LOADS >> 4) << 14);
+                        __syncthreads();
+                    }
+                    const unsigned char* const a = ldsA + (ts < 8 ? buf : nbuf) * p.a_bytes + aoff + (ts < 8 ? ts + 1 : 0) * 2 * MT * 16;
+                    const unsigned char* const b = ldsB + (ts < 8 ? buf : nbuf) * 2 * p.plane_bytes + p.tap_off[ts < 8 ? ts + 1 : 0];
+#pragma unroll
+                    for (int bf = 0; bf < BF; ++bf) {
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int af = 0; af < AF; ++af)
+                            acc[af][bf] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[ts & 1][af], fb[bf], acc[af][bf], 0, 0, 0);
+                        fb[bf] = *reinterpret_cast<const half8*>(b + (ts < 8 ? here[bf] : boff[bf]));
+                        if (bf < AF) fa[(ts + 1) & 1][bf] = *reinterpret_cast<const half8*>(a + bf * 512);
+                        const int at = ts * BF + bf;             // (tap, activation operand) group
+#pragma unroll
+                        for (int j = 0; j < WPIECES; ++j)
+                            if (j * 4 * BF / WPIECES == at) load_weights(nbuf, j);
+#pragma unroll
+                        for (int j = 0; j < WRITES; ++j)
+                            if (5 * BF + j * 9 / WRITES == at) write_act(j / LW, j % LW);
+#pragma unroll
+                        for (int j = 0; j < LOADS; ++j)
+                            if (5 * BF + 9 + j * (2 * BF + BF - 9 - 1) / LOADS == at) load_act(j);
+                    }
+                }
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int af = 0; af < AF; ++af) fa[0][af] = fa[1][af];
+                buf = nbuf;
+            }
+            epilogue(gc, 0);
+            T += nwg;
+            if (T >= ntiles) return;
+            gc = gl;
+            bias_slot = bias_slot == 2 ? 0 : bias_slot + 1;
+            start_acc(gc, bias_slot);
+        }
+    }
+
     // ---- the sequence of (tile, channel block) pairs
     unsigned T = w0;
     TileGeo gc = geometry(T);
@@ -967,11 +1110,14 @@ int stagger_steps(const MfmaParams& p, int grid, long long ntiles, int walk, dou
 template <int AF, int BF, int WM, int WN>
 int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, double block_us, hipStream_t st) {
     const bool full = p.nt == 9;
+    // (one sequence of K steps where the tile shape fills the register file: with two workgroups on a compute unit each
+    // covers the other's waits.  It looks two blocks ahead, into the next tile at most)
+    const bool pipe = AF == 2 && full && !p.nhwc && p.KS == 1 && !p.clist && p.CB >= 2;
     const long long ntiles = (long long)p.tiles_n * p.tiles_m * p.KS;
-#define PCONV_MFMA_CASE1(LWv, KIv, FULLv) PCONV_MFMA_CASE2(LWv, KIv, FULLv, false)
-#define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv)                                                                \
-    if (lw == LWv && ki == KIv && full == FULLv && (p.nhwc != 0) == NHWCv) {                                    \
-        auto kern = mfma_conv_kernel<AF, BF, WM, WN, LWv, KIv, FULLv, NHWCv>;                                   \
+#define PCONV_MFMA_CASE1(LWv, KIv, FULLv) PCONV_MFMA_CASE2(LWv, KIv, FULLv, false, false)
+#define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv, PIPEv)                                                                \
+    if (lw == LWv && ki == KIv && full == FULLv && (p.nhwc != 0) == NHWCv && pipe == PIPEv) {                                    \
+        auto kern = mfma_conv_kernel<AF, BF, WM, WN, LWv, KIv, FULLv, NHWCv, PIPEv>;                                   \
         static LdsAllowance allowed;                                                                            \
         static std::atomic<unsigned> resident{0};                                                               \
         if (lds > 64 * 1024) PCONV_HIP(allowed.ask((const void*)kern));                                         \
@@ -983,12 +1129,20 @@ int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, doub
         return PCONV_OK;                                                                                        \
     }
 #define PCONV_MFMA_CASE(LWv, KIv) PCONV_MFMA_CASE1(LWv, KIv, true) PCONV_MFMA_CASE1(LWv, KIv, false)
+    if constexpr (AF == 2) {
+        PCONV_MFMA_CASE2(8, 1, true, false, true)
+#ifndef PCONV_ONLY_ONE
+        PCONV_MFMA_CASE2(8, 2, true, false, true) PCONV_MFMA_CASE2(4, 2, true, false, true)
+        PCONV_MFMA_CASE2(4, 3, true, false, true) PCONV_MFMA_CASE2(2, 3, true, false, true)
+        PCONV_MFMA_CASE2(1, 3, true, false, true)
+#endif
+    }
 #ifdef PCONV_ONLY_ONE
     PCONV_MFMA_CASE1(8, 1, true)
 #else
     PCONV_MFMA_CASE(8, 1) PCONV_MFMA_CASE(8, 2) PCONV_MFMA_CASE(4, 2) PCONV_MFMA_CASE(4, 3) PCONV_MFMA_CASE(2, 3)
     PCONV_MFMA_CASE(1, 3) PCONV_MFMA_CASE1(2, 4, false) PCONV_MFMA_CASE1(1, 7, false)
-    PCONV_MFMA_CASE2(8, 1, true, true) PCONV_MFMA_CASE2(8, 1, false, true)
+    PCONV_MFMA_CASE2(8, 1, true, true, false) PCONV_MFMA_CASE2(8, 1, false, true, false)
 #endif
 #undef PCONV_MFMA_CASE
 #undef PCONV_MFMA_CASE1

@@ -72,6 +72,25 @@ def test_every_tile_shape(case):
     layer.free()
 
 
+@pytest.mark.parametrize("case", [  # N, C, F, H, W, stride, pad
+    (10, 17, 40, 56, 56, 1, 1),     # 8-pixel loads, two blocks of channels a tile, the second nearly empty
+    (5, 32, 130, 57, 28, 1, 1),     # 4-pixel loads, two tiles of filters
+    (40, 33, 24, 14, 14, 1, 1),     # 2-pixel loads, three blocks
+    (43, 64, 40, 13, 13, 1, 0),     # 1-pixel loads, no padding
+    (9, 48, 33, 64, 224, 1, 1),     # full width
+    (19, 20, 70, 60, 60, 2, 1),     # stride 2
+], ids=lambda c: f"n{c[0]}c{c[1]}f{c[2]}h{c[3]}w{c[4]}s{c[5]}p{c[6]}")
+def test_tiles_in_sequence(case):
+    """The largest tile shape runs the channel blocks of all of a workgroup's tiles as one sequence that looks two blocks
+    ahead: tiles of one row, so that a workgroup has several of them, and of as many rows as fit, the last one ragged."""
+    N, C, F, H, W, stride, pad = case
+    spec = L.LayerSpec(cfg=22, idx=C, name="sequence", N=N, C=C, F=F, H=H, W=W, stride=stride, pad=pad, dtype="f16", K=8,
+                       keep=0.4)
+    layer = GpuLayer(spec)
+    run_forms(layer, L.gen_activations(spec), [dict(kernel=M, mfma_shape=1, rows=r) for r in (1, 2, 0)])
+    layer.free()
+
+
 def test_library_that_leaves_taps_unused():
     """Two patterns over taps {0,1,2,3} and {0,1,2,4}: four of the nine taps carry no weight and are skipped."""
     spec = L.LayerSpec(cfg=21, idx=0, name="taps", N=2, C=24, F=40, H=12, W=20, dtype="f16", K=2, keep=0.5,
