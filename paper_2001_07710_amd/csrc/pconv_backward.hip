@@ -29,7 +29,7 @@
 // loads and LDS reads, take 150 (the clock sinks to 1.95 GHz under them); 512 -> 512 at 28 x 28: 411 -> 258, at 14 x 14 179 -> 110.
 //
 // The pixels are split over S workgroups per tile; each writes its 9 x 64 x 64 partial sums to the workspace, a second
-// kernel adds the S parts in order, and a third gathers the sums of the kept weights into the canonical entry order
+// kernel adds the S parts in order, 16 at a time, and a third adds those sums and gathers the sums of the kept weights into the canonical entry order
 // of the packed layer (deterministic: no atomics).
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
@@ -295,7 +295,7 @@ __device__ __forceinline__ int part_index(int t, int f, int c) {
     return ((t * 4 + (f >> 5) * 2 + (c >> 5)) * 32 + (f & 31)) * 32 + (c & 31);
 }
 
-// The S parts of every tile added into part 0, in order: a dense pass, four neighbouring sums per thread, so the parts
+// The S parts of every tile added up in groups of `cnt`, in order, each into its group's first part: a dense pass, four neighbouring sums per thread, so the parts
 // are read at the rate of a copy.  (Summed inside the gather below instead, one scattered 4-byte read per part and kept
 // weight, the parts of a layer with a single tile -- 256 of them -- took 90 us.)
 __global__ __launch_bounds__(256) void grad_weight_reduce_kernel(float* __restrict__ ws, long long n4, long long part4, int S,

@@ -737,7 +737,8 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
     // block's activations, a block's time after they were asked for, and ask for those of the block after into the same
     // registers.  The barrier stands in front of the last tap, whose operands are in registers by then, and the next
     // block's first operands are read behind it.  Tiles of two blocks or more, without channel lists or splits (the host
-    // sees to it), so the block two ahead is in this tile or the next.
+    // sees to it), so the block two ahead is in this tile or the next.  256 -> 256 channels at 56 x 56, batch 64: 183 -> 170
+    // us.  (Channel-minor, where the activations go to LDS by themselves and one block ahead only: 196 -> 208 us, not kept.)
     if constexpr (PIPE) {
         unsigned T = w0, Tl = w0;                               // the tile that is multiplied, and that is loaded
         TileGeo gc = geometry(T), gl = gc;
