@@ -61,7 +61,7 @@ int pconv_conv3x3_grad_input(const void* dy, void* dx, const pconv_packed* wpt, 
  *   dw4   out, device, float[n_kept][4]: entry e, slot q = gradient of the weight that the canonical form
  *         (pconv_packed_export) holds at w4[e][q]; fp32 accumulation over all pixels, not rounded to fp16
  *   workspace, workspace_bytes   device scratch of at least pconv_conv3x3_grad_weight_workspace() bytes (partial
- *         sums of the workgroups that share a tile); the call allocates nothing
+ *         sums of the workgroups that share a tile), aligned like a float; the call allocates nothing
  * The result is deterministic (fixed summation order).  Asynchronous on `stream`.
  * PCONV_EUNSUPPORTED: fp32 storage, stride 2, padding 0, an image of 2 GiB or more, or a handle that is not a layer
  * from pconv_pack.  PCONV_EINVAL: null or odd pointers, a workspace that is too small.  PCONV_ESTATE: no device copy

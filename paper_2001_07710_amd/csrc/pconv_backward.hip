@@ -59,6 +59,10 @@ constexpr int kMaxSlots = 78;                 // (row, group) slots of a chunk, 
                                               // 64 / 256 of them 16-byte pieces per staging thread, 20 at most
 constexpr int kTile = 64;
 
+// Four neighbouring sums of the workspace.  The caller's pointer need be aligned no better than a float's, and the type says
+// so; the compiler still moves 16 bytes at once, which the hardware does from any address.
+typedef float sums4 __attribute__((ext_vector_type(4), aligned(4)));
+
 struct GwParams {
     const unsigned char* x;
     const unsigned char* dy;
@@ -273,7 +277,7 @@ __global__ __launch_bounds__(512, 2) void grad_weight_kernel(const GwParams p) {
     constexpr int kRow = 36;
     static_assert(4 * 32 * kRow * 4 <= 2 * 10 * kPitch, "a chunk has ten slots at least");
     float* const turn = reinterpret_cast<float*>(lds) + wave * 32 * kRow;
-    float4v* const out = reinterpret_cast<float4v*>(p.ws + ((size_t)split * p.tiles + tile) * (9 * kTile * kTile));
+    sums4* const out = reinterpret_cast<sums4*>(p.ws + ((size_t)split * p.tiles + tile) * (9 * kTile * kTile));
 #pragma unroll
     for (int t = 0; t < 9; ++t) {
         // (lanes read what other lanes of the wave wrote; the hardware takes a wave's LDS accesses in order)
@@ -303,7 +307,7 @@ __global__ __launch_bounds__(256) void grad_weight_reduce_kernel(float* __restri
     // group blockIdx.y: parts group*cnt + s, s < cnt, as far as there are parts, added into the group's first
     const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
     if (i >= n4) return;
-    float4v* const w4 = reinterpret_cast<float4v*>(ws);
+    sums4* const w4 = reinterpret_cast<sums4*>(ws);
     const long long first = (long long)blockIdx.y * cnt;
     float4v sum = w4[first * part4 + i];
     for (int s = 1; s < cnt && first + s < S; ++s) sum += w4[(first + s) * part4 + i];

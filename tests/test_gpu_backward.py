@@ -56,19 +56,20 @@ def test_input_gradient_through_the_transposed_layer(case):
     layer.free()
 
 
-def _grad_weight(layer, x, dy):
+def _grad_weight(layer, x, dy, ws_shift=0):
+    """The kept weights' gradients; the workspace begins `ws_shift` bytes behind an address that torch aligns."""
     import torch
     s = layer.spec
     d_x, d_dy = torch.from_numpy(x).cuda(), torch.from_numpy(dy).cuda()
     nbytes = pc.conv3x3_grad_weight_workspace(layer.packed, s.N, s.H, s.W)
-    ws = torch.empty(max(nbytes, 16) + 4096, dtype=torch.uint8, device="cuda")
-    ws[nbytes:] = 0x5A
+    ws = torch.full((nbytes + ws_shift + 4096,), 0x5A, dtype=torch.uint8, device="cuda")
+    before, ws = ws[:ws_shift], ws[ws_shift:]
     nk = layer.packed.n_kept
     out = torch.full((nk * 4 + 64,), -777.0, dtype=torch.float32, device="cuda")
     pc.conv3x3_grad_weight(d_x, d_dy, layer.packed, out, s.N, s.H, s.W, 1, 1, ws, nbytes,
                            torch.cuda.current_stream().cuda_stream)
     torch.cuda.synchronize()
-    assert bool((ws[nbytes:] == 0x5A).all()), "write outside the workspace"
+    assert bool((ws[nbytes:] == 0x5A).all()) and bool((before == 0x5A).all()), "write outside the workspace"
     o = out.cpu().numpy()
     assert np.all(o[nk * 4:] == -777.0), "write outside the gradient buffer"
     return o[:nk * 4].reshape(nk, 4)
@@ -113,6 +114,20 @@ def test_masked_weight_gradient(case):
     assert err <= TOL_DW, (case, err)
     again = _grad_weight(layer, x, dy)
     assert got.tobytes() == again.tobytes(), "the weight gradient is not reproducible"
+    layer.free()
+
+
+@pytest.mark.parametrize("ws_shift", [4, 8, 12])
+@pytest.mark.parametrize("N", [1, 20])         # one part, which nothing adds up, and twenty in two groups
+def test_weight_gradient_takes_a_workspace_aligned_like_a_float(N, ws_shift):
+    spec = _spec(60 + N, N, 40, 24, 6, 12, "f16")
+    say("grad_weight workspace", N, ws_shift)
+    layer = GpuLayer(spec, use_bias=False)
+    x, dy = L.gen_activations(spec), _gauss((N, 24, 6, 12), 41, np.float16)
+    got = _grad_weight(layer, x, dy, ws_shift)
+    ref = oracle.pack_canonical(oracle.conv3x3_grad_weight(x, dy, 1, 1), layer.pid, layer.mask, layer.lib)[3]
+    assert rel_err(got, ref) <= TOL_DW
+    assert got.tobytes() == _grad_weight(layer, x, dy).tobytes()
     layer.free()
 
 
