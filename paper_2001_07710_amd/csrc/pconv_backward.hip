@@ -121,7 +121,8 @@ __global__ __launch_bounds__(512, 2) void grad_weight_kernel(const GwParams p) {
         // (Loads and LDS writes are unconditional -- a piece that is not there is a load outside the descriptor and a
         // write behind the two chunks -- because a branch around them makes the compiler wait for every load at once.)
         const int ltid = (int)threadIdx.x - 256, first = (wave - 4) * 64;
-        int to[NP], rel[NP], rc[NP];              // rc: relative row + 1 | (relative column + 8) << 16
+        int to[NP], rc[NP];                       // rc: relative row + 1 | (relative column + 8) << 16
+        uint32_t rel[NP];
 #pragma unroll
         for (int i = 0; i < NP; ++i) {
             const int id = ltid + i * 256;
@@ -133,8 +134,11 @@ __global__ __launch_bounds__(512, 2) void grad_weight_kernel(const GwParams p) {
             const int row = is_x ? r - 1 : r, col = is_x ? g * 8 : (g - 1) * 8;
             const bool there = id < p.slots * 64;
             to[i] = there ? ((is_x ? 0 : p.slots_x) + r * groups + g) * kPitch + c * 16 : 2 * buf_bytes + lane * 16;
-            rel[i] = (chan * H * W + row * W + col) * 2;
-            rc[i] = there && chan < (is_x ? p.C : p.F) ? (row + 1) | ((col + 8) << 16) : 0x7FFF;     // (a row beyond any image)
+            // (a piece that is not there, or of a filter or channel that is not: its loads lie outside the descriptor in every
+            // chunk, at 2^31 and a pixel's place in one channel's image, which is below 2^31 as the whole image is)
+            const bool read = there && chan < (is_x ? p.C : p.F);
+            rel[i] = (read ? ((uint32_t)chan * (uint32_t)H + (uint32_t)row) * (uint32_t)W * 2u : kInvalid) + (uint32_t)(col * 2);
+            rc[i] = (row + 1) | ((col + 8) << 16);
         }
         uint4v v[NP];
         // One chunk on: piece by piece, what has arrived is written into half `buf` and its register asks for the same piece
@@ -160,7 +164,7 @@ __global__ __launch_bounds__(512, 2) void grad_weight_kernel(const GwParams p) {
                     uint32_t off[8 / LW];
 #pragma unroll
                     for (int u = 0; u < 8 / LW; ++u)
-                        off[u] = row_ok && (unsigned)(col + u * LW) < (unsigned)W ? (uint32_t)(rel[i] + shift + u * LW * 2) : kInvalid;
+                        off[u] = row_ok && (unsigned)(col + u * LW) < (unsigned)W ? rel[i] + (uint32_t)(shift + u * LW * 2) : kInvalid;
                     v[i] = load8<LW>(first_now + i * 256 < p.slots_x * 64 ? xr : dr, off);
                 }
                 __builtin_amdgcn_sched_barrier(0);
