@@ -54,6 +54,7 @@ static int one_layer(int F, int C, int K, double keep, int dtype) {
     std::vector<uint8_t> pid((size_t)F * C), mask((size_t)F * C);
     CHECK(pconv_assign_patterns(w.data(), F, C, lib.data(), K, pid.data()) == PCONV_OK);
     CHECK(pconv_select_connectivity(w.data(), F, C, lib.data(), K, pid.data(), keep, mask.data()) == PCONV_OK);
+    for (size_t i = 0; i < mask.size(); ++i) mask[i] = (uint8_t)(mask[i] ? 1u << i % 8 : 0u);
     std::vector<uint16_t> wh((size_t)F * C * 9);
     for (size_t i = 0; i < wh.size(); ++i) wh[i] = (uint16_t)(0x3000u + (i * 37u) % 0x0800u);   // finite fp16 patterns
     pconv_packed* p = nullptr;
@@ -72,6 +73,15 @@ static int one_layer(int F, int C, int K, double keep, int dtype) {
     std::vector<unsigned char> w4((n_kept + 1) * 4 * (dtype == PCONV_F16 ? 2 : 4));
     CHECK(pconv_packed_export(p, order.data(), ptr.data(), cin.data(), w4.data(), &n_kept) == PCONV_OK);
     CHECK(ptr[(size_t)F * K] == n_kept);
+    // (the kernels of a mask's bytes that are not zero, whatever their bits, each under its pattern, and no others)
+    size_t set = 0;
+    for (uint8_t m : mask) set += m ? 1 : 0;
+    CHECK(set == n_kept);
+    for (size_t g = 0; g < (size_t)F * K; ++g)
+        for (uint32_t e = ptr[g]; e < ptr[g + 1]; ++e) {
+            const size_t fc = (size_t)order[g / K] * C + cin[e];
+            CHECK(mask[fc] && pid[fc] == g % K && (e == ptr[g] || cin[e] > cin[e - 1]));
+        }
     int f2 = 0, c2 = 0, k2 = 0, d2 = 0;
     CHECK(pconv_packed_stats(p, &f2, &c2, &k2, &d2, &n_kept) == PCONV_OK && f2 == F && c2 == C && k2 == K && d2 == dtype);
     double mean = 0, mx = 0;

@@ -10,13 +10,14 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
 @pytest.mark.skipif(shutil.which("g++") is None, reason="no g++")
-def test_host_code_and_oracle_under_asan_and_ubsan(tmp_path):
+@pytest.mark.parametrize("host", [[], ["-U__SSE2__"]], ids=["this", "without_sse2"])
+def test_host_code_and_oracle_under_asan_and_ubsan(tmp_path, host):
     exe = str(tmp_path / "host_sanitize")
     csrc = os.path.join(ROOT, "paper_2001_07710_amd", "csrc")
     common = ["-fsanitize=address,undefined", "-fno-sanitize-recover=all", "-fno-omit-frame-pointer", "-O1", "-g"]
     obj = str(tmp_path / "conv_oracle.o")
     subprocess.run(["gcc", *common, "-c", os.path.join(ROOT, "oracle", "conv_oracle.c"), "-o", obj], check=True)
-    subprocess.run(["g++", "-std=c++17", *common, "-static-libasan", "-static-libubsan", "-ffp-contract=off",
+    subprocess.run(["g++", "-std=c++17", *common, *host, "-static-libasan", "-static-libubsan", "-ffp-contract=off",
                     "-I" + os.path.join(ROOT, "include"), "-I" + csrc,
                     os.path.join(ROOT, "tests", "host_sanitize_main.cpp"), os.path.join(csrc, "pconv_host.cpp"), obj,
                     "-o", exe], check=True)
