@@ -83,7 +83,7 @@ GW = [  # N, C, F, H, W
     (2, 20, 33, 14, 14),      # 4-byte loads
     (1, 24, 16, 6, 224),      # four column blocks
     (2, 8, 8, 5, 130),        # a ragged last column block, 4-byte loads
-    (40, 64, 64, 28, 28),     # more chunks than workgroups per tile: every workgroup walks several
+    (40, 64, 64, 28, 28),     # 160 parts of one chunk each
     (1, 5, 3, 1, 1),          # a single pixel
     (2, 100, 96, 10, 72),     # nine groups: two column blocks of five and four
 ]
@@ -96,8 +96,25 @@ GW += [
     (17, 16, 16, 2, 16),      # fewest pieces per staging thread; 17 parts: a group of sixteen and one of one
     (300, 16, 16, 1, 8),      # more chunks than parts: workgroups of one and of two chunks, one K step each
     (1, 64, 64, 23, 56),      # a chunk that fills its half of the LDS (78 slots), last row block ragged
-    (1, 9, 5, 33000, 8),      # more rows than 15 bits count; filters and channels that are not there beside those that are
+    (1, 9, 5, 33000, 8),      # seven chunks or eight a workgroup; more rows than 15 bits count; filters and channels that are not there beside those that are
 ]
+
+
+# Layers of four tiles, so of 64 parts, whose workgroups walk three chunks or more, one more in some than in others: both
+# halves of the LDS written and read again, registers refilled piece by piece, K steps that run on from chunk to chunk (an
+# odd number of them in a chunk: the two operand sets change places at its end).  Every load width with every number of
+# pieces per staging thread that the kernel is built for (an image of up to 18 rows of one group of columns is a chunk),
+# then wider chunks.  test_host_backward.py holds the table to this.
+GW_SEQUENCE = [(200, 65, 66, H, W) for W in (8, 4, 6, 7) for H in (6, 10, 14, 18)]
+GW_SEQUENCE += [
+    (70, 66, 65, 27, 16),     # two groups, nine rows: nine K steps a chunk; three chunks an image
+    (110, 65, 65, 17, 14),    # the same of two chunks, the last row empty
+    (70, 65, 65, 21, 28),     # four groups, the chunk as large as the LDS takes it
+    (24, 65, 65, 12, 130),    # three column blocks of six groups, the last one ragged
+    (70, 65, 65, 9, 61),      # eight groups, three rows
+    (40, 65, 65, 23, 56),     # seven groups
+]
+GW += GW_SEQUENCE
 
 
 @pytest.mark.parametrize("case", GW, ids=[f"n{c[0]}c{c[1]}f{c[2]}h{c[3]}w{c[4]}" for c in GW])

@@ -124,3 +124,42 @@ def test_argument_checks():
     assert lib.pconv_conv1x1(one, one, p.handle, None, 1, 8, 8, 1, 0, None) == pc.ESTATE     # not a 1x1 layer
     for h in (par, ph, p):
         h.free()
+
+
+# ---- what the GPU tests of the weight gradient hold, from the workspace the library asks for: 9 x 64 x 64 floats per part
+# and tile, parts as many as chunks or, on the chip's 256 compute units (also what the library takes where there is no GPU),
+# as fill it once
+
+def _grad_weight_chunks(F, C, N, H, W):
+    """Parts per tile, chunks per part at least, K steps per chunk and pieces per staging thread."""
+    def parts(F, C, N):
+        w, pid, _ = _layer(F, C, np.float16)
+        p = pc.pack(w, LIB8, pid, np.ones((F, C), np.uint8), pc.PACK_HOST_ONLY)
+        size = pc.conv3x3_grad_weight_workspace(p, N, H, W)
+        p.free()
+        tiles = -(-F // 64) * -(-C // 64)
+        assert size % (tiles * 9 * 64 * 64 * 4) == 0
+        return size // (tiles * 9 * 64 * 64 * 4)
+    per_image = parts(1, 1, 1)
+    assert per_image < 256                     # (otherwise that is the parts and not the chunks)
+    col_blocks = -(-W // 64)
+    groups = -(-(-(-W // 8)) // col_blocks)
+    assert per_image % col_blocks == 0
+    rows = -(-H // (per_image // col_blocks))
+    rows += rows * groups % 2                  # (a K step is two groups of a row)
+    slots = (rows + 2) * groups + rows * (groups + 2)
+    S = parts(F, C, N)
+    return S, N * per_image // S, rows * groups // 2, max(2, -(-slots // 16)) * 4
+
+
+def test_table_of_the_weight_gradient_walks_sequences_of_chunks():
+    from test_gpu_backward import GW_SEQUENCE
+    forms, odd = set(), 0
+    for N, C, F, H, W in GW_SEQUENCE:
+        S, chunks, steps, pieces = _grad_weight_chunks(F, C, N, H, W)
+        assert S == 64 and chunks >= 3, (N, C, F, H, W)
+        width = 8 if W % 8 == 0 else 4 if W % 4 == 0 else 2 if W % 2 == 0 else 1
+        forms.add((width, pieces))
+        odd += steps % 2
+    assert forms == {(w, n) for w in (8, 4, 2, 1) for n in (8, 12, 16, 20)}
+    assert odd >= 16
