@@ -91,6 +91,31 @@ def test_tiles_in_sequence(case):
     layer.free()
 
 
+# The same with five tiles or more for some workgroups, so that the three places for a tile's bias come round, and one case at
+# least for every load width and number of pieces a lane that the kernel is built for (test_host_logic.py holds the table to
+# both): N, C, F, H, W, stride, pad, most rows of a tile
+SEQUENCE = [
+    (145, 17, 8, 57, 56, 1, 1, 0),       # 8-pixel loads, one piece a lane
+    (1030, 33, 8, 32, 32, 2, 1, 16),     # two pieces; three blocks of channels
+    (19, 17, 8, 224, 224, 2, 1, 0),      # two pieces at full width
+    (566, 17, 8, 29, 28, 1, 1, 0),       # 4-pixel loads, two pieces
+    (206, 17, 8, 20, 220, 2, 1, 0),      # three pieces
+    (2345, 17, 8, 14, 14, 1, 1, 0),      # 2-pixel loads
+    (2145, 17, 8, 13, 13, 1, 0, 0),      # 1-pixel loads, no padding
+]
+
+
+@pytest.mark.parametrize("case", SEQUENCE, ids=lambda c: f"n{c[0]}c{c[1]}h{c[3]}w{c[4]}s{c[5]}p{c[6]}")
+def test_many_tiles_in_sequence(case):
+    N, C, F, H, W, stride, pad, rows = case
+    spec = L.LayerSpec(cfg=23, idx=C + W, name="long sequence", N=N, C=C, F=F, H=H, W=W, stride=stride, pad=pad, dtype="f16",
+                       K=8, keep=0.4)
+    layer = GpuLayer(spec)
+    assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF)      # (nine taps: the form is theirs)
+    run_forms(layer, L.gen_activations(spec), [dict(kernel=M, mfma_shape=1, rows=rows)])
+    layer.free()
+
+
 def test_library_that_leaves_taps_unused():
     """Two patterns over taps {0,1,2,3} and {0,1,2,4}: four of the nine taps carry no weight and are skipped."""
     spec = L.LayerSpec(cfg=21, idx=0, name="taps", N=2, C=24, F=40, H=12, W=20, dtype="f16", K=2, keep=0.5,

@@ -270,3 +270,34 @@ def test_parity_form_of_a_stride2_layer_computes_the_same_function(pad, hw):
     assert np.max(np.abs(via - ref)) <= 1e-12 * max(1.0, np.max(np.abs(ref)))
     q.free()
     p.free()
+
+
+def _sequence_form(N, C, F, H, W, stride, pad, rows):
+    """Pixels per load, pieces per lane and tiles of the busiest workgroup of the matrix-core kernel's largest tile (128
+    filters by 448 pixels, 256 threads, one workgroup on each of 256 compute units) for aligned pointers."""
+    Ho, Wo = (H + 2 * pad - 3) // stride + 1, (W + 2 * pad - 3) // stride + 1
+    pitch = W + 2 * pad
+    while stride == 1 and W <= 16 and (pitch - Wo) % 8:
+        pitch += 1
+    most = {8: 2, 4: 3, 2: 3, 1: 3}                    # pieces a lane
+    for R in range(min(448 // Wo, rows or 448, N * Ho), 0, -1):
+        images = 1 if Ho % R == 0 else min(R, (R + Ho - 2) // Ho + 1)
+        slots = (R - images) * stride + 3 * images
+        lds = 2 * 9 * 2 * 128 * 16 + 4 * slots * pitch * 16 + 3 * 128 * 4 + 4 * 4 * (7 * 32 + 16) * 4 + 16
+        if lds > 160 * 1024:
+            continue
+        for width in (8, 4, 2, 1):
+            if W % width == 0 and slots * (W // width) <= most[width] * 128:
+                pieces = -(-slots * (W // width) // 128)
+                tiles = -(-N * Ho // R) * -(-F // 128)
+                return width, max(pieces, {8: 1, 4: 2}.get(width, 3)), -(-tiles // 256)
+
+
+def test_table_of_tiles_in_sequence_holds_every_form():
+    from test_gpu_mfma import SEQUENCE
+    forms = set()
+    for case in SEQUENCE:
+        width, pieces, tiles = _sequence_form(*case)
+        assert tiles >= 5, case
+        forms.add((width, pieces))
+    assert forms == {(8, 1), (8, 2), (4, 2), (4, 3), (2, 3), (1, 3)}
