@@ -126,23 +126,23 @@ struct KernelList {
 inline uint64_t mask_bits(const uint8_t* m, int n) {
     uint8_t padded[64] = {};
     if (n < 64) m = static_cast<const uint8_t*>(std::memcpy(padded, m, (size_t)n));
-    uint64_t set = 0;
+    uint64_t removed = 0;
 #ifdef __SSE2__
     for (int q = 0; q < 4; ++q) {
         const __m128i v = _mm_loadu_si128(reinterpret_cast<const __m128i*>(m + q * 16));
-        set |= (uint64_t)(0xFFFFu & ~(unsigned)_mm_movemask_epi8(_mm_cmpeq_epi8(v, _mm_setzero_si128()))) << (q * 16);
+        removed |= (uint64_t)(unsigned)_mm_movemask_epi8(_mm_cmpeq_epi8(v, _mm_setzero_si128())) << (q * 16);
     }
 #else
     for (int q = 0; q < 8; ++q) {
         uint64_t v = 0;
         for (int i = 0; i < 8; ++i) v |= (uint64_t)m[q * 8 + i] << (i * 8);
-        // bit 7 of every byte that is not zero, then the eight of them side by side in the top byte: byte i's goes there by
+        // bit 7 of every byte that is zero, then the eight of them side by side in the top byte: byte i's goes there by
         // the factor's term 2^(49 - 7 i), and no two products of other terms meet in it
-        v = (((v & 0x7F7F7F7F7F7F7F7Full) + 0x7F7F7F7F7F7F7F7Full) | v) & 0x8080808080808080ull;
-        set |= (v * 0x0002040810204081ull >> 56) << (q * 8);
+        v = ~(((v & 0x7F7F7F7F7F7F7F7Full) + 0x7F7F7F7F7F7F7F7Full) | v) & 0x8080808080808080ull;
+        removed |= (v * 0x0002040810204081ull >> 56) << (q * 8);
     }
 #endif
-    return set;
+    return ~removed;
 }
 
 // From a dense tensor (of any alignment), pattern ids and a mask; false: the pattern id of a kept kernel is K or more.
