@@ -26,11 +26,12 @@
 // others, their neighbours on the SIMDs, nothing but stage: while chunk k is multiplied out of one half of the LDS they
 // write chunk k + 1, whose loads were issued a chunk's time ago, into the other, and issue the loads of chunk k + 2.
 // One barrier per chunk.  128 -> 128 channels at 112 x 112, batch 64: 341 -> 217 us, where the MFMAs alone, without
-// loads and LDS reads, take 150 (the clock sinks to 1.95 GHz under them); 512 -> 512 at 28 x 28: 411 -> 258, at 14 x 14 179 -> 110.
+// loads and LDS reads, take 150 (the clock sinks to 1.95 GHz under them); 512 -> 512 at 28 x 28: 411 -> 258, at 14 x 14
+// 179 -> 110.  256 -> 256 at 56 x 56: matrix cores busy 55 % of the time, LDS 38 % (a third of that bank conflicts).
 //
 // The pixels are split over S workgroups per tile; each writes its 9 x 64 x 64 partial sums to the workspace, a second
-// kernel adds the S parts in order, 16 at a time, and a third adds those sums and gathers the sums of the kept weights into the canonical entry order
-// of the packed layer (deterministic: no atomics).
+// kernel adds the S parts in order, 16 at a time, and a third adds those sums and gathers the sums of the kept weights into
+// the canonical entry order of the packed layer (deterministic: no atomics).
 #include <hip/hip_fp16.h>
 #include <hip/hip_runtime.h>
 
@@ -164,7 +165,8 @@ __global__ __launch_bounds__(512, 2) void grad_weight_kernel(const GwParams p) {
                     uint32_t off[8 / LW];
 #pragma unroll
                     for (int u = 0; u < 8 / LW; ++u)
-                        off[u] = row_ok && (unsigned)(col + u * LW) < (unsigned)W ? rel[i] + (uint32_t)(shift + u * LW * 2) : kInvalid;
+                        off[u] = row_ok && (unsigned)(col + u * LW) < (unsigned)W ? rel[i] + (uint32_t)(shift + u * LW * 2)
+                                                                                  : kInvalid;
                     v[i] = load8<LW>(first_now + i * 256 < p.slots_x * 64 ? xr : dr, off);
                 }
                 __builtin_amdgcn_sched_barrier(0);
@@ -303,8 +305,8 @@ __device__ __forceinline__ int part_index(int t, int f, int c) {
     return ((t * 4 + (f >> 5) * 2 + (c >> 5)) * 32 + (f & 31)) * 32 + (c & 31);
 }
 
-// The S parts of every tile added up in groups of `cnt`, in order, each into its group's first part: a dense pass, four neighbouring sums per thread, so the parts
-// are read at the rate of a copy.  (Summed inside the gather below instead, one scattered 4-byte read per part and kept
+// The S parts of every tile added up in groups of `cnt`, in order, each into its group's first part: a dense pass, four
+// neighbouring sums per thread, so the parts are read at the rate of a copy.  (Summed inside the gather below instead, one scattered 4-byte read per part and kept
 // weight, the parts of a layer with a single tile -- 256 of them -- took 90 us.)
 __global__ __launch_bounds__(256) void grad_weight_reduce_kernel(float* __restrict__ ws, long long n4, long long part4, int S,
                                                                  int cnt) {

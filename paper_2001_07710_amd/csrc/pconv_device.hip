@@ -484,7 +484,8 @@ int upload_packed(pconv_packed* p) {
     op.clear_quads = (cleared - copied) / 16;
     op.n_clear = (unsigned)std::min<size_t>((op.clear_quads + 255) / 256, 1024);
     if (op.n_order + op.n_clear) {
-        const size_t lds = op.n_order ? 1024 + ((size_t)p->C * 21 + 15) / 16 * 16 + (size_t)std::max(64, most_chunks) * sizeof(uint32_t) : 0;
+        const size_t cursors = (size_t)std::max(64, most_chunks) * sizeof(uint32_t);
+        const size_t lds = op.n_order ? 1024 + ((size_t)p->C * 21 + 15) / 16 * 16 + cursors : 0;
         hipLaunchKernelGGL(order_channels_kernel, dim3(op.n_order + op.n_clear), dim3(256), lds, 0, op);
         PCONV_HIP(hipGetLastError());
     }

@@ -133,7 +133,7 @@ struct TileGeo {
 //
 // Workgroups are persistent: workgroup w takes tiles w, w + G, w + 2G, ... and runs the (tile, channel block) pairs of
 // all of them as one sequence, so the first block of the next tile is loaded while the last block of the current one
-// is multiplied, and the stores of a tile drain while the next tile is computed.
+// is multiplied, and the stores of a tile drain while the next tile is computed (but for PIPE, see there).
 // NHWC: activations and outputs are channel-minor in memory.  That is the order the staged activations have in LDS
 // anyway, so they go from memory straight into LDS like the weights (buffer_load ... lds, 16 bytes = 8 channels of one
 // position per lane, 64 consecutive positions per wave-wide load; positions outside the image are loads outside the
@@ -738,7 +738,11 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
     // registers.  The barrier stands in front of the last tap, whose operands are in registers by then, and the next
     // block's first operands are read behind it.  Tiles of two blocks or more, without channel lists or splits (the host
     // sees to it), so the block two ahead is in this tile or the next.  256 -> 256 channels at 56 x 56, batch 64: 183 -> 170
-    // us.  (Channel-minor, where the activations go to LDS by themselves and one block ahead only: 196 -> 208 us, not kept.)
+    // us, on another card 189 -> 180.  (Channel-minor, where the activations go to LDS by themselves and one block ahead only:
+    // 196 -> 208 us, not kept.)
+    // The loop takes all registers there are: 18 to 29 values, the lane number among them, wait in scratch for the epilogue.
+    // Memory returns in order, so the reload at its head waits for the activation loads under way, and the one in front of the
+    // next tile's accumulators for every store of this tile.
     if constexpr (PIPE) {
         unsigned T = w0, Tl = w0;                               // the tile that is multiplied, and that is loaded
         TileGeo gc = geometry(T), gl = gc;
@@ -836,8 +840,9 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                         __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15) | (LOADS >> 4) << 14);
                         __syncthreads();
                     }
-                    const unsigned char* const a = ldsA + (ts < 8 ? buf : nbuf) * p.a_bytes + aoff + (ts < 8 ? ts + 1 : 0) * 2 * MT * 16;
-                    const unsigned char* const b = ldsB + (ts < 8 ? buf : nbuf) * 2 * p.plane_bytes + p.tap_off[ts < 8 ? ts + 1 : 0];
+                    const int of = ts < 8 ? buf : nbuf, next = ts < 8 ? ts + 1 : 0;
+                    const unsigned char* const a = ldsA + of * p.a_bytes + aoff + next * 2 * MT * 16;
+                    const unsigned char* const b = ldsB + of * 2 * p.plane_bytes + p.tap_off[next];
 #pragma unroll
                     for (int bf = 0; bf < BF; ++bf) {
                         __builtin_amdgcn_sched_barrier(0);
@@ -1066,7 +1071,8 @@ __global__ __launch_bounds__(256) void mfma_arrange_kernel(const unsigned short*
 struct Shape {
     int af, bf, wm, wn;
 };
-// measured time of one channel block of one tile with the device full, microseconds, per tile shape
+// measured time of one channel block of one tile with the device full, microseconds, per tile shape (the first of the largest
+// tile's first form: a block of its sequence of K steps takes about 2.2, see stagger_steps)
 const double kBlockUs[kMfmaShapes] = {3.2, 1.7, 1.7, 1.8};
 // tile shapes: (128 filters x 448 pixels), (64 x 448), (128 x 224), (64 x 224).  (64 x 896, four waves side by
 // side, was tried for layers of 64 filters at 224 x 224 and measured no faster than 64 x 448 there; 128 x 512 on
@@ -1096,10 +1102,10 @@ int persistent_grid(const void* kern, int threads, size_t lds, long long ntiles,
     return (int)std::max<long long>(8, std::min<long long>((ntiles + 7) / 8 * 8, at_once));
 }
 
-// Steps of 2048 clocks by which every second workgroup starts late (0: all start together).  Half a tile's time,
-// and only where the late workgroups do not add a round of their own: the last round is at most half full, and they
+// Steps of 2048 clocks by which every second workgroup starts late (0: all start together).  Half a tile's time by
+// kBlockUs (so some six tenths of a tile of the largest shape's sequence of K steps), and only where the late workgroups do not add a round of their own: the last round is at most half full, and they
 // are the ones that sit it out.  (Measured on 128 x 256 channels at 56 x 56, batch 64, 3.5 rounds: 209 -> 198 us;
-// with 7 or 14 full rounds the half tile more costs as much as the smoother stores gain.)
+// with 7 or 14 full rounds the half tile more costs as much as the smoother stores gain; before the sequence of K steps.)
 int stagger_steps(const MfmaParams& p, int grid, long long ntiles, int walk, double block_us) {
     if (walk == 1 || p.KS != 1 || (grid & 15) || ntiles <= grid) return 0;
     const long long rem = ntiles % grid;
@@ -1116,9 +1122,9 @@ int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, doub
     const bool pipe = AF == 2 && full && !p.nhwc && p.KS == 1 && !p.clist && p.CB >= 2;
     const long long ntiles = (long long)p.tiles_n * p.tiles_m * p.KS;
 #define PCONV_MFMA_CASE1(LWv, KIv, FULLv) PCONV_MFMA_CASE2(LWv, KIv, FULLv, false, false)
-#define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv, PIPEv)                                                                \
-    if (lw == LWv && ki == KIv && full == FULLv && (p.nhwc != 0) == NHWCv && pipe == PIPEv) {                                    \
-        auto kern = mfma_conv_kernel<AF, BF, WM, WN, LWv, KIv, FULLv, NHWCv, PIPEv>;                                   \
+#define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv, PIPEv)                                                         \
+    if (lw == LWv && ki == KIv && full == FULLv && (p.nhwc != 0) == NHWCv && pipe == PIPEv) {                   \
+        auto kern = mfma_conv_kernel<AF, BF, WM, WN, LWv, KIv, FULLv, NHWCv, PIPEv>;                            \
         static LdsAllowance allowed;                                                                            \
         static std::atomic<unsigned> resident{0};                                                               \
         if (lds > 64 * 1024) PCONV_HIP(allowed.ask((const void*)kern));                                         \
@@ -1368,6 +1374,9 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
     // (epilogue, descriptors), microseconds, fitted to the nine VGG-16 shapes at batch 64: two workgroups that share
     // a compute unit take turns on its matrix cores, so each one's block lasts longer; rows of fewer than 56 pixels
     // mean narrower loads and stores.
+    // (shape 1 from before its sequence of K steps.  With it, forced, the shape is 4 to 7 % faster than the one chosen on
+    // layers near the border: 115 against 120 us at 64 -> 128 channels, 112 x 112, batch 64, 30.1 against 32.4 at 128 -> 128,
+    // 56 x 56, batch 32; nowhere was a layer moved to a slower kernel by the sequence)
     const bool narrow = a.W < 56;
     double block_us = kBlockUs[shape - 1], tile_us = 8.0;
     if (shape == 1) block_us = narrow ? 2.65 : 2.3;

@@ -96,7 +96,7 @@ GW += [
     (17, 16, 16, 2, 16),      # fewest pieces per staging thread; 17 parts: a group of sixteen and one of one
     (300, 16, 16, 1, 8),      # more chunks than parts: workgroups of one and of two chunks, one K step each
     (1, 64, 64, 23, 56),      # a chunk that fills its half of the LDS (78 slots), last row block ragged
-    (1, 9, 5, 33000, 8),      # seven chunks or eight a workgroup; more rows than 15 bits count; filters and channels that are not there beside those that are
+    (1, 9, 5, 33000, 8),      # seven chunks or eight a workgroup; more rows than 15 bits count, and channels that are not there
 ]
 
 
