@@ -63,6 +63,9 @@ int pconv_conv3x3_grad_input(const void* dy, void* dx, const pconv_packed* wpt, 
  *   workspace, workspace_bytes   device scratch of at least pconv_conv3x3_grad_weight_workspace() bytes (partial
  *         sums of the workgroups that share a tile), aligned like a float; the call allocates nothing
  * The result is deterministic (fixed summation order).  Asynchronous on `stream`.
+ * Non-finite values: an infinity or NaN in a channel of x or a filter of dy reaches the weights of that channel or filter
+ * and no others.  Where it lies in the first or last row or column of an image it makes NaN also of taps whose sums do not
+ * hold it: the kernel multiplies by the zeros that stand for the padding.
  * PCONV_EUNSUPPORTED: fp32 storage, stride 2, padding 0, an image of 2 GiB or more, or a handle that is not a layer
  * from pconv_pack.  PCONV_EINVAL: null or odd pointers, a workspace that is too small.  PCONV_ESTATE: no device copy
  * on the current device.  N = 0 gives zeros.

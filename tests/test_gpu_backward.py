@@ -149,6 +149,24 @@ def test_weight_gradient_takes_a_workspace_aligned_like_a_float(N, ws_shift):
     layer.free()
 
 
+def test_non_finite_values_stay_with_their_channel_and_filter():
+    N, C, F, H, W = 3, 40, 70, 13, 28
+    layer = GpuLayer(_spec(90, N, C, F, H, W, "f16"), use_bias=False)
+    x, dy = L.gen_activations(layer.spec), _gauss((N, F, H, W), 43, np.float16)
+    clean = _grad_weight(layer, x, dy)
+    x[0, 3, 0, 0], x[1, 3, 5, 9], x[2, 17, H - 1, W - 1] = np.inf, -np.inf, np.nan
+    dy[0, 5, 0, W - 1], dy[2, 66, 6, 6] = np.inf, np.nan
+    got = _grad_weight(layer, x, dy)
+    fo, gp, cin, _ = pc.packed_export(layer.packed)
+    f = fo[(np.searchsorted(gp, np.arange(layer.packed.n_kept), side="right") - 1) // layer.spec.K]
+    touched = np.isin(cin, [3, 17]) | np.isin(f, [5, 66])
+    assert touched.any() and got[~touched].tobytes() == clean[~touched].tobytes()
+    G = oracle.conv3x3_grad_weight(x, dy, 1, 1)
+    ref = oracle.pack_canonical(G, layer.pid, layer.mask, layer.lib)[3]
+    assert not np.isfinite(got[~np.isfinite(ref)]).any()
+    layer.free()
+
+
 def test_masked_weight_gradient_at_a_benchmark_shape_on_sampled_weights():
     # 256 -> 256 channels at 56 x 56, batch 64 (config 4's conv3_2): 2e5 pixels per weight
     spec = [s for s in L.config4(8, 0.28, 64) if s.name == "conv3_2"][0]
