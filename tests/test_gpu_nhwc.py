@@ -138,3 +138,20 @@ def test_channel_minor_form_at_benchmark_shapes(name):
     rms = float(np.sqrt(np.mean(ref_first ** 2)))
     assert np.max(np.abs(pts - ref_pts) / np.maximum(np.abs(ref_pts), rms)) <= tol
     layer.free()
+
+
+@pytest.mark.parametrize("shape", [2, 4])
+def test_equal_images_give_equal_outputs(shape):
+    """Every image of the batch is the same, so are its outputs, bit for bit: a store whose data registers are written
+    again before it has read them shows as an image that differs.  Six taps and 64 filters: two workgroups fit a compute
+    unit and keep the path of the stores busy."""
+    spec = L.LayerSpec(cfg=50, idx=70, name="nhwc", N=1, C=16, F=64, H=28, W=28, dtype="f16", K=2, keep=0.5, lib_kind="fixed4")
+    layer = GpuLayer(spec)
+    one = L.gen_activations(spec)
+    x = np.concatenate([one] * 96, axis=0)
+    ref = layer.oracle(one, True)
+    for _ in range(3):
+        y = run_nhwc(layer, x, True, mfma_shape=shape)
+        assert np.array_equal(y, np.broadcast_to(y[:1], y.shape))
+        assert rel_err(y[0], ref[0]) <= TOL["f16"]
+    layer.free()
