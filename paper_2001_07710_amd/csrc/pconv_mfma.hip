@@ -49,6 +49,8 @@
 #include <cmath>
 #include <cstring>
 #include <mutex>
+#include <type_traits>
+#include <utility>
 
 #include "pconv_internal.h"
 #include "pconv_mfma_util.h"
@@ -65,6 +67,21 @@ namespace pconv {
     } while (0)
 
 namespace {
+
+// body(0) ... body(N - 1), each with its number as a constant (a loop that the compiler may not refuse to unroll: registers
+// are numbered by it)
+template <typename Body, int... I>
+__device__ __forceinline__ void each_of(Body&& body, std::integer_sequence<int, I...>) {
+    (body(std::integral_constant<int, I>{}), ...);
+}
+template <int N, typename Body>
+__device__ __forceinline__ void each(Body&& body) {
+    each_of(body, std::make_integer_sequence<int, N>{});
+}
+
+// The sequence of K steps: a wave's window in its epilogue, 32 filters x 64 pixels of fp16, and 8 bytes from one filter to the
+// next against bank conflicts; and behind the windows a place for pieces of the staging that are not there.
+constexpr int kPipePitch = 2 * 32 * 2 + 8, kPipeWindow = 32 * kPipePitch, kPipeSpare = 64 * 16 + 7 * 16;
 
 struct MfmaParams {
     const unsigned char* x;
@@ -87,7 +104,7 @@ struct MfmaParams {
     int a_bytes;            // weights of one channel block: nt * 2 * MT * 16
     int plane_bytes;        // one half (8 channels) of the activations of one block: max_slots * PW * 16
     int bias_off;           // byte offset in LDS of the bias values (three tiles), behind the staging buffers
-    int sw;                 // pixels per store piece: 8, 4, 2 or 1
+    int sw;                 // pixels per store piece: 8, 4, 2 or 1 (PIPE: of the plane, otherwise of a row)
     unsigned long long y_bytes, x_bytes;
     unsigned wq_bytes;
     unsigned chan_bytes;    // H*W*2
@@ -112,8 +129,7 @@ struct MfmaParams {
     unsigned* counters;     // KS > 1: one arrival counter per tile, zero between launches
     int flag_off;           // byte offset in LDS of the word that tells a workgroup's waves whether it arrived last
     FastDiv div_KS;
-    FastDiv div_Wo, div_Ho, div_G, div_cnt_full, div_tiles_m, div_sw_groups;
-    int sw_groups;          // store pieces per output row: Wo / sw
+    FastDiv div_Wo, div_Ho, div_plane, div_cnt_full, div_tiles_m;
 };
 
 // Geometry of one tile (all wave-uniform): the m-tile, and the R consecutive output rows of the batch it covers.
@@ -431,10 +447,22 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
 
     // The accumulators of a tile start at the bias of their filter (accumulator row r of a 32 x 32 block is filter
     // (r/4)*8 + (lane/32)*4 + r%4), or at zero in the workgroups that take a later part of a split tile's channels.
+    // In the sequence of K steps the operands change places: rows are pixels, and a lane's column is its filter.
     float16v acc[AF][BF];
     auto start_acc = [&](const TileGeo& g, int bias_slot) {
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));                         // (computed here, not ahead of everything)
+        if constexpr (PIPE) {
+#pragma unroll
+            for (int af = 0; af < AF; ++af) {
+                const float b = ldsBias[bias_slot * MT + (wm * AF + af) * 32 + (lane_e & 31)];
+#pragma unroll
+                for (int bf = 0; bf < BF; ++bf)
+#pragma unroll
+                    for (int i = 0; i < 16; ++i) acc[af][bf][i] = b;
+            }
+            return;
+        }
         const float4v* const b4 =
             reinterpret_cast<const float4v*>(ldsBias + bias_slot * MT + wm * AF * 32 + (lane_e >> 5) * 4);
 #pragma unroll
@@ -736,43 +764,170 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
     // ---- PIPE: all K steps as one sequence.  The loop below ends every block with a wait for the next block's loads, their
     // interleaving, LDS writes and a barrier, and begins it with the latency of its first operands, all of it exposed where
     // one wave has the SIMD to itself (1,650 clocks of 5,900 a block).  Here the activations are loaded two blocks ahead: a
-    // block's first taps ask for the next block's weights, which go to LDS by themselves; taps 5 and on write the next
-    // block's activations, a block's time after they were asked for, and ask for those of the block after into the same
-    // registers.  The barrier stands in front of the last tap, whose operands are in registers by then, and the next
+    // block's first taps ask for the next block's weights, which go to LDS by themselves; taps 4 to 6 write the next
+    // block's activations, a block's time after they were asked for, and taps 6 and 7 ask for those of the block after into
+    // the same registers.  The barrier stands in front of the last tap, whose operands are in registers by then, and the next
     // block's first operands are read behind it.  Tiles of two blocks or more, without channel lists or splits (the host
-    // sees to it), so the block two ahead is in this tile or the next.  256 -> 256 channels at 56 x 56, batch 64: 183 -> 170
-    // us, on another card 189 -> 180.  (Channel-minor, where the activations go to LDS by themselves and one block ahead only:
-    // 196 -> 208 us, not kept.)
-    // The loop takes all registers there are: 18 to 29 values, the lane number among them, wait in scratch for the epilogue.
-    // Memory returns in order, so the reload at its head waits for the activation loads under way, and the one in front of the
-    // next tile's accumulators for every store of this tile.
+    // sees to it), so the block two ahead is in this tile or the next.
+    // What bounds it: 126 MFMAs of 32 clocks a block; 5,000 clocks measured where the MFMAs alone take 4,210, and per tile
+    // 6,100 for the outputs and 500 for the start of the accumulators (256 -> 256 channels at 56 x 56, batch 64; before the
+    // instructions beside the MFMAs were spread, the taps' addresses left to the instructions and the outputs' way changed
+    // 5,140, 8,400 and 600; 167 -> 158 us, at 128 -> 128, 112 x 112, 180 -> 167).  The clock is 2.0 to 2.15 GHz meanwhile.
+    // (Channel-minor, where the activations go to LDS by themselves and one block ahead only: 196 -> 208 us, not kept.  The
+    // outputs of a tile beside the MFMAs of the next one's first block, one group of pixels after the other: that block
+    // 9,900 clocks, as much as both had taken, not kept.)
     if constexpr (PIPE) {
+        // The lane number once more, as the compiler cannot see through it: what depends on it in the epilogue is computed
+        // there, not ahead of the channel blocks, where it would sit in registers that the multiply loop needs (or in scratch,
+        // whose reload waits for every load and store under way).
+        auto lane_again = [] {
+            unsigned all = ~0u;
+            asm volatile("" : "+s"(all));
+            return (int)__builtin_amdgcn_mbcnt_hi(all, __builtin_amdgcn_mbcnt_lo(all, 0u));
+        };
+
+        // One K step of one operand tile.
+        auto product = [&](half8 weights, half8 pixels, float16v sum) {
+            sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(pixels, weights, sum, 0, 0, 0);
+            // (nothing, but in its place among loads and barriers: an MFMA by itself is free to go anywhere, and has gone to the
+            // end of the block, with the operands of all nine taps in scratch)
+            asm volatile("" : "+a"(sum));
+            return sum;
+        };
+        // fp16 and ReLU, two values at once (as in the epilogue above), read one by one where they are needed: left to the
+        // compiler, whole accumulators move to vector registers ahead of the epilogue, and what lay there moves to scratch.  (The
+        // accumulator that is read first had its last MFMA twelve MFMAs ago: nothing to wait for.)
+        const half2v floor2 = __builtin_bit_cast(half2v, p.relu ? 0u : 0x7E007E00u);
+        auto value = [&](float acc_value) {
+            float f;
+            asm volatile("v_accvgpr_read_b32 %0, %1" : "=v"(f) : "a"(acc_value));
+            return f;
+        };
+        auto pack2 = [&](float a, float b) {
+            const float2v v = {value(a), value(b)};
+            return __builtin_bit_cast(unsigned, __builtin_elementwise_max(__builtin_convertvector(v, half2v), floor2));
+        };
+        // Byte offset of pixel q of a filter's plane, from the tile's first image, and of a filter's plane in an image; outside
+        // the tensor whatever is added, with saturation, to an offset that is outside.  All of it per lane: behind a 16-byte store
+        // whose offset has a scalar part the compiler writes the data registers again at once, in the belief that such a store
+        // has read them by then, and on this chip it has not (some of the first of the four words then were what came next).
+        auto pixel_off = [&](const TileGeo& g, int q) {
+            const unsigned plane = (unsigned)(Ho * Wo), px = (unsigned)(g.oy0 * Wo + q);
+            unsigned o = (px + fastdiv(px, p.div_plane) * ((unsigned)(p.F - 1) * plane)) * 2u;
+            asm volatile("" : "+v"(o));                              // (a select, no branch)
+            return q < g.Rv * Wo ? o : kInvalid;
+        };
+        auto filter_off = [&](int f) {
+            unsigned o = (unsigned)f * (unsigned)(Ho * Wo) * 2u;
+            asm volatile("" : "+v"(o));
+            return f < p.F ? o : kInvalid;
+        };
+        // Outputs leave through a window in LDS of 32 filters x 64 pixels, [filter][pixel], so that neighbouring lanes store
+        // neighbouring pixels, a line of 128 bytes to eight lanes: a lane writes the runs of four pixels of its filter that it
+        // holds, and reads pieces of p.sw pixels, 64 / p.sw lanes to a filter.  No workgroup barrier: the window is the wave's own,
+        // and LDS operations of one wave complete in order, so the next window is written behind the reads of this one.  (Half a
+        // line to four lanes, windows of 32 pixels: 172 us where this takes 169, 128 -> 128 channels at 112 x 112, batch 64.
+        // Stored as the lanes hold them, eight pixels of 32 filters after an exchange between the halves of the wave, every 16
+        // bytes went to another line: 188, and 263 as streaming stores.)
+        // The pixels of a tile are one run of each filter's plane, until the plane ends and the next image's begins, (F - 1)
+        // planes on.
+        constexpr int kStream = 2;     // cache-policy bit "nt", as above: with it 169, without 181
+        auto leave = [&](const TileGeo& g) {
+            unsigned char* const win = lds + p.bias_off + 3 * MT * 4 + wave * kPipeWindow;
+            const int lane_e = lane_again();
+            const unsigned long long y_off = (unsigned long long)g.n0 * p.F * (unsigned)(Ho * Wo) * 2;
+            const unsigned long long y_left = p.y_bytes - y_off, yb = reinterpret_cast<unsigned long long>(p.y) + y_off;
+            const unsigned yb_lo = __builtin_amdgcn_readfirstlane((unsigned)yb);
+            const unsigned yb_hi = __builtin_amdgcn_readfirstlane((unsigned)(yb >> 32));
+            const unsigned y_records = __builtin_amdgcn_readfirstlane(y_left > 0x7FFFFFFFull ? 0x7FFFFFFFu : (unsigned)y_left);
+            const __amdgpu_buffer_rsrc_t yr =
+                make_rsrc(reinterpret_cast<const void*>(((unsigned long long)yb_hi << 32) | yb_lo), y_records);
+            const int fw = g.tm * MT + wm * AF * 32;                 // the wave's first filter
+            constexpr int GB = 2, GROUPS = (BF + GB - 1) / GB;
+            auto write = [&](auto n) {                               // the n-th window: filters af, groups b0 .. of 32 pixels
+                constexpr int af = n % AF, b0 = n / AF * GB;
+                each<(b0 + GB <= BF ? GB : BF - b0) * 4>([&](auto k) {
+                    constexpr int rq = k % 4, b = k / 4;
+                    const float16v& v = acc[af][b0 + b];
+                    *reinterpret_cast<uint2v*>(win + (lane_e & 31) * kPipePitch + (b * 32 + rq * 8 + (lane_e >> 5) * 4) * 2) =
+                        uint2v{pack2(v[rq * 4], v[rq * 4 + 1]), pack2(v[rq * 4 + 2], v[rq * 4 + 3])};
+                });
+            };
+            auto store = [&](auto width) {
+                constexpr int SW = decltype(width)::value;
+                write(std::integral_constant<int, 0>{});
+                unsigned o = 0;
+                each<GROUPS * AF>([&](auto n) {
+                    constexpr int af = n % AF, b0 = n / AF * GB, nb = b0 + GB <= BF ? GB : BF - b0;
+                    constexpr int PX = nb * 32 / SW, ROWS = 64 / PX, STORES = 32 / ROWS;      // lanes to a row of pixels
+                    const int pix = lane_e % PX, row = lane_e / PX, f = fw + af * 32;
+                    if constexpr (af == 0) o = pixel_off(g, (wn * BF + b0) * 32 + pix * SW);
+                    uint2v piece[STORES][SW == 8 ? 2 : 1];
+                    __builtin_amdgcn_wave_barrier();
+                    each<STORES>([&](auto r) {
+                        const unsigned char* const from = win + (r * ROWS + row) * kPipePitch + pix * SW * 2;
+                        if constexpr (SW >= 4) piece[r][0] = *reinterpret_cast<const uint2v*>(from);
+                        if constexpr (SW == 8) piece[r][1] = *reinterpret_cast<const uint2v*>(from + 8);
+                        if constexpr (SW == 2) piece[r][0].x = *reinterpret_cast<const unsigned*>(from);
+                        if constexpr (SW == 1) piece[r][0].x = *reinterpret_cast<const unsigned short*>(from);
+                    });
+                    __builtin_amdgcn_sched_barrier(0);               // (registers: one window at a time)
+                    if constexpr (n + 1 < GROUPS * AF) write(std::integral_constant<int, n + 1>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                    each<STORES>([&](auto r) {
+                        const int at = (int)__builtin_elementwise_add_sat(o, filter_off(f + r * ROWS + row));
+                        const uint2v v = piece[r][0];
+                        if constexpr (SW == 8) {
+                            const uint2v w = piece[r][1];
+                            __builtin_amdgcn_raw_buffer_store_b128(uint4v{v.x, v.y, w.x, w.y}, yr, at, 0, kStream);
+                        }
+                        if constexpr (SW == 4) __builtin_amdgcn_raw_buffer_store_b64(v, yr, at, 0, kStream);
+                        if constexpr (SW == 2) __builtin_amdgcn_raw_buffer_store_b32(v.x, yr, at, 0, kStream);
+                        if constexpr (SW == 1) __builtin_amdgcn_raw_buffer_store_b16((unsigned short)v.x, yr, at, 0, kStream);
+                    });
+                });
+            };
+            if (p.sw == 8)
+                store(std::integral_constant<int, 8>{});
+            else if (p.sw == 4)
+                store(std::integral_constant<int, 4>{});
+            else if (p.sw == 2)
+                store(std::integral_constant<int, 2>{});
+            else
+                store(std::integral_constant<int, 1>{});
+        };
+
         unsigned T = w0, Tl = w0;                               // the tile that is multiplied, and that is loaded
         TileGeo gc = geometry(T), gl = gc;
         int lcb = 0, bias_l = 0;
         bool l_on = true;
         stage_descriptors(gl);
         stage_bias(gl.tm, 0);
+        // (channels beyond C, and blocks behind the last, are loads from a descriptor of no bytes: a scalar to choose, where
+        // an offset outside would be one per lane)
         auto load_act = [&](int j) {
             const int i = j >> 3;
-            const unsigned chan = (unsigned)(lcb * 16 + kbs * 8 + (j & 7));
-            const bool there = chan < (unsigned)p.C;
+            int first = lcb * 16 + kbs * 8;
+            asm volatile("" : "+s"(first));                      // (worked out here, not ahead of the block)
+            const unsigned chan = (unsigned)(first + (j & 7));
+            const bool there = chan < (unsigned)p.C && l_on;
             const __amdgpu_buffer_rsrc_t xr =
-                make_rsrc(reinterpret_cast<const void*>(((unsigned long long)xb_hi << 32) | xb_lo), x_records);
-            stg[i][j & 7].load(xr, there && l_on ? goff[i] : kInvalid, there ? chan * p.chan_bytes : 0u);
+                make_rsrc(reinterpret_cast<const void*>(((unsigned long long)xb_hi << 32) | xb_lo), there ? x_records : 0u);
+            stg[i][j & 7].load(xr, goff[i], there ? chan * p.chan_bytes : 0u);
         };
         int wblock = gl.wb;                                     // the next block's weights, and where its activations go
-        bool w_on = true;
+        const int w_lane = (wave * 64 + lane) * 16;
+        int w_at = w_lane;
         int to[KI];
         // (no branch between the MFMAs: behind the last block the loads are outside the descriptor and leave zeros, and a
-        // piece that is not there is written to the wave's window, which nothing else uses meanwhile)
+        // piece that is not there is written to a place that nothing reads)
         static_assert(9 * 2 * MT == WPIECES * NTH, "nine taps' weights are whole loads");
         auto load_weights = [&](int buf, int j) {
-            const int first = (j * NW + wave) * 64;
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_ptr)(ldsA + buf * p.a_bytes + first * 16), 16,
-                                                     w_on ? (first + lane) * 16 : (int)kInvalid, wblock * p.a_bytes, 0, 0);
+            int soff = wblock * p.a_bytes, to = buf * p.a_bytes + wave * 1024;
+            asm volatile("" : "+s"(soff), "+s"(to));             // (worked out here, not ahead of the block)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_ptr)(ldsA + to + j * NW * 1024), 16, w_at, soff + j * NW * 1024, 0, 0);
         };
-        const int spare = (int)(reinterpret_cast<unsigned char*>(win_fixed) - lds) + lane * 16;
+        const int spare = p.bias_off + 3 * MT * 4 + NW * kPipeWindow + lane * 16;
         auto place_act = [&](int buf) {
 #pragma unroll
             for (int i = 0; i < KI; ++i)
@@ -801,77 +956,85 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
         for (int j = 0; j < 8 * KI; ++j) load_act(j);
         __syncthreads();
         compute_descriptors(gc);
-        start_acc(gc, 0);
         int buf = 0, bias_slot = 0;
+        const int row_bytes = PW * 16;                          // from a tap to the one below it
         half8 fa[2][AF], fb[BF];
+        int from[BF];                                           // where the next operand of each group of pixels is read
 #pragma unroll
         for (int af = 0; af < AF; ++af) fa[0][af] = *reinterpret_cast<const half8*>(ldsA + aoff + af * 512);
 #pragma unroll
-        for (int bf = 0; bf < BF; ++bf) fb[bf] = *reinterpret_cast<const half8*>(ldsB + boff[bf] + p.tap_off[0]);
+        for (int bf = 0; bf < BF; ++bf) {
+            from[bf] = (int)(ldsB - lds) + boff[bf];
+            fb[bf] = *reinterpret_cast<const half8*>(lds + from[bf]);
+        }
+        constexpr int WRITES = KI * LW, LOADS = 8 * KI;
+        // A block begins: the block that follows it is the one loaded last; on to the one behind that.
+        auto advance = [&](int nbuf) {
+            wblock = gl.wb + lcb;
+            w_at = l_on ? w_lane : (int)kInvalid;
+            place_act(nbuf);
+            if (++lcb == p.CB) {
+                lcb = 0;
+                Tl += nwg;
+                l_on = Tl < ntiles;
+                if (l_on) {
+                    gl = geometry(Tl);
+                    stage_descriptors(gl);
+                    bias_l = bias_l == 2 ? 0 : bias_l + 1;
+                    stage_bias(gl.tm, bias_l);
+                }
+            }
+        };
+        // (the next block's weights have arrived: behind them only `younger` loads and stores are under way)
+        auto publish = [&](auto younger) {
+            constexpr int Y = decltype(younger)::value;
+            __builtin_amdgcn_sched_barrier(0);
+            __builtin_amdgcn_s_waitcnt(0x0F70 | (Y & 15) | (Y >> 4) << 14);
+            __syncthreads();
+        };
+        start_acc(gc, 0);
         for (;;) {
             for (int cb = 0; cb < p.CB; ++cb) {
-                // the block that follows this one is the one loaded last; on to the one behind that
                 const int nbuf = buf ^ 1;
-                wblock = gl.wb + lcb;
-                w_on = l_on;
-                place_act(nbuf);
-                if (++lcb == p.CB) {
-                    lcb = 0;
-                    Tl += nwg;
-                    l_on = Tl < ntiles;
-                    if (l_on) {
-                        gl = geometry(Tl);
-                        stage_descriptors(gl);
-                        bias_l = bias_l == 2 ? 0 : bias_l + 1;
-                        stage_bias(gl.tm, bias_l);
-                    }
-                }
-                int here[BF];                                    // this block's pixels; boff is the next block's from here on
-#pragma unroll
-                for (int bf = 0; bf < BF; ++bf) here[bf] = boff[bf];
+                advance(nbuf);
                 // (the last block told from the others where the compiler cannot see it: it would split it off the loop, in a
                 // second copy whose accumulators lie in other registers -- 450 moves a tile)
                 int next_cb = cb + 1;
                 asm volatile("" : "+s"(next_cb));
-                if (next_cb == p.CB) compute_descriptors(gl);
-                constexpr int WRITES = KI * LW, LOADS = 8 * KI;
-#pragma unroll
-                for (int ts = 0; ts < 9; ++ts) {
-                    if (ts == 8) {
-                        // (the next block's weights have arrived: behind them only its successor's activations are under way)
-                        __builtin_amdgcn_sched_barrier(0);
-                        __builtin_amdgcn_s_waitcnt(0x0F70 | (LOADS & 15) | (LOADS >> 4) << 14);
-                        __syncthreads();
-                    }
-                    const int of = ts < 8 ? buf : nbuf, next = ts < 8 ? ts + 1 : 0;
-                    const unsigned char* const a = ldsA + of * p.a_bytes + aoff + next * 2 * MT * 16;
-                    const unsigned char* const b = ldsB + of * 2 * p.plane_bytes + p.tap_off[next];
-#pragma unroll
-                    for (int bf = 0; bf < BF; ++bf) {
-                        __builtin_amdgcn_sched_barrier(0);
-#pragma unroll
-                        for (int af = 0; af < AF; ++af)
-                            acc[af][bf] = __builtin_amdgcn_mfma_f32_32x32x16_f16(fa[ts & 1][af], fb[bf], acc[af][bf], 0, 0, 0);
-                        fb[bf] = *reinterpret_cast<const half8*>(b + (ts < 8 ? here[bf] : boff[bf]));
-                        if (bf < AF) fa[(ts + 1) & 1][bf] = *reinterpret_cast<const half8*>(a + bf * 512);
-                        const int at = ts * BF + bf;             // (tap, activation operand) group
-#pragma unroll
-                        for (int j = 0; j < WPIECES; ++j)
-                            if (j * 4 * BF / WPIECES == at) load_weights(nbuf, j);
-#pragma unroll
-                        for (int j = 0; j < WRITES; ++j)
-                            if (5 * BF + j * 9 / WRITES == at) write_act(j / LW, j % LW);
-#pragma unroll
-                        for (int j = 0; j < LOADS; ++j)
-                            if (5 * BF + 9 + j * (2 * BF + BF - 9 - 1) / LOADS == at) load_act(j);
-                    }
-                }
+                if (next_cb == p.CB) compute_descriptors(gl);   // (boff is the next block's from here on)
+                const int next_b = (int)(ldsB - lds) + nbuf * 2 * p.plane_bytes;
+                constexpr int W0 = 4 * BF, W1 = 6 * BF + 4, L1 = 8 * BF;
+                each<9 * BF>([&](auto at) {                      // (tap, activation operand) group
+                    constexpr int ts = at / BF, bf = at % BF, next = (ts + 1) % 9;
+                    if constexpr (at == 8 * BF) publish(std::integral_constant<int, LOADS>{});
+                    const unsigned char* const a = ldsA + (ts < 8 ? buf : nbuf) * p.a_bytes + aoff + next * 2 * MT * 16;
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[0][bf] = product(fa[ts & 1][0], fb[bf], acc[0][bf]);
+                    // (what does not read this group's operands stands between its MFMAs, the rest behind them: each
+                    // keeps the pipe busy for 32 clocks, time for some six other instructions of the wave)
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (next % 3 == 0) from[bf] = next ? from[bf] + row_bytes : boff[bf] + next_b;
+                    each<WPIECES>([&](auto j) {
+                        if constexpr (j * 4 * BF / WPIECES == at) load_weights(nbuf, j);
+                    });
+                    each<WRITES>([&](auto j) {
+                        if constexpr (W0 + j * (W1 - W0) / WRITES == at) write_act(j / LW, j % LW);
+                    });
+                    each<LOADS>([&](auto j) {
+                        if constexpr (W1 + j * (L1 - W1) / LOADS == at) load_act(j);
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                    acc[1][bf] = product(fa[ts & 1][1], fb[bf], acc[1][bf]);
+                    __builtin_amdgcn_sched_barrier(0);
+                    fb[bf] = *reinterpret_cast<const half8*>(lds + from[bf] + next % 3 * 16);
+                    if constexpr (bf < AF) fa[(ts + 1) & 1][bf] = *reinterpret_cast<const half8*>(a + bf * 512);
+                });
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int af = 0; af < AF; ++af) fa[0][af] = fa[1][af];
                 buf = nbuf;
             }
-            epilogue(gc, 0);
+            leave(gc);
             T += nwg;
             if (T >= ntiles) return;
             gc = gl;
@@ -1084,6 +1247,12 @@ const double kBlockUs[kMfmaShapes] = {3.2, 1.7, 1.7, 1.8};
 // first shape on the 112-, 56- and 28-column layers of VGG-16 at batch 64.)
 const Shape kShapes[kMfmaShapes] = {{2, 7, 2, 2}, {1, 7, 2, 2}, {1, 7, 4, 1}, {1, 7, 2, 1}};
 
+// One sequence of K steps where the tile shape fills the register file: with two workgroups on a compute unit each covers
+// the other's waits.  It looks two blocks ahead, into the next tile at most.
+bool runs_pipe(const MfmaParams& p, int af) {
+    return af == 2 && p.nt == 9 && !p.nhwc && p.KS == 1 && !p.clist && p.CB >= 2;
+}
+
 // Workgroups of the persistent grid: as many as the device holds at once (compute units x workgroups that fit one),
 // no more than there are tiles, a multiple of 8 (one share per XCD).
 int persistent_grid(const void* kern, int threads, size_t lds, long long ntiles, int walk, std::atomic<unsigned>& resident) {
@@ -1119,10 +1288,7 @@ int stagger_steps(const MfmaParams& p, int grid, long long ntiles, int walk, dou
 
 template <int AF, int BF, int WM, int WN>
 int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, double block_us, hipStream_t st) {
-    const bool full = p.nt == 9;
-    // (one sequence of K steps where the tile shape fills the register file: with two workgroups on a compute unit each
-    // covers the other's waits.  It looks two blocks ahead, into the next tile at most)
-    const bool pipe = AF == 2 && full && !p.nhwc && p.KS == 1 && !p.clist && p.CB >= 2;
+    const bool full = p.nt == 9, pipe = runs_pipe(p, AF);
     const long long ntiles = (long long)p.tiles_n * p.tiles_m * p.KS;
 #define PCONV_MFMA_CASE1(LWv, KIv, FULLv) PCONV_MFMA_CASE2(LWv, KIv, FULLv, false, false)
 #define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv, PIPEv)                                                         \
@@ -1181,6 +1347,7 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
     p.tinfo = a.d_tinfo;
     // (channel-minor activations are loaded eight channels at a time as they lie: no channel lists, whole groups)
     if (a.nhwc && (a.d_clist || a.C % 8 || a.F % 8)) return false;
+    p.nhwc = a.nhwc ? 1 : 0;
     p.KS = a.splits < 1 ? 1 : a.splits;
     p.second_pass = (p.KS > 1 && a.second_pass) ? 1 : 0;
     // (every part of a split tile has at least one block: the sequence of (tile, block) pairs has no empty member)
@@ -1247,7 +1414,9 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
         // windows fit the weights' half of a staging buffer (or, where the weights stay, the activations' half): then
         // they live there
         // (channel-minor outputs: 32 pixels x the wave's filters, see epilogue_nhwc)
-        const size_t windows = a.nhwc ? (size_t)(NTH / 64) * 32 * (sh.af * 64 + 8) : (size_t)(NTH / 64) * 4 * (sh.bf * 32 + 16) * 4;
+        const size_t windows = a.nhwc ? (size_t)(NTH / 64) * 32 * (sh.af * 64 + 8)
+                               : runs_pipe(p, sh.af) ? (size_t)(NTH / 64) * kPipeWindow + kPipeSpare
+                                                     : (size_t)(NTH / 64) * 4 * (sh.bf * 32 + 16) * 4;
         p.win_alias = 0;
         if (shares_cu && !a.nhwc) {
             if (p.a_stages == 2 && windows <= (size_t)p.a_bytes) p.win_alias = 1;
@@ -1274,13 +1443,18 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
     p.G = a.nhwc ? 1 : a.W / lw;                  // (channel-minor staging has no pieces of lw pixels)
     const int need_items = (int)(((long long)p.max_slots * p.groups * p.G + NTH / 2 - 1) / (NTH / 2));
     const int ki = a.nhwc ? 1 : lw == 8 ? std::max(need_items, 1) : lw == 4 ? std::max(need_items, 2) : need_items <= 3 ? 3 : lw == 2 ? 4 : 7;
-    p.nhwc = a.nhwc ? 1 : 0;
     p.div_PW = make_fastdiv((unsigned)p.PW);
     p.R = R;
     p.tiles_n = (int)((total_rows + R - 1) / R);
     p.tiles_m = (a.F + MT - 1) / MT;
     p.sw = (a.Wo % 8 == 0 && ya % 16 == 0) ? 8 : (a.Wo % 4 == 0 && ya % 8 == 0) ? 4 : (a.Wo % 2 == 0 && ya % 4 == 0) ? 2 : 1;
-    p.sw_groups = a.Wo / p.sw;
+    // (the sequence of K steps: the pixels of a tile are one run of a filter's plane, or the end of one and the start of the
+    // next image's, so a piece that divides the plane and the tile lies in one plane and is aligned, wherever rows end)
+    if (runs_pipe(p, sh.af)) {
+        p.sw = 1;
+        for (int w = 8; w > 1 && p.sw == 1; w /= 2)
+            if ((long long)R * a.Wo % w == 0 && (long long)a.Ho * a.Wo % w == 0 && ya % (2 * w) == 0) p.sw = w;
+    }
     for (int t = 0; t < p.nt; ++t) p.tap_off[t] = ((a.taps[t] / 3) * p.PW + a.taps[t] % 3) * (a.nhwc ? 32 : 16);
     // (channel ranges in the place of taps: range t lies max_slots row slots behind range t - 1)
     if (p.groups > 1)
@@ -1299,10 +1473,9 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
     p.wq_bytes = (unsigned)wq_bytes;
     p.div_Wo = make_fastdiv((unsigned)a.Wo);
     p.div_Ho = make_fastdiv((unsigned)a.Ho);
-    p.div_G = make_fastdiv((unsigned)p.G);
+    p.div_plane = make_fastdiv((unsigned)(a.Ho * a.Wo));
     p.div_cnt_full = make_fastdiv((unsigned)p.cnt_full);
     p.div_tiles_m = make_fastdiv((unsigned)p.tiles_m);
-    p.div_sw_groups = make_fastdiv((unsigned)p.sw_groups);
     const long long ntiles = (long long)p.tiles_n * p.tiles_m * p.KS;
     if (ntiles > 0x7FFFFFF0) return false;
     // (the parts of one tile in the workspace are addressed with 32-bit offsets)

@@ -116,6 +116,32 @@ def test_many_tiles_in_sequence(case):
     layer.free()
 
 
+# How the outputs of the sequence of K steps leave: pieces of 8, 4, 2 and 1 pixels by what divides the plane and the tile and
+# by the output's address, rows that no piece divides, planes that end inside a tile, filters that end inside a wave's 32.
+STORES = [  # N, C, F, H, W
+    (3, 32, 136, 28, 28),                # a plane of 98 pieces of 8 in rows of 28 pixels
+    (5, 17, 65, 14, 14),                 # pieces of 4, three images to a tile
+    (7, 24, 30, 9, 14),                  # pieces of 2
+    (11, 40, 130, 7, 7),                 # pieces of 1, ten images to a tile
+    (2, 32, 96, 10, 12),                 # a tile that is a multiple of 8 pixels, a last one that is not full
+]
+
+
+@pytest.mark.parametrize("case", STORES, ids=lambda c: f"n{c[0]}f{c[2]}h{c[3]}w{c[4]}")
+def test_pieces_of_the_outputs(case):
+    N, C, F, H, W = case
+    spec = L.LayerSpec(cfg=24, idx=F + W, name="stores", N=N, C=C, F=F, H=H, W=W, dtype="f16", K=8, keep=0.4)
+    layer = GpuLayer(spec)
+    assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF)
+    x = L.gen_activations(spec)
+    ref = layer.oracle(x)
+    for shape in (1,):
+        for shift in (0, 4, 2, 1):
+            say(case, shape, "y shifted by", shift, "elements")
+            assert rel_err(layer.run(x, y_shift=shift, kernel=M, mfma_shape=shape), ref) <= TOL["f16"]
+    layer.free()
+
+
 def test_library_that_leaves_taps_unused():
     """Two patterns over taps {0,1,2,3} and {0,1,2,4}: four of the nine taps carry no weight and are skipped."""
     spec = L.LayerSpec(cfg=21, idx=0, name="taps", N=2, C=24, F=40, H=12, W=20, dtype="f16", K=2, keep=0.5,
