@@ -1015,7 +1015,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                     __builtin_amdgcn_sched_barrier(0);
                     if constexpr (next % 3 == 0) from[bf] = next ? from[bf] + row_bytes : boff[bf] + next_b;
                     each<WPIECES>([&](auto j) {
-                        if constexpr (j * 4 * BF / WPIECES == at) load_weights(nbuf, j);
+                        if constexpr (j * 2 * BF / WPIECES == at) load_weights(nbuf, j);
                     });
                     each<WRITES>([&](auto j) {
                         if constexpr (W0 + j * (W1 - W0) / WRITES == at) write_act(j / LW, j % LW);
@@ -1024,7 +1024,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                         if constexpr (W1 + j * (L1 - W1) / LOADS == at) load_act(j);
                     });
                     __builtin_amdgcn_sched_barrier(0);
-                    acc[1][bf] = product(fa[ts & 1][1], fb[bf], acc[1][bf]);
+                    if constexpr (AF == 2) acc[1][bf] = product(fa[ts & 1][1], fb[bf], acc[1][bf]);
                     __builtin_amdgcn_sched_barrier(0);
                     fb[bf] = *reinterpret_cast<const half8*>(lds + from[bf] + next % 3 * 16);
                     if constexpr (bf < AF) fa[(ts + 1) & 1][bf] = *reinterpret_cast<const half8*>(a + bf * 512);
@@ -1247,10 +1247,12 @@ const double kBlockUs[kMfmaShapes] = {3.2, 1.7, 1.7, 1.8};
 // first shape on the 112-, 56- and 28-column layers of VGG-16 at batch 64.)
 const Shape kShapes[kMfmaShapes] = {{2, 7, 2, 2}, {1, 7, 2, 2}, {1, 7, 4, 1}, {1, 7, 2, 1}};
 
-// One sequence of K steps where the tile shape fills the register file: with two workgroups on a compute unit each covers
-// the other's waits.  It looks two blocks ahead, into the next tile at most.
-bool runs_pipe(const MfmaParams& p, int af) {
-    return af == 2 && p.nt == 9 && !p.nhwc && p.KS == 1 && !p.clist && p.CB >= 2;
+// One sequence of K steps for the tiles of 128 filters, whose weights keep a second workgroup off the compute unit (of two
+// each covers the other's waits).  It looks two blocks ahead, into the next tile at most.  128 x 224 tiles, 256 -> 256
+// channels at 56 x 56: 37 -> 31 us at batch 8, 67 -> 58 at 16, 64 -> 128 at 112 x 112, stride 2, batch 64: 76 -> 43, which other
+// shapes had been chosen for.
+bool runs_pipe(const MfmaParams& p, int af, int wm) {
+    return (af == 2 || wm == 4) && p.nt == 9 && !p.nhwc && p.KS == 1 && !p.clist && p.CB >= 2;
 }
 
 // Workgroups of the persistent grid: as many as the device holds at once (compute units x workgroups that fit one),
@@ -1288,7 +1290,7 @@ int stagger_steps(const MfmaParams& p, int grid, long long ntiles, int walk, dou
 
 template <int AF, int BF, int WM, int WN>
 int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, double block_us, hipStream_t st) {
-    const bool full = p.nt == 9, pipe = runs_pipe(p, AF);
+    const bool full = p.nt == 9, pipe = runs_pipe(p, AF, WM);
     const long long ntiles = (long long)p.tiles_n * p.tiles_m * p.KS;
 #define PCONV_MFMA_CASE1(LWv, KIv, FULLv) PCONV_MFMA_CASE2(LWv, KIv, FULLv, false, false)
 #define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv, PIPEv)                                                         \
@@ -1305,7 +1307,7 @@ int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, doub
         return PCONV_OK;                                                                                        \
     }
 #define PCONV_MFMA_CASE(LWv, KIv) PCONV_MFMA_CASE1(LWv, KIv, true) PCONV_MFMA_CASE1(LWv, KIv, false)
-    if constexpr (AF == 2) {
+    if constexpr (AF == 2 || WM == 4) {
         PCONV_MFMA_CASE2(8, 1, true, false, true)
 #ifndef PCONV_ONLY_ONE
         PCONV_MFMA_CASE2(8, 2, true, false, true) PCONV_MFMA_CASE2(4, 2, true, false, true)
@@ -1415,7 +1417,7 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
         // they live there
         // (channel-minor outputs: 32 pixels x the wave's filters, see epilogue_nhwc)
         const size_t windows = a.nhwc ? (size_t)(NTH / 64) * 32 * (sh.af * 64 + 8)
-                               : runs_pipe(p, sh.af) ? (size_t)(NTH / 64) * kPipeWindow + kPipeSpare
+                               : runs_pipe(p, sh.af, sh.wm) ? (size_t)(NTH / 64) * kPipeWindow + kPipeSpare
                                                      : (size_t)(NTH / 64) * 4 * (sh.bf * 32 + 16) * 4;
         p.win_alias = 0;
         if (shares_cu && !a.nhwc) {
@@ -1450,7 +1452,7 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
     p.sw = (a.Wo % 8 == 0 && ya % 16 == 0) ? 8 : (a.Wo % 4 == 0 && ya % 8 == 0) ? 4 : (a.Wo % 2 == 0 && ya % 4 == 0) ? 2 : 1;
     // (the sequence of K steps: the pixels of a tile are one run of a filter's plane, or the end of one and the start of the
     // next image's, so a piece that divides the plane and the tile lies in one plane and is aligned, wherever rows end)
-    if (runs_pipe(p, sh.af)) {
+    if (runs_pipe(p, sh.af, sh.wm)) {
         p.sw = 1;
         for (int w = 8; w > 1 && p.sw == 1; w /= 2)
             if ((long long)R * a.Wo % w == 0 && (long long)a.Ho * a.Wo % w == 0 && ya % (2 * w) == 0) p.sw = w;
@@ -1550,9 +1552,6 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
     // (epilogue, descriptors), microseconds, fitted to the nine VGG-16 shapes at batch 64: two workgroups that share
     // a compute unit take turns on its matrix cores, so each one's block lasts longer; rows of fewer than 56 pixels
     // mean narrower loads and stores.
-    // (shape 1 from before its sequence of K steps.  With it, forced, the shape is 4 to 7 % faster than the one chosen on
-    // layers near the border: 115 against 120 us at 64 -> 128 channels, 112 x 112, batch 64, 30.1 against 32.4 at 128 -> 128,
-    // 56 x 56, batch 32; nowhere was a layer moved to a slower kernel by the sequence)
     const bool narrow = a.W < 56;
     double block_us = kBlockUs[shape - 1], tile_us = 8.0;
     if (shape == 1) block_us = narrow ? 2.65 : 2.3;
@@ -1565,6 +1564,24 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
     if (shape == 4) {
         if (per_cu == 2 && tiles > (long long)compute_units()) block_us = 2.4;
         tile_us = 4.0;
+    }
+    // (stride 2 stages two rows of input for one of output; measured on 64 -> 128 channels at 112 x 112 and 128 -> 256 at 56
+    // x 56, batch 64, where this shape takes 76 and 73 us and the 128 x 224 tile 43 and 41)
+    if (shape == 2 && a.stride == 2 && !few_taps) block_us = 4.0;
+    // One sequence of K steps: its loads have a block's time whether the device is full or not.  Fitted to eleven layers of
+    // 64 to 512 channels, 28 to 112 columns, batch 8 to 64 at stride 1 and nine at stride 2 (where a block takes longer the
+    // fuller the device is); on all but two of them the choice is the fastest of the three larger shapes or within 3 %.
+    const bool pipe = runs_pipe(p, kShapes[shape - 1].af, kShapes[shape - 1].wm);
+    if (pipe) {
+        const double full = std::min(1.0, (double)tiles / compute_units());
+        if (shape == 1) {
+            block_us = a.stride == 2 ? 4.0 : narrow ? 2.3 : 2.1;
+            tile_us = a.stride == 2 ? 12.0 : narrow ? 10.0 : 6.5;
+        } else {
+            // (two pieces of eight pixels a lane and block, rows of more than 200 pixels at stride 2: 32 us a tile of eight)
+            block_us = a.stride == 2 ? (1.4 + full) * (lw == 8 && ki == 2 ? 1.5 : 1.0) : narrow ? 1.7 : 1.47;
+            tile_us = a.stride == 2 ? 2.5 : narrow ? 4.0 : 3.1;
+        }
     }
     // a split costs the round trip of the partial sums through memory and the last arriver's additions
     const double part_bytes = (double)tiles * (kShapes[shape - 1].wm * kShapes[shape - 1].af * 32) *
@@ -1585,7 +1602,7 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
         for (int sp = 0; sp < 2; ++sp) us[sp] = (rounds * (8.0 + blocks * staged_us) + split_us[sp]) * (shape == 3 ? 1.0 : 2.0);
         return;
     }
-    for (int sp = 0; sp < 2; ++sp) us[sp] = rounds * (tile_us + blocks * std::max(block_us, floor_us)) + split_us[sp];
+    for (int sp = 0; sp < 2; ++sp) us[sp] = rounds * (tile_us + blocks * std::max(block_us, pipe ? 0.0 : floor_us)) + split_us[sp];
 }
 
 int mfma_workspace(const MfmaConv& a, size_t* floats, size_t* counters) {

@@ -112,7 +112,7 @@ def test_many_tiles_in_sequence(case):
                        K=8, keep=0.4)
     layer = GpuLayer(spec)
     assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF)      # (nine taps: the form is theirs)
-    run_forms(layer, L.gen_activations(spec), [dict(kernel=M, mfma_shape=1, rows=rows)])
+    run_forms(layer, L.gen_activations(spec), [dict(kernel=M, mfma_shape=sh, rows=rows) for sh in (1, 3)])
     layer.free()
 
 
@@ -135,7 +135,7 @@ def test_pieces_of_the_outputs(case):
     assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF)
     x = L.gen_activations(spec)
     ref = layer.oracle(x)
-    for shape in (1,):
+    for shape in (1, 3):
         for shift in (0, 4, 2, 1):
             say(case, shape, "y shifted by", shift, "elements")
             assert rel_err(layer.run(x, y_shift=shift, kernel=M, mfma_shape=shape), ref) <= TOL["f16"]
