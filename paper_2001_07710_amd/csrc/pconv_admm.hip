@@ -217,7 +217,7 @@ __global__ __launch_bounds__(kThreads) void assign_kernel(const T* __restrict__ 
 // Up to kSmallN kernels are one workgroup's work, keys in registers; up to kMidN one workgroup still ranks them, while
 // many compute the keys.  More of them go through a radix selection: one
 // pass computes the keys and counts their exponents, one counts the next 10 bits of the keys with the exponent of the
-// k-th largest, one gathers the keys that share those 21 bits (a few hundred of 1.6 million), and a single workgroup
+// k-th largest, one gathers the keys that share those 21 bits (a few hundred of 1.6 million), and its last workgroup
 // finds the k-th largest among them; the last pass compares every key with it.  Every pass works out the position of
 // the k-th largest from the counts of the passes before it, redundantly in each workgroup, so that nothing waits for
 // anything but the end of the kernel before.  Where more keys share 21 bits than the list holds -- many equal norms:
@@ -242,23 +242,25 @@ struct SelectState {
     unsigned slow;                     // more of them than the list holds: 1, or 2 where they are all the same
     unsigned last_index;               // of the keys equal to `threshold`, those with at most this index are kept
     unsigned ties_kept;                // slow: how many of them
+    unsigned exponent, exponent_rank;  // of the k-th largest, and its rank among the keys with that exponent
+    unsigned arrived;                  // workgroups of the gathering pass that are done
     unsigned long long threshold;      // the k-th largest key
     unsigned long long prefix[3];      // slow: its leading bits before each of the three passes, and its rank among the keys with them
     unsigned prefix_rank[3];
     alignas(16) unsigned hist0[kReplicas][kBins];
     unsigned hist1[kBins1];
-    unsigned slow_hist[3][kSlowBins];
     union {
         unsigned run_ties[kRuns];
         // (before that) of each workgroup's keys that share the first 21 bits with the k-th largest: the largest, and the
         // largest complement
         unsigned long long ends[kPassGrid][2];
     };
+    unsigned slow_hist[3][kSlowBins];  // (the second and third are zeroed where the passes that use them run)
     unsigned list_index[kListCap];
     unsigned long long list_key[kListCap];
 };
-// words that have to be zero before the first pass: everything in front of the list
-constexpr unsigned kStateWords = offsetof(SelectState, list_index) / 4;
+// words that have to be zero before the first pass
+constexpr unsigned kStateWords = (offsetof(SelectState, slow_hist) + sizeof(unsigned[kSlowBins])) / 4;
 
 template <typename T>
 __device__ __forceinline__ unsigned long long norm_key(const T* k9, unsigned m) {
@@ -510,21 +512,35 @@ __device__ __forceinline__ void find_digit(const unsigned* __restrict__ hist, in
 
 // A workgroup's keys, kAhead per thread in flight at a time.
 constexpr int kAhead = 8;
-template <typename Fn>
-__device__ __forceinline__ void for_keys(const unsigned long long* __restrict__ key, long long n, Fn fn) {
-    constexpr long long RUN = (long long)kSelThreads * kAhead;
-    for (long long first = (long long)blockIdx.x * RUN; first < n; first += (long long)gridDim.x * RUN) {
-        unsigned long long e[kAhead];
+struct Keys {
+    unsigned long long e[kAhead];
+};
+__device__ __forceinline__ Keys keys_from(const unsigned long long* __restrict__ key, long long n, long long first) {
+    Keys k;
 #pragma unroll
-        for (int j = 0; j < kAhead; ++j) {
-            const long long i = first + j * kSelThreads + threadIdx.x;
-            e[j] = i < n ? key[i] : 0ull;
-        }
+    for (int j = 0; j < kAhead; ++j) {
+        const long long i = first + j * kSelThreads + threadIdx.x;
+        k.e[j] = i < n ? key[i] : 0ull;
+    }
+    return k;
+}
+// (the first of them, to be asked for ahead of what the pass has to find out before it can use them)
+constexpr long long kKeyRun = (long long)kSelThreads * kAhead;
+__device__ __forceinline__ Keys first_keys(const unsigned long long* __restrict__ key, long long n) {
+    return keys_from(key, n, (long long)blockIdx.x * kKeyRun);
+}
+template <typename Fn>
+__device__ __forceinline__ void for_keys(const Keys& ahead, const unsigned long long* __restrict__ key, long long n, Fn fn) {
+    Keys k = ahead;
+    for (long long first = (long long)blockIdx.x * kKeyRun; first < n;) {
+        const unsigned long long* const e = k.e;
 #pragma unroll
         for (int j = 0; j < kAhead; ++j) {
             const long long i = first + j * kSelThreads + threadIdx.x;
             fn(e[j], i, i < n);
         }
+        first += (long long)gridDim.x * kKeyRun;
+        if (first < n) k = keys_from(key, n, first);
     }
 }
 
@@ -548,10 +564,15 @@ __device__ __forceinline__ void add_digit(unsigned* hist, bool hit, unsigned dig
 __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const unsigned long long* __restrict__ key, long long n,
                                                                    unsigned k, SelectState* st) {
     __shared__ unsigned hist[kBins1], scratch[18];
+    const Keys ahead = first_keys(key, n);
     for (int b = threadIdx.x; b < kBins1; b += kSelThreads) hist[b] = 0u;
     unsigned exponent, rank;
     find_digit<kBins>(&st->hist0[0][0], kReplicas, k, scratch, &exponent, &rank);
-    for_keys(key, n, [&](unsigned long long e, long long, bool there) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) {                // (for the passes behind this one)
+        st->exponent = exponent;
+        st->exponent_rank = rank;
+    }
+    for_keys(ahead, key, n, [&](unsigned long long e, long long, bool there) {
         add_digit(hist, there && (unsigned)(e >> 52) == exponent, (unsigned)(e >> 42) & (unsigned)(kBins1 - 1));
     });
     __syncthreads();
@@ -559,26 +580,99 @@ __global__ __launch_bounds__(kSelThreads) void select_count_kernel(const unsigne
         if (hist[b]) atomicAdd(&st->hist1[b], hist[b]);
 }
 
-__device__ __forceinline__ unsigned first_bits(const SelectState* st, unsigned k, unsigned* scratch, unsigned* rank) {
-    unsigned exponent, next;
-    find_digit<kBins>(&st->hist0[0][0], kReplicas, k, scratch, &exponent, rank);
-    find_digit<kBins1>(st->hist1, 1, *rank, scratch, &next, rank);
-    return exponent << 10 | next;
+// The k-th largest of the workgroup's keys, all of them at least `base` and alike above the lowest `bits`, and of those
+// equal to it the index of the last to be kept, lowest index first (`late`: ~index, 0 where there is no key).
+template <int PER>
+__device__ __forceinline__ void block_rank(const unsigned long long (&key)[PER], unsigned (&late)[PER],
+                                           unsigned long long base, int bits, unsigned k, uint4v* slots,
+                                           unsigned long long* ends, unsigned long long* kth, unsigned* last_index) {
+    unsigned turn = 0, above = 0;
+    const unsigned long long t = block_kth(key, base, bits, k, slots, turn, ends);
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        above += (unsigned)__popcll(__ballot(key[j] > t));
+        if (key[j] != t) late[j] = 0u;
+    }
+    above = block_total(above, slots, turn);
+    *kth = t;
+    unsigned first_late = 0u;
+    block_bits(late, first_late, 32, 0, k - above, slots, turn);
+    *last_index = ~first_late;
 }
 
+// What the last workgroup of a pass reads of the others' work: stored and loaded at device scope (see the pass), like the
+// partial sums of a channel split.
+template <typename T>
+__device__ __forceinline__ void put_for_all(T* to, T v) {
+    __hip_atomic_store(to, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <typename T>
+__device__ __forceinline__ T get_of_all(const T* from) {
+    return __hip_atomic_load(const_cast<T*>(from), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One workgroup: the k-th largest among the gathered keys, the rank-th of those with the first 21 bits `prefix`, equal ones
+// by index.
+__device__ __forceinline__ void finish_selection(SelectState* st, unsigned prefix, unsigned rank, uint4v* slots,
+                                                 unsigned long long* ends) {
+    const unsigned m = get_of_all(&st->listed);
+    if (m > (unsigned)kListCap) {
+        // (workgroups that found none have left zeros)
+        unsigned long long high = 0, not_low = 0;
+        if (threadIdx.x < kPassGrid) {
+            high = get_of_all(&st->ends[threadIdx.x][0]);
+            not_low = get_of_all(&st->ends[threadIdx.x][1]);
+        }
+        block_ends(high, not_low, ends, &high, &not_low);
+        for (int i = threadIdx.x; i < 2 * kSlowBins; i += kSelThreads) (&st->slow_hist[1][0])[i] = 0u;
+        if (threadIdx.x == 0) {
+            if (high == ~not_low) {
+                st->threshold = high;
+                st->ties_kept = rank;
+            }
+            st->prefix[0] = prefix;
+            st->prefix_rank[0] = rank;
+            st->slow = high == ~not_low ? 2u : 1u;
+        }
+        return;
+    }
+    constexpr int PER = kListCap / kSelThreads;
+    unsigned long long key[PER];
+    unsigned late[PER];                                       // ~index: equal keys, lowest index first
+#pragma unroll
+    for (int j = 0; j < PER; ++j) {
+        const unsigned at = (unsigned)j * kSelThreads + threadIdx.x;
+        key[j] = at < m ? get_of_all(&st->list_key[at]) : 0ull;
+        late[j] = at < m ? ~get_of_all(&st->list_index[at]) : 0u;
+    }
+    unsigned long long t;
+    unsigned last;
+    block_rank(key, late, (unsigned long long)prefix << 42, 42, rank, slots, ends, &t, &last);
+    if (threadIdx.x == 0) {
+        st->threshold = t;
+        st->last_index = last;
+    }
+}
+
+// Lists the keys that share the first 21 bits with the k-th largest, and counts the next 14 of them for the case that the
+// list does not hold them; the workgroup that is done last ranks the list.  (As a launch of its own the ranking took 5 us,
+// the counting pass 4.4 where there was nothing to count: the end of one kernel and the start of the next.)
 __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const unsigned long long* __restrict__ key, long long n,
-                                                                    unsigned k, SelectState* st) {
+                                                                    SelectState* st) {
     __shared__ unsigned scratch[18], found, at0;
-    __shared__ unsigned index[kSelThreads];
+    __shared__ uint4v slots[8];
+    __shared__ unsigned index[kSelThreads], hist[kSlowBins];
     __shared__ unsigned long long ends[2];
     if (threadIdx.x == 0) {
         found = 0u;
         ends[0] = ends[1] = 0ull;
     }
-    unsigned rank;
+    const Keys ahead = first_keys(key, n);
+    unsigned next, rank;
     unsigned long long high = 0, not_low = 0;
-    const unsigned prefix = first_bits(st, k, scratch, &rank);
-    for_keys(key, n, [&](unsigned long long e, long long i, bool there) {
+    find_digit<kBins1>(st->hist1, 1, st->exponent_rank, scratch, &next, &rank);
+    const unsigned prefix = st->exponent << 10 | next;
+    for_keys(ahead, key, n, [&](unsigned long long e, long long i, bool there) {
         const bool hit = there && (unsigned)(e >> 42) == prefix;
         const unsigned long long hits = __ballot(hit);
         if (!hits) return;
@@ -605,80 +699,43 @@ __global__ __launch_bounds__(kSelThreads) void select_gather_kernel(const unsign
         }
     }
     __syncthreads();
-    // (more than a workgroup can hold: the list counts as overflown)
     const unsigned m = found;
-    if (m == 0) return;
-    if (threadIdx.x < 2) st->ends[blockIdx.x][threadIdx.x] = ends[threadIdx.x];
-    if (threadIdx.x == 0) at0 = atomicAdd(&st->listed, m <= (unsigned)kSelThreads ? m : (unsigned)kListCap + 1u);
-    __syncthreads();
-    const unsigned at = at0 + threadIdx.x;
-    if (m <= (unsigned)kSelThreads && threadIdx.x < m && at < (unsigned)kListCap) {
-        st->list_key[at] = key[index[threadIdx.x]];
-        st->list_index[at] = index[threadIdx.x];
-    }
-}
-
-// The k-th largest of the workgroup's keys, all of them at least `base` and alike above the lowest `bits`, and of those
-// equal to it the index of the last to be kept, lowest index first (`late`: ~index, 0 where there is no key).
-template <int PER>
-__device__ __forceinline__ void block_rank(const unsigned long long (&key)[PER], unsigned (&late)[PER],
-                                           unsigned long long base, int bits, unsigned k, uint4v* slots,
-                                           unsigned long long* ends, unsigned long long* kth, unsigned* last_index) {
-    unsigned turn = 0, above = 0;
-    const unsigned long long t = block_kth(key, base, bits, k, slots, turn, ends);
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        above += (unsigned)__popcll(__ballot(key[j] > t));
-        if (key[j] != t) late[j] = 0u;
-    }
-    above = block_total(above, slots, turn);
-    *kth = t;
-    unsigned first_late = 0u;
-    block_bits(late, first_late, 32, 0, k - above, slots, turn);
-    *last_index = ~first_late;
-}
-
-// One workgroup: the k-th largest among the gathered keys, equal ones by index.
-__global__ __launch_bounds__(kSelThreads) void select_finish_kernel(unsigned k, SelectState* st) {
-    __shared__ unsigned scratch[18];
-    __shared__ uint4v slots[8];
-    __shared__ unsigned long long ends[2];
-    unsigned rank;
-    const unsigned prefix = first_bits(st, k, scratch, &rank);
-    const unsigned m = st->listed;
-    if (m > (unsigned)kListCap) {
-        // (workgroups that found none have left zeros)
-        unsigned long long high = 0, not_low = 0;
-        if (threadIdx.x < kPassGrid) {
-            high = st->ends[threadIdx.x][0];
-            not_low = st->ends[threadIdx.x][1];
+    auto digit = [](unsigned long long e) { return (unsigned)(e >> (42 - kSlowBits)) & (unsigned)(kSlowBins - 1); };
+    if (m != 0) {                                             // (uniform)
+        if (threadIdx.x < 2) put_for_all(&st->ends[blockIdx.x][threadIdx.x], ends[threadIdx.x]);
+        // (more than a workgroup can hold: the list counts as overflown)
+        if (threadIdx.x == 0) at0 = atomicAdd(&st->listed, m <= (unsigned)kSelThreads ? m : (unsigned)kListCap + 1u);
+        if (m > (unsigned)kSelThreads && ends[0] != ~ends[1]) {
+            for (int b = threadIdx.x; b < kSlowBins; b += kSelThreads) hist[b] = 0u;
+            __syncthreads();
+            for_keys(first_keys(key, n), key, n, [&](unsigned long long e, long long, bool there) {
+                add_digit(hist, there && (unsigned)(e >> 42) == prefix, digit(e));
+            });
+            __syncthreads();
+            for (int b = threadIdx.x; b < kSlowBins; b += kSelThreads)
+                if (hist[b]) atomicAdd(&st->slow_hist[0][b], hist[b]);
+        } else if (m > (unsigned)kSelThreads) {
+            if (threadIdx.x == 0) atomicAdd(&st->slow_hist[0][digit(ends[0])], m);
         }
-        block_ends(high, not_low, ends, &high, &not_low);
-        if (threadIdx.x == 0) {
-            if (high == ~not_low) {
-                st->threshold = high;
-                st->ties_kept = rank;
+        __syncthreads();
+        if (m <= (unsigned)kSelThreads && threadIdx.x < m) {
+            const unsigned long long e = key[index[threadIdx.x]];
+            const unsigned at = at0 + threadIdx.x;
+            atomicAdd(&st->slow_hist[0][digit(e)], 1u);
+            if (at < (unsigned)kListCap) {
+                put_for_all(&st->list_key[at], e);
+                put_for_all(&st->list_index[at], index[threadIdx.x]);
             }
-            st->slow = high == ~not_low ? 2u : 1u;
         }
-        return;
     }
-    constexpr int PER = kListCap / kSelThreads;
-    unsigned long long key[PER];
-    unsigned late[PER];                                       // ~index: equal keys, lowest index first
-#pragma unroll
-    for (int j = 0; j < PER; ++j) {
-        const unsigned at = (unsigned)j * kSelThreads + threadIdx.x;
-        key[j] = at < m ? st->list_key[at] : 0ull;
-        late[j] = at < m ? ~st->list_index[at] : 0u;
-    }
-    unsigned long long t;
-    unsigned last;
-    block_rank(key, late, (unsigned long long)prefix << 42, 42, rank, slots, ends, &t, &last);
-    if (threadIdx.x == 0) {
-        st->threshold = t;
-        st->last_index = last;
-    }
+    // (every wave waits until its stores and additions have reached the level at which all XCDs agree; then the workgroup
+    // counts as done.  What the last one reads was never in its own caches)
+    __builtin_amdgcn_s_waitcnt(0x0F70);                       // vmcnt(0)
+    __syncthreads();
+    if (threadIdx.x == 0)
+        at0 = __hip_atomic_fetch_add(&st->arrived, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == gridDim.x - 1u ? 1u : 0u;
+    __syncthreads();
+    if (at0) finish_selection(st, prefix, rank, slots, ends);
 }
 
 // The index of the rank-th (from 1) of the PER * kSelThreads keys that is equal to t.  `counts` is PER * 16 words of LDS,
@@ -873,27 +930,26 @@ __global__ __launch_bounds__(kSelThreads) void select_mid_kernel(const unsigned 
 }
 
 // The bits below the first 21, 14 at a time, where too many keys share those: what is known of the k-th largest after
-// `passes` of them, from what the pass before has left and its counts.
-__device__ __forceinline__ unsigned long long slow_prefix(const SelectState* st, unsigned k, int passes, unsigned* scratch,
+// `passes` (1 to 3) counts of them, from what the pass before has left and its counts.
+__device__ __forceinline__ unsigned long long slow_prefix(const SelectState* st, int passes, unsigned* scratch,
                                                           unsigned* rank) {
-    if (passes == 0) return first_bits(st, k, scratch, rank);
     unsigned digit;
     find_digit<kSlowBins>(st->slow_hist[passes - 1], 1, st->prefix_rank[passes - 1], scratch, &digit, rank);
     return st->prefix[passes - 1] << kSlowBits | digit;
 }
 __global__ __launch_bounds__(kSelThreads) void select_slow_kernel(const unsigned long long* __restrict__ key, long long n,
-                                                                  unsigned k, int pass, SelectState* st) {
+                                                                  int pass, SelectState* st) {
     if (st->slow != 1u) return;
     __shared__ unsigned hist[kSlowBins], scratch[18];
     for (int b = threadIdx.x; b < kSlowBins; b += kSelThreads) hist[b] = 0u;
     unsigned rank;
-    const unsigned long long prefix = slow_prefix(st, k, pass, scratch, &rank);
+    const unsigned long long prefix = slow_prefix(st, pass, scratch, &rank);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         st->prefix[pass] = prefix;
         st->prefix_rank[pass] = rank;
     }
     const int top = 42 - kSlowBits * pass, low = top - kSlowBits;
-    for_keys(key, n, [&](unsigned long long e, long long, bool there) {
+    for_keys(first_keys(key, n), key, n, [&](unsigned long long e, long long, bool there) {
         add_digit(hist, there && (e >> top) == prefix, (unsigned)(e >> low) & (unsigned)(kSlowBins - 1));
     });
     __syncthreads();
@@ -907,13 +963,13 @@ __host__ __device__ __forceinline__ long long run_length(long long n) {
     return (per + kSelThreads - 1) / kSelThreads * kSelThreads;
 }
 __global__ __launch_bounds__(kSelThreads) void select_ties_kernel(const unsigned long long* __restrict__ key, long long n,
-                                                                  unsigned k, SelectState* st) {
+                                                                  SelectState* st) {
     if (!st->slow) return;
     __shared__ unsigned scratch[18];
     __shared__ uint4v slots[8];
     unsigned rank, turn = 0;
     const bool known = st->slow == 2u;
-    const unsigned long long t = known ? st->threshold : slow_prefix(st, k, 3, scratch, &rank);
+    const unsigned long long t = known ? st->threshold : slow_prefix(st, 3, scratch, &rank);
     const long long run = run_length(n);
     for (int r = blockIdx.x; r < kRuns && (long long)r * run < n; r += gridDim.x) {
         const long long first = (long long)r * run;
@@ -1059,12 +1115,11 @@ extern "C" int pconv_select_connectivity_device(const void* w, int dtype, long l
 #undef PCONV_NORMS
     const dim3 pass_grid((unsigned)std::min<long long>((n + kAhead * kSelThreads - 1) / (kAhead * kSelThreads), kPassGrid));
     hipLaunchKernelGGL(select_count_kernel, pass_grid, sel, 0, st, key, n, k, state);
-    hipLaunchKernelGGL(select_gather_kernel, pass_grid, sel, 0, st, key, n, k, state);
-    hipLaunchKernelGGL(select_finish_kernel, dim3(1), sel, 0, st, k, state);
-    for (int p = 0; p < 3; ++p) hipLaunchKernelGGL(select_slow_kernel, pass_grid, sel, 0, st, key, n, k, p, state);
+    hipLaunchKernelGGL(select_gather_kernel, pass_grid, sel, 0, st, key, n, state);
+    for (int p = 1; p < 3; ++p) hipLaunchKernelGGL(select_slow_kernel, pass_grid, sel, 0, st, key, n, p, state);
     // (a run at a time where equal keys are ranked: one workgroup a run as far as they go)
     const dim3 run_grid((unsigned)std::min<long long>((n + kSelThreads - 1) / kSelThreads, kPassGrid));
-    hipLaunchKernelGGL(select_ties_kernel, run_grid, sel, 0, st, key, n, k, state);
+    hipLaunchKernelGGL(select_ties_kernel, run_grid, sel, 0, st, key, n, state);
     if (n % 4 == 0 && reinterpret_cast<uintptr_t>(mask) % 4 == 0)
         hipLaunchKernelGGL(mark_kept_kernel<true>, run_grid, sel, 0, st, key, n, state, mask);
     else
