@@ -277,7 +277,8 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
             for (int bf = 0; bf < BF; ++bf)
 #pragma unroll
                 for (int af = 0; af < AF; ++af)
-                    acc[af][bf] = __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ts][af], fb[ts & 1][bf], acc[af][bf], 0, 0, 0);
+                    acc[af][bf] = NHWC ? __builtin_amdgcn_mfma_f32_32x32x16_f16(a[ts][af], fb[ts & 1][bf], acc[af][bf], 0, 0, 0)
+                                       : __builtin_amdgcn_mfma_f32_32x32x16_f16(fb[ts & 1][bf], a[ts][af], acc[af][bf], 0, 0, 0);
             if constexpr (decltype(more)::value) load_a(b + 1, ts);
         }
         if constexpr (decltype(more)::value) hand_over();
@@ -293,13 +294,21 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
     }
 
     // ---- the waves' partial sums, 32 filters at a time, added in the order of the waves; bias, ReLU, store.
-    // Channel-major: [wave][filter][pixel], a thread adds and stores pixels of a filter next to its neighbours;
-    // channel-minor: [wave][pixel][filter].  (A sum's parts and the bias come from LDS together: with the bias from
-    // memory and the parts one after the other this took longer than the multiplications, 10 us a tile for 64 filters.)
+    // Channel-major (rows of the result are pixels, a lane's column its filter): [wave][filter][pixel], a thread adds and
+    // stores pixels of a filter next to its neighbours; channel-minor (the other way round): [wave][pixel][filter].  Either
+    // way a lane writes runs of four.
+    // A workgroup comes here once, and what it runs comes from memory with it: this is one loop over the filters, not two
+    // copies, and its inner loop is not unrolled.  (3,300 instructions for each 32 filters before, of which a workgroup ran
+    // 200 in a dozen places: 3,500 to 4,300 clocks for the first 32 filters and 2,000 to 2,400 for the next, of 17,000 to
+    // 34,000 in all.)
     float* const parts = reinterpret_cast<float*>(lds);
     float* const bias = reinterpret_cast<float*>(lds + p.bias_off);
     const int pitch = p.pitch, part = (NHWC ? PX : 32) * pitch;
     if (tid < AF * 32) bias[tid] = bias_value;               // (behind everything the waves still read)
+    auto rounded = [&](float u) {
+        if (p.relu) u = u > 0.f ? u : (u != u ? u : 0.f);
+        return (_Float16)u;
+    };
     auto store = [&](auto wave_count, int af) {
         constexpr int WAVES = decltype(wave_count)::value;
         const int fbase = f0 + af * 32;
@@ -308,12 +317,11 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
             // a thread: four filters of one pixel
             const int fq = (tid & 7) * 4;
             if (fbase + fq >= p.F) return;                       // (F is a multiple of 8)
-#pragma unroll
-            for (int k = 0; k < (PX + WAVES * 8 - 1) / (WAVES * 8); ++k) {
-                const int px = (tid >> 3) + k * WAVES * 8;
+#pragma unroll 1
+            for (int px = tid >> 3; px < PX; px += WAVES * 8) {
                 const unsigned py = fastdiv((unsigned)px, p.div_TW);
                 const int oy = oy0 + (int)py, ox = ox0 + px - (int)py * p.TW;
-                if (px >= PX || (int)py >= p.TH || oy >= p.Ho || ox >= p.Wo) continue;
+                if ((int)py >= p.TH || oy >= p.Ho || ox >= p.Wo) continue;
                 float4v v[WAVES];
 #pragma unroll
                 for (int w = 0; w < WAVES; ++w) v[w] = *reinterpret_cast<const float4v*>(parts + w * part + px * pitch + fq);
@@ -321,13 +329,7 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
 #pragma unroll
                 for (int w = 1; w < WAVES; ++w) sum += v[w];
                 sum += *reinterpret_cast<const float4v*>(b + fq);
-                _Float16 out[4];
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    float u = sum[i];
-                    if (p.relu) u = u > 0.f ? u : (u != u ? u : 0.f);
-                    out[i] = (_Float16)u;
-                }
+                const _Float16 out[4] = {rounded(sum[0]), rounded(sum[1]), rounded(sum[2]), rounded(sum[3])};
                 uint2v o;
                 __builtin_memcpy(&o, out, 8);
                 *reinterpret_cast<uint2v*>(p.y + (((size_t)n * p.Ho + oy) * p.Wo + ox) * p.F + fbase + fq) = o;
@@ -341,28 +343,24 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
                 const unsigned py = fastdiv((unsigned)px, p.div_TW);
                 const int oy = oy0 + (int)py, ox = ox0 + px - (int)py * p.TW;
                 if ((int)py >= p.TH || oy >= p.Ho || ox >= p.Wo) return;
-                const int fa = tid / QX;
-                _Float16* const y = p.y + (((size_t)n * p.F + fbase + fa) * p.Ho + oy) * p.Wo + ox;
-                const size_t plane = (size_t)p.Ho * p.Wo;
-#pragma unroll
-                for (int k = 0; k < (32 + STEP - 1) / STEP; ++k) {
-                    const int f = fa + k * STEP;
-                    if (f >= 32 || fbase + f >= p.F) break;
+                int f = tid / QX;
+                const size_t step = (size_t)STEP * p.Ho * p.Wo;
+                _Float16* y = p.y + (((size_t)n * p.F + fbase + f) * p.Ho + oy) * p.Wo + ox;
+                const int most = min(32, p.F - fbase);
+                const float* from = parts + f * pitch + px;
+#pragma unroll 1
+                for (; f < most; f += STEP, y += step, from += STEP * pitch) {
                     Vec v[WAVES];
 #pragma unroll
-                    for (int w = 0; w < WAVES; ++w) __builtin_memcpy(&v[w], __builtin_assume_aligned(parts + w * part + f * pitch + px, sizeof(Vec)), sizeof(Vec));
+                    for (int w = 0; w < WAVES; ++w) __builtin_memcpy(&v[w], __builtin_assume_aligned(from + w * part, sizeof(Vec)), sizeof(Vec));
                     Vec sum = v[0];
 #pragma unroll
                     for (int w = 1; w < WAVES; ++w) sum += v[w];
                     sum += b[f];
                     _Float16 out[PV];
 #pragma unroll
-                    for (int i = 0; i < PV; ++i) {
-                        float u = sum[i];
-                        if (p.relu) u = u > 0.f ? u : (u != u ? u : 0.f);
-                        out[i] = (_Float16)u;
-                    }
-                    __builtin_memcpy(__builtin_assume_aligned(y + (size_t)(k * STEP) * plane, 2 * PV), out, 2 * PV);
+                    for (int i = 0; i < PV; ++i) out[i] = rounded(sum[i]);
+                    __builtin_memcpy(__builtin_assume_aligned(y, 2 * PV), out, 2 * PV);
                 }
             };
             if (p.pv == 4) rows(std::integral_constant<int, 4>{});
@@ -370,24 +368,25 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
             else rows(std::integral_constant<int, 1>{});
         }
     };
-#pragma unroll
-    for (int af = 0; af < AF; ++af) {
-        __syncthreads();
+    auto put = [&](const float16v (&sums)[BF]) {
+        float* const to = parts + wave * part + li * pitch + lk * 4;
 #pragma unroll
         for (int bf = 0; bf < BF; ++bf)
 #pragma unroll
             for (int rq = 0; rq < 4; ++rq) {
-                if constexpr (NHWC) {
-                    float4v v;
+                float4v v;
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) v[i] = acc[af][bf][rq * 4 + i];
-                    *reinterpret_cast<float4v*>(parts + wave * part + (bf * 32 + li) * pitch + rq * 8 + lk * 4) = v;
-                } else {
-#pragma unroll
-                    for (int i = 0; i < 4; ++i)
-                        parts[wave * part + (rq * 8 + lk * 4 + i) * pitch + bf * 32 + li] = acc[af][bf][rq * 4 + i];
-                }
+                for (int i = 0; i < 4; ++i) v[i] = sums[bf][rq * 4 + i];
+                *reinterpret_cast<float4v*>(to + (NHWC ? bf * 32 * pitch + rq * 8 : bf * 32 + rq * 8)) = v;
             }
+    };
+    int halves = AF;
+    asm volatile("" : "+s"(halves));                          // (one copy of the loop)
+#pragma unroll 1
+    for (int af = 0; af < halves; ++af) {
+        __syncthreads();
+        if (af == 0) put(acc[0]);
+        else put(acc[AF - 1]);
         __syncthreads();
         if (waves == 8) store(std::integral_constant<int, 8>{}, af);
         else if (waves == 4) store(std::integral_constant<int, 4>{}, af);
@@ -483,7 +482,7 @@ bool plan(const MfmaConv& a, int shape, double bar, SmallPlan* out) {
             if (lw == 2) while (gp % 16 < 5 || gp % 16 > 11) ++gp;
             if (lw == 4) while (gp % 8 < 3 || gp % 8 > 5) ++gp;
             const int row_slots = gp * piece;
-            const int pitch = a.nhwc ? 36 : PX + 8;
+            const int pitch = a.nhwc ? 36 : PX + 4;
             // a wave's step: bytes it fetches, and the instructions that take them
             // (a row of the patch comes in whole memory lines; the rows of a 1x1 layer are one run of pixels)
             const double row_bytes = ext == 1 && s == 1 ? pw * 2.0 : 64.0 + pw * cs * 2.0;
