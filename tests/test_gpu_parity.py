@@ -680,6 +680,28 @@ def test_maxpool(dtype):
     assert np.array_equal(dy.cpu().numpy().astype(np.float32), oracle.maxpool2x2(x))
 
 
+# Widths with and without whole 16-byte pieces, odd heights and widths (the last row and column have no partner), addresses
+# that only single elements are aligned for, more planes than a workgroup has threads.
+@pytest.mark.parametrize("dtype", ["f32", "f16"])
+@pytest.mark.parametrize("planes,H,W,shift", [(3, 15, 8, 0), (2, 16, 24, 0), (2, 6, 24, 1), (5, 9, 11, 0), (300, 2, 2, 0), (1, 2, 130, 0),
+                                              (2, 16, 24, 4)])
+def test_maxpool_pieces(dtype, planes, H, W, shift):
+    import torch
+    x = L.gen_activations(L.LayerSpec(cfg=13, idx=1, name="pool", N=1, C=planes, F=1, H=H, W=W, dtype=dtype))
+    x = x - x.dtype.type(0.3)
+    say("maxpool", dtype, planes, H, W, shift)
+    buf = torch.zeros(x.size + shift, dtype=torch.float16 if dtype == "f16" else torch.float32, device="cuda")
+    buf[shift:] = torch.from_numpy(x).cuda().reshape(-1)
+    n = planes * (H // 2) * (W // 2)
+    out = torch.full((n + shift + 64,), -777.0, dtype=buf.dtype, device="cuda")
+    pc.maxpool2x2(buf[shift:], out[shift:], pc.F16 if dtype == "f16" else pc.F32, 1, planes, H, W,
+                  torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    got = out.cpu().numpy().astype(np.float32)
+    assert np.all(got[:shift] == -777.0) and np.all(got[shift + n:] == -777.0)
+    assert np.array_equal(got[shift:shift + n].reshape(1, planes, H // 2, W // 2), oracle.maxpool2x2(x))
+
+
 @pytest.mark.parametrize("C,F,keep", [(1030, 40, 0.05), (2100, 17, 0.3), (3, 130, 1.0), (16, 1, 0.5)])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 def test_layouts_made_on_the_device(C, F, keep, dtype):
