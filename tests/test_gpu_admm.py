@@ -140,7 +140,8 @@ def test_device_connectivity_selection_matches_the_oracle_bit_for_bit(dtype, kee
     (32769, 0, 0.28), (32769, 1, 0.5), (100003, 0, 0.15), (100004, 0, 0.0001), (262144, 5, 0.61),
     (300000, 1, 0.999), (1048577, 40, 0.28),
     (500, -1, 0.3), (8193, -1, 0.3), (20000, -1, 0.9), (32768, -1, 0.28), (32769, -1, 0.28), (100003, -1, 0.5),   # nearly equal
-    (256, -2, 0.3), (5000, -2, 0.3), (9000, -2, 0.1), (32768, -2, 0.28), (32768, -2, 0.99), (40000, -2, 0.28), (200001, -2, 0.5)])
+    (256, -2, 0.3), (5000, -2, 0.3), (9000, -2, 0.1), (32768, -2, 0.28), (32768, -2, 0.99), (40000, -2, 0.28), (200001, -2, 0.5),
+    (700001, -1, 0.4), (1500000, 1, 0.9)])       # a workgroup with more candidates than it can list: unlike ones, all alike
 def test_device_connectivity_selection_over_its_sizes(n, values, keep):
     """One workgroup and several passes; `values` > 0: weights from so few values that thousands of norms are equal (the
     list of candidates overflows, the ties are ranked by index), 0: all different, below 0: see there.  Indices and marks are exact."""
