@@ -391,17 +391,23 @@ int upload_packed(pconv_packed* p) {
     int dev = -1;
     PCONV_HIP(hipGetDevice(&dev));
     // the allocation: first what is copied, then the matrix-core weights (cleared), then what kernels fill whole
-    std::vector<unsigned char> host;
     size_t size = 0;
     auto take = [&](size_t bytes) {
         const size_t at = size;
         size += (bytes + 255) / 256 * 256;
         return at;
     };
+    // (the copy's source is put together in one piece of memory, whose size is known by then: grown piece by piece it was
+    // moved, and cleared, several times over)
+    struct Part {
+        size_t at;
+        const void* data;
+        size_t bytes;
+    };
+    std::vector<Part> copies;
     auto put = [&](const void* data, size_t bytes) {
         const size_t at = take(std::max<size_t>(bytes, 16));
-        host.resize(size);
-        if (bytes) std::memcpy(&host[at], data, bytes);
+        copies.push_back({at, data, bytes});
         return at;
     };
     auto put_vector = [&](const auto& v) { return put(v.data(), v.size() * sizeof(v[0])); };
@@ -442,6 +448,11 @@ int upload_packed(pconv_packed* p) {
     for (size_t t = 0; t < nl; ++t) {
         at_ent[t] = take(ent_bytes);
         at_eptr[t] = take(((size_t)p->F * p->balanced[t].n_chunks + 1) * sizeof(uint32_t));
+    }
+    Array<unsigned char> host(copied);
+    for (const Part& c : copies) {
+        if (c.bytes) std::memcpy(&host[c.at], c.data, c.bytes);
+        std::memset(&host[c.at + c.bytes], 0, (std::max<size_t>(c.bytes, 16) + 255) / 256 * 256 - c.bytes);
     }
     PCONV_HIP(hipMalloc(&p->d_arena, size));
     unsigned char* const base = static_cast<unsigned char*>(p->d_arena);

@@ -116,9 +116,9 @@ namespace {
 // pack_list.
 struct KernelList {
     std::vector<uint32_t> row;        // [F+1]
-    std::vector<uint16_t> c;          // channel
-    std::vector<uint8_t> pid;         // pattern id
-    std::vector<unsigned char> w4;    // the kept weights, taps ascending, four of the storage type (missing ones zero)
+    pconv::Array<uint16_t> c;         // channel
+    pconv::Array<uint8_t> pid;        // pattern id
+    pconv::Array<unsigned char> w4;   // the kept weights, taps ascending, four of the storage type (missing ones zero)
 };
 
 // Which of up to 64 mask bytes are set, as bits.  Where the host has no SSE2, eight bytes at a time in one word (256 x 256

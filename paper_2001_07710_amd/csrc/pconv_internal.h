@@ -3,12 +3,34 @@
 
 #include <cstddef>
 #include <cstdint>
+#include <memory>
 #include <mutex>
+#include <new>
+#include <utility>
 #include <vector>
 
 #include "pconv.h"
 
 namespace pconv {
+
+// A vector whose elements are not set to zero when it grows: for arrays of which every element is written right behind.
+template <typename T>
+struct Unset : std::allocator<T> {
+    template <typename U>
+    struct rebind {
+        typedef Unset<U> other;
+    };
+    template <typename U>
+    void construct(U* at) {
+        ::new (static_cast<void*>(at)) U;
+    }
+    template <typename U, typename... Args>
+    void construct(U* at, Args&&... args) {
+        ::new (static_cast<void*>(at)) U(std::forward<Args>(args)...);
+    }
+};
+template <typename T>
+using Array = std::vector<T, Unset<T>>;
 
 // The packed entries of a filter are bucketed by input channel in buckets of this many channels.  The tiled kernel
 // stages a chunk of 1, 2 or 4 consecutive buckets of activations in LDS at a time.
@@ -105,14 +127,14 @@ struct pconv_packed {
     // canonical form (what pconv_packed_export returns)
     std::vector<uint32_t> filter_order;   // [F]
     std::vector<uint32_t> grp_ptr;        // [F*K+1]
-    std::vector<uint16_t> cin;            // [n_kept]
-    std::vector<unsigned char> w4;        // [n_kept*4] in the storage dtype, raw bytes
+    pconv::Array<uint16_t> cin;           // [n_kept]
+    pconv::Array<unsigned char> w4;       // [n_kept*4] in the storage dtype, raw bytes
 
     // device layout: entries ordered by (position i in filter_order, channel bucket, pattern, channel); made on the device
     int n_buckets = 0;
     // per canonical entry {filter, channel | mask << 16}: what the weight-gradient pass needs to find an entry's sums,
     // and what the device's layouts are made from
-    std::vector<uint32_t> canon;              // [n_kept*2]
+    pconv::Array<uint32_t> canon;             // [n_kept*2]
     uint32_t* d_canon = nullptr;
 
     // balanced layouts for the tilings that the automatic choice uses (see pconv::BalancedLayout)
