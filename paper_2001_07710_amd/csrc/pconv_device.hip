@@ -451,8 +451,8 @@ int upload_packed(pconv_packed* p) {
     }
     Array<unsigned char> host(copied);
     for (const Part& c : copies) {
-        if (c.bytes) std::memcpy(&host[c.at], c.data, c.bytes);
-        std::memset(&host[c.at + c.bytes], 0, (std::max<size_t>(c.bytes, 16) + 255) / 256 * 256 - c.bytes);
+        if (c.bytes) std::memcpy(host.data() + c.at, c.data, c.bytes);
+        std::memset(host.data() + c.at + c.bytes, 0, (std::max<size_t>(c.bytes, 16) + 255) / 256 * 256 - c.bytes);
     }
     PCONV_HIP(hipMalloc(&p->d_arena, size));
     unsigned char* const base = static_cast<unsigned char*>(p->d_arena);
