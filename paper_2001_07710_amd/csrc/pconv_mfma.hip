@@ -123,7 +123,9 @@ struct MfmaParams {
                                  // weights, 2 = its activations; 0 = in a place of their own behind the bias
     int a_stages;                // 2; or 1: the layer has a single block of weights, staged once per workgroup
     int b_stages;                // 2; or 1: one buffer for the activations, written between two barriers (where that
-                                 // makes the LDS small enough for a second workgroup on the compute unit)
+                                 // makes the LDS small enough for a second workgroup on the compute unit); or 3: the
+                                 // sequence of K steps on channel-minor tensors, whose loads fill LDS two blocks ahead
+    int pipe;                    // the layer runs as one sequence of K steps
     int stagger;                 // every second workgroup starts this many steps of 2048 clocks late (0: none)
     float* ws;              // KS > 1: partial sums [tile][split][wave][operand tile][4 rows][64 lanes][4], as held
     unsigned* counters;     // KS > 1: one arrival counter per tile, zero between launches
@@ -157,9 +159,10 @@ struct TileGeo {
 // epilogue turns 32 pixels at a time through a wave-private LDS window so that whole runs of a pixel's filters are
 // stored.
 template <int AF, int BF, int WM, int WN, int LW, int KI, bool FULL, bool NHWC, bool PIPE = false>
-__global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 1) void mfma_conv_kernel(const MfmaParams p) {
+__global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIPE) ? 2 : 1) void mfma_conv_kernel(const MfmaParams p) {
     constexpr int kItems = NHWC ? 0 : KI;
-    constexpr int kAL = NHWC ? 12 : 0;      // NHWC: wave-wide activation loads per wave and block, at most
+    // NHWC: wave-wide activation loads per wave and block, at most (PIPE: those that the form issues, 6 or 12)
+    constexpr int kAL = !NHWC ? 0 : PIPE ? 6 * KI : 12;
     constexpr bool CAN_ALIAS = AF == 1 && WM == 2 && WN == 2;
     constexpr int NW = WM * WN, NTH = NW * 64, MT = WM * AF * 32, HALF = NTH / 2;
     constexpr int WPIECES = (9 * 2 * MT + NTH - 1) / NTH;      // 16-byte pieces of weights per lane and block, at most
@@ -447,12 +450,13 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
 
     // The accumulators of a tile start at the bias of their filter (accumulator row r of a 32 x 32 block is filter
     // (r/4)*8 + (lane/32)*4 + r%4), or at zero in the workgroups that take a later part of a split tile's channels.
-    // In the sequence of K steps the operands change places: rows are pixels, and a lane's column is its filter.
+    // In the sequence of K steps on channel-major tensors the operands change places: rows are pixels, and a lane's column
+    // is its filter.
     float16v acc[AF][BF];
     auto start_acc = [&](const TileGeo& g, int bias_slot) {
         int lane_e = lane;
         asm volatile("" : "+v"(lane_e));                         // (computed here, not ahead of everything)
-        if constexpr (PIPE) {
+        if constexpr (PIPE && !NHWC) {
 #pragma unroll
             for (int af = 0; af < AF; ++af) {
                 const float b = ldsBias[bias_slot * MT + (wm * AF + af) * 32 + (lane_e & 31)];
@@ -773,8 +777,10 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
     // 6,100 for the outputs and 500 for the start of the accumulators (256 -> 256 channels at 56 x 56, batch 64; before the
     // instructions beside the MFMAs were spread, the taps' addresses left to the instructions and the outputs' way changed
     // 5,140, 8,400 and 600; 167 -> 158 us, at 128 -> 128, 112 x 112, 180 -> 167).  The clock is 2.0 to 2.15 GHz meanwhile.
-    // (Channel-minor, where the activations go to LDS by themselves and one block ahead only: 196 -> 208 us, not kept.  The
-    // outputs of a tile beside the MFMAs of the next one's first block, one group of pixels after the other: that block
+    // Channel-minor activations go to LDS by themselves, so they have no registers to wait in and three buffers instead: a
+    // block's taps 2 to 5 fill the one that the block before has left (128 -> 128 at 112 x 112, batch 64: 197 -> 166 us; with
+    // two buffers, one block ahead, 208).
+    // (The outputs of a tile beside the MFMAs of the next one's first block, one group of pixels after the other: that block
     // 9,900 clocks, as much as both had taken, not kept.)
     if constexpr (PIPE) {
         // The lane number once more, as the compiler cannot see through it: what depends on it in the epilogue is computed
@@ -788,7 +794,8 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
 
         // One K step of one operand tile.
         auto product = [&](half8 weights, half8 pixels, float16v sum) {
-            sum = __builtin_amdgcn_mfma_f32_32x32x16_f16(pixels, weights, sum, 0, 0, 0);
+            sum = NHWC ? __builtin_amdgcn_mfma_f32_32x32x16_f16(weights, pixels, sum, 0, 0, 0)
+                       : __builtin_amdgcn_mfma_f32_32x32x16_f16(pixels, weights, sum, 0, 0, 0);
             // (nothing, but in its place among loads and barriers: an MFMA by itself is free to go anywhere, and has gone to the
             // end of the block, with the operands of all nine taps in scratch)
             asm volatile("" : "+a"(sum));
@@ -843,6 +850,43 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
             const __amdgpu_buffer_rsrc_t yr =
                 make_rsrc(reinterpret_cast<const void*>(((unsigned long long)yb_hi << 32) | yb_lo), y_records);
             const int fw = g.tm * MT + wm * AF * 32;                 // the wave's first filter
+            if constexpr (NHWC) {
+                // [pixel][the wave's filters], 32 pixels at a time, as in epilogue_nhwc(); the pixels of a tile are one run
+                // of memory
+                constexpr int LPP = AF * 4, PPR = 64 / LPP, READS = 32 / PPR;      // lanes to a pixel; pixels per read
+                const int part = lane_e % LPP, px = lane_e / LPP;
+                const unsigned first = ((unsigned)(g.oy0 * Wo + wn * BF * 32 + px) * (unsigned)p.F + (unsigned)(fw + part * 8)) * 2u;
+                const int valid = fw + part * 8 < p.F ? g.Rv * Wo - wn * BF * 32 - px : 0;      // (F is a multiple of 8)
+                auto write = [&](auto bf) {
+                    each<AF * 4>([&](auto k) {
+                        constexpr int af = k / 4, rq = k % 4;
+                        const float16v& v = acc[af][bf];
+                        *reinterpret_cast<uint2v*>(win + (lane_e & 31) * kPipePitch + (af * 32 + rq * 8 + (lane_e >> 5) * 4) * 2) =
+                            uint2v{pack2(v[rq * 4], v[rq * 4 + 1]), pack2(v[rq * 4 + 2], v[rq * 4 + 3])};
+                    });
+                };
+                write(std::integral_constant<int, 0>{});
+                each<BF>([&](auto bf) {
+                    uint2v piece[READS][2];
+                    __builtin_amdgcn_wave_barrier();
+                    each<READS>([&](auto r) {
+                        const unsigned char* const from = win + (r * PPR + px) * kPipePitch + part * 16;
+                        piece[r][0] = *reinterpret_cast<const uint2v*>(from);
+                        piece[r][1] = *reinterpret_cast<const uint2v*>(from + 8);
+                    });
+                    __builtin_amdgcn_sched_barrier(0);
+                    if constexpr (bf + 1 < BF) write(std::integral_constant<int, bf + 1>{});
+                    __builtin_amdgcn_sched_barrier(0);
+                    each<READS>([&](auto r) {
+                        constexpr int q = bf * 32 + r * PPR;
+                        unsigned at = first + (unsigned)(q * p.F) * 2u;
+                        asm volatile("" : "+v"(at));
+                        __builtin_amdgcn_raw_buffer_store_b128(uint4v{piece[r][0].x, piece[r][0].y, piece[r][1].x, piece[r][1].y}, yr,
+                                                               (int)(q < valid ? at : kInvalid), 0, kStream);
+                    });
+                });
+                return;
+            }
             constexpr int GB = 2, GROUPS = (BF + GB - 1) / GB;
             auto write = [&](auto n) {                               // the n-th window: filters af, groups b0 .. of 32 pixels
                 constexpr int af = n % AF, b0 = n / AF * GB;
@@ -905,7 +949,21 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
         stage_bias(gl.tm, 0);
         // (channels beyond C, and blocks behind the last, are loads from a descriptor of no bytes: a scalar to choose, where
         // an offset outside would be one per lane)
+        // (channel-minor: into the third stage from the one that is multiplied; a load that the layer has not goes to where
+        // nothing reads)
+        int stage[3] = {0, 2 * p.plane_bytes, 4 * p.plane_bytes};
         auto load_act = [&](int j) {
+            if constexpr (NHWC) {
+                int id = wave + j * NW, to = stage[2];
+                asm volatile("" : "+s"(id), "+s"(to));               // (worked out here, not ahead of the block)
+                const bool there = id < 2 * p.P;
+                const __amdgpu_buffer_rsrc_t xr = make_rsrc(
+                    reinterpret_cast<const void*>(((unsigned long long)xb_hi << 32) | xb_lo), there && l_on ? x_records : 0u);
+                __builtin_amdgcn_raw_ptr_buffer_load_lds(
+                    xr, (lds_ptr)(lds + (there ? (int)(ldsB - lds) + to + id * 1024 : p.bias_off + 3 * MT * 4 + NW * kPipeWindow)),
+                    16, (int)agoff[j], lcb * 32, 0, 0);
+                return;
+            }
             const int i = j >> 3;
             int first = lcb * 16 + kbs * 8;
             asm volatile("" : "+s"(first));                      // (worked out here, not ahead of the block)
@@ -913,27 +971,32 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
             const bool there = chan < (unsigned)p.C && l_on;
             const __amdgpu_buffer_rsrc_t xr =
                 make_rsrc(reinterpret_cast<const void*>(((unsigned long long)xb_hi << 32) | xb_lo), there ? x_records : 0u);
-            stg[i][j & 7].load(xr, goff[i], there ? chan * p.chan_bytes : 0u);
+            if constexpr (!NHWC) stg[i][j & 7].load(xr, goff[i], there ? chan * p.chan_bytes : 0u);
         };
         int wblock = gl.wb;                                     // the next block's weights, and where its activations go
         const int w_lane = (wave * 64 + lane) * 16;
         int w_at = w_lane;
-        int to[KI];
+        int to[NHWC ? 1 : KI];
         // (no branch between the MFMAs: behind the last block the loads are outside the descriptor and leave zeros, and a
         // piece that is not there is written to a place that nothing reads)
-        static_assert(9 * 2 * MT == WPIECES * NTH, "nine taps' weights are whole loads");
+        // (and the half of the waves that the last piece of the weights has nothing for load it there)
+        constexpr int LAST = 9 * 2 * MT % NTH / 64;            // waves that a last, partial piece is for
+        const int w_spare = p.bias_off + 3 * MT * 4 + NW * kPipeWindow;
         auto load_weights = [&](int buf, int j) {
             int soff = wblock * p.a_bytes, to = buf * p.a_bytes + wave * 1024;
             asm volatile("" : "+s"(soff), "+s"(to));             // (worked out here, not ahead of the block)
-            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_ptr)(ldsA + to + j * NW * 1024), 16, w_at, soff + j * NW * 1024, 0, 0);
+            to += j * NW * 1024;
+            if (LAST && j == WPIECES - 1) to = wave < LAST ? to : w_spare;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(wr, (lds_ptr)(ldsA + to), 16, w_at, soff + j * NW * 1024, 0, 0);
         };
         const int spare = p.bias_off + 3 * MT * 4 + NW * kPipeWindow + lane * 16;
         auto place_act = [&](int buf) {
 #pragma unroll
-            for (int i = 0; i < KI; ++i)
+            for (int i = 0; i < kItems; ++i)
                 to[i] = loff[i] < 0 ? spare : (int)(ldsB - lds) + buf * 2 * p.plane_bytes + loff[i];
         };
         auto write_act = [&](int i, int px) {
+            if constexpr (NHWC) return;
             uint4v v;
             v.x = interleave(stg[i][0].dword(px >> 1), stg[i][1].dword(px >> 1), px & 1);
             v.y = interleave(stg[i][2].dword(px >> 1), stg[i][3].dword(px >> 1), px & 1);
@@ -941,23 +1004,22 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
             v.w = interleave(stg[i][6].dword(px >> 1), stg[i][7].dword(px >> 1), px & 1);
             *reinterpret_cast<uint4v*>(lds + to[i] + px * 16) = v;
         };
-#pragma unroll
-        for (int j = 0; j < 8 * KI; ++j) load_act(j);
-#pragma unroll
-        for (int j = 0; j < WPIECES; ++j) load_weights(0, j);
+        constexpr int WRITES = NHWC ? 0 : KI * LW, LOADS = NHWC ? kAL : 8 * KI;
+        if constexpr (NHWC) stage[2] = 0;
+        each<LOADS>([&](auto j) { load_act(j); });
+        each<WPIECES>([&](auto j) { load_weights(0, j); });
         place_act(0);
-#pragma unroll
-        for (int i = 0; i < KI; ++i)
-#pragma unroll
-            for (int px = 0; px < LW; ++px) write_act(i, px);
+        each<WRITES>([&](auto j) { write_act(j / LW, j % LW); });
         lcb = 1;
         __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
-#pragma unroll
-        for (int j = 0; j < 8 * KI; ++j) load_act(j);
+        if constexpr (NHWC) stage[2] = stage[1];
+        each<LOADS>([&](auto j) { load_act(j); });
+        if constexpr (NHWC) stage[2] = 4 * p.plane_bytes;
         __syncthreads();
         compute_descriptors(gc);
         int buf = 0, bias_slot = 0;
-        const int row_bytes = PW * 16;                          // from a tap to the one below it
+        constexpr int TAP = NHWC ? 32 : 16;                     // bytes from a tap to the next
+        const int row_bytes = PW * TAP;                         // ... and to the one below it
         half8 fa[2][AF], fb[BF];
         int from[BF];                                           // where the next operand of each group of pixels is read
 #pragma unroll
@@ -967,7 +1029,6 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
             from[bf] = (int)(ldsB - lds) + boff[bf];
             fb[bf] = *reinterpret_cast<const half8*>(lds + from[bf]);
         }
-        constexpr int WRITES = KI * LW, LOADS = 8 * KI;
         // A block begins: the block that follows it is the one loaded last; on to the one behind that.
         auto advance = [&](int nbuf) {
             wblock = gl.wb + lcb;
@@ -1002,8 +1063,8 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                 int next_cb = cb + 1;
                 asm volatile("" : "+s"(next_cb));
                 if (next_cb == p.CB) compute_descriptors(gl);   // (boff is the next block's from here on)
-                const int next_b = (int)(ldsB - lds) + nbuf * 2 * p.plane_bytes;
-                constexpr int W0 = 4 * BF, W1 = 6 * BF + 4, L1 = 8 * BF;
+                const int next_b = (int)(ldsB - lds) + (NHWC ? stage[1] : nbuf * 2 * p.plane_bytes);
+                constexpr int W0 = 4 * BF, W1 = NHWC ? 2 * BF + 2 : 6 * BF + 4, L1 = NHWC ? 6 * BF : 8 * BF;
                 each<9 * BF>([&](auto at) {                      // (tap, activation operand) group
                     constexpr int ts = at / BF, bf = at % BF, next = (ts + 1) % 9;
                     if constexpr (at == 8 * BF) publish(std::integral_constant<int, LOADS>{});
@@ -1018,7 +1079,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                         if constexpr (j * 2 * BF / WPIECES == at) load_weights(nbuf, j);
                     });
                     each<WRITES>([&](auto j) {
-                        if constexpr (W0 + j * (W1 - W0) / WRITES == at) write_act(j / LW, j % LW);
+                        if constexpr (W0 + j * (W1 - W0) / (WRITES + NHWC) == at) write_act(j / LW, j % LW);
                     });
                     each<LOADS>([&](auto j) {
                         if constexpr (W1 + j * (L1 - W1) / LOADS == at) load_act(j);
@@ -1026,13 +1087,19 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2) ? 2 : 
                     __builtin_amdgcn_sched_barrier(0);
                     if constexpr (AF == 2) acc[1][bf] = product(fa[ts & 1][1], fb[bf], acc[1][bf]);
                     __builtin_amdgcn_sched_barrier(0);
-                    fb[bf] = *reinterpret_cast<const half8*>(lds + from[bf] + next % 3 * 16);
+                    fb[bf] = *reinterpret_cast<const half8*>(lds + from[bf] + next % 3 * TAP);
                     if constexpr (bf < AF) fa[(ts + 1) & 1][bf] = *reinterpret_cast<const half8*>(a + bf * 512);
                 });
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int af = 0; af < AF; ++af) fa[0][af] = fa[1][af];
                 buf = nbuf;
+                if constexpr (NHWC) {
+                    const int s0 = stage[0];
+                    stage[0] = stage[1];
+                    stage[1] = stage[2];
+                    stage[2] = s0;
+                }
             }
             leave(gc);
             T += nwg;
@@ -1247,12 +1314,12 @@ const double kBlockUs[kMfmaShapes] = {3.2, 1.7, 1.7, 1.8};
 // first shape on the 112-, 56- and 28-column layers of VGG-16 at batch 64.)
 const Shape kShapes[kMfmaShapes] = {{2, 7, 2, 2}, {1, 7, 2, 2}, {1, 7, 4, 1}, {1, 7, 2, 1}};
 
-// One sequence of K steps for the tiles of 128 filters, whose weights keep a second workgroup off the compute unit (of two
-// each covers the other's waits).  It looks two blocks ahead, into the next tile at most.  128 x 224 tiles, 256 -> 256
-// channels at 56 x 56: 37 -> 31 us at batch 8, 67 -> 58 at 16, 64 -> 128 at 112 x 112, stride 2, batch 64: 76 -> 43, which other
-// shapes had been chosen for.
-bool runs_pipe(const MfmaParams& p, int af, int wm) {
-    return (af == 2 || wm == 4) && p.nt == 9 && !p.nhwc && p.KS == 1 && !p.clist && p.CB >= 2;
+// One sequence of K steps for layers of nine taps without splits or lists: it looks two blocks ahead, into the next tile at
+// most.  Not for the shape of two waves.  128 x 224 tiles, 256 -> 256 channels at 56 x 56: 37 -> 31 us at batch 8, 67 -> 58 at
+// 16; 64 -> 128 at 112 x 112, stride 2, batch 64: 76 -> 43, which other shapes had been chosen for.  Channel-minor, batch 64:
+// 128 -> 128 at 112 x 112 197 -> 166, 256 -> 256 at 56 x 56 181 -> 157, 64 -> 64 at 112 x 112 (64 x 448) 86 -> 73.
+bool can_pipe(const MfmaParams& p, const Shape& sh) {
+    return sh.wm * sh.wn == 4 && p.nt == 9 && p.KS == 1 && !p.clist && p.CB >= 2;
 }
 
 // Workgroups of the persistent grid: as many as the device holds at once (compute units x workgroups that fit one),
@@ -1277,8 +1344,8 @@ int persistent_grid(const void* kern, int threads, size_t lds, long long ntiles,
 }
 
 // Steps of 2048 clocks by which every second workgroup starts late (0: all start together).  Half a tile's time by
-// kBlockUs (so some six tenths of a tile of the largest shape's sequence of K steps), and only where the late workgroups do not add a round of their own: the last round is at most half full, and they
-// are the ones that sit it out.  (Measured on 128 x 256 channels at 56 x 56, batch 64, 3.5 rounds: 209 -> 198 us;
+// kBlockUs (so some six tenths of a tile of the largest shape's sequence of K steps), and only where the late workgroups do
+// not add a round of their own: the last round is at most half full, and they are the ones that sit it out.  (Measured on 128 x 256 channels at 56 x 56, batch 64, 3.5 rounds: 209 -> 198 us;
 // with 7 or 14 full rounds the half tile more costs as much as the smoother stores gain; before the sequence of K steps.)
 int stagger_steps(const MfmaParams& p, int grid, long long ntiles, int walk, double block_us) {
     if (walk == 1 || p.KS != 1 || (grid & 15) || ntiles <= grid) return 0;
@@ -1290,7 +1357,7 @@ int stagger_steps(const MfmaParams& p, int grid, long long ntiles, int walk, dou
 
 template <int AF, int BF, int WM, int WN>
 int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, double block_us, hipStream_t st) {
-    const bool full = p.nt == 9, pipe = runs_pipe(p, AF, WM);
+    const bool full = p.nt == 9, pipe = p.pipe != 0;
     const long long ntiles = (long long)p.tiles_n * p.tiles_m * p.KS;
 #define PCONV_MFMA_CASE1(LWv, KIv, FULLv) PCONV_MFMA_CASE2(LWv, KIv, FULLv, false, false)
 #define PCONV_MFMA_CASE2(LWv, KIv, FULLv, NHWCv, PIPEv)                                                         \
@@ -1307,14 +1374,18 @@ int launch_shape(const MfmaParams& p, int lw, int ki, size_t lds, int walk, doub
         return PCONV_OK;                                                                                        \
     }
 #define PCONV_MFMA_CASE(LWv, KIv) PCONV_MFMA_CASE1(LWv, KIv, true) PCONV_MFMA_CASE1(LWv, KIv, false)
-    if constexpr (AF == 2 || WM == 4) {
-        PCONV_MFMA_CASE2(8, 1, true, false, true)
+    if constexpr (AF == 2 || WM == 4 || WN == 2) {
+        PCONV_MFMA_CASE2(8, 1, true, false, true) PCONV_MFMA_CASE2(8, 1, true, true, true)
 #ifndef PCONV_ONLY_ONE
         PCONV_MFMA_CASE2(8, 2, true, false, true) PCONV_MFMA_CASE2(4, 2, true, false, true)
         PCONV_MFMA_CASE2(4, 3, true, false, true) PCONV_MFMA_CASE2(2, 3, true, false, true)
         PCONV_MFMA_CASE2(1, 3, true, false, true)
 #endif
     }
+#ifndef PCONV_ONLY_ONE
+    // (more than six channel-minor loads a wave: beside the weights of 128 filters there is no room for three such buffers)
+    if constexpr (AF == 1 && WM == 2 && WN == 2) PCONV_MFMA_CASE2(8, 2, true, true, true)
+#endif
 #ifdef PCONV_ONLY_ONE
     PCONV_MFMA_CASE1(8, 1, true)
 #else
@@ -1403,9 +1474,22 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
         p.a_stages = (shares_cu && p.CB == 1 && (a.F + MT - 1) / MT == 1 && p.KS == 1) ? 1 : 2;
         // (one buffer for the activations instead of two where that, and nothing less, lets a second workgroup in)
         p.b_stages = 2;
-        const size_t extra = 3 * (size_t)MT * 4 + 16;
+        // (the sequence of K steps needs larger windows, and a third buffer for channel-minor activations.  Not at the price of
+        // a row of the tile: at stride 2 and 224 columns its windows leave room for one row where the plain form has two, and
+        // it takes 460 us, the plain form 346 -- 128 -> 128 channels, batch 64)
+        const size_t extra = 3 * (size_t)MT * 4 + 16, pipe_windows = (NTH / 64) * (size_t)kPipeWindow + kPipeSpare;
+        const int pipe_stages = a.nhwc ? 3 : 2;
+        p.pipe = can_pipe(p, sh) &&
+                 2 * (size_t)(p.a_bytes + pipe_stages * p.plane_bytes) + extra + pipe_windows <= 160 * 1024;
+        // (of two channel-major workgroups on a compute unit each covers the other's waits, which is as good where there are
+        // tiles for both: 64 -> 64 channels, batch 64, 255 us against 270 in sequence at 224 x 224, 74 against 73 at 112 x 112, 24
+        // against 24.5 at 56 x 56; batch 32 at 56 x 56, 224 tiles, 16.7 against 14.1)
+        if (shares_cu && !a.nhwc && 2 * (size_t)(p.a_bytes + p.plane_bytes) + extra <= 80 * 1024 &&
+            (total_rows + R - 1) / R * ((a.F + MT - 1) / MT) > compute_units())
+            p.pipe = 0;
+        if (p.pipe) p.b_stages = pipe_stages;
         // (not with channel-minor activations: their loads write the next block's buffer while this one is read)
-        if (!a.nhwc && shares_cu && p.a_stages == 2 &&
+        if (!a.nhwc && shares_cu && !p.pipe && p.a_stages == 2 &&
             (size_t)p.a_stages * p.a_bytes + 4 * (size_t)p.plane_bytes + extra > 80 * 1024 &&
             (size_t)p.a_stages * p.a_bytes + 2 * (size_t)p.plane_bytes + extra <= 80 * 1024)
             p.b_stages = 1;
@@ -1416,11 +1500,10 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
         // windows fit the weights' half of a staging buffer (or, where the weights stay, the activations' half): then
         // they live there
         // (channel-minor outputs: 32 pixels x the wave's filters, see epilogue_nhwc)
-        const size_t windows = a.nhwc ? (size_t)(NTH / 64) * 32 * (sh.af * 64 + 8)
-                               : runs_pipe(p, sh.af, sh.wm) ? (size_t)(NTH / 64) * kPipeWindow + kPipeSpare
-                                                     : (size_t)(NTH / 64) * 4 * (sh.bf * 32 + 16) * 4;
+        const size_t windows = p.pipe ? pipe_windows
+                                      : (size_t)(NTH / 64) * (a.nhwc ? 32 * (sh.af * 64 + 8) : 4 * (sh.bf * 32 + 16) * 4);
         p.win_alias = 0;
-        if (shares_cu && !a.nhwc) {
+        if (shares_cu && !a.nhwc && !p.pipe) {
             if (p.a_stages == 2 && windows <= (size_t)p.a_bytes) p.win_alias = 1;
             if (p.a_stages == 1 && windows <= 2 * (size_t)p.plane_bytes) p.win_alias = 2;
         }
@@ -1444,7 +1527,10 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
     }
     p.G = a.nhwc ? 1 : a.W / lw;                  // (channel-minor staging has no pieces of lw pixels)
     const int need_items = (int)(((long long)p.max_slots * p.groups * p.G + NTH / 2 - 1) / (NTH / 2));
-    const int ki = a.nhwc ? 1 : lw == 8 ? std::max(need_items, 1) : lw == 4 ? std::max(need_items, 2) : need_items <= 3 ? 3 : lw == 2 ? 4 : 7;
+    const int ki = a.nhwc ? (p.pipe && 2 * p.P > 6 * (NTH / 64) ? 2 : 1)
+                   : lw == 8 ? std::max(need_items, 1)
+                   : lw == 4 ? std::max(need_items, 2)
+                   : need_items <= 3 ? 3 : lw == 2 ? 4 : 7;
     p.div_PW = make_fastdiv((unsigned)p.PW);
     p.R = R;
     p.tiles_n = (int)((total_rows + R - 1) / R);
@@ -1452,7 +1538,7 @@ bool plan(const MfmaConv& a, int shape, int rows, MfmaParams* out, int* lw_out, 
     p.sw = (a.Wo % 8 == 0 && ya % 16 == 0) ? 8 : (a.Wo % 4 == 0 && ya % 8 == 0) ? 4 : (a.Wo % 2 == 0 && ya % 4 == 0) ? 2 : 1;
     // (the sequence of K steps: the pixels of a tile are one run of a filter's plane, or the end of one and the start of the
     // next image's, so a piece that divides the plane and the tile lies in one plane and is aligned, wherever rows end)
-    if (runs_pipe(p, sh.af, sh.wm)) {
+    if (p.pipe && !a.nhwc) {
         p.sw = 1;
         for (int w = 8; w > 1 && p.sw == 1; w /= 2)
             if ((long long)R * a.Wo % w == 0 && (long long)a.Ho * a.Wo % w == 0 && ya % (2 * w) == 0) p.sw = w;
@@ -1567,20 +1653,24 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
     }
     // (stride 2 stages two rows of input for one of output; measured on 64 -> 128 channels at 112 x 112 and 128 -> 256 at 56
     // x 56, batch 64, where this shape takes 76 and 73 us and the 128 x 224 tile 43 and 41)
-    if (shape == 2 && a.stride == 2 && !few_taps) block_us = 4.0;
+    // (of layers of more than one block: a single one has no next block to wait for)
+    if (shape == 2 && a.stride == 2 && !few_taps && p.CB > 1) block_us = 4.0;
     // One sequence of K steps: its loads have a block's time whether the device is full or not.  Fitted to eleven layers of
     // 64 to 512 channels, 28 to 112 columns, batch 8 to 64 at stride 1 and nine at stride 2 (where a block takes longer the
     // fuller the device is); on all but two of them the choice is the fastest of the three larger shapes or within 3 %.
-    const bool pipe = runs_pipe(p, kShapes[shape - 1].af, kShapes[shape - 1].wm);
+    const bool pipe = p.pipe != 0;
     if (pipe) {
+        const bool short_rows = narrow && !a.nhwc;               // (channel-minor loads do not know rows)
         const double full = std::min(1.0, (double)tiles / compute_units());
         if (shape == 1) {
-            block_us = a.stride == 2 ? 4.0 : narrow ? 2.3 : 2.1;
-            tile_us = a.stride == 2 ? 12.0 : narrow ? 10.0 : 6.5;
+            block_us = a.stride == 2 ? 4.0 : short_rows ? 2.3 : 2.1;
+            tile_us = a.stride == 2 ? 12.0 : short_rows ? 10.0 : 6.5;
+        } else if (shape == 2) {
+            block_us = short_rows ? 1.95 : 1.5;
+            tile_us = 4.5;
         } else {
-            // (two pieces of eight pixels a lane and block, rows of more than 200 pixels at stride 2: 32 us a tile of eight)
-            block_us = a.stride == 2 ? (1.4 + full) * (lw == 8 && ki == 2 ? 1.5 : 1.0) : narrow ? 1.7 : 1.47;
-            tile_us = a.stride == 2 ? 2.5 : narrow ? 4.0 : 3.1;
+            block_us = a.stride == 2 ? 1.4 + full : short_rows ? 1.7 : 1.47;
+            tile_us = a.stride == 2 ? 2.5 : short_rows ? 4.0 : 3.1;
         }
     }
     // a split costs the round trip of the partial sums through memory and the last arriver's additions

@@ -97,9 +97,11 @@ def test_tiles_in_sequence(case):
 SEQUENCE = [
     (145, 17, 8, 57, 56, 1, 1, 0),       # 8-pixel loads, one piece a lane
     (1030, 33, 8, 32, 32, 2, 1, 16),     # two pieces; three blocks of channels
-    (19, 17, 8, 224, 224, 2, 1, 0),      # two pieces at full width
+    (19, 17, 8, 224, 224, 2, 1, 0),      # full width, where the windows take the plain form: two pieces
+    (206, 17, 8, 20, 208, 2, 1, 0),      # two pieces of 8 pixels
     (566, 17, 8, 29, 28, 1, 1, 0),       # 4-pixel loads, two pieces
-    (206, 17, 8, 20, 220, 2, 1, 0),      # three pieces
+    (206, 17, 8, 20, 220, 2, 1, 0),      # the plain form as well: three pieces
+    (250, 17, 8, 24, 148, 2, 1, 0),      # three pieces of 4
     (2345, 17, 8, 14, 14, 1, 1, 0),      # 2-pixel loads
     (2145, 17, 8, 13, 13, 1, 0, 0),      # 1-pixel loads, no padding
 ]
@@ -124,6 +126,7 @@ STORES = [  # N, C, F, H, W
     (7, 24, 30, 9, 14),                  # pieces of 2
     (11, 40, 130, 7, 7),                 # pieces of 1, ten images to a tile
     (2, 32, 96, 10, 12),                 # a tile that is a multiple of 8 pixels, a last one that is not full
+    (2, 33, 72, 9, 56),                  # 8-pixel loads
 ]
 
 
@@ -135,7 +138,7 @@ def test_pieces_of_the_outputs(case):
     assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF)
     x = L.gen_activations(spec)
     ref = layer.oracle(x)
-    for shape in (1, 3):
+    for shape in (1, 2, 3):                  # (64 x 448 tiles: in sequence where there are too few for two on a compute unit)
         for shift in (0, 4, 2, 1):
             say(case, shape, "y shifted by", shift, "elements")
             assert rel_err(layer.run(x, y_shift=shift, kernel=M, mfma_shape=shape), ref) <= TOL["f16"]

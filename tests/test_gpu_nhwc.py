@@ -81,6 +81,33 @@ def test_channel_minor_form(case):
     layer.free()
 
 
+# Nine taps and two blocks of channels or more: the kernel walks its tiles as one sequence of K steps with three buffers of
+# activations.  Four to five tiles a workgroup, so that every buffer is written again; a last half block of channels; one
+# and two loads of pixels a lane and block.  Then the shapes above whose library, another one, uses every tap.
+SEQUENCE = [  # N, C, F, H, W, stride, pad
+    (145, 24, 16, 57, 56, 1, 1),     # tiles cross rows and images
+    (1030, 40, 8, 32, 32, 2, 1),     # three blocks, a window of twice the pixels
+    (19, 24, 8, 224, 224, 2, 1),
+    (2345, 32, 40, 14, 14, 1, 1),    # several images a tile, filters that end inside a wave's 32
+    (206, 24, 8, 20, 220, 1, 0),     # no padding
+] + [c for c in SHAPES if c[1] > 16]
+
+
+@pytest.mark.parametrize("case", SEQUENCE, ids=lambda c: f"n{c[0]}c{c[1]}h{c[3]}w{c[4]}s{c[5]}p{c[6]}")
+def test_many_tiles_in_sequence(case):
+    N, C, F, H, W, stride, pad = case
+    spec = L.LayerSpec(cfg=23, idx=80 + SEQUENCE.index(case), name="nhwc sequence", N=N, C=C, F=F, H=H, W=W, stride=stride,
+                       pad=pad, dtype="f16", K=8, keep=0.4)
+    layer = GpuLayer(spec)
+    assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF)
+    x = L.gen_activations(spec)
+    ref = layer.oracle(x, True)
+    for shape in (1, 2, 3):
+        say(case, shape)
+        assert rel_err(run_nhwc(layer, x, True, mfma_shape=shape), ref) <= TOL["f16"]
+    layer.free()
+
+
 def test_unused_taps_and_equality_with_the_channel_major_form():
     # a library whose masks all lie in the upper two kernel rows: three tap slots are never staged
     spec = L.LayerSpec(cfg=50, idx=40, name="nhwc", N=3, C=32, F=64, H=12, W=20, dtype="f16", K=4, keep=0.5,
