@@ -1666,10 +1666,12 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
             block_us = a.stride == 2 ? 4.0 : short_rows ? 2.3 : 2.1;
             tile_us = a.stride == 2 ? 12.0 : short_rows ? 10.0 : 6.5;
         } else if (shape == 2) {
-            block_us = short_rows ? 1.95 : 1.5;
+            // (stride 2: 256 -> 128 at 172 x 172, batch 4, 53 us for 16 blocks, 47 in 128 x 224 tiles)
+            block_us = a.stride == 2 ? 3.0 : short_rows ? 1.95 : 1.5;
             tile_us = 4.5;
         } else {
-            block_us = a.stride == 2 ? 1.4 + full : short_rows ? 1.7 : 1.47;
+            // (128 -> 512 at 28 x 28, stride 2, batch 32: 22 us, 20 in the kernel for few tiles)
+            block_us = a.stride == 2 ? (short_rows ? 1.75 : 1.4) + full : short_rows ? 1.7 : 1.47;
             tile_us = a.stride == 2 ? 2.5 : short_rows ? 4.0 : 3.1;
         }
     }
