@@ -331,7 +331,9 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
 #pragma unroll
                 for (int w = 1; w < WAVES; ++w) sum += v[w];
                 sum += *reinterpret_cast<const float4v*>(b + fq);
-                const _Float16 out[4] = {rounded(sum[0]), rounded(sum[1]), rounded(sum[2]), rounded(sum[3])};
+                _Float16 out[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) out[i] = rounded(sum[i]);
                 uint2v o;
                 __builtin_memcpy(&o, out, 8);
                 *reinterpret_cast<uint2v*>(p.y + (((size_t)n * p.Ho + oy) * p.Wo + ox) * p.F + fbase + fq) = o;
@@ -382,7 +384,23 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
                 *reinterpret_cast<float4v*>(to + (NHWC ? bf * 32 * pitch + rq * 8 : bf * 32 + rq * 8)) = v;
             }
     };
-    auto leave = [&](int af) {
+    if constexpr (NHWC) {
+#pragma unroll
+        for (int af = 0; af < AF; ++af) {
+            __syncthreads();
+            put(acc[af]);
+            __syncthreads();
+            if (waves == 8) store(std::integral_constant<int, 8>{}, af);
+            else if (waves == 4) store(std::integral_constant<int, 4>{}, af);
+            else if (waves == 2) store(std::integral_constant<int, 2>{}, af);
+            else store(std::integral_constant<int, 1>{}, af);
+        }
+        return;
+    }
+    int halves = AF;
+    asm volatile("" : "+s"(halves));                          // (one copy of the loop)
+#pragma unroll 1
+    for (int af = 0; af < halves; ++af) {
         __syncthreads();
         if (af == 0) put(acc[0]);
         else put(acc[AF - 1]);
@@ -391,15 +409,6 @@ __global__ __launch_bounds__(512, 2) void small_conv_kernel(const SmallParams p)
         else if (waves == 4) store(std::integral_constant<int, 4>{}, af);
         else if (waves == 2) store(std::integral_constant<int, 2>{}, af);
         else store(std::integral_constant<int, 1>{}, af);
-    };
-    if constexpr (NHWC) {
-#pragma unroll
-        for (int af = 0; af < AF; ++af) leave(af);
-    } else {
-        int halves = AF;
-        asm volatile("" : "+s"(halves));                      // (one copy of the loop)
-#pragma unroll 1
-        for (int af = 0; af < halves; ++af) leave(af);
     }
 }
 
