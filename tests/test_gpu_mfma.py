@@ -101,7 +101,7 @@ SEQUENCE = [
     (206, 17, 8, 20, 208, 2, 1, 0),      # two pieces of 8 pixels
     (566, 17, 8, 29, 28, 1, 1, 0),       # 4-pixel loads, two pieces
     (206, 17, 8, 20, 220, 2, 1, 0),      # the plain form as well: three pieces
-    (250, 17, 8, 24, 148, 2, 1, 0),      # three pieces of 4
+    (330, 17, 8, 24, 148, 2, 1, 0),      # three pieces of 4
     (2345, 17, 8, 14, 14, 1, 1, 0),      # 2-pixel loads
     (2145, 17, 8, 13, 13, 1, 0, 0),      # 1-pixel loads, no padding
 ]

@@ -274,7 +274,8 @@ def test_parity_form_of_a_stride2_layer_computes_the_same_function(pad, hw):
 
 def _sequence_form(N, C, F, H, W, stride, pad, rows):
     """Pixels per load, pieces per lane and tiles of the busiest workgroup of the matrix-core kernel's largest tile (128
-    filters by 448 pixels, 256 threads, one workgroup on each of 256 compute units) for aligned pointers."""
+    filters by 448 pixels, 256 threads, one workgroup on each of 256 compute units) for aligned pointers, with the rows that
+    the sequence of K steps has room for beside its windows."""
     Ho, Wo = (H + 2 * pad - 3) // stride + 1, (W + 2 * pad - 3) // stride + 1
     pitch = W + 2 * pad
     while stride == 1 and W <= 16 and (pitch - Wo) % 8:
@@ -283,7 +284,7 @@ def _sequence_form(N, C, F, H, W, stride, pad, rows):
     for R in range(min(448 // Wo, rows or 448, N * Ho), 0, -1):
         images = 1 if Ho % R == 0 else min(R, (R + Ho - 2) // Ho + 1)
         slots = (R - images) * stride + 3 * images
-        lds = 2 * 9 * 2 * 128 * 16 + 4 * slots * pitch * 16 + 3 * 128 * 4 + 4 * 4 * (7 * 32 + 16) * 4 + 16
+        lds = 2 * 9 * 2 * 128 * 16 + 4 * slots * pitch * 16 + 3 * 128 * 4 + 4 * 32 * (64 * 2 + 8) + 64 * 16 + 7 * 16 + 16
         if lds > 160 * 1024:
             continue
         for width in (8, 4, 2, 1):
