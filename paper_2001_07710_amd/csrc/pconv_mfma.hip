@@ -598,10 +598,13 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIP
             // (the piece width is chosen once per pass: with the choice around every single store, each sat behind
             // half a dozen branches, and those, not the stores, were most of the epilogue's time)
             if (sw == 8) {
+                // (no scalar part in the offset of a 16-byte store, see epilogue_nhwc; an offset that is outside stays
+                // outside: the planes of a filter that exists end below 2^31 bytes)
 #pragma unroll
-                for (int t = 0; t < 4; ++t)
-                    __builtin_amdgcn_raw_buffer_store_b128(uint4v{o[t][0], o[t][1], o[t][2], o[t][3]}, yr, at(t, 0), foff[t],
-                                                           kStream);
+                for (int t = 0; t < 4; ++t) {
+                    const int to = f_ok[t] ? (int)(dst0[0] + (unsigned)foff[t]) : (int)kInvalid;
+                    __builtin_amdgcn_raw_buffer_store_b128(uint4v{o[t][0], o[t][1], o[t][2], o[t][3]}, yr, to, 0, kStream);
+                }
             } else if (sw == 4) {
 #pragma unroll
                 for (int t = 0; t < 4; ++t) {
