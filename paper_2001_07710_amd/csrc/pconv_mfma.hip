@@ -347,6 +347,18 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIP
         x_records = __builtin_amdgcn_readfirstlane(x_left > 0x7FFFFFFFull ? 0x7FFFFFFFu : (unsigned)x_left);
     };
 
+    // (channel-minor, a last block of eight channels: the places of the other eight hold, in memory, the next pixel's
+    // first channels, which must not meet the zeros that stand for the missing weights -- an infinity among them would reach
+    // outputs whose window does not hold it.  The lanes of that half load from outside the descriptor, until the next
+    // tile's offsets are worked out)
+    auto leave_out = [&](int cb) {
+        if constexpr (NHWC) {
+            if (cb * 16 + 8 < p.C) return;
+#pragma unroll
+            for (int i = 0; i < kAL; ++i) agoff[i] |= (uint32_t)(lane & 1) << 31;
+        }
+    };
+
     Piece<LW> stg[kItems > 0 ? kItems : 1][8];
     const int w_pieces = p.a_bytes >> 4;                       // (a multiple of 128: whole waves)
 
@@ -1014,6 +1026,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIP
         place_act(0);
         each<WRITES>([&](auto j) { write_act(j / LW, j % LW); });
         lcb = 1;
+        leave_out(1);
         __builtin_amdgcn_s_waitcnt(0x0F70);      // vmcnt(0)
         if constexpr (NHWC) stage[2] = stage[1];
         each<LOADS>([&](auto j) { load_act(j); });
@@ -1048,6 +1061,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIP
                     stage_bias(gl.tm, bias_l);
                 }
             }
+            leave_out(lcb);                                     // (two blocks or more: of a new tile's first, nothing)
         };
         // (the next block's weights have arrived: behind them only `younger` loads and stores are under way)
         auto publish = [&](auto younger) {
@@ -1119,6 +1133,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIP
     stage_descriptors(gc);
     stage_bias(gc.tm, 0);
     block_channels(gc.cb0);
+    leave_out(gc.cb0);
 #pragma unroll
     for (int j = 0; j < NLOADS; ++j) issue_one(gc.cb0, 0, j);
     if (a_stages == 1) weights_on = false;
@@ -1147,6 +1162,7 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIP
                 }
             }
             block_channels(ncb);
+            leave_out(ncb);
             const unsigned char* const a = ldsA + (a_stages == 2 ? buf : 0) * p.a_bytes + aoff;
             const unsigned char* const b = ldsB + (b_stages == 2 ? buf : 0) * 2 * p.plane_bytes;
             auto load_a = [&](int ts, int af) {

@@ -122,6 +122,49 @@ def test_unused_taps_and_equality_with_the_channel_major_form():
     layer.free()
 
 
+@pytest.mark.parametrize("case", [  # N, C, F, H, W, stride, pad, every tap used
+    (3, 24, 40, 9, 12, 1, 1, True),       # two blocks of channels, the second half full
+    (2, 8, 32, 10, 20, 1, 1, True),       # half a block
+    (2, 40, 72, 15, 18, 2, 1, True),
+    (3, 24, 16, 9, 12, 1, 0, False),
+    (700, 24, 8, 14, 14, 1, 1, False),    # several tiles a workgroup
+    (700, 24, 8, 14, 14, 1, 1, True),
+], ids=lambda c: f"n{c[0]}c{c[1]}h{c[3]}w{c[4]}s{c[5]}p{c[6]}{'' if c[7] else 'u'}")
+def test_infinities_stay_in_their_windows(case):
+    """A last block of eight channels: in memory the next pixel's first channels lie where its other eight would, and an
+    infinity there must not reach outputs whose window holds the pixel before only (at the ends of rows and images too)."""
+    N, C, F, H, W, stride, pad, full = case
+    spec = L.LayerSpec(cfg=23, idx=90, name="nhwc", N=N, C=C, F=F, H=H, W=W, stride=stride, pad=pad, dtype="f16", K=8,
+                       keep=0.4)
+    if not full:
+        spec = L.LayerSpec(**{**spec.__dict__, "K": 2, "lib_kind": "fixed4"})
+    layer = GpuLayer(spec)
+    assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF) == full
+    clean = L.gen_activations(spec)
+    ref = layer.oracle(clean)
+    x, inside = clean.copy(), np.zeros((N, spec.Ho, spec.Wo), bool)
+    for n, iy, ix, c in ((0, 4, 6, 0), (0, 7, 0, 7), (N - 1, 0, 0, 3), (N - 2, H - 1, 3, 1)):
+        x[n, c, iy, ix] = np.inf
+        oy, ox = np.arange(spec.Ho) * stride - pad, np.arange(spec.Wo) * stride - pad
+        inside[n] |= ((oy <= iy) & (iy <= oy + 2))[:, None] & ((ox <= ix) & (ix <= ox + 2))[None, :]
+    outside = np.broadcast_to(~inside[:, None], ref.shape)
+    ran = 0
+    for t in [{}] + [dict(mfma_shape=s, channel_splits=k) for s in (1, 2, 3, 4) for k in (1, 2)]:
+        say(case, t)
+        try:
+            want = run_nhwc(layer, clean, False, **t)
+        except pc.PconvError as e:
+            assert e.code == pc.EUNSUPPORTED and t, (case, t, e.code)
+            continue
+        ran += 1
+        assert rel_err(want, ref) <= TOL["f16"]
+        got = run_nhwc(layer, x, False, **t)
+        assert not np.isfinite(got).all()
+        assert np.array_equal(got[outside], want[outside]), (case, t)
+    assert ran >= 4
+    layer.free()
+
+
 def test_what_the_form_refuses():
     import torch
     one = torch.zeros(4096, dtype=torch.float16, device="cuda")
