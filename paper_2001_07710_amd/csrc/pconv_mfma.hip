@@ -817,8 +817,13 @@ __global__ __launch_bounds__(WM* WN * 64, (AF == 1 && WM == 2 && WN == 2 && !PIP
             return sum;
         };
         // fp16 and ReLU, two values at once (as in the epilogue above), read one by one where they are needed: left to the
-        // compiler, whole accumulators move to vector registers ahead of the epilogue, and what lay there moves to scratch.  (The
-        // accumulator that is read first had its last MFMA twelve MFMAs ago: nothing to wait for.)
+        // compiler, whole accumulators move to vector registers ahead of the epilogue, and what lay there moves to scratch.
+        // In front of such a read the compiler does not put the wait that an MFMA's result needs (11 issue slots behind one of
+        // eight passes, as these are, 19 behind the longest), so other instructions have to fill it.  The groups of pixels that
+        // the first window holds, one or two of them, have AF * (BF - 2) MFMAs or more behind their own, eight slots each; a
+        // later window has the 16 reads or more of every window before it in front, and at least another MFMA's slots or a
+        // second window's reads.
+        static_assert(AF * (BF - 2) >= 3, "24 slots between a result of the first window and its read");
         const half2v floor2 = __builtin_bit_cast(half2v, p.relu ? 0u : 0x7E007E00u);
         auto value = [&](float acc_value) {
             float f;
