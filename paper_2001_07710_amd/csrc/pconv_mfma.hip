@@ -1626,6 +1626,23 @@ int mfma_shape_height(int shape) {
     return shape >= 1 && shape <= kMfmaShapes ? kShapes[shape - 1].wm * kShapes[shape - 1].af * 32 : 0;
 }
 
+// Prices of nine-tap layers of two blocks or more on channel-major tensors, microseconds: a block with loads of 8, 4, 2 and 1
+// pixels and the fewest pieces a lane that the kernel is built for, what every further piece adds, the part of a block's time
+// that a device without work for it saves; a tile besides its blocks; a million bytes of outputs stored in pieces of 8, 4, 2 and
+// 1 pixels, and what they cost more without padding.  Fitted to 3,300 forced launches of 1,970 random layers (17 to 512
+// channels, maps of 7 to 224, batch 1 to 64), which they meet within 6 to 8 % (standard deviation; 15 to 26 % by one price for
+// all widths, as this was: 160 -> 512 channels at 127 x 127, 2 images, went to 128 x 224 tiles and took 111 us, 67 in the kernel
+// for few tiles).
+struct Price {
+    double block[4], piece, idle, tile, store[4], unpadded;
+};
+const Price kSequencePrice[3] = {
+    {{2.1, 2.4, 2.65, 2.65}, 0.6, 0.1, 2.8, {0.05, 0.17, 0.27, 0.75}, 0.22},
+    {{1.55, 1.85, 2.3, 1.95}, 0.5, 0.0, 0.2, {0.13, 0.28, 0.34, 0.8}, 0.1},
+    {{1.47, 1.72, 1.87, 1.87}, 0.8, 0.15, 1.6, {0.03, 0.11, 0.21, 0.48}, 0.08},
+};
+const Price kSharedPrice = {{2.77, 2.65, 2.89, 2.7}, 1.05, 0.0, 3.3, {0.02, 0.16, 0.3, 0.75}, 0.0};   // (64 x 448, two to a compute unit)
+
 // Estimated run time, in microseconds, of the layer with tile shape `shape` (1..kMfmaShapes); negative if the shape
 // cannot take it.  Rounds of resident workgroups times (a fixed part + channel blocks x time per block).  The block
 // times are measured ones (MI355X, VGG-16 and ResNet-50 shapes); while a workgroup has its compute unit to itself a
@@ -1665,8 +1682,8 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
     const bool narrow = a.W < 56;
     double block_us = kBlockUs[shape - 1], tile_us = 8.0;
     if (shape == 1) block_us = narrow ? 2.65 : 2.3;
+    const bool shared = shape == 2 && per_cu == 2 && tiles > (long long)compute_units();
     if (shape == 2) {
-        const bool shared = per_cu == 2 && tiles > (long long)compute_units();
         block_us = shared ? (narrow ? 2.85 : 2.7) : 1.7;
         tile_us = shared ? 5.0 : 2.8;
     }
@@ -1679,24 +1696,35 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
     // x 56, batch 64, where this shape takes 76 and 73 us and the 128 x 224 tile 43 and 41)
     // (of layers of more than one block: a single one has no next block to wait for)
     if (shape == 2 && a.stride == 2 && !few_taps && p.CB > 1) block_us = 4.0;
-    // One sequence of K steps: its loads have a block's time whether the device is full or not.  Fitted to eleven layers of
-    // 64 to 512 channels, 28 to 112 columns, batch 8 to 64 at stride 1 and nine at stride 2 (where a block takes longer the
-    // fuller the device is); on all but two of them the choice is the fastest of the three larger shapes or within 3 %.
-    const bool pipe = p.pipe != 0;
-    if (pipe) {
-        const bool short_rows = narrow && !a.nhwc;               // (channel-minor loads do not know rows)
+    // Nine taps, channel-major: the price by the width of the loads and stores.  (One sequence of K steps: its loads have a
+    // block's time whether the device is full or not.  64 x 448 tiles two to a compute unit: each has the other's.)
+    const bool priced = p.nt == 9 && p.CB >= 2 && p.KS == 1 && !a.nhwc && (p.pipe || shared);
+    double stores_us = 0.0;
+    if (priced) {
+        const Price& price = p.pipe ? kSequencePrice[shape - 1] : kSharedPrice;
+        const int w = lw == 8 ? 0 : lw == 4 ? 1 : lw == 2 ? 2 : 3, least = w == 0 ? 1 : w == 1 ? 2 : 3;
+        const double full = std::min(1.0, (double)tiles / compute_units());
+        block_us = (price.block[w] + price.piece * std::max(0, ki - least)) * (1.0 - price.idle * (1.0 - full));
+        if (a.stride == 2) block_us += 0.25;
+        tile_us = price.tile;
+        // (the sequence's pieces of 8 pixels are no better than pieces of 4 where a tile's run of pixels or a plane ends inside
+        // a sector of 32 bytes)
+        const bool whole = p.sw == 8 && (!p.pipe || ((long long)p.R * a.Wo % 16 == 0 && (long long)a.Ho * a.Wo % 16 == 0));
+        const double store = price.store[whole ? 0 : p.sw >= 4 ? 1 : p.sw == 2 ? 2 : 3] + (a.pad == 0 ? price.unpadded : 0.0);
+        stores_us = (double)p.y_bytes / 1e6 * store;
+    } else if (p.pipe) {
+        // (channel-minor, whose loads and stores are of 16 bytes whatever the sizes; at stride 2 a block takes longer the
+        // fuller the device is)
         const double full = std::min(1.0, (double)tiles / compute_units());
         if (shape == 1) {
-            block_us = a.stride == 2 ? 4.0 : short_rows ? 2.3 : 2.1;
-            tile_us = a.stride == 2 ? 12.0 : short_rows ? 10.0 : 6.5;
+            block_us = a.stride == 2 ? 4.0 : 2.1;
+            tile_us = a.stride == 2 ? 12.0 : 6.5;
         } else if (shape == 2) {
-            // (stride 2: 256 -> 128 at 172 x 172, batch 4, 53 us for 16 blocks, 47 in 128 x 224 tiles)
-            block_us = a.stride == 2 ? 3.0 : short_rows ? 1.95 : 1.5;
+            block_us = a.stride == 2 ? 3.0 : 1.5;
             tile_us = 4.5;
         } else {
-            // (128 -> 512 at 28 x 28, stride 2, batch 32: 22 us, 20 in the kernel for few tiles)
-            block_us = a.stride == 2 ? (short_rows ? 1.75 : 1.4) + full : short_rows ? 1.7 : 1.47;
-            tile_us = a.stride == 2 ? 2.5 : short_rows ? 4.0 : 3.1;
+            block_us = a.stride == 2 ? 1.4 + full : 1.47;
+            tile_us = a.stride == 2 ? 2.5 : 3.1;
         }
     }
     // a split costs the round trip of the partial sums through memory and the last arriver's additions
@@ -1718,7 +1746,7 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
         for (int sp = 0; sp < 2; ++sp) us[sp] = (rounds * (8.0 + blocks * staged_us) + split_us[sp]) * (shape == 3 ? 1.0 : 2.0);
         return;
     }
-    for (int sp = 0; sp < 2; ++sp) us[sp] = rounds * (tile_us + blocks * std::max(block_us, pipe ? 0.0 : floor_us)) + split_us[sp];
+    for (int sp = 0; sp < 2; ++sp) us[sp] = rounds * (tile_us + blocks * std::max(block_us, priced || p.pipe ? 0.0 : floor_us)) + stores_us + split_us[sp];
 }
 
 int mfma_workspace(const MfmaConv& a, size_t* floats, size_t* counters) {

@@ -249,3 +249,21 @@ def test_1x1_layers_whose_planes_crowd_the_cache_are_priced_as_such(case):
     kernel, shape = pc.conv3x3_choice(p, N, H, W, 1, 1)                 # (a 1x1 layer is a 3x3 one of centre taps)
     assert kernel == M and shape not in (5, 6) and (shape != 7 or H == 32)
     p.free()
+
+
+@pytest.mark.parametrize("case", [  # N, C, F, H, W
+    (2, 160, 512, 127, 127), (4, 96, 96, 158, 158), (25, 226, 208, 43, 57), (32, 149, 144, 45, 61), (1, 96, 448, 167, 150),
+    (2, 128, 384, 121, 121)])
+def test_rows_that_only_narrow_loads_divide_are_priced_as_such(case):
+    """Nine taps, rows of an odd number of pixels or of pairs: small tiles took 67, 33, 103, 75, 36 and 47 us on these layers,
+    128 x 224 tiles 111, 50, 152, 100, 52 and 65 (and the other large tiles more)."""
+    N, C, F, H, W = case
+    say("narrow rows", case)
+    r = np.random.default_rng(C + F)
+    lib = L.drawn_library(23, 8)
+    assert np.bitwise_or.reduce(lib) == 0x1FF
+    p = pc.pack((r.standard_normal((F, C, 3, 3)) * 0.05).astype(np.float16), lib, r.integers(0, 8, (F, C)).astype(np.uint8),
+                (r.random((F, C)) < 0.28).astype(np.uint8))
+    kernel, shape = pc.conv3x3_choice(p, N, H, W, 1, 1)
+    assert kernel == M and shape >= 5
+    p.free()
