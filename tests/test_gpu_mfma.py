@@ -92,29 +92,33 @@ def test_tiles_in_sequence(case):
 
 
 # The same with five tiles or more for some workgroups, so that the three places for a tile's bias come round, and one case at
-# least for every load width and number of pieces a lane that the kernel is built for (test_host_logic.py holds the table to
-# both): N, C, F, H, W, stride, pad, most rows of a tile
+# least for every load width and number of pieces a lane that the kernel is built for, in every shape that comes to several
+# tiles with them; the last column is the shapes that run the row in sequence, the others take the plain form (test_host_logic.py
+# holds the table to all of it): N, C, F, H, W, stride, pad, most rows of a tile, shapes
 SEQUENCE = [
-    (145, 17, 8, 57, 56, 1, 1, 0),       # 8-pixel loads, one piece a lane
-    (1030, 33, 8, 32, 32, 2, 1, 16),     # two pieces; three blocks of channels
-    (19, 17, 8, 224, 224, 2, 1, 0),      # full width, where the windows take the plain form: two pieces
-    (206, 17, 8, 20, 208, 2, 1, 0),      # two pieces of 8 pixels
-    (566, 17, 8, 29, 28, 1, 1, 0),       # 4-pixel loads, two pieces
-    (206, 17, 8, 20, 220, 2, 1, 0),      # the plain form as well: three pieces
-    (330, 17, 8, 24, 148, 2, 1, 0),      # three pieces of 4
-    (2345, 17, 8, 14, 14, 1, 1, 0),      # 2-pixel loads
-    (2145, 17, 8, 13, 13, 1, 0, 0),      # 1-pixel loads, no padding
+    (145, 17, 8, 57, 56, 1, 1, 0, (1, 3)),             # 8-pixel loads, one piece a lane
+    (1030, 33, 8, 32, 32, 2, 1, 14, (1, 3)),           # three blocks of channels
+    (19, 17, 8, 224, 224, 2, 1, 0, ()),                # full width: no room for the windows of the sequence
+    (310, 33, 8, 20, 208, 2, 1, 0, (1, 2, 3)),         # two pieces of 8 pixels, three blocks
+    (12895, 33, 8, 8, 8, 1, 0, 0, (2, 3)),             # 8-pixel loads, up to 14 images a tile
+    (566, 17, 8, 29, 28, 1, 1, 0, (1, 3)),             # 4-pixel loads, two pieces
+    (206, 17, 8, 20, 220, 2, 1, 0, ()),
+    (330, 17, 8, 24, 148, 2, 1, 0, (1, 3)),            # three pieces of 4
+    (314, 40, 8, 20, 172, 2, 1, 0, (1, 2, 3)),         # two, of 64 x 448 three
+    (2345, 17, 8, 14, 14, 1, 1, 0, (1, 3)),            # 2-pixel loads
+    (12895, 33, 8, 6, 6, 1, 1, 0, (2, 3)),
+    (2145, 17, 8, 13, 13, 1, 0, 0, (1, 3)),            # 1-pixel loads, no padding
 ]
 
 
 @pytest.mark.parametrize("case", SEQUENCE, ids=lambda c: f"n{c[0]}c{c[1]}h{c[3]}w{c[4]}s{c[5]}p{c[6]}")
 def test_many_tiles_in_sequence(case):
-    N, C, F, H, W, stride, pad, rows = case
+    N, C, F, H, W, stride, pad, rows, _ = case
     spec = L.LayerSpec(cfg=23, idx=C + W, name="long sequence", N=N, C=C, F=F, H=H, W=W, stride=stride, pad=pad, dtype="f16",
                        K=8, keep=0.4)
     layer = GpuLayer(spec)
     assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF)      # (nine taps: the form is theirs)
-    run_forms(layer, L.gen_activations(spec), [dict(kernel=M, mfma_shape=sh, rows=rows) for sh in (1, 3)])
+    run_forms(layer, L.gen_activations(spec), [dict(kernel=M, mfma_shape=sh, rows=rows) for sh in (1, 2, 3)])
     layer.free()
 
 

@@ -82,20 +82,24 @@ def test_channel_minor_form(case):
 
 
 # Nine taps and two blocks of channels or more: the kernel walks its tiles as one sequence of K steps with three buffers of
-# activations.  Four to five tiles a workgroup, so that every buffer is written again; a last half block of channels; one
-# and two loads of pixels a lane and block.  Then the shapes above whose library, another one, uses every tap.
-SEQUENCE = [  # N, C, F, H, W, stride, pad
-    (145, 24, 16, 57, 56, 1, 1),     # tiles cross rows and images
-    (1030, 40, 8, 32, 32, 2, 1),     # three blocks, a window of twice the pixels
-    (19, 24, 8, 224, 224, 2, 1),
-    (2345, 32, 40, 14, 14, 1, 1),    # several images a tile, filters that end inside a wave's 32
-    (206, 24, 8, 20, 220, 1, 0),     # no padding
+# activations.  Five tiles or more for some workgroups, so that every buffer is written again; a last half block of channels;
+# one and two loads of pixels a lane and block; the last column is the shapes that run the row in sequence (test_host_logic.py
+# holds the table to it).  Then the shapes above whose library, another one, uses every tap.
+SEQUENCE = [  # N, C, F, H, W, stride, pad, shapes
+    (145, 24, 16, 57, 56, 1, 1, (1, 2, 3)),     # tiles cross rows and images
+    (566, 40, 8, 29, 28, 1, 1, (1, 2, 3)),      # three blocks
+    (73, 40, 8, 29, 150, 1, 1, (2, 3)),         # 64 x 448: two loads of pixels
+    (70, 40, 8, 29, 204, 2, 1, (1, 3)),         # stride 2, a window of twice the pixels
+    (206, 40, 8, 20, 192, 2, 1, (2,)),
+    (19, 24, 8, 224, 224, 2, 1, (1,)),
+    (2345, 32, 40, 14, 14, 1, 1, (2, 3)),       # several images a tile, filters that end inside a wave's 32
+    (206, 24, 8, 20, 220, 1, 0, (2, 3)),        # no padding
 ] + [c for c in SHAPES if c[1] > 16]
 
 
 @pytest.mark.parametrize("case", SEQUENCE, ids=lambda c: f"n{c[0]}c{c[1]}h{c[3]}w{c[4]}s{c[5]}p{c[6]}")
 def test_many_tiles_in_sequence(case):
-    N, C, F, H, W, stride, pad = case
+    N, C, F, H, W, stride, pad = case[:7]
     spec = L.LayerSpec(cfg=23, idx=80 + SEQUENCE.index(case), name="nhwc sequence", N=N, C=C, F=F, H=H, W=W, stride=stride,
                        pad=pad, dtype="f16", K=8, keep=0.4)
     layer = GpuLayer(spec)

@@ -272,33 +272,74 @@ def test_parity_form_of_a_stride2_layer_computes_the_same_function(pad, hw):
     p.free()
 
 
-def _sequence_form(N, C, F, H, W, stride, pad, rows):
-    """Pixels per load, pieces per lane and tiles of the busiest workgroup of the matrix-core kernel's largest tile (128
-    filters by 448 pixels, 256 threads, one workgroup on each of 256 compute units) for aligned pointers, with the rows that
-    the sequence of K steps has room for beside its windows."""
+TILES = {1: (128, 448, 2), 2: (64, 448, 1), 3: (128, 224, 1)}    # filters, pixels, operands of 32 filters a wave
+
+
+def _sequence_form(shape, N, C, F, H, W, stride, pad, rows=0, channel_minor=False):
+    """Whether the matrix-core kernel runs a nine-tap layer in tiles of this shape as one sequence of K steps: pixels per
+    load, pieces per lane (channel-minor: 8 and the loads of pixels, in sixes) and tiles of the busiest workgroup, for
+    aligned pointers and one workgroup of 256 threads on each of 256 compute units; None where it takes the plain form."""
+    filters, pixels, operands = TILES[shape]
     Ho, Wo = (H + 2 * pad - 3) // stride + 1, (W + 2 * pad - 3) // stride + 1
     pitch = W + 2 * pad
     while stride == 1 and W <= 16 and (pitch - Wo) % 8:
         pitch += 1
+    blocks, pair, full = -(-C // 16), shape == 2, 160 * 1024      # (pair: two workgroups fit a compute unit)
+    weights, rest = 9 * 2 * filters * 16, 3 * filters * 4 + 16
+    wide, buffers = 4 * 32 * (64 * 2 + 8) + 64 * 16 + 7 * 16, 3 if channel_minor else 2      # the sequence's windows, buffers
     most = {8: 2, 4: 3, 2: 3, 1: 3}                    # pieces a lane
-    for R in range(min(448 // Wo, rows or 448, N * Ho), 0, -1):
+    for R in range(min(pixels // Wo, rows or pixels, N * Ho), 0, -1):
         images = 1 if Ho % R == 0 else min(R, (R + Ho - 2) // Ho + 1)
         slots = (R - images) * stride + 3 * images
-        lds = 2 * 9 * 2 * 128 * 16 + 4 * slots * pitch * 16 + 3 * 128 * 4 + 4 * 32 * (64 * 2 + 8) + 64 * 16 + 7 * 16 + 16
-        if lds > 160 * 1024:
+        loads = -(-slots * pitch // 64)
+        plane = loads * 1024 if channel_minor else slots * pitch * 16
+        tiles = -(-N * Ho // R) * -(-F // filters)
+        sequence = blocks >= 2 and 2 * (weights + buffers * plane) + rest + wide <= full
+        if pair and not channel_minor and 2 * (weights + plane) + rest <= full // 2 and tiles > 256:
+            sequence = False
+        # the rows are those that the form has room for; a row less for the sequence's sake is never taken
+        kept = 1 if pair and blocks == 1 and F <= filters else 2
+        held, windows = 2, 4 * (32 * (operands * 64 + 8) if channel_minor else 4 * (7 * 32 + 16) * 4)
+        if sequence:
+            held, windows = buffers, wide
+        elif pair and not channel_minor:
+            if kept == 2 and 2 * weights + 4 * plane + rest > full // 2 and 2 * weights + 2 * plane + rest <= full // 2:
+                held = 1
+            if windows <= (weights if kept == 2 else 2 * plane):
+                windows = 0
+        if kept * weights + 2 * held * plane + rest + windows > full:
             continue
-        for width in (8, 4, 2, 1):
-            if W % width == 0 and slots * (W // width) <= most[width] * 128:
-                pieces = -(-slots * (W // width) // 128)
-                tiles = -(-N * Ho // R) * -(-F // 128)
-                return width, max(pieces, {8: 1, 4: 2}.get(width, 3)), -(-tiles // 256)
+        if channel_minor:
+            if 2 * loads > 12 * 4:
+                continue
+            width, pieces = 8, -(-2 * loads // (6 * 4))
+        else:
+            width = next((w for w in (8, 4, 2, 1) if W % w == 0 and slots * (W // w) <= most[w] * 128), 0)
+            if not width:
+                continue
+            pieces = max(-(-slots * (W // width) // 128), {8: 1, 4: 2}.get(width, 3))
+        return (width, pieces, -(-tiles // 256)) if sequence else None
 
 
-def test_table_of_tiles_in_sequence_holds_every_form():
-    from test_gpu_mfma import SEQUENCE
-    forms = set()
-    for case in SEQUENCE:
-        width, pieces, tiles = _sequence_form(*case)
-        assert tiles >= 5, case
-        forms.add((width, pieces))
-    assert forms == {(8, 1), (8, 2), (4, 2), (4, 3), (2, 3), (1, 3)}
+def test_tables_of_tiles_in_sequence_hold_every_form():
+    import test_gpu_mfma
+    import test_gpu_nhwc
+    tables = [[(case[:7], case[7], case[8]) for case in test_gpu_mfma.SEQUENCE],
+              [(case[:7], 0, case[7]) for case in test_gpu_nhwc.SEQUENCE if len(case) == 8]]
+    every = {(8, 1), (8, 2), (4, 2), (4, 3), (2, 3), (1, 3)}
+    # (64 x 448 tiles, channel-major: with 4-pixel loads in two pieces and 1-pixel loads there is room for a second workgroup
+    # wherever there are tiles for it)
+    want = [{1: every, 2: {(8, 1), (8, 2), (4, 3), (2, 3)}, 3: every}, {1: {(8, 1)}, 2: {(8, 1), (8, 2)}, 3: {(8, 1)}}]
+    for channel_minor, table in enumerate(tables):
+        forms, deep = {1: set(), 2: set(), 3: set()}, set()
+        for case, rows, shapes in table:
+            found = {s: _sequence_form(s, *case, rows, bool(channel_minor)) for s in (1, 2, 3)}
+            assert tuple(s for s in found if found[s]) == shapes, (case, found)
+            for s in shapes:
+                width, pieces, tiles = found[s]
+                assert tiles >= 5, (case, s, tiles)              # (the three places for a tile's bias come round)
+                forms[s].add((width, pieces))
+                if case[1] > 32:
+                    deep.add(s)
+        assert forms == want[channel_minor]
+        assert deep == {1, 2, 3}                                 # three blocks of channels or more, in every shape
