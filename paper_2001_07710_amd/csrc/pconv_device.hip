@@ -2897,17 +2897,19 @@ static int conv3x3_impl(const void* x, void* y, const pconv_packed* wp, const fl
         // Against each other, the kernels' estimates need a common scale: this one's is of the whole launch, the tile
         // kernel's leaves out some 6 us (measured on layers of few blocks), and so does what the vector kernels are
         // compared with below -- there the tile kernel stands with its own number.
-        // (nine taps, channel-major, two blocks of channels or more, where the tile kernel's estimate is good to 8 %: this
-        // kernel takes 0.95 of its own at 15 us, 0.9 at 30, 0.75 at 100 and above, in the mean of 1,600 random layers, and at
-        // stride 2 less still: 128 -> 512 at 28 x 28, batch 32, 19.2 us of 25.7)
-        const bool by_width = !nhwc && a.n_taps == 9 && wp->C > 16;
+        // (nine taps, channel-major, no lists, two blocks of channels or more, where the tile kernel's estimate is good to 8 %:
+        // this kernel takes 0.95 of its own at 15 us, 0.9 at 30, 0.75 at 100 and above, in the mean of 1,600 random layers,
+        // and at stride 2 less still: 128 -> 512 at 28 x 28, batch 32, 19.2 us of 25.7)
+        bool by_width = !nhwc && a.n_taps == 9 && wp->C > 16;
+        for (const MfmaWeights& m : wp->mfma)
+            if (m.mt == mfma_shape_height(a.shape) && m.groups == a.groups) by_width = by_width && !m.d_clist;
         const double tile_us = best_us;
         double bar_us = tile_us >= 0.0 ? tile_us + 6.0 : -1.0;
         if (by_width && bar_us >= 0.0) bar_us = (bar_us + 0.5) * std::min(1.3, 1.0 + (bar_us + 0.5) / (stride == 2 ? 150.0 : 300.0));
         // (channel-minor at stride 2 a step reads a quarter of each 128-byte line, and where the input does not stay in the
         // caches the next step fetches the line again: this kernel takes 1.3 to 1.6 times its estimate above 128 MB.  416 -> 48
         // channels at 139 x 93, 20 images: 150 us, 85 in 64 x 448 tiles)
-        if (nhwc && stride == 2 && bar_us >= 0.0 && 2.0 * N * wp->C * H * W > 128e6) bar_us *= 0.65;
+        if (nhwc && stride == 2 && !wp->is_1x1 && bar_us >= 0.0 && 2.0 * N * wp->C * H * W > 128e6) bar_us *= 0.65;
         if (!known && (want_shape == 0 ? !forced || (nhwc && all_auto) : want_shape > kMfmaShapes) && use_weights(wp, 64, 1, &small)) {
             const MfmaConv base = small;
             for (int sh = 0; sh < kSmallShapes; ++sh) {

@@ -1626,13 +1626,13 @@ int mfma_shape_height(int shape) {
     return shape >= 1 && shape <= kMfmaShapes ? kShapes[shape - 1].wm * kShapes[shape - 1].af * 32 : 0;
 }
 
-// Prices of nine-tap layers of two blocks or more on channel-major tensors, microseconds: a block with loads of 8, 4, 2 and 1
-// pixels and the fewest pieces a lane that the kernel is built for, what every further piece adds, the part of a block's time
-// that a device without work for it saves; a tile besides its blocks; a million bytes of outputs stored in pieces of 8, 4, 2 and
-// 1 pixels, and what they cost more without padding.  Fitted to 3,300 forced launches of 1,970 random layers (17 to 512
-// channels, maps of 7 to 224, batch 1 to 64), which they meet within 6 to 8 % (standard deviation; 15 to 26 % by one price for
-// all widths, as this was: 160 -> 512 channels at 127 x 127, 2 images, went to 128 x 224 tiles and took 111 us, 67 in the kernel
-// for few tiles).
+// Prices of nine-tap layers of two blocks or more without lists on channel-major tensors, microseconds: a block with loads of
+// 8, 4, 2 and 1 pixels and the fewest pieces a lane that the kernel is built for, what every further piece adds, the part of a
+// block's time that a device without work for it saves; a tile besides its blocks; a million bytes of outputs stored in pieces
+// of 8, 4, 2 and 1 pixels, and what they cost more without padding.  Fitted to 3,300 forced launches of 1,970 random layers (17
+// to 512 channels, maps of 7 to 224, batch 1 to 64), which they meet within 6 to 8 % (standard deviation; 15 to 26 % by one
+// price for all widths, as this was: 160 -> 512 channels at 127 x 127, 2 images, went to 128 x 224 tiles and took 111 us, 67 in
+// the kernel for few tiles).
 struct Price {
     double block[4], piece, idle, tile, store[4], unpadded;
 };
@@ -1696,9 +1696,11 @@ void mfma_estimate_us(const MfmaConv& a0, int shape, int splits, double us[2]) {
     // x 56, batch 64, where this shape takes 76 and 73 us and the 128 x 224 tile 43 and 41)
     // (of layers of more than one block: a single one has no next block to wait for)
     if (shape == 2 && a.stride == 2 && !few_taps && p.CB > 1) block_us = 4.0;
-    // Nine taps, channel-major: the price by the width of the loads and stores.  (One sequence of K steps: its loads have a
-    // block's time whether the device is full or not.  64 x 448 tiles two to a compute unit: each has the other's.)
-    const bool priced = p.nt == 9 && p.CB >= 2 && p.KS == 1 && !a.nhwc && (p.pipe || shared);
+    // Nine taps, channel-major, no lists: the price by the width of the loads and stores.  (One sequence of K steps: its loads
+    // have a block's time whether the device is full or not.  64 x 448 tiles two to a compute unit: each has the other's.
+    // Layers with lists run the plain form in every shape, and the prices of that compare with each other: 512 -> 512 at 28 x 28,
+    // batch 64, 108 of 128 blocks, 209 us in 128 x 448 tiles and 228 in 64 x 448.)
+    const bool priced = p.nt == 9 && p.CB >= 2 && p.KS == 1 && !a.nhwc && !p.clist && (p.pipe || shared);
     double stores_us = 0.0;
     if (priced) {
         const Price& price = p.pipe ? kSequencePrice[shape - 1] : kSharedPrice;

@@ -161,3 +161,18 @@ def test_clustered_layer_at_a_benchmark_shape():
     rms = float(np.sqrt(np.mean(ref_first ** 2)))
     assert np.max(np.abs(pts - ref_pts) / np.maximum(np.abs(ref_pts), rms)) <= tol
     packed.free()
+
+
+def test_layers_with_lists_are_priced_alike_in_every_shape():
+    """Filters of a clustered layer in their own order, 512 -> 512 at 28 x 28, batch 64: 128 x 448 tiles take 209 us, the
+    64 x 448 ones, whose price for layers without lists is another, 228."""
+    spec = [s for s in L.config4(8, 0.28, 64) if s.name == "conv4_2"][0]
+    say("lists", spec.name)
+    w, _ = L.gen_clustered_weights(spec, spec.F // 128, 1.25 * spec.keep)
+    lib, w32 = spec.library(), w.astype(np.float32)
+    pid = pc.assign_patterns(w32, lib)
+    packed = pc.pack(w, lib, pid, pc.select_connectivity(w32, lib, pid, spec.keep))
+    listed, every = pc.packed_mfma_blocks(packed, 128)
+    assert listed < every
+    assert pc.conv3x3_choice(packed, spec.N, spec.H, spec.W, 1, 1) == (pc.KERNEL_MFMA, 1)
+    packed.free()
