@@ -406,8 +406,8 @@ def sweep_bench(args, torch, pc, L, stream):
                      "dense_us": None if dense_per is None else dense_per[i] * 1e3})
     tot_t = sum(per) * 1e-3
     # the dominant kernel: mfma_conv_kernel.  Its launches fall under two roofs: the matrix cores for most layers, HBM
-    # for the two 224 x 224 layers (64 filters or fewer: little arithmetic per byte).  `roofline` is that of the
-    # launches the matrix cores bind; the others are in `roofline_hbm_bound_launches`; the time-weighted fraction of
+    # for the two 224 x 224 layers (64 filters or fewer: little arithmetic per byte): the roof that a launch is nearer to,
+    # which is not to say that it is what holds the launch back.  `roofline` is that of the launches under the matrix cores'; the others are in `roofline_hbm_bound_launches`; the time-weighted fraction of
     # the binding roof over all of the kernel's launches is in `roofline` as well.  Per launch = the mean over them.
     all_mfma = on_mfma if on_mfma else list(range(len(specs)))
     dom = [i for i in all_mfma if rows[i]["bound"] != "hbm"] or all_mfma

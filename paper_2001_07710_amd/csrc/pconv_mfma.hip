@@ -12,7 +12,8 @@
 //
 // Roles.  D[filter][pixel] += A[filter][channel] * B[channel][pixel] per tap: A = weights, B = activations shifted by
 // the tap.  With that assignment a lane of the result holds one pixel and its registers hold filters, so NCHW rows
-// are contiguous across lanes.
+// are contiguous across lanes.  (In the sequence of K steps on channel-major tensors the operands change places: a lane holds
+// runs of pixels of one filter.)
 //
 // Tile.  A workgroup of WM x WN waves owns MT = WM*AF*32 filters and R consecutive output rows of the batch (rows
 // numbered n*Ho + oy, so a tile may run from one image into the next) = up to NT = WN*BF*32 output pixels; a wave
@@ -1332,7 +1333,8 @@ struct Shape {
 // tile's first form: a block of its sequence of K steps takes about 2.2, see stagger_steps)
 const double kBlockUs[kMfmaShapes] = {3.2, 1.7, 1.7, 1.8};
 // tile shapes: (128 filters x 448 pixels), (64 x 448), (128 x 224), (64 x 224).  (64 x 896, four waves side by
-// side, was tried for layers of 64 filters at 224 x 224 and measured no faster than 64 x 448 there; 128 x 512 on
+// side, was tried for layers of 64 filters at 224 x 224: no faster than 64 x 448 there in the plain form, 254 against 261 us as
+// one sequence of K steps, a trial that is not built in; 128 x 512 on
 // eight waves of 64 x 128 each -- two waves per SIMD with the first shape's operand economy -- fits 256 registers
 // only with spills, wastes the pixels that 512 has over a multiple of the row, and measured 4 to 45 % slower than the
 // first shape on the 112-, 56- and 28-column layers of VGG-16 at batch 64.)
