@@ -702,6 +702,33 @@ def test_maxpool_pieces(dtype, planes, H, W, shift):
     assert np.array_equal(got[shift:shift + n].reshape(1, planes, H // 2, W // 2), oracle.maxpool2x2(x))
 
 
+@pytest.mark.parametrize("planes,H,W", [(4099, 2049, 1025), (1, 65538, 131073)])
+def test_maxpool_in_several_launches(planes, H, W):
+    """More than 2^31 outputs: as many planes a launch, or rows of the one plane, as 32-bit numbers count (odd widths, an
+    output a thread).  Compared around the ends of the launches and of the tensor; 17 GB of inputs."""
+    import torch
+    say("maxpool, several launches", planes, H, W)
+    Ho, Wo = H // 2, W // 2
+    block = torch.randn(200_000_033, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda").half()
+    x = torch.empty(planes * H * W, dtype=torch.float16, device="cuda")
+    for part in x.split(block.numel()):
+        part.copy_(block[:part.numel()])
+    y = torch.full((planes * Ho * Wo + 64,), -777.0, dtype=torch.float16, device="cuda")
+    pc.maxpool2x2(x, y, pc.F16, 1, planes, H, W, torch.cuda.current_stream().cuda_stream)
+    torch.cuda.synchronize()
+    assert bool((y[-64:] == -777.0).all())
+    rows = y[:-64].view(planes * Ho, Wo)
+    most = 0x7FFFFF00 // Wo                                       # rows of a launch
+    if planes > 1:
+        most = most // Ho * Ho
+    assert planes * Ho > most
+    for row in (0, 1, most // 2, most - 1, most, most + 1, planes * Ho - 1):
+        pl, oy = divmod(row, Ho)
+        first = (pl * H + 2 * oy) * W
+        pair = x[first:first + 2 * W].view(2, W)[:, :2 * Wo]
+        assert torch.equal(rows[row], pair.reshape(2, Wo, 2).float().amax((0, 2)).half()), row
+
+
 @pytest.mark.parametrize("C,F,keep", [(1030, 40, 0.05), (2100, 17, 0.3), (3, 130, 1.0), (16, 1, 0.5)])
 @pytest.mark.parametrize("dtype", ["f32", "f16"])
 def test_layouts_made_on_the_device(C, F, keep, dtype):
