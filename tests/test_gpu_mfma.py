@@ -270,3 +270,24 @@ def test_dense_baseline_on_the_matrix_cores_and_direct(stride, pad):
                          torch.cuda.current_stream().cuda_stream)
         torch.cuda.synchronize()
         assert rel_err(dy.cpu().numpy(), ref) <= TOL["f16"]
+
+
+@pytest.mark.parametrize("shape", [1, 2, 3, 4])
+@pytest.mark.parametrize("full", [False, True], ids=["six taps", "nine taps"])
+def test_equal_images_give_equal_outputs(shape, full):
+    """Every image of the batch is the same, so are its outputs, bit for bit: a store whose data registers are written
+    again before it has read them shows as an image that differs.  Rows leave in pieces of 8 pixels, of the plain form and (nine
+    taps, tiles of four waves) of the sequence of K steps."""
+    kind = dict(K=8) if full else dict(K=2, lib_kind="fixed4")
+    spec = L.LayerSpec(cfg=23, idx=60, name="equal", N=1, C=32, F=64, H=28, W=56, dtype="f16", keep=0.5, **kind)
+    layer = GpuLayer(spec)
+    assert np.all(np.bitwise_or.reduce(layer.lib) == 0x1FF) == full
+    one = L.gen_activations(spec)
+    x = np.concatenate([one] * 96, axis=0)
+    ref = layer.oracle(one, True)
+    for _ in range(3):
+        say("equal images", shape, full)
+        y = layer.run(x, True, kernel=M, mfma_shape=shape)
+        assert np.array_equal(y, np.broadcast_to(y[:1], y.shape))
+        assert rel_err(y[0], ref[0]) <= TOL["f16"]
+    layer.free()
